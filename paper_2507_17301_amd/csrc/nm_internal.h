@@ -87,7 +87,7 @@ struct Prepack {
     int par = 0;                      // kind 4: 0 or 1 elements of lead-in per run (alignment of the run start)
     uint32_t* d_rows = nullptr;
     float* d_wfrag = nullptr;
-    size_t rows_bytes = 0, wfrag_bytes = 0;
+    size_t rows_bytes = 0, wfrag_bytes = 0, ktab_bytes = 0;   // (all inside the handle's d_tables block)
     uint32_t* d_ktab = nullptr;       // scalar mode only: [nchunks*CK] (kh | kw << 8 | ci << 16) per im2col row
 };
 
@@ -121,6 +121,7 @@ struct nm_packed {
     int sig = 0;      // hash of the operand tables built for this handle (part of the tuning-cache key)
     int32_t* d_idx = nullptr;   // [n_tiles][kprime]
     float* d_vals = nullptr;    // [n_tiles][kprime][tile]
+    char* d_tables = nullptr;   // one block: the table builders' error flag (256 bytes), then every operand table
     std::vector<int32_t> h_idx; // host copy of d_idx
     std::vector<nm::Prepack> prepacks;
 };
@@ -193,7 +194,8 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
 
 // prune-side kernels (nm_prune_kernels.hip)
 int run_prune(const float* d_w, nm_packed* wp, hipStream_t s);
-int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s);   // any kind
+// fills the (zeroed) tables of pp, any kind; enqueues only: an overfull chunk sets the int at wp->d_tables
+int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s);
 int run_build_mask(const nm_packed* wp, uint8_t* d_mask, hipStream_t s);
 int run_quantize_e4m3(nm_packed* wp, hipStream_t s);   // d_vals -> the E4M3 values they are stored as (needs wp->scale)
 int run_fill_random(void* d, size_t n_elems, nm_dtype_t dt, uint32_t seed, hipStream_t s);
