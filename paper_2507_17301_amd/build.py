@@ -104,6 +104,16 @@ def _shapes_f8():
     """(NBLK, WP, NJ) of NMF8_SHAPES in nm_variants.h."""
     text = open(os.path.join(CSRC, "nm_variants.h")).read()
     body = text[text.index("#define NMF8_SHAPES(X)"):]
+    body = body[:body.index("\n\n")]
+    return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
+
+
+def _shapes_split(name):
+    """(NBLK, WP, NJ) of NMSS_SHAPES or NMSD_SHAPES in nm_variants.h."""
+    text = open(os.path.join(CSRC, "nm_variants.h")).read()
+    body = text[text.index(f"#define {name}(X)"):]
+    body = body[len(name) + 11:]
+    body = body[:body.index("#define") if "#define" in body else len(body)]
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
 
 
@@ -141,6 +151,12 @@ def _jobs():
     for nb, wp, nj in _shapes_run():
         jobs.append((instrun, os.path.join(OBJDIR, f"nm_conv_run16_inst_{nb}_{wp}_{nj}.o"),
                      [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}"]))
+    insts = os.path.join(CSRC, "nm_conv_split_inst.hip")
+    for name, sparse in (("NMSS_SHAPES", 1), ("NMSD_SHAPES", 0)):
+        for nb, wp, nj in _shapes_split(name):
+            jobs.append((insts, os.path.join(OBJDIR, f"nm_conv_split_inst_{sparse}_{nb}_{wp}_{nj}.o"),
+                         [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}",
+                          f"-DNM_INST_SPARSE={sparse}"]))
     instf8 = os.path.join(CSRC, "nm_conv_f8_inst.hip")
     for nb, wp, nj in _shapes_f8():
         jobs.append((instf8, os.path.join(OBJDIR, f"nm_conv_f8_inst_{nb}_{wp}_{nj}.o"),

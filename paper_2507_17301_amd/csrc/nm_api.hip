@@ -103,6 +103,9 @@ const DeviceId* device_id(int dev)
     return &ids.emplace(dev, id).first->second;
 }
 
+// kinds 8 (sparse instruction) and 9 (dense): fp32 tensors as three bf16 planes
+inline bool is_split_kind(int kind) { return kind == 8 || kind == 9; }
+
 // Which variants may run a layer depends on its weights, not only on its shape: the
 // k-steps per chunk its kept sets need (groups wider than a chunk spread unevenly) and
 // which operand tables were built.  Two layers of one shape that differ there must not
@@ -112,7 +115,7 @@ int prepack_signature(const nm_packed* wp)
     unsigned h = 2166136261u;
     for (const Prepack& pp : wp->prepacks) {
         const int t[5] = {pp.kind, pp.geom.CK, pp.geom.vec, pp.SPC, pp.par};
-        h = fnv(h, t, sizeof(t));
+        if (!is_split_kind(pp.kind)) h = fnv(h, t, sizeof(t));   // (implied by the rest of the key)
     }
     return (int)(h & 0x7fffffffu);
 }
@@ -135,6 +138,8 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
 {
     // the epilogue's output tile [BP][channels of the workgroup] plus 16 bytes per pixel
     const size_t otile = (size_t)d.BP * ((size_t)(4 / d.WP) * d.NJ * 16 * (d.kind == 0 || d.kind == 5 ? 4 : 2) + 16);
+    if (is_split_kind(d.kind))   // two stages of three bf16 planes [BP][64], and each contracting wavefront's output piece
+        return (size_t)2 * d.BP * 384 + (size_t)4 * (d.NBLK > 1 ? 32 : 16) * (d.NJ * 64 + 16);
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
         return (size_t)4 * 16 * d.NBLK * (d.NJ * 32 + 16);
     if (d.kind == 7) {   // up to three stages of the strip [BP][CK] bytes plus each wave's operands (1 KB per k-step and row block)
@@ -188,7 +193,7 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     if (v < 0 || v >= variant_count()) return false;
     const VariantDesc& d = variant_desc(v);
     if (lds_bytes(d, wp) > (size_t)kMaxLdsBytes) return false;
-    if (d.kind == 5 && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
+    if ((d.kind == 5 || is_split_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
     // fp8: E4M3 tensors with an E4M3 handle run the fp8 kernels and nothing else does
     if (is_f8_kind(d.kind) != (xdt == NM_F8E4M3) || is_f8_kind(d.kind) != (wp->value_dtype == NM_F8E4M3)) return false;
     if (d.kind >= 1 && d.kind <= 4) {
@@ -347,9 +352,13 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     p.P = g.P; p.K = wp->K;
     p.nchunks = pp.geom.nchunks; p.ncpt = pp.geom.ncpt;
     p.tile = wp->tile; p.rbpt = wp->rbpt; p.n_rowblocks = wp->n_rowblocks;
+    if (is_split_kind(d.kind)) {   // row blocks of 16 consecutive output channels, whatever the column tile
+        p.tile = 16; p.rbpt = 1; p.n_rowblocks = (wp->cout + 15) / 16;
+    }
+    p.idx = wp->d_idx; p.vals = wp->d_vals; p.kprime = wp->kprime; p.ctile = wp->tile;
     const int rb_per_wg = (4 / d.WP) * d.NJ;
     p.n_ptiles = (g.P + d.BP - 1) / d.BP;
-    p.n_cblocks = (wp->n_rowblocks + rb_per_wg - 1) / rb_per_wg;
+    p.n_cblocks = (p.n_rowblocks + rb_per_wg - 1) / rb_per_wg;
     p.oscale = 1.0f / wp->scale;
     p.ksplit = d.ksplit > 1 ? d.ksplit : 1;
     p.cps = (pp.geom.nchunks + p.ksplit - 1) / p.ksplit;
@@ -366,6 +375,40 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     magic_div((unsigned)wp->cin, &p.cin_mul, &p.cin_shift);
 }
 
+// The three-plane form of an fp32 layer that runs without tuning, -1 where the fp32 instruction does it.
+//
+// Clocks of the matrix cores per 64 channels and 16 x 16 outputs: 16 x 32 times the kept fraction on the fp32
+// instruction (more where T leaves rows of its 16 empty), 6 x 16 on the sparse bf16 one, 12 x 16 on the dense one;
+// what surrounds them costs the three-plane kernel as much again.  Measured over 210 random layers (1:4, 2:4, 1:8,
+// 2:8, 4:8 and half of all channels, T 8 to 32, 100 to 180 000 pixels), fp32 instruction against three planes:
+//   sparse, 256 clocks and more (2:4; 1:4 at T = 8): x1.04 to x1.7 faster on every layer;
+//           128 clocks (1:4, 2:8): x0.66 to x1.13, 64 clocks (1:8): x0.78 to x1.0
+//   dense, 256 clocks (4:8, half of all channels): x1.04 to x1.5 from 300 000 outputs and 128 channels on, x0.9 below
+//   fewer than 48 channels (a chunk of 64 mostly empty): x0.6 to x0.9
+// and the ends of the first range at ResNet-50's sizes: 64 output channels and at most 9 chunks are x0.9 to x0.97.
+// Tiles: 64 pixels x 128 channels where they give every CU one, else 32 pixels, else 32 x 64; 64 channels
+// where the layer has no more, or where (dense form) 128 would leave more than an eighth of them empty.
+int split_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
+{
+    if (wp->cin < 48) return -1;
+    const double fp32_clocks = 512.0 * wp->n / wp->m * (16.0 * wp->rbpt / wp->tile);
+    const int cout = wp->cout;
+    const bool sparse = wp->n <= 2 && wp->m % 4 == 0;
+    if (fp32_clocks < 256.0) return -1;
+    if (sparse && cout <= 64 && wp->kh * wp->kw * ((wp->cin + 63) / 64) <= 9 && P > 16 * kNumCU) return -1;
+    if (!sparse && fp32_clocks < 512.0 && (cout < 128 || (long)P * cout < 300000)) return -1;
+    const int c64 = (cout + 63) / 64, c128 = (cout + 127) / 128;
+    const bool wide = cout > 64 && (sparse || 16 * c128 <= 9 * c64);
+    const long t64 = (long)((P + 63) / 64) * (wide ? c128 : c64), t32 = (long)((P + 31) / 32) * c128;
+    const int nblk = t64 >= kNumCU ? 4 : 2, nj = wide && (nblk == 4 || t32 >= 100) ? 2 : 1;
+    for (int v = 0; v < variant_count(); ++v) {
+        const VariantDesc& d = variant_desc(v);
+        if (is_split_kind(d.kind) && d.ksplit <= 1 && d.NBLK == nblk && d.WP == 1 && d.NJ == nj && variant_legal(v, wp, xdt, ra))
+            return v;
+    }
+    return -1;
+}
+
 // Deterministic default when the shape has not been tuned: a small model of
 // "rounds of workgroups x work per workgroup", preferring tiles that fill the
 // 256 CUs and reuse the staged strip across many row blocks.
@@ -378,6 +421,10 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
 // chunks on deep, small layers, 64 otherwise.  Variants are ranked by their distance from that.
 int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 {
+    if (xdt == NM_F32) {
+        const int v = split_default(wp, P, xdt, ra);
+        if (v >= 0) return v;
+    }
     {
         const long wg128 = (long)((P + 127) / 128) * ((wp->n_rowblocks + 7) / 8);
         const int bp_t = wg128 >= kNumCU / 2 ? 128 : 64;
@@ -408,6 +455,7 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
     for (int v = 0; v < variant_count(); ++v) {
         if (!variant_legal(v, wp, xdt, ra)) continue;
         const VariantDesc& d = variant_desc(v);
+        if (is_split_kind(d.kind)) continue;   // (split_default)
         if (d.ksplit > 1) continue;   // a K split needs a workspace: only where the tuner has shown that it pays
         const int rb_per_wg = (4 / d.WP) * d.NJ;
         const long n_pt = (P + d.BP - 1) / d.BP;
@@ -658,6 +706,16 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
             if (cin % d.CK != 0 || find_prepack(wp, d)) continue;
             pp.geom = make_chunk_geom(cin, wp->K, d.CK, 1);
             pp.wfrag_bytes = (size_t)wp->n_rowblocks * (wp->K / 64) * 64 * 16;
+            if (pp.wfrag_bytes < kWindow) wp->prepacks.push_back(pp);
+            continue;
+        }
+        if (is_split_kind(d.kind)) {
+            // 16-byte loads; the sparse instruction where no aligned group of four keeps more than two columns
+            if (value_dtype != NM_F32 || !vec_ok || (d.kind == 8) != (n <= 2 && m % 4 == 0) || find_prepack(wp, d)) continue;
+            pp.geom = make_chunk_geom(cin, wp->K, 64, 1);
+            const size_t blocks = (size_t)((cout + 15) / 16) * pp.geom.nchunks;
+            pp.rows_bytes = d.kind == 8 ? blocks * 256 : 0;
+            pp.wfrag_bytes = blocks * 3 * (d.kind == 8 ? 1 : 2) * 1024;
             if (pp.wfrag_bytes < kWindow) wp->prepacks.push_back(pp);
             continue;
         }
@@ -1140,8 +1198,8 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
         if (!variant_legal(v, wp, xdt, &ra)) continue;
         {   // a K split is worth its second kernel only where the output tiles are one short, ragged round (at most two per CU)
             const VariantDesc& d = variant_desc(v);
-            const long tiles = (long)((g.P + d.BP - 1) / d.BP) *
-                               ((wp->n_rowblocks + (4 / d.WP) * d.NJ - 1) / ((4 / d.WP) * d.NJ));
+            const int nrb = is_split_kind(d.kind) ? (wp->cout + 15) / 16 : wp->n_rowblocks;
+            const long tiles = (long)((g.P + d.BP - 1) / d.BP) * ((nrb + (4 / d.WP) * d.NJ - 1) / ((4 / d.WP) * d.NJ));
             if (d.ksplit > 1 && (tiles > 2 * kNumCU || tiles * d.ksplit > 8 * kNumCU)) continue;
         }
         if (time_group(v, 1) < 0.f) { cleanup(); return rc_t; }

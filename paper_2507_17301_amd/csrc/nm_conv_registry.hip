@@ -69,13 +69,20 @@ struct Entry {
      nullptr, &launch_sp16_t<NB, WP, NJ, CK, false, true, true, true>},
 #define NM_SHAPE_ENTRIESF8S(NB, WP, NJ) NMF8S_CHUNKS(NM_ENTRYF8S, NB, WP, NJ)
 
+// kinds 8, 9: fp32 tensors as three bf16 planes
+#define NM_ENTRYSS(NB, WP, NJ)                                                                  \
+    {{"X3S_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 8, 1, 1, 0, 1}, &launch_split_t<NB, WP, NJ, true>, nullptr},
+#define NM_ENTRYSD(NB, WP, NJ)                                                                  \
+    {{"X3D_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 9, 1, 1, 0, 1}, &launch_split_t<NB, WP, NJ, false>, nullptr},
+
 const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTRY)
                           NM16_SHAPES(NM_SHAPE_ENTRIES16) NMSP_SHAPES(NM_SHAPE_ENTRIESSP) NMSPW_SHAPES(NM_SHAPE_ENTRIESSPW) NMSPR_SHAPES(NM_SHAPE_ENTRIESSPR)
                           NMRUN_SHAPES(NM_SHAPE_ENTRIESRUN) NMVAR_SHAPES(NM_SHAPE_ENTRIESVAR)
-                          NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)};
+                          NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)
+                          NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
-// The fp32 MFMA kernel also runs with its K axis split over several workgroups per output
+// The fp32 kernels also run with their K axis split over several workgroups per output
 // tile (for layers with too few output tiles to fill the chip).  Those forms are variants of
 // their own -- ids kCount and up, the base variant's name with "_S<splits>" appended -- so that
 // the tuner, the cache and the test hook treat them like any other.
@@ -94,7 +101,8 @@ Table build_table()
     }
     for (int s : kSplits)
         for (int i = 0; i < kCount; ++i) {
-            if (kEntries[i].d.kind != 0 && kEntries[i].d.kind != 5) continue;
+            const int kind = kEntries[i].d.kind;
+            if (kind != 0 && kind != 5 && kind != 8 && kind != 9) continue;
             VariantDesc d = kEntries[i].d;
             t.names.push_back(std::string(d.name) + "_S" + std::to_string(s));
             d.name = t.names.back().c_str();

@@ -65,6 +65,7 @@ struct Prepack {
                                       // 4: bf16 kernel-row runs, 5: fp32 MFMA kernel with per-chunk step counts,
                                       // 6, 7: fp8 kernels (dense instruction on zero-filled weights), register-streaming
                                       // and LDS-staged
+                                      // 8, 9: fp32 as three bf16 planes (sparse instruction, dense instruction)
     ChunkGeom geom{};
     int SPC = 0;                      // k-steps per chunk (1, 2, 4 or 8)
     // kind 0: a k-step is 4 kept columns
@@ -84,6 +85,10 @@ struct Prepack {
     //   d_wfrag [n_rowblocks][SPC][2][64][8] bf16   A-operand lane values, zero in padding slots
     // kind 6 and 7 (fp8 E4M3, dense instruction): a k-step is 64 channels of one tap, a chunk CK / 64 of them
     //   d_wfrag [n_rowblocks][K / 64][64][16] bytes   lane i + 16 q, byte e = channel 16 q + e of the k-step
+    // kind 8 (sparse instruction) and 9 (dense): a k-step is 64 channels of one tap, a chunk is one k-step, a row
+    //   block is 16 consecutive output channels whatever the column tile
+    //   d_rows  [row blocks][nchunks][64] u32         kind 8: index operand of each lane
+    //   d_wfrag [row blocks][nchunks][3][AH][64][8] bf16   A-operand lane values of the three planes, AH = 1 (kind 8) or 2
     int par = 0;                      // kind 4: 0 or 1 elements of lead-in per run (alignment of the run start)
     uint32_t* d_rows = nullptr;
     float* d_wfrag = nullptr;
@@ -160,6 +165,10 @@ struct ConvParams {
     // them up and applies bias, residual and activation.  ksplit <= 1: no split, partial unused.
     float* partial;
     int ksplit, cps;
+    // the compressed format itself (kinds 8, 9 compute outputs that came out infinite or NaN from it again)
+    const int32_t* idx;
+    const float* vals;
+    int kprime, ctile;
     float oscale;      // fp8: factor that takes the accumulator back to the weights' own scale (1 / handle scale)
 };
 
@@ -177,8 +186,9 @@ struct VariantDesc {
                // 4 = bf16 dense kernel on contiguous kernel-row runs (very few input channels),
                // 5 = fp32 MFMA kernel that runs only the k-steps holding kept columns of each (tile, chunk)
                // 6 = fp8 E4M3 kernel (fp8 activations, bf16 output): dense instruction on zero-filled weights
+               // 8, 9 = fp32 tensors as three bf16 planes on the sparse / dense bf16 instruction
     int share; // kind 1: row blocks fed from one gathered operand
-    int ksplit; // kinds 0, 5: workgroups that share the K axis of one output tile (1 = no split)
+    int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)
     int areg;  // kinds 2, 3, 7: 1 = weights and index words go straight to registers, the LDS stages hold the strip alone
     int spec;  // kinds 2, 3, 7: 1 = four producer wavefronts issue the loads (512 threads)
 };

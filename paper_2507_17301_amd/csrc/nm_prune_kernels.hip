@@ -431,6 +431,72 @@ __global__ __launch_bounds__(256) void build_prepack_f8_kernel(
     }
 }
 
+// Operand tables of the three-plane fp32 kernel: one thread per (row block, chunk, half, lane) writes that
+// lane's 8 A-operand values in each plane.  The assignment of elements to channels is that of the
+// gather-free bf16 kernel; the weight is cut as the activations are (w1 = rne(w), w2 = rne(w - w1),
+// w3 = w - w1 - w2).  Row i of a block is output channel 16 rb + i, with the kept set of its own
+// column tile: the index word is per lane.
+__global__ __launch_bounds__(256) void build_prepack_split_kernel(
+    const int32_t* __restrict__ idx, const float* __restrict__ vals, int kprime, int T, int cout,
+    int n_rowblocks, int cin, int ncpt, int nchunks, int sparse, uint32_t* __restrict__ rows,
+    unsigned short* __restrict__ wfrag, int* __restrict__ err)
+{
+    const int AH = sparse ? 1 : 2;
+    const size_t total = (size_t)n_rowblocks * nchunks * AH * 64;
+    for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < total;
+         id += (size_t)gridDim.x * blockDim.x) {
+        const int lane = (int)(id % 64);
+        size_t r = id / 64;
+        const int h = (int)(r % AH); r /= AH;
+        const int c = (int)(r % nchunks);
+        const int rb = (int)(r / nchunks);
+        const int i = lane & 15, qa = lane >> 4;
+        const int co = rb * 16 + i, j = co < cout ? co / T : 0, t = co - j * T;
+        const bool live = co < cout;
+        const int32_t* idxj = idx + (size_t)j * kprime;
+        const int tap = c / ncpt, ci0 = (c - tap * ncpt) * 64;
+        const int kend = (tap + 1) * cin;                 // a chunk's channels end with its tap
+        float w[8];
+        unsigned fields = 0;
+        if (sparse) {
+            for (int pair = 0; pair < 4; ++pair) {        // elements 2 pair, 2 pair + 1 share a group of four
+                const int ea = 2 * pair;
+                const int k0 = tap * cin + ci0 + 16 * (2 * (qa % 2) + ea / 4) + 8 * (qa / 2) + 4 * ((ea % 4) / 2);
+                int cnt = 0, pos[2] = {0, 0}, kk[2] = {-1, -1};
+                if (live && k0 < kend)
+                    for (int u = lower_bound_idx(idxj, kprime, k0); u < kprime && idxj[u] < k0 + 4; ++u) {
+                        if (cnt < 2) { pos[cnt] = idxj[u] - k0; kk[cnt] = u; }
+                        ++cnt;
+                    }
+                if (cnt > 2) err[0] = 1;
+                if (cnt == 0) {
+                    pos[0] = 0; pos[1] = 1;
+                } else if (cnt == 1) {
+                    if (pos[0] == 3) { pos[1] = 3; kk[1] = kk[0]; pos[0] = 0; kk[0] = -1; }
+                    else pos[1] = 3;
+                }
+                for (int e = 0; e < 2; ++e) w[ea + e] = kk[e] >= 0 ? vals[((size_t)j * kprime + kk[e]) * T + t] : 0.f;
+                fields |= (unsigned)(pos[0] | (pos[1] << 2)) << (4 * pair);
+            }
+            rows[((size_t)rb * nchunks + c) * 64 + lane] = fields;
+        } else {
+            for (int e = 0; e < 8; ++e) {
+                const int k = tap * cin + ci0 + 16 * qa + 8 * h + e;
+                const int lb = live && k < kend ? lower_bound_idx(idxj, kprime, k) : kprime;
+                w[e] = lb < kprime && idxj[lb] == k ? vals[((size_t)j * kprime + lb) * T + t] : 0.f;
+            }
+        }
+        for (int pl = 0; pl < 3; ++pl) {
+            unsigned short* dst = wfrag + ((((size_t)rb * nchunks + c) * 3 + pl) * AH + h) * 512 + lane * 8;
+            for (int e = 0; e < 8; ++e) {
+                const float top = round_bf16_rne(w[e]);
+                dst[e] = (unsigned short)(__float_as_uint(top) >> 16);
+                w[e] -= top;
+            }
+        }
+    }
+}
+
 int grid_for(size_t total, int threads)
 {
     size_t g = (total + threads - 1) / threads;
@@ -467,7 +533,13 @@ int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s)
     const ChunkGeom& g = pp.geom;
     int* const d_err = reinterpret_cast<int*>(wp->d_tables);
     const size_t lds = (size_t)2 * g.nchunks * sizeof(int);
-    if (pp.kind == 6 || pp.kind == 7) {
+    if (pp.kind == 8 || pp.kind == 9) {
+        const int nrb = (wp->cout + 15) / 16;
+        const size_t total = (size_t)nrb * g.nchunks * (pp.kind == 8 ? 1 : 2) * 64;
+        hipLaunchKernelGGL(build_prepack_split_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, wp->d_idx, wp->d_vals,
+                           wp->kprime, wp->tile, wp->cout, nrb, wp->cin, g.ncpt, g.nchunks, pp.kind == 8 ? 1 : 0,
+                           pp.d_rows, reinterpret_cast<unsigned short*>(pp.d_wfrag), d_err);
+    } else if (pp.kind == 6 || pp.kind == 7) {
         // the table is made of 64-channel k-steps whatever the variant's chunk size
         const int ncpt64 = wp->cin / 64, nk64 = wp->K / 64;
         const size_t total = (size_t)wp->n_rowblocks * nk64 * 64;

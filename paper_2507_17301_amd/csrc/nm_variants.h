@@ -96,3 +96,10 @@
 // X(NBLK, WP, NJ)
 #define NMF8_SHAPES(X) \
     X(4, 1, 4) X(4, 2, 4) X(4, 4, 4) X(2, 1, 4) X(2, 2, 4) X(2, 4, 4) X(4, 1, 2) X(4, 2, 2) X(8, 1, 2) X(8, 2, 2)
+
+// fp32 tensors as three bf16 planes (64-channel chunks, four producer and four contracting wavefronts):
+// the sparse instruction and the dense one.  (128-pixel tiles were tried: their two stages leave a CU one
+// workgroup, and they were first on no layer of the ResNet-50 stack.)
+// X(NBLK, WP, NJ)
+#define NMSS_SHAPES(X) X(4, 1, 2) X(4, 1, 4) X(3, 1, 2) X(2, 1, 2) X(2, 2, 2) X(4, 1, 1) X(2, 1, 1)
+#define NMSD_SHAPES(X) X(4, 1, 2) X(2, 1, 2) X(2, 2, 2) X(4, 1, 1) X(2, 1, 1)

@@ -1,0 +1,127 @@
+"""fp32 tensors as three bf16 planes (variants X3S / X3D): every form forced on shapes at the edges of
+its tiles, against the CPU oracle and, for accuracy and for infinities, against the fp32-instruction form."""
+import numpy as np
+import pytest
+
+from paper_2507_17301_amd import binding as nm
+from paper_2507_17301_amd import workloads as wl
+from gpu_util import FP32_TOL, say, norm_err, oracle_conv
+
+pytestmark = pytest.mark.gpu
+
+L = wl.ConvLayer
+
+# H, W, Cin, Cout, Kh, Kw, stride, pad, dil, n, m, tile (+ batch): pixel counts around 32 / 64 / 96 / 128, channel counts
+# that end inside a chunk or a row block, one chunk and odd and even numbers of them, column tiles that are no row block
+GRID = [
+    (L("one_pixel", 3, 3, 64, 16, 3, 3, 1, 0, 1, 2, 4, 16), 1),
+    (L("P31_cin4", 31, 1, 4, 9, 1, 1, 1, 0, 1, 2, 4, 16), 1),
+    (L("P33_cin68", 11, 3, 68, 36, 1, 1, 1, 0, 1, 1, 4, 8), 1),
+    (L("P64_T1", 8, 8, 64, 20, 3, 3, 1, 1, 1, 2, 8, 1), 1),
+    (L("P129_T5", 43, 3, 128, 37, 1, 1, 1, 0, 1, 2, 4, 5), 1),
+    (L("s2_dil2", 15, 13, 48, 72, 3, 3, 2, 2, 2, 1, 8, 8), 3),
+    (L("T32", 10, 10, 192, 144, 1, 1, 1, 0, 1, 2, 4, 32), 2),
+    (L("multi", 19, 17, 64, 272, 3, 3, 1, 1, 1, 2, 4, 16), 2),
+    (L("dense", 9, 11, 72, 48, 3, 3, 1, 1, 1, 1, 1, 16), 2),
+    (L("k4of8", 9, 7, 64, 80, 3, 3, 1, 1, 1, 4, 8, 16), 2),
+    (L("cin_groups", 10, 9, 128, 40, 3, 3, 1, 1, 1, 64, 128, 16), 2),
+]
+
+
+def split_variants(wp):
+    return [v for v in range(nm.nm_variant_count())
+            if nm.nm_variant_name(v).startswith("X3") and nm.nm_variant_legal(v, wp)]
+
+
+def fp32_instruction(wp):
+    return next(v for v in range(nm.nm_variant_count())
+                if nm.nm_variant_name(v).startswith("NB4_WP1_NJ1") and nm.nm_variant_legal(v, wp))
+
+
+def run(v, x, wp, b, layer, relu=True, res=None):
+    import torch
+    nm.nm_force_variant(v)
+    try:
+        y = nm.nm_conv2d_res(x, wp, res, b, layer.stride, layer.pad, layer.dil, relu)
+        torch.cuda.synchronize()
+        assert nm.nm_last_variant() == v
+        return y.cpu().numpy()
+    finally:
+        nm.nm_force_variant(-1)
+
+
+@pytest.mark.parametrize("layer,batch", GRID, ids=[g[0].name for g in GRID])
+def test_every_form(layer, batch):
+    import torch
+    x, w, bias = wl.make_tensors(layer, batch, 31, weight_sigma=0.1)
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = oracle_conv(layer, x, w, bias, relu=False)
+    res = np.random.default_rng(5).standard_normal(ref.shape, dtype=np.float32)
+    vs = split_variants(wp)
+    assert vs
+    for v in vs:
+        say(f"{layer.name} {nm.nm_variant_name(v)}")
+        assert norm_err(run(v, xd, wp, bd, layer, relu=True), np.maximum(ref, 0)) <= FP32_TOL, nm.nm_variant_name(v)
+        got = run(v, xd, wp, bd, layer, relu=False, res=torch.from_numpy(res).cuda())
+        assert norm_err(got, ref + res) <= FP32_TOL, nm.nm_variant_name(v)
+
+
+@pytest.mark.parametrize("layer", [L("k18", 20, 20, 36, 64, 1, 1, 1, 0, 1, 2, 4, 16), L("k32", 20, 20, 64, 64, 1, 1, 1, 0, 1, 2, 4, 16),
+                                   L("k288", 20, 20, 64, 64, 3, 3, 1, 1, 1, 2, 4, 16),
+                                   L("k2304", 14, 14, 512, 64, 3, 3, 1, 1, 1, 2, 4, 16),
+                                   L("dense576", 14, 14, 64, 64, 3, 3, 1, 1, 1, 1, 1, 16)], ids=lambda l: l.name)
+@pytest.mark.parametrize("kind", ["uniform", "signed", "tiny"])
+def test_no_further_from_float64_than_the_fp32_instruction(layer, kind):
+    import torch
+    x, w, bias = wl.make_tensors(layer, 2, 17)
+    if kind != "uniform":
+        x = np.random.default_rng(3).standard_normal(x.shape, dtype=np.float32)
+    if kind == "tiny":                          # the third planes are subnormal
+        x, bias = x * np.float32(1e-33), bias * 0
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    idx = nm.nm_packed_indices(wp).reshape(-1, layer.K // layer.m * layer.n)
+    vals = nm.nm_packed_values(wp).reshape(*idx.shape, layer.tile)
+    wz = np.zeros((layer.Cout, layer.K))
+    for j in range(idx.shape[0]):
+        for t in range(layer.tile):
+            wz[j * layer.tile + t, idx[j]] = vals[j, :, t]
+    wt = torch.from_numpy(wz.reshape(layer.Cout, layer.Kh, layer.Kw, layer.Cin)).permute(0, 3, 1, 2)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2), wt,
+                                     torch.from_numpy(bias).double(), layer.stride, layer.pad, layer.dil)
+    ref = ref.permute(0, 2, 3, 1).numpy()
+
+    def err(v):
+        d = run(v, xd, wp, bd, layer, relu=False).astype(np.float64) - ref
+        return float(np.sqrt((d * d).sum() / (ref * ref).sum()))
+
+    old = err(fp32_instruction(wp))
+    for v in split_variants(wp):
+        e = err(v)
+        say(f"{layer.name} {nm.nm_variant_name(v)} {e:.3g} (fp32 instruction {old:.3g})")
+        assert e <= old, nm.nm_variant_name(v)
+
+
+@pytest.mark.parametrize("relu", [False, True])
+def test_infinities_and_nan(relu):
+    """Infinite and NaN activations give what the fp32 instruction gives."""
+    import torch
+    layer = L("inf", 12, 12, 64, 64, 3, 3, 1, 1, 1, 2, 4, 16)
+    x, w, bias = wl.make_tensors(layer, 2, 19)
+    w[w == 0] = 0.01
+    x[0, 2, 3, 5], x[0, 9, 9, 40], x[1, 4, 4, 10] = np.inf, -np.inf, np.nan
+    x[1, 9, 9, 3] = 3.4e38                      # next to the largest number; the sums stay finite
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = run(fp32_instruction(wp), xd, wp, bd, layer, relu)
+    assert np.isnan(ref).any() or relu
+    assert np.isinf(ref).any()
+    for v in split_variants(wp):
+        say(f"inf {nm.nm_variant_name(v)}")
+        got = run(v, xd, wp, bd, layer, relu)
+        assert (np.isnan(got) == np.isnan(ref)).all(), nm.nm_variant_name(v)
+        same = (got == ref) | ~np.isinf(ref)
+        assert same.all() and not np.isinf(got[np.isfinite(ref)]).any(), nm.nm_variant_name(v)
+        ok = np.isfinite(ref)
+        assert norm_err(got[ok], ref[ok]) <= FP32_TOL
