@@ -325,8 +325,14 @@ __global__ __launch_bounds__(SPEC ? 512 : 256) void nm_conv_sp16_kernel(const Co
                 if (c + 2 < p.nchunks) fetch_stage(wst);
                 wst = wst + 1 == D ? 0 : wst + 1;
             }
-            if (tile_path) {   // the consumers' two epilogue barriers
+            if (tile_path) {   // the barriers of the epilogue; the residual is requested while the last chunk is contracted
+                ResTile<bf16_t, BP, WGC> rt;
+                if (p.res) rt.load(p, tid - 256, p0, cblock * WGC);
                 __syncthreads();
+                if (p.res) {
+                    rt.put(lds8, tid - 256);
+                    __syncthreads();
+                }
                 __syncthreads();
             }
             return;
@@ -556,20 +562,26 @@ __global__ __launch_bounds__(SPEC ? 512 : 256) void nm_conv_sp16_kernel(const Co
     if (tile_path) {
         // whole 128-byte lines through the LDS tile, once every wavefront is past its last strip read
         constexpr int PITCH = tile_pitch<bf16_t>(WGC);
-        __syncthreads();
+        if constexpr (SPEC) {
+            __syncthreads();
+            if (p.res) __syncthreads();          // the producers have put the residual in its place
+        } else {
+            ResTile<bf16_t, BP, WGC> rt;
+            if (p.res) rt.load(p, tid, p0, cblock * WGC);
+            __syncthreads();
+            if (p.res) {
+                rt.put(lds8, tid);
+                __syncthreads();
+            }
+        }
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
-            const int rb = rb0 + jj;
-            const int co = rb * 16 + q * 4;       // T is a multiple of 16: row block rb is channels 16 rb ..
-            const bool row_live = rb < p.n_rowblocks && co < p.Cout;
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
                 const int pl = wpix + b * 16 + n;
-                const int pp = p0 + pl;
                 // (bf16: the bias is already in the accumulator)
-                tile_put4<bf16_t>(p, lds8 + pl * PITCH + ((wcx * NJ + jj) * 16 + q * 4) * 2,
-                                  (unsigned)pp * (unsigned)p.Cout + (unsigned)co, row_live && pp < p.P,
-                                  F8 ? acc[jj][b] * p.oscale + bb[jj] : acc[jj][b]);
+                tile_put4_lds<bf16_t>(p, lds8 + pl * PITCH + ((wcx * NJ + jj) * 16 + q * 4) * 2,
+                                      F8 ? acc[jj][b] * p.oscale + bb[jj] : acc[jj][b]);
             }
         }
         __syncthreads();
