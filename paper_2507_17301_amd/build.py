@@ -157,6 +157,9 @@ def _jobs():
             jobs.append((insts, os.path.join(OBJDIR, f"nm_conv_split_inst_{sparse}_{nb}_{wp}_{nj}.o"),
                          [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}",
                           f"-DNM_INST_SPARSE={sparse}"]))
+    instrows = os.path.join(CSRC, "nm_conv_rows_inst.hip")
+    for pl in (1, 3):
+        jobs.append((instrows, os.path.join(OBJDIR, f"nm_conv_rows_inst_{pl}.o"), [f"-DNM_INST_PL={pl}"]))
     instf8 = os.path.join(CSRC, "nm_conv_f8_inst.hip")
     for nb, wp, nj in _shapes_f8():
         jobs.append((instf8, os.path.join(OBJDIR, f"nm_conv_f8_inst_{nb}_{wp}_{nj}.o"),

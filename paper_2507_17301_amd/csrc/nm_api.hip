@@ -105,6 +105,10 @@ const DeviceId* device_id(int dev)
 
 // kinds 8 (sparse instruction) and 9 (dense): fp32 tensors as three bf16 planes
 inline bool is_split_kind(int kind) { return kind == 8 || kind == 9; }
+// kinds 10 (bf16) and 11 (fp32): few input channels out of staged rows
+inline bool is_rows_kind(int kind) { return kind == 10 || kind == 11; }
+// kinds whose row blocks are 16 consecutive output channels, whatever the column tile
+inline bool flat_rowblocks(int kind) { return is_split_kind(kind) || is_rows_kind(kind); }
 
 // Which variants may run a layer depends on its weights, not only on its shape: the
 // k-steps per chunk its kept sets need (groups wider than a chunk spread unevenly) and
@@ -115,7 +119,7 @@ int prepack_signature(const nm_packed* wp)
     unsigned h = 2166136261u;
     for (const Prepack& pp : wp->prepacks) {
         const int t[5] = {pp.kind, pp.geom.CK, pp.geom.vec, pp.SPC, pp.par};
-        if (!is_split_kind(pp.kind)) h = fnv(h, t, sizeof(t));   // (implied by the rest of the key)
+        if (!flat_rowblocks(pp.kind)) h = fnv(h, t, sizeof(t));   // (implied by the rest of the key)
     }
     return (int)(h & 0x7fffffffu);
 }
@@ -132,6 +136,8 @@ ShapeKey make_key(nm_dtype_t xdt, nm_dtype_t ydt, int b, int h, int w, const nm_
     return k;
 }
 
+constexpr size_t kRowsPieces = 4 * 16 * 144;   // kinds 10, 11: the output pieces of four wavefronts
+
 // LDS footprint of variant d on the layer wp (the ring of the gather-free bf16
 // kernel is only as deep as the layer's K loop is long).
 size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
@@ -140,6 +146,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
     const size_t otile = (size_t)d.BP * ((size_t)(4 / d.WP) * d.NJ * 16 * (d.kind == 0 || d.kind == 5 ? 4 : 2) + 16);
     if (is_split_kind(d.kind))   // two stages of three bf16 planes [BP][64], and each contracting wavefront's output piece
         return (size_t)2 * d.BP * 384 + (size_t)4 * (d.NBLK > 1 ? 32 : 16) * (d.NJ * 64 + 16);
+    if (is_rows_kind(d.kind)) return kRowsPieces;   // and the staged rows, which depend on the image (rows_layout)
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
         return (size_t)4 * 16 * d.NBLK * (d.NJ * 32 + 16);
     if (d.kind == 7) {   // up to three stages of the strip [BP][CK] bytes plus each wave's operands (1 KB per k-step and row block)
@@ -162,11 +169,33 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
     return std::max(otile, (size_t)2 * d.CK * strip_stride(d.BP, d.CK, d.vec != 0) * sizeof(float));
 }
 
-// The part of the convolution arguments that decides whether the kernel-row-run
-// kernel applies and which of its two operand tables it needs.
+// The part of the convolution arguments that decides whether the kernels for few input
+// channels apply and which of their two operand tables they need.
 struct RunArgs {
-    int w, sw, pw, dw;
+    int w, sw, pw, dw, sh, dh;
 };
+
+// Layout of the staged rows of kinds 10 and 11 (bytes of one plane; the data starts on 16 bytes, the run of
+// column 0 at `front`, 2 * lead bytes before it).
+struct RowsLayout {
+    int n, pitch, front, data;
+    size_t lds;   // all planes, whole 1 KB windows
+};
+RowsLayout rows_layout(const VariantDesc& d, const nm_packed* wp, const RunArgs& ra)
+{
+    const int par = (ra.pw * wp->cin) % 2, lead = ra.pw * wp->cin + par, gr = (par + wp->kw * wp->cin + 7) / 8;
+    const int wo = (ra.w + 2 * ra.pw - wp->kw) / ra.sw + 1;
+    RowsLayout r;
+    r.n = (d.NBLK - 1) * ra.sh + (wp->kh - 1) * ra.dh + 1;
+    r.data = (2 * lead + 15) / 16 * 16;
+    r.front = r.data - 2 * lead;
+    const long end = std::max((long)r.data + 2L * ra.w * wp->cin, (long)r.front + 2L * (wo - 1) * ra.sw * wp->cin + gr * 16L);
+    const long pitch = (end + 15) / 16 * 16;
+    const long bytes = (long)r.n * pitch * (d.kind == 10 ? 1 : 3);
+    r.pitch = (int)std::min(pitch, 1L << 28);
+    r.lds = (size_t)((bytes + 1023) / 1024 * 1024);
+    return r;
+}
 
 // k-steps the kernel-row-run kernel needs for this layer when runs start `par` elements early
 int run_ksteps(const nm_packed* wp, int par)
@@ -179,7 +208,7 @@ const Prepack* find_prepack(const nm_packed* wp, const VariantDesc& d, int par =
 {
     for (const Prepack& pp : wp->prepacks)
         if (pp.kind == d.kind && pp.geom.CK == d.CK && pp.geom.vec == d.vec && pp.SPC == d.SPC &&
-            (d.vec || pp.d_ktab) && (d.kind != 4 || par < 0 || pp.par == par))
+            (d.vec || pp.d_ktab) && ((d.kind != 4 && !is_rows_kind(d.kind)) || par < 0 || pp.par == par))
             return &pp;
     return nullptr;
 }
@@ -193,15 +222,16 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     if (v < 0 || v >= variant_count()) return false;
     const VariantDesc& d = variant_desc(v);
     if (lds_bytes(d, wp) > (size_t)kMaxLdsBytes) return false;
-    if ((d.kind == 5 || is_split_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
+    if ((d.kind == 5 || d.kind == 11 || is_split_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
     // fp8: E4M3 tensors with an E4M3 handle run the fp8 kernels and nothing else does
     if (is_f8_kind(d.kind) != (xdt == NM_F8E4M3) || is_f8_kind(d.kind) != (wp->value_dtype == NM_F8E4M3)) return false;
-    if (d.kind >= 1 && d.kind <= 4) {
+    if ((d.kind >= 1 && d.kind <= 4) || d.kind == 10) {
         // bf16 matrix cores: bf16 tensors, weights already rounded to bf16, and a
         // shared operand only for column tiles made of exactly two row blocks
         if (xdt != NM_BF16 || wp->value_dtype != NM_BF16) return false;
         if (d.share != 1 && d.share != wp->rbpt) return false;
     }
+    if (is_rows_kind(d.kind) && wp->cout % (d.kind == 10 ? 8 : 4) != 0) return false;   // whole 16-byte output granules
     if (d.ksplit > 1) {
         // every split must own at least one chunk of the K axis
         const Prepack* pp = find_prepack(wp, d);
@@ -209,9 +239,10 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
         const int cps = (pp->geom.nchunks + d.ksplit - 1) / d.ksplit;
         if ((d.ksplit - 1) * cps >= pp->geom.nchunks) return false;
     }
-    if (d.kind == 4 && ra) {
+    if ((d.kind == 4 || is_rows_kind(d.kind)) && ra) {
         // a kernel row must be one contiguous, 4-byte aligned run of every pixel
         if (ra->dw != 1 || (ra->sw * wp->cin) % 2 != 0 || (ra->w * wp->cin) % 2 != 0) return false;
+        if (is_rows_kind(d.kind) && rows_layout(d, wp, *ra).lds + kRowsPieces > (size_t)kMaxLdsBytes) return false;
         return find_prepack(wp, d, (ra->pw * wp->cin) % 2) != nullptr;
     }
     return find_prepack(wp, d) != nullptr;
@@ -352,7 +383,7 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     p.P = g.P; p.K = wp->K;
     p.nchunks = pp.geom.nchunks; p.ncpt = pp.geom.ncpt;
     p.tile = wp->tile; p.rbpt = wp->rbpt; p.n_rowblocks = wp->n_rowblocks;
-    if (is_split_kind(d.kind)) {   // row blocks of 16 consecutive output channels, whatever the column tile
+    if (flat_rowblocks(d.kind)) {
         p.tile = 16; p.rbpt = 1; p.n_rowblocks = (wp->cout + 15) / 16;
     }
     p.idx = wp->d_idx; p.vals = wp->d_vals; p.kprime = wp->kprime; p.ctile = wp->tile;
@@ -363,6 +394,13 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     p.ksplit = d.ksplit > 1 ? d.ksplit : 1;
     p.cps = (pp.geom.nchunks + p.ksplit - 1) / p.ksplit;
     p.partial = nullptr;   // the caller points it at a workspace of split_bytes()
+    if (is_rows_kind(d.kind)) {
+        const RowsLayout r = rows_layout(d, wp, RunArgs{w, sw, pw, dw, sh, dh});
+        p.rows_r = d.NBLK; p.rows_n = r.n; p.rows_pitch = r.pitch; p.rows_front = r.front; p.rows_data = r.data;
+        p.rows_lds = (int)r.lds;
+        magic_div((unsigned)(r.pitch / 16), &p.rowg_mul, &p.rowg_shift);
+        p.n_ptiles = b * ((g.Ho + d.NBLK - 1) / d.NBLK);
+    }
     p.n_wg = p.n_ptiles * p.n_cblocks * p.ksplit;
     p.wg_per_xcd = (p.n_wg + 7) / 8;
     magic_div((unsigned)(g.Ho * g.Wo), &p.howo_mul, &p.howo_shift);
@@ -373,6 +411,26 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     p.run_gr = (pp.par + wp->kw * wp->cin + 7) / 8;
     magic_div((unsigned)p.run_gr, &p.gr_mul, &p.gr_shift);
     magic_div((unsigned)wp->cin, &p.cin_mul, &p.cin_shift);
+}
+
+// The variants without a K split, in table order: what an untuned call chooses from.  Of these only the kinds
+// that the handle has operand tables for are looked at: the choice is made on every untuned call, and a look at
+// all 1500 variants took 20 us of it.
+const std::vector<int>& base_variants()
+{
+    static const std::vector<int> t = [] {
+        std::vector<int> r;
+        for (int v = 0; v < variant_count(); ++v)
+            if (variant_desc(v).ksplit <= 1) r.push_back(v);
+        return r;
+    }();
+    return t;
+}
+unsigned kinds_of(const nm_packed* wp)
+{
+    unsigned m = 0;
+    for (const Prepack& pp : wp->prepacks) m |= 1u << pp.kind;
+    return m;
 }
 
 // The three-plane form of an fp32 layer that runs without tuning, -1 where the fp32 instruction does it.
@@ -401,12 +459,31 @@ int split_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
     const bool wide = cout > 64 && (sparse || 16 * c128 <= 9 * c64);
     const long t64 = (long)((P + 63) / 64) * (wide ? c128 : c64), t32 = (long)((P + 31) / 32) * c128;
     const int nblk = t64 >= kNumCU ? 4 : 2, nj = wide && (nblk == 4 || t32 >= 100) ? 2 : 1;
-    for (int v = 0; v < variant_count(); ++v) {
+    for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
-        if (is_split_kind(d.kind) && d.ksplit <= 1 && d.NBLK == nblk && d.WP == 1 && d.NJ == nj && variant_legal(v, wp, xdt, ra))
+        if (is_split_kind(d.kind) && d.NBLK == nblk && d.WP == 1 && d.NJ == nj && variant_legal(v, wp, xdt, ra))
             return v;
     }
     return -1;
+}
+
+// The row-staged form of a layer with few input channels that runs without tuning: as many output rows a
+// workgroup as leave every CU two workgroups, at most 8 in bf16 and 4 in fp32 (the planes' LDS).  Measured on the
+// 224x224x3 -> 64 7x7 layer, 1, 2, 4, 8 rows: bf16 batch 64 58, 47, 39, 36 us (a strip of runs per pixel: 80), batch 1
+// 5.6, 6.7, 8.6, 12.7 (5.6); fp32 batch 64 146, 121, 112, 155 (element-wise: 190), batch 1 10.2, 13.2, 20.6, 35 (9.7).
+int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
+{
+    const int wo = (ra.w + 2 * ra.pw - ra.dw * (wp->kw - 1) - 1) / ra.sw + 1;
+    int pick = -1;
+    for (int v : base_variants()) {
+        const VariantDesc& d = variant_desc(v);
+        if (!is_rows_kind(d.kind) || !variant_legal(v, wp, xdt, &ra)) continue;
+        const long n_wg = (long)(P / wo + d.NBLK - 1) / d.NBLK * ((wp->cout + 63) / 64);
+        if (d.NBLK > (d.kind == 10 ? 8 : 4) || (d.NBLK > 1 && n_wg < 2L * kNumCU)) continue;
+        // (within one form the table lists the heights in ascending order, and the wider form last)
+        pick = v;
+    }
+    return pick;
 }
 
 // Deterministic default when the shape has not been tuned: a small model of
@@ -421,11 +498,16 @@ int split_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 // chunks on deep, small layers, 64 otherwise.  Variants are ranked by their distance from that.
 int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 {
-    if (xdt == NM_F32) {
+    const unsigned kinds = kinds_of(wp);
+    if (ra && (kinds & (1u << 10 | 1u << 11))) {
+        const int v = rows_default(wp, P, xdt, *ra);
+        if (v >= 0) return v;
+    }
+    if (xdt == NM_F32 && (kinds & (1u << 8 | 1u << 9))) {
         const int v = split_default(wp, P, xdt, ra);
         if (v >= 0) return v;
     }
-    {
+    if (kinds & (1u << 2 | 1u << 3 | 1u << 7)) {
         const long wg128 = (long)((P + 127) / 128) * ((wp->n_rowblocks + 7) / 8);
         const int bp_t = wg128 >= kNumCU / 2 ? 128 : 64;
         const int wgc_t = wp->n_rowblocks >= 8 ? 128 : 64;
@@ -435,9 +517,9 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
         auto lg = [](double a, double b) { return fabs(log2(a / b)); };
         int pick = -1;
         double pick_score = 0;
-        for (int v = 0; v < variant_count(); ++v) {
+        for (int v : base_variants()) {
             const VariantDesc& d = variant_desc(v);
-            if (d.kind != 2 && d.kind != 3 && d.kind != 7) continue;
+            if ((d.kind != 2 && d.kind != 3 && d.kind != 7) || !(kinds >> d.kind & 1u)) continue;
             if (!variant_legal(v, wp, xdt, ra)) continue;
             const int wgc = (4 / d.WP) * d.NJ * 16;
             double score = 4.0 * lg(d.BP, bp_t) + 4.0 * lg(wgc, wgc_t) + 1.0 * lg(d.CK, ck_t) + (d.WP != 1 ? 1.5 : 0.0);
@@ -452,11 +534,11 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
     }
     int best = -1;
     double best_cost = 0;
-    for (int v = 0; v < variant_count(); ++v) {
-        if (!variant_legal(v, wp, xdt, ra)) continue;
+    // (a K split needs a workspace: only where the tuner has shown that it pays)
+    for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
-        if (is_split_kind(d.kind)) continue;   // (split_default)
-        if (d.ksplit > 1) continue;   // a K split needs a workspace: only where the tuner has shown that it pays
+        if (flat_rowblocks(d.kind) || !(kinds >> d.kind & 1u)) continue;   // (split_default, rows_default)
+        if (!variant_legal(v, wp, xdt, ra)) continue;
         const int rb_per_wg = (4 / d.WP) * d.NJ;
         const long n_pt = (P + d.BP - 1) / d.BP;
         const long n_cb = (wp->n_rowblocks + rb_per_wg - 1) / rb_per_wg;
@@ -719,6 +801,18 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
             if (pp.wfrag_bytes < kWindow) wp->prepacks.push_back(pp);
             continue;
         }
+        if (is_rows_kind(d.kind)) {
+            // the same runs out of staged rows: one table per alignment and number of k-steps
+            if (d.kind == 10 ? value_dtype != NM_BF16 || cin % 8 == 0 : value_dtype != NM_F32 || cin % 4 == 0) continue;
+            for (int par = 0; par < 2; ++par) {
+                if (run_ksteps(wp, par) != d.SPC || find_prepack(wp, d, par)) continue;
+                pp.geom.vec = 1; pp.geom.CK = d.CK; pp.geom.ncpt = 1; pp.geom.nchunks = 1;
+                pp.par = par;
+                pp.wfrag_bytes = (size_t)((cout + 15) / 16) * d.SPC * 2 * (d.kind == 10 ? 1 : 3) * 1024;
+                if (pp.wfrag_bytes < kWindow) wp->prepacks.push_back(pp);
+            }
+            continue;
+        }
         if (d.kind == 4) {
             // kernel-row runs: only where channel runs are too short for the other bf16 kernels
             if (value_dtype != NM_BF16 || cin % 8 == 0) continue;
@@ -958,7 +1052,7 @@ static int conv2d_impl(const void* x, nm_dtype_t xdt, int b, int h, int w, int c
             if (it != g_cache.end()) v = it->second.variant;
         }
     }
-    const RunArgs ra = {w, sw, pw, dw};
+    const RunArgs ra = {w, sw, pw, dw, sh, dh};
     if (v >= 0 && !variant_legal(v, wp, xdt, &ra)) {
         if (forced) {
             set_error("variant %d (%s) cannot run this layer", v, nm_variant_name(v));
@@ -1107,7 +1201,7 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
     int rc = conv_geometry(b, h, w, wp, sh, sw, ph, pw, dh, dw, elem_size(xdt), &g);
     if (rc != NM_OK) return rc;
     const ShapeKey key = make_key(xdt, ydt, b, h, w, wp, sh, sw, ph, pw, dh, dw, has_bias, relu);
-    const RunArgs ra = {w, sw, pw, dw};
+    const RunArgs ra = {w, sw, pw, dw, sh, dh};
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
@@ -1198,7 +1292,7 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
         if (!variant_legal(v, wp, xdt, &ra)) continue;
         {   // a K split is worth its second kernel only where the output tiles are one short, ragged round (at most two per CU)
             const VariantDesc& d = variant_desc(v);
-            const int nrb = is_split_kind(d.kind) ? (wp->cout + 15) / 16 : wp->n_rowblocks;
+            const int nrb = flat_rowblocks(d.kind) ? (wp->cout + 15) / 16 : wp->n_rowblocks;
             const long tiles = (long)((g.P + d.BP - 1) / d.BP) * ((nrb + (4 / d.WP) * d.NJ - 1) / ((4 / d.WP) * d.NJ));
             if (d.ksplit > 1 && (tiles > 2 * kNumCU || tiles * d.ksplit > 8 * kNumCU)) continue;
         }

@@ -75,11 +75,18 @@ struct Entry {
 #define NM_ENTRYSD(NB, WP, NJ)                                                                  \
     {{"X3D_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 9, 1, 1, 0, 1}, &launch_split_t<NB, WP, NJ, false>, nullptr},
 
+// kinds 10 (bf16) and 11 (fp32): few input channels out of staged rows; NBLK is the number of output rows
+#define NM_ENTRYROWB(R, NJ, KS) {{"RUN_ROWS" #R "_NJ" #NJ "_KS" #KS, 16, R, 4 / (4 / NJ), NJ, 64 * KS, KS, 1, 10, 1, 1, 0}, nullptr, &launch_rows_t<1, NJ, KS>},
+#define NM_ENTRYROWF(R, NJ, KS) {{"ROWF_R" #R "_NJ" #NJ "_KS" #KS, 16, R, 4 / (4 / NJ), NJ, 64 * KS, KS, 1, 11, 1, 1, 0}, &launch_rows_t<3, NJ, KS>, nullptr},
+#define NM_HEIGHTSB(NJ, KS) NMROW_HEIGHTS(NM_ENTRYROWB, NJ, KS)
+#define NM_HEIGHTSF(NJ, KS) NMROW_HEIGHTS(NM_ENTRYROWF, NJ, KS)
+
 const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTRY)
                           NM16_SHAPES(NM_SHAPE_ENTRIES16) NMSP_SHAPES(NM_SHAPE_ENTRIESSP) NMSPW_SHAPES(NM_SHAPE_ENTRIESSPW) NMSPR_SHAPES(NM_SHAPE_ENTRIESSPR)
                           NMRUN_SHAPES(NM_SHAPE_ENTRIESRUN) NMVAR_SHAPES(NM_SHAPE_ENTRIESVAR)
                           NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)
-                          NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)};
+                          NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)
+                          NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
 // The fp32 kernels also run with their K axis split over several workgroups per output

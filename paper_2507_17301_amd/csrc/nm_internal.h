@@ -65,6 +65,7 @@ struct Prepack {
                                       // 4: bf16 kernel-row runs, 5: fp32 MFMA kernel with per-chunk step counts,
                                       // 6, 7: fp8 kernels (dense instruction on zero-filled weights), register-streaming
                                       // and LDS-staged
+                                      // 10, 11: few input channels out of staged rows (bf16, fp32)
                                       // 8, 9: fp32 as three bf16 planes (sparse instruction, dense instruction)
     ChunkGeom geom{};
     int SPC = 0;                      // k-steps per chunk (1, 2, 4 or 8)
@@ -89,7 +90,9 @@ struct Prepack {
     //   block is 16 consecutive output channels whatever the column tile
     //   d_rows  [row blocks][nchunks][64] u32         kind 8: index operand of each lane
     //   d_wfrag [row blocks][nchunks][3][AH][64][8] bf16   A-operand lane values of the three planes, AH = 1 (kind 8) or 2
-    int par = 0;                      // kind 4: 0 or 1 elements of lead-in per run (alignment of the run start)
+    // kinds 10 and 11: as kind 4 with 1 or 3 planes and row blocks of 16 consecutive output channels:
+    //   d_wfrag [row blocks][SPC][2][planes][64][8] bf16
+    int par = 0;                      // kinds 4, 10, 11: 0 or 1 elements of lead-in per run (alignment of the run start)
     uint32_t* d_rows = nullptr;
     float* d_wfrag = nullptr;
     size_t rows_bytes = 0, wfrag_bytes = 0, ktab_bytes = 0;   // (all inside the handle's d_tables block)
@@ -157,6 +160,10 @@ struct ConvParams {
     unsigned howo_mul, howo_shift, wo_mul, wo_shift;
     int run_gr, run_d; // kind 4: granules per kernel-row run, lead-in elements of a run
     unsigned gr_mul, gr_shift, cin_mul, cin_shift;   // kind 4: multiply-shift pairs for / run_gr and / Cin
+    // kinds 10, 11: output rows a workgroup, staged input rows, bytes of one, of the room before the run of column 0
+    // and before the data, of all planes together (whole 1 KB windows)
+    int rows_r, rows_n, rows_pitch, rows_front, rows_data, rows_lds;
+    unsigned rowg_mul, rowg_shift;   // division by the 16-byte granules of a row
     unsigned x_elems;  // elements of x
     unsigned x_bytes;  // size of x in bytes (< 2 GiB), the range of the buffer descriptor
     unsigned wfrag_bytes, rows_bytes;
@@ -186,6 +193,7 @@ struct VariantDesc {
                // 4 = bf16 dense kernel on contiguous kernel-row runs (very few input channels),
                // 5 = fp32 MFMA kernel that runs only the k-steps holding kept columns of each (tile, chunk)
                // 6 = fp8 E4M3 kernel (fp8 activations, bf16 output): dense instruction on zero-filled weights
+               // 10, 11 = few input channels out of staged rows, bf16 and fp32 (NBLK = output rows a workgroup)
                // 8, 9 = fp32 tensors as three bf16 planes on the sparse / dense bf16 instruction
     int share; // kind 1: row blocks fed from one gathered operand
     int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)

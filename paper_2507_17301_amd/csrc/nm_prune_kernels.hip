@@ -332,7 +332,7 @@ __global__ __launch_bounds__(256) void build_prepack_sp16_kernel(
 // E / (8 GR); positions outside [0, Kw*Cin) and rows >= Kh are padding (weight 0).
 __global__ __launch_bounds__(256) void build_prepack_run16_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ vals, int kprime, int T, int rbpt,
-    int n_rowblocks, int Kh, int KwC, int KS, int GR, int par, unsigned short* __restrict__ wfrag)
+    int cout, int n_rowblocks, int planes, int Kh, int KwC, int KS, int GR, int par, unsigned short* __restrict__ wfrag)
 {
     const size_t total = (size_t)n_rowblocks * KS * 2 * 64;
     for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < total;
@@ -343,10 +343,13 @@ __global__ __launch_bounds__(256) void build_prepack_run16_kernel(
         const int s = (int)(r % KS);
         const int rb = (int)(r / KS);
         const int i = lane & 15, q = lane >> 4;
-        const int j = rb / rbpt, sub = rb - j * rbpt;
-        const int t = sub * 16 + i;
+        // planes = 0: row blocks of the column tiles, one bf16 value; else 16 consecutive output channels, 1 or 3 planes
+        const int co = rb * 16 + i;
+        const int j = planes ? (co < cout ? co / T : 0) : rb / rbpt;
+        const int t = planes ? (co < cout ? co - j * T : T) : (rb - j * rbpt) * 16 + i;   // (T: no such row)
         const int32_t* idxj = idx + (size_t)j * kprime;
-        unsigned short* dst = wfrag + id * 8;
+        const int np = planes ? planes : 1;
+        unsigned short* dst = wfrag + (id / 64 * np * 64 + lane) * 8;
         for (int e = 0; e < 8; ++e) {
             const int E = 64 * s + 16 * q + 8 * h + e;
             const int kh = E / (8 * GR);
@@ -357,7 +360,11 @@ __global__ __launch_bounds__(256) void build_prepack_run16_kernel(
                 const int lb = lower_bound_idx(idxj, kprime, k);
                 if (lb < kprime && idxj[lb] == k) v = vals[((size_t)j * kprime + lb) * T + t];
             }
-            dst[e] = (unsigned short)(__float_as_uint(v) >> 16);
+            for (int pl = 0; pl < np; ++pl) {
+                const float top = round_bf16_rne(v);   // (bf16 handles: the value itself)
+                dst[pl * 512 + e] = (unsigned short)(__float_as_uint(top) >> 16);
+                v -= top;
+            }
         }
     }
 }
@@ -550,12 +557,13 @@ int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s)
         hipLaunchKernelGGL(build_prepack_kernel, dim3(wp->n_tiles), dim3(256), lds, s, wp->d_idx,
                            wp->d_vals, wp->kprime, wp->tile, wp->rbpt, wp->cin, g.CK, g.vec, g.ncpt,
                            g.nchunks, pp.SPC, pp.kind == 5 ? 1 : 0, pp.d_rows, pp.d_wfrag, d_err);
-    else if (pp.kind == 4) {
+    else if (pp.kind == 4 || pp.kind >= 10) {
         const int KwC = wp->kw * wp->cin, GR = (pp.par + KwC + 7) / 8;
-        const size_t total = (size_t)wp->n_rowblocks * pp.SPC * 2 * 64;
+        const int nrb = pp.kind == 4 ? wp->n_rowblocks : (wp->cout + 15) / 16;
+        const size_t total = (size_t)nrb * pp.SPC * 2 * 64;
         hipLaunchKernelGGL(build_prepack_run16_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s,
-                           wp->d_idx, wp->d_vals, wp->kprime, wp->tile, wp->rbpt, wp->n_rowblocks, wp->kh,
-                           KwC, pp.SPC, GR, pp.par, reinterpret_cast<unsigned short*>(pp.d_wfrag));
+                           wp->d_idx, wp->d_vals, wp->kprime, wp->tile, wp->rbpt, wp->cout, nrb,
+                           pp.kind == 4 ? 0 : pp.kind == 10 ? 1 : 3, wp->kh, KwC, pp.SPC, GR, pp.par, reinterpret_cast<unsigned short*>(pp.d_wfrag));
     } else if (pp.kind >= 2) {
         const size_t total = (size_t)wp->n_rowblocks * g.nchunks * pp.SPC * (pp.kind == 2 ? 1 : 2) * 64;
         hipLaunchKernelGGL(build_prepack_sp16_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s,

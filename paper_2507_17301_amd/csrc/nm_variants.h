@@ -77,10 +77,11 @@
     Y(NB, WP, NJ, 64, 0) Y(NB, WP, NJ, 128, 0)
 
 // bf16 kernel for layers with very few input channels (contiguous kernel-row
-// runs, one chunk of KS 64-element k-steps).
+// runs, one chunk of KS 64-element k-steps): where output pixels are not whole
+// 16-byte granules, and for very few pixels.
 // X(NBLK, WP, NJ)
 #define NMRUN_SHAPES(X) \
-    X(4, 1, 1) X(8, 1, 1) X(2, 1, 1) X(2, 2, 2) X(4, 2, 2) X(2, 4, 4) X(4, 4, 4) X(1, 4, 4) X(3, 4, 4) X(7, 1, 1)
+    X(4, 1, 1) X(8, 1, 1) X(2, 1, 1) X(2, 2, 2) X(4, 2, 2)
 // Y(NBLK, WP, NJ, KS)
 #define NMRUN_CHUNKS(Y, NB, WP, NJ) Y(NB, WP, NJ, 1) Y(NB, WP, NJ, 2) Y(NB, WP, NJ, 3) Y(NB, WP, NJ, 4)
 
@@ -103,3 +104,9 @@
 // X(NBLK, WP, NJ)
 #define NMSS_SHAPES(X) X(4, 1, 2) X(4, 1, 4) X(3, 1, 2) X(2, 1, 2) X(2, 2, 2) X(4, 1, 1) X(2, 1, 1)
 #define NMSD_SHAPES(X) X(4, 1, 2) X(2, 1, 2) X(2, 2, 2) X(4, 1, 1) X(2, 1, 1)
+
+// few input channels out of staged input rows: R output rows a workgroup, 64 channels, KS 64-element k-steps
+// Y(NJ, KS); X(R, NJ, KS)
+#define NMROWB_CHUNKS(Y) Y(4, 1) Y(4, 2) Y(4, 3) Y(4, 4)
+#define NMROWF_CHUNKS(Y) Y(1, 1) Y(1, 2) Y(1, 3) Y(1, 4) Y(2, 1) Y(2, 2) Y(2, 3)
+#define NMROW_HEIGHTS(X, NJ, KS) X(1, NJ, KS) X(2, NJ, KS) X(4, NJ, KS) X(8, NJ, KS)

@@ -1,0 +1,85 @@
+"""Few input channels out of staged rows (variants RUN_ROWS and ROWF): every form forced on images whose rows, columns and
+output heights end inside a workgroup, both alignments of a run, against the CPU oracle."""
+import numpy as np
+import pytest
+
+from paper_2507_17301_amd import binding as nm
+from paper_2507_17301_amd import workloads as wl
+from gpu_util import FP32_TOL, BF16_TOL, say, norm_err, oracle_conv
+
+pytestmark = pytest.mark.gpu
+
+L = wl.ConvLayer
+
+# H, W, Cin, Cout, Kh, Kw, stride, pad, dil: even and odd heights, rows of x on and off 16 bytes, a lead-in element or
+# none, one to four k-steps, output channels that end inside 64, one output pixel
+GRID = [
+    (L("stem", 30, 32, 3, 64, 7, 7, 2, 3, 1, 1, 1, 16), 2),
+    (L("stem_odd", 29, 26, 3, 64, 7, 7, 2, 3, 1, 1, 1, 16), 3),
+    (L("one_pixel", 7, 8, 3, 16, 7, 7, 2, 0, 1, 1, 1, 16), 1),
+    (L("cin1", 13, 18, 1, 40, 5, 5, 2, 2, 1, 1, 1, 8), 2),
+    (L("cin2_s1", 9, 37, 2, 136, 3, 3, 1, 1, 1, 1, 1, 16), 2),
+    (L("cin3_3x3_pruned", 17, 34, 3, 72, 3, 3, 2, 1, 1, 1, 3, 16), 1),
+    (L("cin5_wide", 11, 16, 5, 64, 6, 5, 2, 1, 1, 1, 1, 16), 1),
+    (L("four_ksteps", 12, 20, 3, 24, 7, 9, 2, 3, 1, 1, 1, 16), 1),
+    (L("cin6_T5", 9, 10, 6, 48, 3, 3, 1, 1, 1, 1, 2, 5), 2),
+]
+
+
+@pytest.mark.parametrize("layer,batch", GRID, ids=[g[0].name for g in GRID])
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+def test_every_form(layer, batch, bf16):
+    import torch
+    x, w, bias = wl.make_tensors(layer, batch, 51, weight_sigma=0.1)
+    dt, tdt = (nm.NM_BF16, torch.bfloat16) if bf16 else (nm.NM_F32, torch.float32)
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile, dt)
+    xd, bd = torch.from_numpy(x).cuda().to(tdt), torch.from_numpy(bias).cuda()
+    ref = oracle_conv(layer, x, w, bias, relu=False, bf16=bf16)
+    res = torch.from_numpy(np.random.default_rng(5).standard_normal(ref.shape, dtype=np.float32)).cuda().to(tdt)
+    tol = BF16_TOL if bf16 else FP32_TOL
+    ran = 0
+    try:
+        for v in range(nm.nm_variant_count()):
+            name = nm.nm_variant_name(v)
+            if not name.startswith(("RUN_ROWS", "ROWF")) or not nm.nm_variant_legal(v, wp, dt, dt):
+                continue
+            say(f"{layer.name} {name}")
+            nm.nm_force_variant(v)
+            try:
+                y = nm.nm_conv2d_res(xd, wp, None, bd, layer.stride, layer.pad, layer.dil, True)
+            except nm.NMError:                  # the k-steps of the other alignment
+                continue
+            z = nm.nm_conv2d_res(xd, wp, res, None, layer.stride, layer.pad, layer.dil, False)
+            torch.cuda.synchronize()
+            assert norm_err(y.float().cpu().numpy(), np.maximum(ref, 0)) <= tol, name
+            assert norm_err(z.float().cpu().numpy(), ref - bias + res.float().cpu().numpy()) <= 2 * tol, name   # (ref is rounded too)
+            ran += 1
+    finally:
+        nm.nm_force_variant(-1)
+    # cin6 is a multiple of neither 4 nor 8, cin 1, 2, 3, 5 likewise: both tensor types have the form wherever rows are even
+    assert ran or (layer.W * layer.Cin) % 2 or (layer.stride * layer.Cin) % 2
+
+
+def test_infinity_and_default():
+    """An infinite pixel reaches exactly the outputs that the element-wise form gives it, and the untuned default runs."""
+    import torch
+    layer = L("stem", 30, 32, 3, 64, 7, 7, 2, 3, 1, 1, 1, 16)
+    x, w, bias = wl.make_tensors(layer, 2, 53)
+    x[0, 10, 10, 1], x[1, 0, 0, 2] = np.inf, 1e-38
+    wp = nm.nm_prune(w, 1, 1, 16)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    y = nm.nm_conv2d(xd, wp, bd, 2, 3, 1, False)
+    assert nm.nm_variant_name(nm.nm_last_variant()).startswith("ROWF")
+    base = next(v for v in range(nm.nm_variant_count()) if nm.nm_variant_name(v).startswith("NB4_WP1_NJ1") and nm.nm_variant_legal(v, wp))
+    nm.nm_force_variant(base)
+    try:
+        ref = nm.nm_conv2d(xd, wp, bd, 2, 3, 1, False)
+        torch.cuda.synchronize()
+    finally:
+        nm.nm_force_variant(-1)
+    y, ref = y.cpu().numpy(), ref.cpu().numpy()
+    fin = np.isfinite(ref)
+    # (a run's padding slots are read with weight 0: next to the infinity they may turn a finite sum into NaN, and such
+    #  a sum is computed again without them)
+    assert (np.isinf(y) == np.isinf(ref)).all() and (np.isnan(y) == np.isnan(ref)).all()
+    assert norm_err(y[fin], ref[fin]) <= FP32_TOL
