@@ -232,20 +232,22 @@ __global__ __launch_bounds__(256) void nm_conv_bf16_kernel(const ConvParams p)
     if (WGC * 2 >= 128 && tile_out_ok<bf16_t>(p)) {
         // whole 128-byte lines through the LDS tile (the last chunk ended with a barrier)
         constexpr int PITCH = tile_pitch<bf16_t>(WGC);
+        if (p.res) {
+            ResTile<bf16_t, BP, WGC> rt;
+            rt.load(p, tid, p0, cblock * WGC);
+            rt.put(lds8, tid);
+            __syncthreads();
+        }
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             const int rb = rb0 + jj;
             const int co = rb * 16 + q * 4;       // T is a multiple of 16: row block rb is channels 16 rb ..
-            const bool row_live = rb < p.n_rowblocks && co < p.Cout;
             f4 bb = {0.f, 0.f, 0.f, 0.f};
-            if (p.bias && row_live) bb = *reinterpret_cast<const f4*>(p.bias + co);
+            if (p.bias && rb < p.n_rowblocks && co < p.Cout) bb = *reinterpret_cast<const f4*>(p.bias + co);
 #pragma unroll
             for (int b = 0; b < NBLK; ++b) {
                 const int pl = wpix + b * 16 + n;
-                const int pp = p0 + pl;
-                tile_put4<bf16_t>(p, lds8 + pl * PITCH + ((wcx * NJ + jj) * 16 + q * 4) * 2,
-                                  (unsigned)pp * (unsigned)p.Cout + (unsigned)co, row_live && pp < p.P,
-                                  acc[jj][b] + bb);
+                tile_put4_lds<bf16_t>(p, lds8 + pl * PITCH + ((wcx * NJ + jj) * 16 + q * 4) * 2, acc[jj][b] + bb);
             }
         }
         __syncthreads();

@@ -1,5 +1,5 @@
-"""The residual of the bf16 and fp8 convolutions, fetched in whole rows into the output tile: every form of the
-gather-free kernel on pixel and channel counts that end inside a tile, against the CPU oracle."""
+"""The residual of the bf16 and fp8 convolutions, fetched in whole rows into the output tile: every form of the gather and
+gather-free kernels on pixel and channel counts that end inside a tile, against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -41,7 +41,7 @@ def test_residual_every_form(layer, batch, dtype):
     try:
         for v in range(nm.nm_variant_count()):
             name = nm.nm_variant_name(v)
-            if not name.startswith(("SP", "F8S", "F8W", "F8R")) or not nm.nm_variant_legal(v, wp, dt, nm.NM_BF16):
+            if not name.startswith(("SP", "B16", "F8S", "F8W", "F8R")) or not nm.nm_variant_legal(v, wp, dt, nm.NM_BF16):
                 continue
             say(f"{layer.name} {dtype} {name}")
             nm.nm_force_variant(v)
