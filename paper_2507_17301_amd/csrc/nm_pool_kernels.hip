@@ -193,25 +193,30 @@ __global__ __launch_bounds__(256) void stream_floor_kernel(const u4v* __restrict
 // Where the partial sums of a K split meet: one thread per 4 consecutive channels of one
 // pixel (or per element when Cout is not a multiple of 4) adds the splits in ascending order,
 // then bias, residual, activation, one rounding.
-template <typename TOUT>
+// S splits are all requested before the first is added.
+template <typename TOUT, int S>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ConvParams p)
 {
-    const size_t total = (size_t)p.P * p.Cout;
+    const unsigned total = (unsigned)p.P * (unsigned)p.Cout;   // below 2^31
     TOUT* __restrict__ y = reinterpret_cast<TOUT*>(p.y);
+    const float* __restrict__ part = p.partial;
     if (p.Cout % 4 == 0) {
-        const size_t n4 = total / 4;
-        for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x) {
-            f4 v = *reinterpret_cast<const f4*>(p.partial + i * 4);
-            for (int s = 1; s < p.ksplit; ++s) v = v + *reinterpret_cast<const f4*>(p.partial + (size_t)s * total + i * 4);
-            if (p.bias) v = v + *reinterpret_cast<const f4*>(p.bias + (i * 4) % (size_t)p.Cout);
-            emit4(p, y, (unsigned)(i * 4), v);
+        for (unsigned i = (blockIdx.x * blockDim.x + threadIdx.x) * 4; i < total; i += gridDim.x * blockDim.x * 4) {
+            f4 v[S];
+#pragma unroll
+            for (int s = 0; s < S; ++s) v[s] = *reinterpret_cast<const f4*>(part + (size_t)s * total + i);
+            f4 t = v[0];
+#pragma unroll
+            for (int s = 1; s < S; ++s) t = t + v[s];
+            if (p.bias) t = t + *reinterpret_cast<const f4*>(p.bias + i % (unsigned)p.Cout);
+            emit4(p, y, i, t);
         }
     } else {
-        for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-            float v = p.partial[i];
-            for (int s = 1; s < p.ksplit; ++s) v += p.partial[(size_t)s * total + i];
-            if (p.bias) v += p.bias[i % (size_t)p.Cout];
-            emit1(p, y, (unsigned)i, v);
+        for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+            float v = part[i];
+            for (int s = 1; s < S; ++s) v += part[(size_t)s * total + i];
+            if (p.bias) v += p.bias[i % (unsigned)p.Cout];
+            emit1(p, y, i, v);
         }
     }
 }
@@ -223,10 +228,22 @@ int run_splitk_reduce(const ConvParams& p, nm_dtype_t ydt, hipStream_t s)
     const size_t total = (size_t)p.P * p.Cout;
     const size_t items = p.Cout % 4 == 0 ? total / 4 : total;
     const int grid = grid_for_items(items);
-    if (ydt == NM_F32)
-        hipLaunchKernelGGL(splitk_reduce_kernel<float>, dim3(grid), dim3(256), 0, s, p);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<bf16_t>, dim3(grid), dim3(256), 0, s, p);
+#define NM_REDUCE(T, S) hipLaunchKernelGGL((splitk_reduce_kernel<T, S>), dim3(grid), dim3(256), 0, s, p)
+#define NM_REDUCE_ANY(T)              \
+    switch (p.ksplit) {               \
+    case 2: NM_REDUCE(T, 2); break;   \
+    case 4: NM_REDUCE(T, 4); break;   \
+    case 8: NM_REDUCE(T, 8); break;   \
+    case 16: NM_REDUCE(T, 16); break; \
+    default: set_error("internal: no reduction of %d splits", p.ksplit); return NM_ERR_UNSUPPORTED; \
+    }
+    if (ydt == NM_F32) {
+        NM_REDUCE_ANY(float)
+    } else {
+        NM_REDUCE_ANY(bf16_t)
+    }
+#undef NM_REDUCE_ANY
+#undef NM_REDUCE
     NM_HIP_CHECK(hipGetLastError());
     return NM_OK;
 }
