@@ -776,7 +776,7 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
     GeomNeeds needs{wp, {}, {}};
     const bool vec_ok = cin % 4 == 0;
     const size_t kWindow = 0x80000000ull;   // the kernels read a table through a 2 GiB buffer window
-    for (int v = 0; v < variant_count(); ++v) {
+    for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
         if (is_f8_kind(d.kind) != (value_dtype == NM_F8E4M3)) continue;   // E4M3 handles feed the fp8 kernels only
         Prepack pp;

@@ -134,62 +134,71 @@ __device__ inline void chunk_of(int k, int cin, int CK, int vec, int ncpt, int* 
     }
 }
 
-// One workgroup per column tile.  Kept columns are ascending in k, hence
+__device__ inline int lower_bound_idx(const int32_t* a, int n, int key)
+{
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (a[mid] < key) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// First k of the chunk that column k belongs to, its number, and the first k beyond it.
+__device__ inline void chunk_span(int k, int cin, int CK, int vec, int ncpt, int* c, int* k0, int* k1)
+{
+    int r;
+    chunk_of(k, cin, CK, vec, ncpt, c, &r);
+    *k0 = k - r;
+    const int tap_end = vec ? (k / cin + 1) * cin : 0x7fffffff;
+    *k1 = *k0 + CK < tap_end ? *k0 + CK : tap_end;
+}
+
+// One thread per (kept column, row of its column tile's row blocks).  Kept columns are ascending in k, hence
 // grouped by chunk; the i-th kept column of a chunk becomes quarter i % 4 of
 // k-step i / 4 of that chunk.  Outputs (zero-initialised by the caller):
-//   rows [j][c][q][SPC] u32      LDS row (strip_row() in vector mode) of the kept column used by quarter q in step s
+//   rows [j][c][q][SPC] u32      LDS row (strip_row() in vector mode) of the kept column used by quarter q in step s;
+//                                with_counts: the chunk's number of k-steps in the upper half of the first word
 //   wfrag[rb][c][lane][SPC]      weight for MFMA A-operand lane (q*16 + t)
 // err[0] is set if a chunk holds more than 4*SPC kept columns.
+// (One workgroup per column tile, its columns counted per chunk by one thread, took 38 us for 512x3x3x512.)
 __global__ __launch_bounds__(256) void build_prepack_kernel(
-    const int32_t* __restrict__ idx, const float* __restrict__ vals, int kprime, int T, int rbpt,
+    const int32_t* __restrict__ idx, const float* __restrict__ vals, int n_tiles, int kprime, int T, int rbpt,
     int cin, int CK, int vec, int ncpt, int nchunks, int SPC, int with_counts,
     uint32_t* __restrict__ rows, float* __restrict__ wfrag, int* __restrict__ err)
 {
-    extern __shared__ int sm_int[];
-    int* cnt = sm_int;             // [nchunks]
-    int* first = sm_int + nchunks; // [nchunks]
-    const int j = blockIdx.x;
-    const int32_t* idxj = idx + (size_t)j * kprime;
-    for (int c = threadIdx.x; c < nchunks; c += blockDim.x) cnt[c] = 0;
-    __syncthreads();
-    for (int kk = threadIdx.x; kk < kprime; kk += blockDim.x) {
-        int c, r;
-        chunk_of(idxj[kk], cin, CK, vec, ncpt, &c, &r);
-        atomicAdd(&cnt[c], 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int c = 0; c < nchunks; ++c) {
-            first[c] = run;
-            run += cnt[c];
-            if (cnt[c] > 4 * SPC) err[0] = 1;
+    const int R = rbpt * 16;                     // rows of a column tile, whole row blocks
+    const size_t total = (size_t)n_tiles * kprime * R;
+    for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < total; id += (size_t)gridDim.x * blockDim.x) {
+        const int tt = (int)(id % R);
+        const size_t jk = id / R;
+        const int j = (int)(jk / kprime), kk = (int)(jk - (size_t)j * kprime);
+        const int32_t* idxj = idx + (size_t)j * kprime;
+        const int k = idxj[kk];
+        int c, k0, k1;
+        chunk_span(k, cin, CK, vec, ncpt, &c, &k0, &k1);
+        const int first = lower_bound_idx(idxj, kprime, k0);
+        const int i = kk - first, step = i >> 2, q = i & 3;
+        if (step >= SPC) {
+            err[0] = 1;
+            continue;
         }
-    }
-    __syncthreads();
-    for (int kk = threadIdx.x; kk < kprime; kk += blockDim.x) {
-        int c, r;
-        chunk_of(idxj[kk], cin, CK, vec, ncpt, &c, &r);
-        const int i = kk - first[c];
-        const int step = i >> 2, q = i & 3;
-        if (step >= SPC) continue;
-        rows[(((size_t)j * nchunks + c) * 4 + q) * SPC + step] = (uint32_t)(vec ? strip_row(r, CK) : r);
-        for (int sub = 0; sub < rbpt; ++sub) {
-            const size_t rb = (size_t)j * rbpt + sub;
-            for (int t = 0; t < 16; ++t) {
-                const int tt = sub * 16 + t;
-                const float v = tt < T ? vals[((size_t)j * kprime + kk) * T + tt] : 0.f;
-                wfrag[((rb * nchunks + c) * 64 + q * 16 + t) * SPC + step] = v;
+        if (tt == 0) {
+            const uint32_t row = (uint32_t)(vec ? strip_row(k - k0, CK) : k - k0);
+            uint32_t* const w = rows + (((size_t)j * nchunks + c) * 4 + q) * SPC + step;
+            if (with_counts && i < 4) {
+                // (all four quarters carry the count, also those without a column)
+                const int cnt = lower_bound_idx(idxj, kprime, k1) - first;
+                const uint32_t steps = (uint32_t)((cnt + 3) >> 2) << 16;
+                *w = row | steps;
+                if (i == 0)
+                    for (int e = cnt; e < 4; ++e) w[(size_t)e * SPC] = steps;
+            } else {
+                *w = row;
             }
         }
-    }
-    if (with_counts) {
-        // number of k-steps that hold kept columns, in the upper half of each quarter's first word
-        __syncthreads();
-        for (int i = threadIdx.x; i < nchunks * 4; i += blockDim.x) {
-            const int c = i >> 2, q = i & 3;
-            rows[(((size_t)j * nchunks + c) * 4 + q) * SPC] |= (uint32_t)((cnt[c] + 3) >> 2) << 16;
-        }
+        const size_t rb = (size_t)j * rbpt + (tt >> 4);
+        wfrag[((rb * nchunks + c) * 64 + q * 16 + (tt & 15)) * SPC + step] = tt < T ? vals[jk * T + tt] : 0.f;
     }
 }
 
@@ -255,16 +264,6 @@ __global__ __launch_bounds__(256) void build_prepack16_kernel(
 //     positions go to field ea of the lane group's index operand.
 //   dense: element e of lane i + 16 q, half h is channel 16 q + 8 h + e of the
 //     k-step, its weight or 0.
-__device__ inline int lower_bound_idx(const int32_t* a, int n, int key)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 __global__ __launch_bounds__(256) void build_prepack_sp16_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ vals, int kprime, int T, int rbpt,
     int n_rowblocks, int cin, int CK, int ncpt, int nchunks, int sparse,
@@ -554,8 +553,8 @@ int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s)
                            wp->d_vals, wp->kprime, wp->tile, wp->rbpt, wp->n_rowblocks, wp->cin, ncpt64,
                            nk64, wp->scale, reinterpret_cast<unsigned char*>(pp.d_wfrag));
     } else if (pp.kind == 0 || pp.kind == 5)
-        hipLaunchKernelGGL(build_prepack_kernel, dim3(wp->n_tiles), dim3(256), lds, s, wp->d_idx,
-                           wp->d_vals, wp->kprime, wp->tile, wp->rbpt, wp->cin, g.CK, g.vec, g.ncpt,
+        hipLaunchKernelGGL(build_prepack_kernel, dim3(grid_for((size_t)wp->n_tiles * wp->kprime * wp->rbpt * 16, 256)),
+                           dim3(256), 0, s, wp->d_idx, wp->d_vals, wp->n_tiles, wp->kprime, wp->tile, wp->rbpt, wp->cin, g.CK, g.vec, g.ncpt,
                            g.nchunks, pp.SPC, pp.kind == 5 ? 1 : 0, pp.d_rows, pp.d_wfrag, d_err);
     else if (pp.kind == 4 || pp.kind >= 10) {
         const int KwC = wp->kw * wp->cin, GR = (pp.par + KwC + 7) / 8;
