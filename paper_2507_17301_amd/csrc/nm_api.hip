@@ -486,12 +486,45 @@ int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
     return pick;
 }
 
-// Deterministic default when the shape has not been tuned: a small model of
-// "rounds of workgroups x work per workgroup", preferring tiles that fill the
-// 256 CUs and reuse the staged strip across many row blocks.
+// Clocks of one launch of an fp32-instruction (kinds 0, 5) or gather (kind 1) variant, up to a constant: the
+// contraction, staging and barrier of a chunk in one wavefront, shared by the wavefronts of a SIMD, times the
+// chunks; the start and the output of a workgroup; the rounds of workgroups that the CUs hold.  The factors were
+// fitted to every variant's time on 407 random layers (4 to 500 odd and even channels, 1:4 to 4:8 and half of all
+// channels, T 8 to 32, 100 to 300 000 pixels): the variant it picks takes x1.04 (fp32) and x1.05 (bf16) of the time
+// of the fastest without a K split on average, x1.36 at worst.  "Rounds x tile area", which knows neither the
+// number nor the depth of the chunks, was x1.23 and x1.42 (x2.3 and x4.0 at worst: 256-channel chunks on eight
+// channels, say).
+double model_clocks(const VariantDesc& d, const nm_packed* wp, int P)
+{
+    const int rb_per_wg = (4 / d.WP) * d.NJ;
+    const double n_wg = (double)((P + d.BP - 1) / d.BP) * ((wp->n_rowblocks + rb_per_wg - 1) / rb_per_wg);
+    const int nchunks = d.vec ? wp->kh * wp->kw * ((wp->cin + d.CK - 1) / d.CK) : (wp->K + d.CK - 1) / d.CK;
+    const double kept = (double)std::min(d.CK, d.vec ? wp->cin : wp->K) * wp->n / wp->m;   // columns of a chunk
+    const bool gather = d.kind == 1;
+    const double items = (double)d.BP * d.CK / (gather ? 2048 : 1024);                    // staged 16 bytes a thread
+    // registers: accumulators, two sets of operands, staged values and their addresses; the forms beyond 200 spill
+    const double regs = 40.0 + 4.0 * d.NBLK * d.NJ + 8.0 * items + 4.0 * d.NJ * d.SPC * (d.kind == 0 ? 1.0 : gather ? 3.0 : 2.4);
+    if (regs > 200.0) return 1e18 + regs;
+    const double steps = d.kind == 5 ? kept / 4 : d.SPC;
+    const double mfma = gather ? d.NBLK * d.SPC * (d.NJ * 16.0 + 29.0 * d.NJ / d.share)    // and the 2-byte reads
+                               : d.NBLK * d.NJ * 32.0 * (d.kind == 5 ? steps + 0.3 : steps);
+    const double reads = gather ? 0.0 : 6.9 * (d.NBLK / 4.0 + 2.1) * d.NJ * steps;
+    const double chunk = mfma + reads + items * (gather ? 45.0 : 36.6) + 16.0 + (d.kind == 5 ? 10.0 * d.NJ : 0.0);
+    const double ends = 453.0 * d.NBLK * d.NJ + 18.0 * items;   // the workgroup's output and its first staging
+    const int occ = std::max(1, std::min({(int)(kMaxLdsBytes / lds_bytes(d, wp)), (int)(512.0 / regs), 8}));
+    const double per_cu = n_wg / kNumCU;
+    if (per_cu <= occ) {
+        const double w = ceil(per_cu);
+        return nchunks * std::max(431.0, w * chunk) + (w + 1.13) * ends;
+    }
+    const double rounds = per_cu / occ;
+    return (0.32 * ceil(rounds) + 0.68 * rounds) * (5020.0 + nchunks * std::max(431.0, occ * chunk) + occ * ends) + 1.13 * ends;
+}
+
+// Deterministic default when the shape has not been tuned: rows_default, split_default, else the cheapest by
+// model_clocks.
 //
-// For the gather-free bf16 and the staged fp8 kernels the model is replaced by a rule read off
-// tuned ResNet stacks (the model's picks ran x1.46 behind the tuned ones there): a tile of 128
+// For the gather-free bf16 and the staged fp8 kernels there is a rule read off tuned ResNet stacks: a tile of 128
 // pixels x 128 channels (64 pixels where that leaves under half the CUs a workgroup, 64 channels
 // where the layer has no more), all four wavefronts along the channels; producer wavefronts and
 // register-held weights unless the launch is many rounds of workgroups on a 1x1 layer; 128-channel
@@ -532,25 +565,30 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
         }
         if (pick >= 0) return pick;
     }
+    // (a K split needs a workspace: only where the tuner has shown that it pays)
     int best = -1;
     double best_cost = 0;
-    // (a K split needs a workspace: only where the tuner has shown that it pays)
+    // the kernel-row-run and the register-streaming fp8 forms where they apply: rounds of workgroups x work of one
+    if (kinds & (1u << 4 | 1u << 6))
+        for (int v : base_variants()) {
+            const VariantDesc& d = variant_desc(v);
+            if ((d.kind != 4 && d.kind != 6) || !variant_legal(v, wp, xdt, ra)) continue;
+            const int rb_per_wg = (4 / d.WP) * d.NJ;
+            const long n_wg = (long)((P + d.BP - 1) / d.BP) * ((wp->n_rowblocks + rb_per_wg - 1) / rb_per_wg);
+            const int occ = std::max(1, (int)std::min<size_t>(2, kMaxLdsBytes / lds_bytes(d, wp)));
+            const long rounds = (n_wg + (long)kNumCU * occ - 1) / ((long)kNumCU * occ);
+            const double cost = (double)rounds * occ * d.BP * (rb_per_wg + 2.0);
+            if (best < 0 || cost < best_cost * 0.999) {
+                best = v;
+                best_cost = cost;
+            }
+        }
+    if (best >= 0) return best;
     for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
-        if (flat_rowblocks(d.kind) || !(kinds >> d.kind & 1u)) continue;   // (split_default, rows_default)
+        if ((d.kind != 0 && d.kind != 1 && d.kind != 5) || !(kinds >> d.kind & 1u)) continue;
         if (!variant_legal(v, wp, xdt, ra)) continue;
-        const int rb_per_wg = (4 / d.WP) * d.NJ;
-        const long n_pt = (P + d.BP - 1) / d.BP;
-        const long n_cb = (wp->n_rowblocks + rb_per_wg - 1) / rb_per_wg;
-        const long n_wg = n_pt * n_cb;
-        int occ = (int)std::min<size_t>(2, kMaxLdsBytes / lds_bytes(d, wp));
-        if (occ < 1) occ = 1;
-        const long rounds = (n_wg + (long)kNumCU * occ - 1) / ((long)kNumCU * occ);
-        const double mfma = (double)d.BP * rb_per_wg;            // per chunk step, relative
-        const double stage = (double)d.BP * 2.0;                 // staging cost per chunk, relative
-        // the bf16 matrix-core kernel contracts several times faster where it applies
-        const double speed[8] = {1.0, 0.3, 0.1, 0.2, 0.1, 0.7, 0.12, 0.1};   // relative cost of a unit of contraction
-        const double cost = (double)rounds * occ * (mfma + stage) * speed[d.kind];
+        const double cost = model_clocks(d, wp, P);
         if (best < 0 || cost < best_cost * 0.999) {
             best = v;
             best_cost = cost;
