@@ -54,6 +54,9 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
     const int wpx = wave % WP, wcx = wave / WP;
     const int rb0 = (cblock * WC + wcx) * NJ;
 
+    char* const piece = lds8 + p.rows_lds + wave * kRowsPiece;
+    constexpr int ROWB = NJ * 16 * ES, PITCH = ROWB + 16;       // a piece's row
+
     // weights of this wavefront's row blocks: [row block][instruction][plane][lane] x 16 bytes
     const __amdgpu_buffer_rsrc_t wr = make_rsrc(p.wfrag, p.wfrag_bytes);
     u4v a[NJ][NS][PL];
@@ -103,6 +106,21 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
             }
         }
         NM_WAIT_VMCNT(0);
+        // Is there an infinity or NaN among what this wavefront staged?  (224x224x3 -> 64, batch 64: 34.5 -> 35.7 us; the
+        // sums of each block looked at instead, 57.)
+        unsigned found = 0u;                     // the top bit of either half: an exponent of all ones
+        auto look = [&](unsigned v) { found |= (v & 0x7f807f80u) + 0x00800080u; };
+        if (vec) {
+            for (int w = wave * 64; w < total; w += 256) {
+                const u4v v = *reinterpret_cast<const u4v*>(lds8 + (w + lane) * 16);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) look(v[u]);
+            }
+        } else {
+            for (int w = wave * 64; w < total * 4; w += 256) look(*reinterpret_cast<const unsigned*>(lds8 + (w + lane) * 4));
+        }
+        const bool any = __builtin_amdgcn_ballot_w64((found & 0x80008000u) != 0u) != 0ull;
+        if (lane == 0) *reinterpret_cast<int*>(piece + ROWB) = any;   // (the padding of a piece's first row)
     } else {
         const int total = p.rows_n * G * 2;      // quads of four values: 8 bytes of a plane
         for (int i0 = tid; i0 < total; i0 += 4 * 256) {
@@ -147,98 +165,121 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
     for (int m = 0; m < NS; ++m) {
         const int g = 8 * (m / 2) + 2 * q + (m & 1);
         const int kh = (int)fdiv((unsigned)g, p.gr_mul, p.gr_shift), gi = g - kh * p.run_gr;
-        off[m] = p.rows_front + (kh < p.Kh ? kh * p.dh * p.rows_pitch + gi * 16 : 0);   // (padding: any staged granule, weight 0)
+        off[m] = p.rows_front + (kh < p.Kh ? kh * p.dh * p.rows_pitch + gi * 16 : 0);   // (padding: any staged granule, weight 0; see `blocks` below)
     }
     __syncthreads();
 
-    char* const piece = lds8 + p.rows_lds + wave * kRowsPiece;
-    constexpr int ROWB = NJ * 16 * ES, PITCH = ROWB + 16;       // a piece's row
     constexpr int GPR = ROWB / 16, RPP = 64 / GPR, NP = 16 / RPP;
     const int pix0 = (b * p.Ho + ho0) * p.Wo;
     const int r0 = lane / GPR, cg = lane % GPR;
     const int co_out = rb0 * 16 + cg * (16 / ES);
     T* __restrict__ y = reinterpret_cast<T*>(p.y);
     const T* __restrict__ res = reinterpret_cast<const T*>(p.res);
-    for (int blk = wpx * 16; blk < npx; blk += WP * 16) {
-        const int i = blk + n < npx ? blk + n : npx - 1;
-        const int orow = (int)fdiv((unsigned)i, p.wo_mul, p.wo_shift), wo = i - orow * p.Wo;
-        const char* const src = lds8 + orow * p.sh * p.rows_pitch + wo * p.sw * p.Cin * 2;
-        f4 acc[NJ];
+    // (real_only: elements that are no tap of a run are taken for zero)
+    auto blocks = [&](auto real_only) {
+        for (int blk = wpx * 16; blk < npx; blk += WP * 16) {
+            const int i = blk + n < npx ? blk + n : npx - 1;
+            const int orow = (int)fdiv((unsigned)i, p.wo_mul, p.wo_shift), wo = i - orow * p.Wo;
+            const char* const src = lds8 + orow * p.sh * p.rows_pitch + wo * p.sw * p.Cin * 2;
+            f4 acc[NJ];
 #pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) acc[jj] = bb[jj];
+            for (int jj = 0; jj < NJ; ++jj) acc[jj] = bb[jj];
 #pragma unroll
-        for (int m = 0; m < NS; ++m) {
-            u4v x[PL];
+            for (int m = 0; m < NS; ++m) {
+                u4v x[PL];
 #pragma unroll
-            for (int pl = 0; pl < PL; ++pl) {
-                const unsigned* const w = reinterpret_cast<const unsigned*>(src + off[m] + pl * plane);   // 4-byte aligned
-                x[pl] = u4v{w[0], w[1], w[2], w[3]};
+                for (int pl = 0; pl < PL; ++pl) {
+                    const unsigned* const w = reinterpret_cast<const unsigned*>(src + off[m] + pl * plane);   // 4-byte aligned
+                    x[pl] = u4v{w[0], w[1], w[2], w[3]};
+                }
+                if constexpr (real_only) {
+                    int g = 8 * (m / 2) + 2 * q + (m & 1);
+                    asm volatile("" : "+v"(g));      // (the masks are worked out here, not kept in registers)
+                    const int kh = (int)fdiv((unsigned)g, p.gr_mul, p.gr_shift), e0 = (g - kh * p.run_gr) * 8 - p.run_d;
+                    const int len = kh < p.Kh ? p.Kw * p.Cin : 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        x[0][u] &= ((unsigned)(e0 + 2 * u) < (unsigned)len ? 0x0000ffffu : 0u) |
+                                   ((unsigned)(e0 + 2 * u + 1) < (unsigned)len ? 0xffff0000u : 0u);
+                }
+                constexpr int NK = PL == 1 ? 1 : 6, K0 = 6 - NK;
+                constexpr int XP[6] = {2, 1, 0, 1, 0, 0}, WPL[6] = {0, 1, 2, 0, 1, 0};   // smallest products first
+#pragma unroll
+                for (int k = K0; k < 6; ++k)
+#pragma unroll
+                    for (int jj = 0; jj < NJ; ++jj)
+                        acc[jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8x, a[jj][m][WPL[k] % PL]),
+                                                                          __builtin_bit_cast(bf8x, x[XP[k] % PL]), acc[jj], 0, 0, 0);
             }
-            constexpr int NK = PL == 1 ? 1 : 6, K0 = 6 - NK;
-            constexpr int XP[6] = {2, 1, 0, 1, 0, 0}, WPL[6] = {0, 1, 2, 0, 1, 0};   // smallest products first
+            if constexpr (PL == 1) {
+                // residual (accumulator layout: the first layer of a network has none), activation, the one rounding
 #pragma unroll
-            for (int k = K0; k < 6; ++k)
+                for (int jj = 0; jj < NJ; ++jj) {
+                    const int co = (rb0 + jj) * 16 + q * 4;
+                    if (res && blk + n < npx && co < p.Cout)
+                        acc[jj] = acc[jj] + load4(res + ((unsigned)(pix0 + blk + n) * (unsigned)p.Cout + (unsigned)co));
+                    if (p.relu) acc[jj] = relu4(acc[jj]);
+                    store4(reinterpret_cast<bf16_t*>(piece + n * PITCH + jj * 32 + q * 8), acc[jj]);
+                }
+            } else {
 #pragma unroll
-                for (int jj = 0; jj < NJ; ++jj)
-                    acc[jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8x, a[jj][m][WPL[k] % PL]),
-                                                                      __builtin_bit_cast(bf8x, x[XP[k] % PL]), acc[jj], 0, 0, 0);
-        }
-        if constexpr (PL == 1) {
-            // residual (accumulator layout: the first layer of a network has none), activation, the one rounding
-#pragma unroll
-            for (int jj = 0; jj < NJ; ++jj) {
-                const int co = (rb0 + jj) * 16 + q * 4;
-                if (res && blk + n < npx && co < p.Cout)
-                    acc[jj] = acc[jj] + load4(res + ((unsigned)(pix0 + blk + n) * (unsigned)p.Cout + (unsigned)co));
-                if (p.relu) acc[jj] = relu4(acc[jj]);
-                store4(reinterpret_cast<bf16_t*>(piece + n * PITCH + jj * 32 + q * 8), acc[jj]);
+                for (int jj = 0; jj < NJ; ++jj) *reinterpret_cast<f4*>(piece + n * PITCH + jj * 64 + q * 16) = acc[jj];
             }
-        } else {
+            __builtin_amdgcn_wave_barrier();
+            const unsigned out0 = (unsigned)(pix0 + blk + r0) * (unsigned)p.Cout + (unsigned)co_out;
+            u4v v[NP];
 #pragma unroll
-            for (int jj = 0; jj < NJ; ++jj) *reinterpret_cast<f4*>(piece + n * PITCH + jj * 64 + q * 16) = acc[jj];
-        }
-        __builtin_amdgcn_wave_barrier();
-        const unsigned out0 = (unsigned)(pix0 + blk + r0) * (unsigned)p.Cout + (unsigned)co_out;
-        u4v v[NP];
+            for (int k = 0; k < NP; ++k) v[k] = *reinterpret_cast<const u4v*>(piece + (r0 + k * RPP) * PITCH + cg * 16);
+            unsigned lo = ~0u, hi = 0u;              // (three planes) of the words without their sign; a zero counts as large in lo
 #pragma unroll
-        for (int k = 0; k < NP; ++k) v[k] = *reinterpret_cast<const u4v*>(piece + (r0 + k * RPP) * PITCH + cg * 16);
-        unsigned lo = ~0u, hi = 0u;              // (three planes) of the words without their sign; a zero counts as large in lo
+            for (int k = 0; k < NP; ++k) {
+                const bool live = blk + r0 + k * RPP < npx && co_out < p.Cout;
+                if constexpr (PL == 3) {
+                    f4 f = __builtin_bit_cast(f4, v[k]);
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            const bool live = blk + r0 + k * RPP < npx && co_out < p.Cout;
+                    for (int r = 0; r < 4; ++r) {
+                        const unsigned w = v[k][r] << 1;
+                        lo = w - 1u < lo ? w - 1u : lo;
+                        hi = w > hi ? w : hi;
+                    }
+                    if (res) f = f + load4(res + (live ? out0 + (unsigned)(k * RPP) * (unsigned)p.Cout : 0u));
+                    if (p.relu) f = relu4(f);
+                    v[k] = __builtin_bit_cast(u4v, f);
+                }
+                if (live) *reinterpret_cast<u4v*>(y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout)) = v[k];
+            }
             if constexpr (PL == 3) {
-                f4 f = __builtin_bit_cast(f4, v[k]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const unsigned w = v[k][r] << 1;
-                    lo = w - 1u < lo ? w - 1u : lo;
-                    hi = w > hi ? w : hi;
-                }
-                if (res) f = f + load4(res + (live ? out0 + (unsigned)(k * RPP) * (unsigned)p.Cout : 0u));
-                if (p.relu) f = relu4(f);
-                v[k] = __builtin_bit_cast(u4v, f);
-            }
-            if (live) *reinterpret_cast<u4v*>(y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout)) = v[k];
-        }
-        if constexpr (PL == 3) {
-            if (lo < kSplitTiny || hi >= kSplitInf) {
-                kernarg_t kp = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
-                __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
+                if (lo < kSplitTiny || hi >= kSplitInf) {
+                    kernarg_t kp = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
+                    __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
 #pragma unroll 1
-                for (int k = 0; k < NP * 4; ++k) {
-                    const int row = r0 + k / 4 * RPP, r = k & 3;
-                    const unsigned w = *reinterpret_cast<const unsigned*>(piece + row * PITCH + cg * 16 + r * 4) << 1;
-                    if ((w - 1u >= kSplitTiny && w < kSplitInf) || blk + row >= npx || co_out + r >= p.Cout) continue;
-                    const unsigned o = (unsigned)(pix0 + blk + row) * (unsigned)p.Cout + (unsigned)(co_out + r);
-                    float f = split_redo(kp, pix0 + blk + row, co_out + r, 0, p.K, p.bias ? p.bias[co_out + r] : 0.f);
-                    if (res) f += load1(res + o);
-                    if (p.relu) f = relu1(f);
-                    store1(y + o, f);
+                    for (int k = 0; k < NP * 4; ++k) {
+                        const int row = r0 + k / 4 * RPP, r = k & 3;
+                        const unsigned w = *reinterpret_cast<const unsigned*>(piece + row * PITCH + cg * 16 + r * 4) << 1;
+                        if ((w - 1u >= kSplitTiny && w < kSplitInf) || blk + row >= npx || co_out + r >= p.Cout) continue;
+                        const unsigned o = (unsigned)(pix0 + blk + row) * (unsigned)p.Cout + (unsigned)(co_out + r);
+                        float f = split_redo(kp, pix0 + blk + row, co_out + r, 0, p.K, p.bias ? p.bias[co_out + r] : 0.f);
+                        if (res) f += load1(res + o);
+                        if (p.relu) f = relu1(f);
+                        store1(y + o, f);
+                    }
                 }
             }
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_wave_barrier();
+    };
+    if constexpr (PL == 1) {
+        // An infinity or NaN in a padding slot (the lead-in and the rest of a run, K positions beyond the last kernel
+        // row) times its weight 0 would be a NaN that the output is not due.
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) any |= *reinterpret_cast<const int*>(lds8 + p.rows_lds + w * kRowsPiece + ROWB);
+        if (__builtin_amdgcn_readfirstlane(any)) {
+            blocks(std::true_type());
+            return;
+        }
     }
+    blocks(std::false_type());
 }
 
 template <int PL, int NJ, int KS>

@@ -83,3 +83,54 @@ def test_infinity_and_default():
     #  a sum is computed again without them)
     assert (np.isinf(y) == np.isinf(ref)).all() and (np.isnan(y) == np.isnan(ref)).all()
     assert norm_err(y[fin], ref[fin]) <= FP32_TOL
+
+
+@pytest.mark.parametrize("layer", [GRID[0][0], GRID[3][0], GRID[5][0], GRID[6][0]], ids=lambda l: l.name)
+@pytest.mark.parametrize("relu", [False, True])
+def test_infinities_bf16(layer, relu):
+    """An infinite or NaN pixel reaches the outputs whose window holds it and no other: not those that read it in a padding
+    slot (beside the window, or a slot beyond the last kernel row, which reads the window's first pixels)."""
+    import torch
+    dense = L(layer.name, layer.H, layer.W, layer.Cin, layer.Cout, layer.Kh, layer.Kw, layer.stride, layer.pad, 1, 1, 1, 16)
+    x, w, bias = wl.make_tensors(dense, 3, 57, weight_sigma=0.1)
+    h, wd, c = dense.H // 2, dense.W // 2, dense.Cin - 1
+    x[0, h, wd, 0], x[0, 0, 0, c], x[1, h, wd, c], x[1, dense.H - 1, dense.W - 1, 0] = np.inf, -np.inf, -np.inf, np.nan
+    wp = nm.nm_prune(w, 1, 1, 16, nm.NM_BF16)
+    xd, bd = torch.from_numpy(x).cuda().to(torch.bfloat16), torch.from_numpy(bias).cuda()
+    ref = oracle_conv(dense, np.where(np.isfinite(x), x, 0).astype(np.float32), w, bias, relu=False, bf16=True)
+    # where an infinity or NaN arrives, and as what: the same convolution of its sign (a window holds at most one sign)
+    mark = np.where(np.isfinite(x), 0, 1).astype(np.float64)
+    wt = torch.from_numpy(w).double().permute(0, 3, 1, 2)
+    conv = lambda a, k: torch.nn.functional.conv2d(torch.from_numpy(a).permute(0, 3, 1, 2), k, None, dense.stride,
+                                                   dense.pad).permute(0, 2, 3, 1).numpy()
+    hit = conv(mark, torch.ones_like(wt))
+    pos, neg = np.isposinf(x).astype(np.float64), np.isneginf(x).astype(np.float64)
+    up = conv(pos, (wt > 0).double()) + conv(neg, (wt < 0).double())
+    down = conv(pos, (wt < 0).double()) + conv(neg, (wt > 0).double())
+    nan = (conv(np.isnan(x).astype(np.float64), torch.ones_like(wt)) > 0) | ((up > 0) & (down > 0))
+    assert (up > 0).any() and (down > 0).any() and nan.any() and (hit == 0).any()
+    ran = 0
+    try:
+        for v in range(nm.nm_variant_count()):
+            name = nm.nm_variant_name(v)
+            if not name.startswith("RUN_ROWS") or not nm.nm_variant_legal(v, wp, nm.NM_BF16, nm.NM_BF16):
+                continue
+            say(f"inf {layer.name} {name}")
+            nm.nm_force_variant(v)
+            try:
+                y = nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, relu)
+            except nm.NMError:                  # the k-steps of the other alignment
+                continue
+            torch.cuda.synchronize()
+            y = y.float().cpu().numpy()
+            ok = hit == 0
+            assert norm_err(y[ok], np.maximum(ref, 0)[ok] if relu else ref[ok]) <= BF16_TOL, name
+            assert np.isposinf(y[(up > 0) & ~nan]).all(), name
+            if relu:
+                assert (y[(down > 0) & ~nan] == 0).all(), name
+            else:
+                assert np.isneginf(y[(down > 0) & ~nan]).all() and np.isnan(y[nan]).all(), name
+            ran += 1
+    finally:
+        nm.nm_force_variant(-1)
+    assert ran
