@@ -114,9 +114,9 @@ inline bool flat_rowblocks(int kind) { return is_split_kind(kind) || is_rows_kin
 // k-steps per chunk its kept sets need (groups wider than a chunk spread unevenly) and
 // which operand tables were built.  Two layers of one shape that differ there must not
 // share a cache entry.
-int prepack_signature(const nm_packed* wp)
+int prepack_signature(const nm_packed* wp, bool no_planes)
 {
-    unsigned h = 2166136261u;
+    unsigned h = no_planes ? 2166136262u : 2166136261u;
     for (const Prepack& pp : wp->prepacks) {
         const int t[5] = {pp.kind, pp.geom.CK, pp.geom.vec, pp.SPC, pp.par};
         if (!flat_rowblocks(pp.kind)) h = fnv(h, t, sizeof(t));   // (implied by the rest of the key)
@@ -324,6 +324,16 @@ size_t first_not_finite(const float* w, size_t n)
     return i;
 }
 
+// Outputs below this (as a word shifted left by one) are computed again by the three-plane kernels where they meet
+// activations under 2^-110: what the planes of those lose, 2^-132 |w| a product, is then more than 2^-27 of the output.
+unsigned redo_below(float max_w, int kprime)
+{
+    const float t = (float)std::min(std::max(ldexp((double)max_w * kprime, -105), ldexp(1.0, -100)), 3e38);
+    uint32_t u;
+    memcpy(&u, &t, sizeof(u));
+    return u << 1;
+}
+
 struct Geometry {
     int Ho, Wo, P;
 };
@@ -387,6 +397,7 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
         p.tile = 16; p.rbpt = 1; p.n_rowblocks = (wp->cout + 15) / 16;
     }
     p.idx = wp->d_idx; p.vals = wp->d_vals; p.kprime = wp->kprime; p.ctile = wp->tile;
+    p.redo_below = wp->redo_below;
     const int rb_per_wg = (4 / d.WP) * d.NJ;
     p.n_ptiles = (g.P + d.BP - 1) / d.BP;
     p.n_cblocks = (p.n_rowblocks + rb_per_wg - 1) / rb_per_wg;
@@ -905,9 +916,10 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
         if (!g.vec && kh <= 255 && kw <= 255 && cin <= 65535) pp.ktab_bytes = (size_t)g.nchunks * g.CK * sizeof(uint32_t);
         wp->prepacks.push_back(pp);
     }
+    bool no_planes = false;
     {
         auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-        size_t total = 256;   // the builders' error flag
+        size_t total = 256;   // the builders' flags
         for (const Prepack& pp : wp->prepacks) total += up(pp.rows_bytes) + up(pp.wfrag_bytes) + up(pp.ktab_bytes);
         NM_TRY_HIP(hipMalloc(reinterpret_cast<void**>(&wp->d_tables), total), NM_ERR_ALLOC);
         NM_TRY_HIP(hipMemsetAsync(wp->d_tables, 0, total, s), NM_ERR_HIP);
@@ -935,13 +947,21 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
                            NM_ERR_HIP);
             }
         }
-        int h_err = 0;
-        NM_TRY_HIP(hipMemcpyAsync(&h_err, wp->d_tables, sizeof(int), hipMemcpyDeviceToHost, s), NM_ERR_HIP);
+        int h_err[3] = {0, 0, 0};
+        NM_TRY_HIP(hipMemcpyAsync(h_err, wp->d_tables, sizeof(h_err), hipMemcpyDeviceToHost, s), NM_ERR_HIP);
         NM_TRY_HIP(hipStreamSynchronize(s), NM_ERR_HIP);
-        if (h_err) {
+        if (h_err[0]) {
             set_error("internal: a K chunk holds more kept columns than the operand table allows");
             return fail(NM_ERR_UNSUPPORTED);
         }
+        if (h_err[1]) {   // a weight that three bf16 planes do not hold exactly: the fp32 instruction runs this layer
+            no_planes = true;
+            auto planes = [](const Prepack& pp) { return is_split_kind(pp.kind) || pp.kind == 11; };
+            wp->prepacks.erase(std::remove_if(wp->prepacks.begin(), wp->prepacks.end(), planes), wp->prepacks.end());
+        }
+        float max_w;
+        memcpy(&max_w, &h_err[2], sizeof(max_w));
+        wp->redo_below = redo_below(max_w, wp->kprime);
     }
 #undef NM_TRY_HIP
     (void)hipFree(d_w);
@@ -950,7 +970,7 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
         free_packed(wp);
         return NM_ERR_UNSUPPORTED;
     }
-    wp->sig = prepack_signature(wp);
+    wp->sig = prepack_signature(wp, no_planes);
     *out = wp;
     return NM_OK;
 }

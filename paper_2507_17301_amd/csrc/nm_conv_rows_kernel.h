@@ -123,6 +123,7 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
         if (lane == 0) *reinterpret_cast<int*>(piece + ROWB) = any;   // (the padding of a piece's first row)
     } else {
         const int total = p.rows_n * G * 2;      // quads of four values: 8 bytes of a plane
+        unsigned lost = 0u;                      // (see the three-plane kernel)
         for (int i0 = tid; i0 < total; i0 += 4 * 256) {
             f4 v[4];
 #pragma unroll
@@ -145,11 +146,15 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
             for (int u = 0; u < 4; ++u) {
                 if (i0 + u * 256 >= total) continue;
                 u2v pl[3];
-                split_planes(v[u], pl);
+                f4 rest[2];
+                split_planes(v[u], pl, rest);
+                split_lost(rest, lost);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) *reinterpret_cast<u2v*>(lds8 + k * plane + (i0 + u * 256) * 8) = pl[k];
             }
         }
+        const bool any = __builtin_amdgcn_ballot_w64((lost & 0xffffu) != 0u) != 0ull;
+        if (lane == 0) *reinterpret_cast<int*>(piece + ROWB) = any;   // (the padding of a piece's first row)
     }
 
     // bias of this lane's rows, and where instruction m of a pixel finds this lane's granule
@@ -173,6 +178,11 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
     const int pix0 = (b * p.Ho + ho0) * p.Wo;
     const int r0 = lane / GPR, cg = lane % GPR;
     const int co_out = rb0 * 16 + cg * (16 / ES);
+    // what the wavefronts found among the staged values: an infinity or NaN (bf16), values whose planes leave bits out (fp32)
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) any |= *reinterpret_cast<const int*>(lds8 + p.rows_lds + w * kRowsPiece + ROWB);
+    any = __builtin_amdgcn_readfirstlane(any);
     T* __restrict__ y = reinterpret_cast<T*>(p.y);
     const T* __restrict__ res = reinterpret_cast<const T*>(p.res);
     // (real_only: elements that are no tap of a run are taken for zero)
@@ -249,14 +259,15 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
                 if (live) *reinterpret_cast<u4v*>(y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout)) = v[k];
             }
             if constexpr (PL == 3) {
-                if (lo < kSplitTiny || hi >= kSplitInf) {
+                if (lo < kSplitTiny || hi >= kSplitInf || any) {
                     kernarg_t kp = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
                     __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
+                    const unsigned below = any ? kp->redo_below : kSplitTiny;
 #pragma unroll 1
                     for (int k = 0; k < NP * 4; ++k) {
                         const int row = r0 + k / 4 * RPP, r = k & 3;
                         const unsigned w = *reinterpret_cast<const unsigned*>(piece + row * PITCH + cg * 16 + r * 4) << 1;
-                        if ((w - 1u >= kSplitTiny && w < kSplitInf) || blk + row >= npx || co_out + r >= p.Cout) continue;
+                        if (((any ? w : w - 1u) >= below && w < kSplitInf) || blk + row >= npx || co_out + r >= p.Cout) continue;
                         const unsigned o = (unsigned)(pix0 + blk + row) * (unsigned)p.Cout + (unsigned)(co_out + r);
                         float f = split_redo(kp, pix0 + blk + row, co_out + r, 0, p.K, p.bias ? p.bias[co_out + r] : 0.f);
                         if (res) f += load1(res + o);
@@ -271,10 +282,7 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
     if constexpr (PL == 1) {
         // An infinity or NaN in a padding slot (the lead-in and the rest of a run, K positions beyond the last kernel
         // row) times its weight 0 would be a NaN that the output is not due.
-        int any = 0;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) any |= *reinterpret_cast<const int*>(lds8 + p.rows_lds + w * kRowsPiece + ROWB);
-        if (__builtin_amdgcn_readfirstlane(any)) {
+        if (any) {
             blocks(std::true_type());
             return;
         }

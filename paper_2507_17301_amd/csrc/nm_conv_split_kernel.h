@@ -25,9 +25,13 @@
 // every row has its own index operand, so rows of different column tiles (T < 16) share a block.
 //
 // What the planes cannot carry: an infinite x1 makes inf * 0 = NaN in the products with an empty w2 or w3, and
-// the matrix cores take subnormal bf16 numbers for zero, so that sums under about 2^-100 would lose their lower
-// planes.  An output that comes out infinite, NaN or below 2^-90 (and not zero) is therefore computed again,
-// one fp32 multiply-add per kept column (split_redo).
+// bits below 2^-133, bf16's smallest subnormal (which the matrix cores do count, as fp32 instructions do).
+//   weights: nm_prune makes no tables for a layer whose kept weights the planes do not hold exactly.
+//   activations (under 2^-110): the producers say so, each product is then off by at most 2^-132 |w|, and outputs
+//     below redo_below = K' max|w| 2^-105, where that may be more than 2^-27 of them, are computed again, zeros
+//     among them.
+// An output that comes out infinite, NaN or (not zero and) below 2^-100, where lower planes' products meet the
+// end of fp32's subnormals, is computed again as well, one fp32 multiply-add per kept column (split_redo).
 //
 // Bound: on the 3x3 layers the matrix cores (14x14 256 -> 256, batch 64: 78 -> 56 us; with staging and weight
 // loads switched off 40 us, of which 8 are the launch and the rest 196 of 256 CUs at 36 x 96 instructions);
@@ -40,7 +44,7 @@ namespace nm {
 
 constexpr int kSplitCK = 64;   // channels per chunk
 constexpr unsigned kSplitInf = 0xff000000u;              // infinity, as a word shifted left by one
-constexpr unsigned kSplitTiny = (127u - 90u) << 24;      // 2^-90, likewise
+constexpr unsigned kSplitTiny = (127u - 100u) << 24;     // 2^-100, likewise
 // one LDS stage: three planes [BP][64] bf16
 constexpr int split_stage_bytes(int BP) { return 3 * BP * kSplitCK * 2; }
 // each contracting wavefront's output piece: up to 32 pixels x its 16 NJ channels, 16 bytes of padding a row
@@ -61,9 +65,10 @@ constexpr int split_waves(int NBLK, int WP, int NJ, bool sparse)
 
 // Four fp32 values as three planes of four bf16 values (8 bytes each), cut at bits 16 and 8: the first
 // plane is the upper half of the word, the second the next 8 significant bits, the third the last 8
-// (both exact differences).  22 full-rate instructions; the converting instruction instead of the
+// (both exact differences, rest[0] and rest[1]: what the planes leave out, bits below 2^-133, are lower halves of
+// theirs that are not zero).  22 full-rate instructions; the converting instruction instead of the
 // byte permutes: 14x14 3x3 256 -> 256, 128-pixel tiles, 66.8 us against 63.0.
-__device__ inline void split_planes(const f4 v, u2v (&out)[3])
+__device__ inline void split_planes(const f4 v, u2v (&out)[3], f4 (&rest)[2])
 {
     auto pair = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
     auto top = [](float a, unsigned mask) { return __uint_as_float(__float_as_uint(a) & mask); };
@@ -73,6 +78,14 @@ __device__ inline void split_planes(const f4 v, u2v (&out)[3])
     out[0] = u2v{pair(v.x, v.y), pair(v.z, v.w)};
     out[1] = u2v{pair(b.x, b.y), pair(b.z, b.w)};
     out[2] = u2v{pair(c.x, c.y), pair(c.z, c.w)};
+    rest[0] = b;
+    rest[1] = c;
+}
+
+__device__ inline void split_lost(const f4 (&rest)[2], unsigned& lost)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) lost |= __float_as_uint(rest[0][r]) | __float_as_uint(rest[1][r]);
 }
 
 // The kernel's arguments where they lie: what only the end of a tile needs is read there, not held in scalar
@@ -203,15 +216,32 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
                 retap();
             }
         };
+        // Whether planes left bits out so far: a word per producer in the padding of an output piece's first row, written
+        // with the last chunk of a tile, so that the others find it when they finish that tile.
+        unsigned lost = 0u;
+        int s_left = nc;
+        int* const lossy = reinterpret_cast<int*>(lds8 + 2 * STAGE + (wave_id - 4) * (split_out_rows(NBLK) * split_out_pitch(NJ)) + NJ * 64);
         char* const wdst = lds8 + pl0 * RB + (((quad >> 1) ^ sp16_swz(pl0, RB)) * 16) + (quad & 1) * 8;
+        f4 rest[NIT][2];
         auto stash = [&](const f4 (&st)[NIT], int stage) {
 #pragma unroll
             for (int it = 0; it < NIT; ++it) {
                 u2v pl[3];
-                split_planes(st[it], pl);
+                split_planes(st[it], pl, rest[it]);
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
                     *reinterpret_cast<u2v*>(wdst + stage * STAGE + k * PLANE + it * (16 * RB)) = pl[k];
+            }
+        };
+        // (behind the writes and the next loads, which it would hold up.  14x14 3x3 256 -> 256, batch 32: 30.7 us without
+        // the look, 31.6 with it in front of them, 31.2 here; ResNet-50 in fp32, batch 64, 2803 and 2838.)
+        auto note = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) split_lost(rest[it], lost);
+            if (--s_left == 0) {
+                *lossy = __builtin_amdgcn_ballot_w64((lost & 0xffffu) != 0u) != 0ull;
+                s_left = nc;
             }
         };
         open_tile();
@@ -219,16 +249,19 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
         fetch(sb);
         stash(sa, 0);
         fetch(sa);
+        note();
         int g = 0;
         // barrier g: chunk g is staged; then chunk g + 1 goes to the stage the others left at that barrier
         for (; g + 1 < total; g += 2) {
             split_barrier();
             stash(sb, 1);
             fetch(sb);
+            note();
             split_barrier();
             if (g + 2 < total) {
                 stash(sa, 0);
                 fetch(sa);
+                note();
             }
         }
         if (g < total) split_barrier();
@@ -368,6 +401,10 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
         const char* const src = piece + r0 * PITCH + cg * 16;
         const int P = kp->P, Cout = kp->Cout;
         constexpr int NP = PB * 16 / RPP;               // passes per piece
+        int inexact = 0;                                // the planes of some activation so far left bits out
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            inexact |= *reinterpret_cast<const int*>(lds8 + 2 * STAGE + w * (split_out_rows(NBLK) * PITCH) + NJ * 64);
 #pragma unroll
         for (int b0 = 0; b0 < NBLK; b0 += PB) {
 #pragma unroll
@@ -428,15 +465,16 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
                     }
                 }
             }
-            if (lo < kSplitTiny || hi >= kSplitInf) {
+            if (lo < kSplitTiny || hi >= kSplitInf || inexact) {
                 __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
+                const unsigned below = inexact ? kp->redo_below : kSplitTiny;
                 const int k_lo = (c_begin / kp->ncpt) * kp->Cin + (c_begin % kp->ncpt) * kSplitCK;
                 const int k_hi = c_end < kp->nchunks ? (c_end / kp->ncpt) * kp->Cin + (c_end % kp->ncpt) * kSplitCK : kp->K;
 #pragma unroll 1
                 for (int i = 0; i < rows / RPP * 4; ++i) {
                     const int row = i / 4 * RPP, r = i & 3, pp = pp0 + row;
                     const unsigned w = *reinterpret_cast<const unsigned*>(src + row * PITCH + r * 4) << 1;
-                    if ((w - 1u >= kSplitTiny && w < kSplitInf) || pp >= P || co + r >= Cout) continue;
+                    if (((inexact ? w : w - 1u) >= below && w < kSplitInf) || pp >= P || co + r >= Cout) continue;
                     const unsigned off = (unsigned)pp * (unsigned)Cout + (unsigned)(co + r);
                     float o = split_redo(kp, pp, co + r, k_lo, k_hi, kp->bias && kp->ksplit <= 1 ? kp->bias[co + r] : 0.f);
                     if (res) o += res[off];

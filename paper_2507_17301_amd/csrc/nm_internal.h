@@ -126,10 +126,11 @@ struct nm_packed {
     nm_dtype_t value_dtype;
     int device;
     float scale = 1.f;   // fp8 handles: the stored E4M3 value is weight * scale (a power of two)
+    unsigned redo_below = 0;   // kinds 8, 9, 11: see ConvParams
     int sig = 0;      // hash of the operand tables built for this handle (part of the tuning-cache key)
     int32_t* d_idx = nullptr;   // [n_tiles][kprime]
     float* d_vals = nullptr;    // [n_tiles][kprime][tile]
-    char* d_tables = nullptr;   // one block: the table builders' error flag (256 bytes), then every operand table
+    char* d_tables = nullptr;   // one block: the table builders' flags (256 bytes), then every operand table
     std::vector<int32_t> h_idx; // host copy of d_idx
     std::vector<nm::Prepack> prepacks;
 };
@@ -176,6 +177,7 @@ struct ConvParams {
     const int32_t* idx;
     const float* vals;
     int kprime, ctile;
+    unsigned redo_below;   // and, where activations are too small for their planes, outputs below this (word shifted left by one)
     float oscale;      // fp8: factor that takes the accumulator back to the weights' own scale (1 / handle scale)
 };
 
@@ -212,7 +214,8 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
 
 // prune-side kernels (nm_prune_kernels.hip)
 int run_prune(const float* d_w, nm_packed* wp, hipStream_t s);
-// fills the (zeroed) tables of pp, any kind; enqueues only: an overfull chunk sets the int at wp->d_tables
+// fills the (zeroed) tables of pp, any kind; enqueues only: an overfull chunk sets the int at wp->d_tables, a weight that
+// three bf16 planes do not hold exactly the one after it; the one after that takes the largest magnitude among such weights
 int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s);
 int run_build_mask(const nm_packed* wp, uint8_t* d_mask, hipStream_t s);
 int run_quantize_e4m3(nm_packed* wp, hipStream_t s);   // d_vals -> the E4M3 values they are stored as (needs wp->scale)

@@ -144,6 +144,17 @@ __device__ inline int lower_bound_idx(const int32_t* a, int n, int key)
     return lo;
 }
 
+// The largest magnitude among a wavefront's weights (`most`, as a word) joins that of the layer.  Every lane calls this.
+__device__ inline void join_largest(unsigned most, int* err)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const unsigned o = (unsigned)__shfl_xor((int)most, d);
+        most = o > most ? o : most;
+    }
+    if ((threadIdx.x & 63) == 0) atomicMax(reinterpret_cast<unsigned*>(err) + 2, most);
+}
+
 // First k of the chunk that column k belongs to, its number, and the first k beyond it.
 __device__ inline void chunk_span(int k, int cin, int CK, int vec, int ncpt, int* c, int* k0, int* k1)
 {
@@ -331,9 +342,11 @@ __global__ __launch_bounds__(256) void build_prepack_sp16_kernel(
 // E / (8 GR); positions outside [0, Kw*Cin) and rows >= Kh are padding (weight 0).
 __global__ __launch_bounds__(256) void build_prepack_run16_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ vals, int kprime, int T, int rbpt,
-    int cout, int n_rowblocks, int planes, int Kh, int KwC, int KS, int GR, int par, unsigned short* __restrict__ wfrag)
+    int cout, int n_rowblocks, int planes, int Kh, int KwC, int KS, int GR, int par, unsigned short* __restrict__ wfrag,
+    int* __restrict__ err)
 {
-    const size_t total = (size_t)n_rowblocks * KS * 2 * 64;
+    const size_t total = (size_t)n_rowblocks * KS * 2 * 64;   // (whole wavefronts)
+    unsigned most = 0u;
     for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < total;
          id += (size_t)gridDim.x * blockDim.x) {
         const int lane = (int)(id % 64);
@@ -359,13 +372,17 @@ __global__ __launch_bounds__(256) void build_prepack_run16_kernel(
                 const int lb = lower_bound_idx(idxj, kprime, k);
                 if (lb < kprime && idxj[lb] == k) v = vals[((size_t)j * kprime + lb) * T + t];
             }
+            const unsigned mag = __float_as_uint(v) & 0x7fffffffu;
+            most = mag > most ? mag : most;
             for (int pl = 0; pl < np; ++pl) {
                 const float top = round_bf16_rne(v);   // (bf16 handles: the value itself)
                 dst[pl * 512 + e] = (unsigned short)(__float_as_uint(top) >> 16);
                 v -= top;
             }
+            if (np == 3 && v != 0.f) err[1] = 1;   // (bits below 2^-133, or a first plane rounded to infinity)
         }
     }
+    if (planes == 3) join_largest(most, err);
 }
 
 __global__ void build_mask_kernel(const int32_t* __restrict__ idx, int cout, int K, int kprime,
@@ -448,7 +465,8 @@ __global__ __launch_bounds__(256) void build_prepack_split_kernel(
     unsigned short* __restrict__ wfrag, int* __restrict__ err)
 {
     const int AH = sparse ? 1 : 2;
-    const size_t total = (size_t)n_rowblocks * nchunks * AH * 64;
+    const size_t total = (size_t)n_rowblocks * nchunks * AH * 64;   // (whole wavefronts)
+    unsigned most = 0u;
     for (size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x; id < total;
          id += (size_t)gridDim.x * blockDim.x) {
         const int lane = (int)(id % 64);
@@ -492,6 +510,10 @@ __global__ __launch_bounds__(256) void build_prepack_split_kernel(
                 w[e] = lb < kprime && idxj[lb] == k ? vals[((size_t)j * kprime + lb) * T + t] : 0.f;
             }
         }
+        for (int e = 0; e < 8; ++e) {
+            const unsigned mag = __float_as_uint(w[e]) & 0x7fffffffu;
+            most = mag > most ? mag : most;
+        }
         for (int pl = 0; pl < 3; ++pl) {
             unsigned short* dst = wfrag + ((((size_t)rb * nchunks + c) * 3 + pl) * AH + h) * 512 + lane * 8;
             for (int e = 0; e < 8; ++e) {
@@ -500,7 +522,10 @@ __global__ __launch_bounds__(256) void build_prepack_split_kernel(
                 w[e] -= top;
             }
         }
+        for (int e = 0; e < 8; ++e)
+            if (w[e] != 0.f) err[1] = 1;           // (bits below 2^-133, or a first plane rounded to infinity)
     }
+    join_largest(most, err);
 }
 
 int grid_for(size_t total, int threads)
@@ -562,7 +587,7 @@ int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s)
         const size_t total = (size_t)nrb * pp.SPC * 2 * 64;
         hipLaunchKernelGGL(build_prepack_run16_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s,
                            wp->d_idx, wp->d_vals, wp->kprime, wp->tile, wp->rbpt, wp->cout, nrb,
-                           pp.kind == 4 ? 0 : pp.kind == 10 ? 1 : 3, wp->kh, KwC, pp.SPC, GR, pp.par, reinterpret_cast<unsigned short*>(pp.d_wfrag));
+                           pp.kind == 4 ? 0 : pp.kind == 10 ? 1 : 3, wp->kh, KwC, pp.SPC, GR, pp.par, reinterpret_cast<unsigned short*>(pp.d_wfrag), d_err);
     } else if (pp.kind >= 2) {
         const size_t total = (size_t)wp->n_rowblocks * g.nchunks * pp.SPC * (pp.kind == 2 ? 1 : 2) * 64;
         hipLaunchKernelGGL(build_prepack_sp16_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s,

@@ -134,3 +134,48 @@ def test_infinities_bf16(layer, relu):
     finally:
         nm.nm_force_variant(-1)
     assert ran
+
+
+@pytest.mark.parametrize("layer", [GRID[0][0], GRID[3][0], GRID[5][0]], ids=lambda l: l.name)
+@pytest.mark.parametrize("xe,we", [(-118, 40), (-126, 100), (-142, 12), (40, -118)])
+def test_values_too_small_for_their_planes(layer, xe, we):
+    """fp32: activations whose lower bits lie under bf16's smallest subnormal are computed again; a layer with such
+    weights has no row-staged form."""
+    import torch
+    dense = L(layer.name, layer.H, layer.W, layer.Cin, layer.Cout, layer.Kh, layer.Kw, layer.stride, layer.pad, 1, 1, 1, 16)
+    x, w, bias = wl.make_tensors(dense, 2, 59)
+    x = np.ldexp(np.random.default_rng(9).standard_normal(x.shape, dtype=np.float32), xe).astype(np.float32)
+    w, bias = np.ldexp(w, we).astype(np.float32), bias * 0
+    x[:, 3:6] = 0
+    wp = nm.nm_prune(w, 1, 1, 16)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2), torch.from_numpy(w).double().permute(0, 3, 1, 2),
+                                     None, dense.stride, dense.pad).permute(0, 2, 3, 1).numpy()
+
+    def err(y):
+        torch.cuda.synchronize()
+        d = y.cpu().numpy().astype(np.float64) - ref
+        return float(np.sqrt((d * d).sum() / (ref * ref).sum()))
+
+    legal = [v for v in range(nm.nm_variant_count()) if nm.nm_variant_legal(v, wp)]
+    forms = [v for v in legal if nm.nm_variant_name(v).startswith("ROWF")]
+    try:
+        nm.nm_force_variant(next(v for v in legal if nm.nm_variant_name(v).startswith("NB4_WP1_NJ1")))
+        old = err(nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False))
+        ran = 0
+        for v in forms:
+            nm.nm_force_variant(v)
+            try:
+                y = nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False)
+            except nm.NMError:                  # the k-steps of the other alignment
+                continue
+            e = err(y)
+            say(f"{layer.name} 2^{xe} * 2^{we} {nm.nm_variant_name(v)} {e:.3g} (fp32 instruction {old:.3g})")
+            # one rounding per kept column, where the fp32 instruction has one per four: at most twice its distance
+            assert e <= 2 * old + 1e-7, nm.nm_variant_name(v)
+            ran += 1
+    finally:
+        nm.nm_force_variant(-1)
+    assert ran if we > -100 else not forms
+    nm.nm_force_variant(-1)
+    assert err(nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False)) <= 2 * old + 1e-7

@@ -125,3 +125,87 @@ def test_infinities_and_nan(relu):
         assert same.all() and not np.isinf(got[np.isfinite(ref)]).any(), nm.nm_variant_name(v)
         ok = np.isfinite(ref)
         assert norm_err(got[ok], ref[ok]) <= FP32_TOL
+
+
+def zero_filled(wp, layer):
+    idx = nm.nm_packed_indices(wp).reshape(-1, layer.K // layer.m * layer.n)
+    vals = nm.nm_packed_values(wp).reshape(*idx.shape, layer.tile)
+    wz = np.zeros((layer.Cout, layer.K))
+    for j in range(idx.shape[0]):
+        for t in range(layer.tile):
+            if j * layer.tile + t < layer.Cout:
+                wz[j * layer.tile + t, idx[j]] = vals[j, :, t]
+    return wz.reshape(layer.Cout, layer.Kh, layer.Kw, layer.Cin)
+
+
+def conv64(layer, x, wz, bias):
+    import torch
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2), torch.from_numpy(wz).permute(0, 3, 1, 2),
+                                     torch.from_numpy(bias).double(), layer.stride, layer.pad, layer.dil)
+    return ref.permute(0, 2, 3, 1).numpy()
+
+
+def rel64(got, ref):
+    d = got.astype(np.float64) - ref
+    return float(np.sqrt((d * d).sum() / (ref * ref).sum()))
+
+
+SMALL = [L("sparse", 12, 11, 64, 64, 3, 3, 1, 1, 1, 2, 4, 16), L("dense", 12, 11, 64, 72, 3, 3, 1, 1, 1, 1, 1, 16)]
+
+
+@pytest.mark.parametrize("layer", SMALL, ids=lambda l: l.name)
+@pytest.mark.parametrize("xe,we", [(-118, 40), (-118, 0), (-126, 100), (-132, 60), (-142, 12), (-95, 0)])
+@pytest.mark.parametrize("zeros", [False, True], ids=["full", "sparse"])
+def test_activations_too_small_for_their_planes(layer, xe, we, zeros):
+    """Activations whose lower bits lie under bf16's smallest subnormal, or that vanish in bf16 altogether, with weights that
+    lift the sums out of there: as near to float64 as the fp32 instruction."""
+    import torch
+    x, w, bias = wl.make_tensors(layer, 2, 23)
+    x = np.random.default_rng(7).standard_normal(x.shape, dtype=np.float32)
+    if zeros:
+        x[:, 4:8] = 0
+    x, w, bias = np.ldexp(x, xe).astype(np.float32), np.ldexp(w, we).astype(np.float32), bias * 0
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = conv64(layer, x, zero_filled(wp, layer), bias)
+    old = rel64(run(fp32_instruction(wp), xd, wp, bd, layer, relu=False), ref)
+    vs = split_variants(wp)
+    assert vs
+    for v in vs:
+        e = rel64(run(v, xd, wp, bd, layer, relu=False), ref)
+        say(f"{layer.name} 2^{xe} * 2^{we} {nm.nm_variant_name(v)} {e:.3g} (fp32 instruction {old:.3g})")
+        # one rounding per kept column, where the fp32 instruction has one per four: at most twice its distance
+        assert e <= 2 * old + 1e-7, nm.nm_variant_name(v)
+
+
+@pytest.mark.parametrize("layer", SMALL, ids=lambda l: l.name)
+@pytest.mark.parametrize("xe,we", [(40, -118), (100, -126), (60, -142)])
+def test_weights_too_small_for_their_planes(layer, xe, we):
+    """A kept weight that three bf16 planes do not hold exactly keeps its layer off the three-plane kernel; one that was
+    pruned does not."""
+    import torch
+    x, w, bias = wl.make_tensors(layer, 2, 29)
+    x = np.ldexp(np.random.default_rng(8).standard_normal(x.shape, dtype=np.float32), xe).astype(np.float32)
+    tiny, bias = np.ldexp(w, we).astype(np.float32), bias * 0
+    wp = nm.nm_prune(tiny, layer.n, layer.m, layer.tile)
+    assert not split_variants(wp)
+    y = nm.nm_conv2d(torch.from_numpy(x).cuda(), wp, torch.from_numpy(bias).cuda(), layer.stride, layer.pad, layer.dil, False)
+    torch.cuda.synchronize()
+    assert rel64(y.cpu().numpy(), conv64(layer, x, zero_filled(wp, layer), bias)) <= 1e-6
+    if layer.n < layer.m:
+        mask = nm.nm_packed_mask(nm.nm_prune(w, layer.n, layer.m, layer.tile)).reshape(w.shape)
+        assert split_variants(nm.nm_prune(np.where(mask, w, tiny), layer.n, layer.m, layer.tile))
+
+
+def test_one_tiny_activation_among_ordinary_ones():
+    """The other outputs stay what they are, bit for bit."""
+    import torch
+    layer = SMALL[0]
+    x, w, bias = wl.make_tensors(layer, 2, 31)
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    bd = torch.from_numpy(bias).cuda()
+    z = x.copy()
+    x[0, 5, 5, 3], z[0, 5, 5, 3] = 1e-40, 0
+    for v in split_variants(wp):
+        a, b = (run(v, torch.from_numpy(t).cuda(), wp, bd, layer, relu=False) for t in (x, z))
+        assert (a == b).all(), nm.nm_variant_name(v)
