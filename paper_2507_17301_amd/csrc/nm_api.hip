@@ -248,6 +248,24 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     return find_prepack(wp, d) != nullptr;
 }
 
+// Three planes take the place of the fp32 instruction only where that loses nothing: they leave out three of the nine
+// partial products (about one fp32 rounding of each product), and their fewer roundings of the sum make up for it from
+// some number of kept columns on.  Distance from float64 over the fp32 instruction's, 1x1 and small kernels, worst of
+// uniform and signed activations, with bias and without: 1 column x1.95, 2 x1.5, 3 x1.3, 4 x1.2, 5 x1.02, 6 x1.01,
+// 7 x0.94, 9 x0.91, 18 x0.8 and falling.  Of a K split each part counts.  (A forced variant runs all the same.)
+constexpr int kPlanesMinKept = 7;
+bool keeps_precision(int v, const nm_packed* wp)
+{
+    const VariantDesc& d = variant_desc(v);
+    if (!is_split_kind(d.kind) && d.kind != 11) return true;
+    long kept = wp->kprime;
+    if (d.ksplit > 1) {
+        const int nchunks = wp->kh * wp->kw * ((wp->cin + d.CK - 1) / d.CK);
+        kept = kept * ((nchunks + d.ksplit - 1) / d.ksplit) / nchunks;
+    }
+    return kept >= kPlanesMinKept;
+}
+
 // Largest number of kept columns any (tile, chunk) pair holds.  Kept positions ascend inside a
 // tile, so a chunk's columns are one run: the chunk is worked out once per run, not per column.
 int max_kept_per_chunk(const nm_packed* wp, const ChunkGeom& g)
@@ -488,7 +506,7 @@ int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
     int pick = -1;
     for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
-        if (!is_rows_kind(d.kind) || !variant_legal(v, wp, xdt, &ra)) continue;
+        if (!is_rows_kind(d.kind) || !keeps_precision(v, wp) || !variant_legal(v, wp, xdt, &ra)) continue;
         const long n_wg = (long)(P / wo + d.NBLK - 1) / d.NBLK * ((wp->cout + 63) / 64);
         if (d.NBLK > (d.kind == 10 ? 8 : 4) || (d.NBLK > 1 && n_wg < 2L * kNumCU)) continue;
         // (within one form the table lists the heights in ascending order, and the wider form last)
@@ -1111,7 +1129,7 @@ static int conv2d_impl(const void* x, nm_dtype_t xdt, int b, int h, int w, int c
         }
     }
     const RunArgs ra = {w, sw, pw, dw, sh, dh};
-    if (v >= 0 && !variant_legal(v, wp, xdt, &ra)) {
+    if (v >= 0 && (!variant_legal(v, wp, xdt, &ra) || (!forced && !keeps_precision(v, wp)))) {
         if (forced) {
             set_error("variant %d (%s) cannot run this layer", v, nm_variant_name(v));
             return NM_ERR_UNSUPPORTED;
@@ -1263,7 +1281,7 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
-        if (it != g_cache.end() && variant_legal(it->second.variant, wp, xdt, &ra)) {
+        if (it != g_cache.end() && variant_legal(it->second.variant, wp, xdt, &ra) && keeps_precision(it->second.variant, wp)) {
             if (chosen) *chosen = it->second.variant;
             if (best_ms) *best_ms = it->second.ms;
             return NM_OK;
@@ -1347,7 +1365,7 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
     // pick variants a few percent off the best from run to run.
     std::vector<std::pair<float, int>> first;
     for (int v = 0; v < variant_count(); ++v) {
-        if (!variant_legal(v, wp, xdt, &ra)) continue;
+        if (!variant_legal(v, wp, xdt, &ra) || !keeps_precision(v, wp)) continue;
         {   // a K split is worth its second kernel only where the output tiles are one short, ragged round (at most two per CU)
             const VariantDesc& d = variant_desc(v);
             const int nrb = flat_rowblocks(d.kind) ? (wp->cout + 15) / 16 : wp->n_rowblocks;

@@ -14,7 +14,10 @@
 //
 // PL = 1: bf16 tensors.  PL = 3: fp32 tensors cut into three bf16 planes while they are staged (once per
 // value), six products per operand; see the three-plane kernel for the arithmetic and for the outputs
-// that are computed again.
+// that are computed again.  The five products of lower planes have accumulators of their own: a layer
+// of few columns spreads them over several half-empty instructions, and added to the sum one by one they
+// would round it more often than the fp32 instruction does (3x3x3: x1.06 of its distance from float64, so
+// x0.45; 7x7x3 x0.84 and x0.33).
 //
 // Bound: memory (bf16, batch 64, 224x224x3 -> 112x112x64: 122 MB) and, in fp32, the matrix cores (K = 147
 // padded to 192, six products: 54 us).  36 and 112 us; the kernel before this one staged every pixel's 24 granules separately, 48 KB
@@ -191,9 +194,12 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
             const int i = blk + n < npx ? blk + n : npx - 1;
             const int orow = (int)fdiv((unsigned)i, p.wo_mul, p.wo_shift), wo = i - orow * p.Wo;
             const char* const src = lds8 + orow * p.sh * p.rows_pitch + wo * p.sw * p.Cin * 2;
-            f4 acc[NJ];
+            f4 acc[NJ], low[NJ];                 // low: the products of lower planes, so that they do not meet the sum one by one
 #pragma unroll
-            for (int jj = 0; jj < NJ; ++jj) acc[jj] = bb[jj];
+            for (int jj = 0; jj < NJ; ++jj) {
+                acc[jj] = bb[jj];
+                low[jj] = f4{0.f, 0.f, 0.f, 0.f};
+            }
 #pragma unroll
             for (int m = 0; m < NS; ++m) {
                 u4v x[PL];
@@ -217,9 +223,15 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
 #pragma unroll
                 for (int k = K0; k < 6; ++k)
 #pragma unroll
-                    for (int jj = 0; jj < NJ; ++jj)
-                        acc[jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8x, a[jj][m][WPL[k] % PL]),
-                                                                          __builtin_bit_cast(bf8x, x[XP[k] % PL]), acc[jj], 0, 0, 0);
+                    for (int jj = 0; jj < NJ; ++jj) {
+                        f4& to = k < 5 ? low[jj] : acc[jj];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8x, a[jj][m][WPL[k] % PL]),
+                                                                     __builtin_bit_cast(bf8x, x[XP[k] % PL]), to, 0, 0, 0);
+                    }
+            }
+            if constexpr (PL == 3) {
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj) acc[jj] = acc[jj] + low[jj];
             }
             if constexpr (PL == 1) {
                 // residual (accumulator layout: the first layer of a network has none), activation, the one rounding

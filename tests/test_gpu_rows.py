@@ -179,3 +179,62 @@ def test_values_too_small_for_their_planes(layer, xe, we):
     assert ran if we > -100 else not forms
     nm.nm_force_variant(-1)
     assert err(nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False)) <= 2 * old + 1e-7
+
+
+def dist64(y, x, w, bias, layer):
+    import torch
+    torch.cuda.synchronize()
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2), torch.from_numpy(w).double().permute(0, 3, 1, 2),
+                                     torch.from_numpy(bias).double(), layer.stride, layer.pad).permute(0, 2, 3, 1).numpy()
+    d = y.cpu().numpy().astype(np.float64) - ref
+    return float(np.sqrt((d * d).sum() / (ref * ref).sum()))
+
+
+@pytest.mark.parametrize("kh,kw,cin,pad", [(1, 1, 7, 0), (3, 3, 1, 1), (1, 9, 1, 0), (2, 2, 2, 0), (1, 1, 10, 0), (4, 4, 1, 1),
+                                           (7, 3, 1, 0), (3, 3, 3, 1), (5, 5, 2, 1), (7, 3, 3, 1), (7, 7, 3, 3)])
+@pytest.mark.parametrize("kind", ["uniform", "signed"])
+@pytest.mark.parametrize("bias_on", [False, True])
+def test_no_further_from_float64_than_the_fp32_instruction(kh, kw, cin, pad, kind, bias_on):
+    """fp32, also where the kernel's columns are spread thinly over its instructions."""
+    import torch
+    layer = L("few", 30, 24, cin, 64, kh, kw, 2 if cin % 2 else 1, pad, 1, 1, 1, 16)
+    x, w, bias = wl.make_tensors(layer, 4, 61)
+    if kind == "signed":
+        x = np.random.default_rng(3).standard_normal(x.shape, dtype=np.float32)
+    bias = bias * np.float32(bias_on)
+    wp = nm.nm_prune(w, 1, 1, 16)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    legal = [v for v in range(nm.nm_variant_count()) if nm.nm_variant_legal(v, wp)]
+    run = lambda: nm.nm_conv2d(xd, wp, bd, layer.stride, layer.pad, 1, False)
+    try:
+        nm.nm_force_variant(next(v for v in legal if nm.nm_variant_name(v).startswith("NB4_WP1_NJ1")))
+        old, ran = dist64(run(), x, w, bias, layer), 0
+        for v in legal:
+            if not nm.nm_variant_name(v).startswith("ROWF"):
+                continue
+            nm.nm_force_variant(v)
+            try:
+                y = run()
+            except nm.NMError:                  # the k-steps of the other alignment
+                continue
+            assert dist64(y, x, w, bias, layer) <= old, nm.nm_variant_name(v)
+            ran += 1
+        assert ran
+    finally:
+        nm.nm_force_variant(-1)
+
+
+def test_fewest_columns_keep_the_fp32_instruction():
+    """Up to six kept columns the planes' missing products weigh more than the roundings they save."""
+    import torch
+    for kh, kw, cin in [(1, 1, 1), (1, 3, 1), (2, 2, 1), (1, 1, 5), (1, 3, 2), (1, 1, 6)]:
+        layer = L("fewest", 30, 24, cin, 64, kh, kw, 2 if cin % 2 else 1, 0, 1, 1, 1, 16)
+        x, w, bias = wl.make_tensors(layer, 2, 63)
+        wp = nm.nm_prune(w, 1, 1, 16)
+        xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+        say(f"fewest {kh}x{kw}x{cin}")
+        nm.nm_conv2d(xd, wp, bd, layer.stride, 0, 1, False)
+        assert not nm.nm_variant_name(nm.nm_last_variant()).startswith("ROWF")
+        v, _ = nm.nm_autotune(nm.NM_F32, 2, layer.H, layer.W, cin, wp, True, layer.stride, 0, 1, False)
+        assert not nm.nm_variant_name(v).startswith("ROWF")
+    nm.nm_cache_clear()

@@ -209,3 +209,36 @@ def test_one_tiny_activation_among_ordinary_ones():
     for v in split_variants(wp):
         a, b = (run(v, torch.from_numpy(t).cuda(), wp, bd, layer, relu=False) for t in (x, z))
         assert (a == b).all(), nm.nm_variant_name(v)
+
+
+@pytest.mark.parametrize("n,m,cin", [(1, 4, 28), (2, 4, 16), (2, 4, 20), (1, 1, 8), (1, 1, 12), (4, 8, 16)])
+@pytest.mark.parametrize("kind", ["uniform", "signed"])
+@pytest.mark.parametrize("bias_on", [False, True])
+def test_few_columns_no_further_from_float64(n, m, cin, kind, bias_on):
+    import torch
+    layer = L("few", 24, 24, cin, 64, 1, 1, 1, 0, 1, n, m, 16)
+    x, w, bias = wl.make_tensors(layer, 4, 37)
+    if kind == "signed":
+        x = np.random.default_rng(3).standard_normal(x.shape, dtype=np.float32)
+    bias = bias * np.float32(bias_on)
+    wp = nm.nm_prune(w, n, m, 16)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = conv64(layer, x, zero_filled(wp, layer), bias)
+    old = rel64(run(fp32_instruction(wp), xd, wp, bd, layer, relu=False), ref)
+    for v in split_variants(wp):
+        assert rel64(run(v, xd, wp, bd, layer, relu=False), ref) <= old, nm.nm_variant_name(v)
+
+
+def test_fewest_columns_keep_the_fp32_instruction():
+    """Up to six kept columns, of a whole layer or of one part of a K split, the planes' missing products weigh more than the
+    roundings they save: the tuner leaves the three-plane forms out."""
+    import torch
+    for layer in (L("k1", 9, 9, 4, 64, 1, 1, 1, 0, 1, 1, 4, 16), L("k6", 9, 9, 12, 64, 1, 1, 1, 0, 1, 2, 4, 16),
+                  L("k6d", 9, 9, 8, 64, 1, 1, 1, 0, 1, 6, 8, 16)):
+        _, w, _ = wl.make_tensors(layer, 1, 41)
+        wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+        assert split_variants(wp)
+        say(layer.name)
+        v, _ = nm.nm_autotune(nm.NM_F32, 1, 9, 9, layer.Cin, wp, True, 1, 0, 1, False)
+        assert not nm.nm_variant_name(v).startswith("X3")
+    nm.nm_cache_clear()
