@@ -602,6 +602,9 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
         for (int v : base_variants()) {
             const VariantDesc& d = variant_desc(v);
             if ((d.kind != 4 && d.kind != 6) || !variant_legal(v, wp, xdt, ra)) continue;
+            // (7 blocks, and 4 wavefronts along the pixels: rounds x work takes them where they are the slower ones, 45.5 us
+            // for 42.1 with 224x224x3 -> 68 7x7 at batch 16, 33.5 for 27.5 with 112x112x2 -> 100 5x5)
+            if (d.kind == 4 && (d.NBLK == 7 || d.WP == 4)) continue;
             const int rb_per_wg = (4 / d.WP) * d.NJ;
             const long n_wg = (long)((P + d.BP - 1) / d.BP) * ((wp->n_rowblocks + rb_per_wg - 1) / rb_per_wg);
             const int occ = std::max(1, (int)std::min<size_t>(2, kMaxLdsBytes / lds_bytes(d, wp)));

@@ -78,10 +78,10 @@
 
 // bf16 kernel for layers with very few input channels (contiguous kernel-row
 // runs, one chunk of KS 64-element k-steps): where output pixels are not whole
-// 16-byte granules, and for very few pixels.
+// 16-byte granules or the staged rows do not fit the CU, and for very few pixels.
 // X(NBLK, WP, NJ)
 #define NMRUN_SHAPES(X) \
-    X(4, 1, 1) X(8, 1, 1) X(2, 1, 1) X(2, 2, 2) X(4, 2, 2)
+    X(4, 1, 1) X(8, 1, 1) X(2, 1, 1) X(2, 2, 2) X(4, 2, 2) X(2, 4, 4) X(4, 4, 4) X(1, 4, 4) X(3, 4, 4) X(7, 1, 1)
 // Y(NBLK, WP, NJ, KS)
 #define NMRUN_CHUNKS(Y, NB, WP, NJ) Y(NB, WP, NJ, 1) Y(NB, WP, NJ, 2) Y(NB, WP, NJ, 3) Y(NB, WP, NJ, 4)
 
