@@ -175,25 +175,29 @@ struct RunArgs {
     int w, sw, pw, dw, sh, dh;
 };
 
+// Elements of lead-in, 0 or 1, that put a kernel-row run on 4 bytes.
+int run_par(int pw, int cin) { return (int)((long)pw * cin % 2); }
+
 // Layout of the staged rows of kinds 10 and 11 (bytes of one plane; the data starts on 16 bytes, the run of
-// column 0 at `front`, 2 * lead bytes before it).
+// column 0 at `front`, 2 * lead bytes before it).  Worked out in 64 bits, since any padding and stride may be
+// asked for: a layout that fits the LDS fits an int.
 struct RowsLayout {
     int n, pitch, front, data;
-    size_t lds;   // all planes, whole 1 KB windows
+    size_t lds;   // all planes, whole 1 KB windows; (size_t)-1 and nothing else where they do not fit
 };
 RowsLayout rows_layout(const VariantDesc& d, const nm_packed* wp, const RunArgs& ra)
 {
-    const int par = (ra.pw * wp->cin) % 2, lead = ra.pw * wp->cin + par, gr = (par + wp->kw * wp->cin + 7) / 8;
-    const int wo = (ra.w + 2 * ra.pw - wp->kw) / ra.sw + 1;
-    RowsLayout r;
-    r.n = (d.NBLK - 1) * ra.sh + (wp->kh - 1) * ra.dh + 1;
-    r.data = (2 * lead + 15) / 16 * 16;
-    r.front = r.data - 2 * lead;
-    const long end = std::max((long)r.data + 2L * ra.w * wp->cin, (long)r.front + 2L * (wo - 1) * ra.sw * wp->cin + gr * 16L);
+    const int par = run_par(ra.pw, wp->cin);
+    const long lead = (long)ra.pw * wp->cin + par, gr = (par + wp->kw * wp->cin + 7) / 8;
+    const long wo = (ra.w + 2L * ra.pw - wp->kw) / ra.sw + 1;
+    const long n = (d.NBLK - 1L) * ra.sh + (wp->kh - 1L) * ra.dh + 1;
+    const long data = (2 * lead + 15) / 16 * 16, front = data - 2 * lead;
+    const long end = std::max(data + 2L * ra.w * wp->cin, front + 2 * (wo - 1) * ra.sw * wp->cin + gr * 16);
     const long pitch = (end + 15) / 16 * 16;
-    const long bytes = (long)r.n * pitch * (d.kind == 10 ? 1 : 3);
-    r.pitch = (int)std::min(pitch, 1L << 28);
-    r.lds = (size_t)((bytes + 1023) / 1024 * 1024);
+    RowsLayout r = {0, 0, 0, 0, (size_t)-1};
+    if (n > kMaxLdsBytes || pitch > kMaxLdsBytes) return r;
+    r.n = (int)n; r.pitch = (int)pitch; r.front = (int)front; r.data = (int)data;
+    r.lds = (size_t)((n * pitch * (d.kind == 10 ? 1 : 3) + 1023) / 1024 * 1024);
     return r;
 }
 
@@ -241,9 +245,9 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     }
     if ((d.kind == 4 || is_rows_kind(d.kind)) && ra) {
         // a kernel row must be one contiguous, 4-byte aligned run of every pixel
-        if (ra->dw != 1 || (ra->sw * wp->cin) % 2 != 0 || (ra->w * wp->cin) % 2 != 0) return false;
-        if (is_rows_kind(d.kind) && rows_layout(d, wp, *ra).lds + kRowsPieces > (size_t)kMaxLdsBytes) return false;
-        return find_prepack(wp, d, (ra->pw * wp->cin) % 2) != nullptr;
+        if (ra->dw != 1 || ((long)ra->sw * wp->cin) % 2 != 0 || ((long)ra->w * wp->cin) % 2 != 0) return false;
+        if (is_rows_kind(d.kind) && rows_layout(d, wp, *ra).lds > (size_t)kMaxLdsBytes - kRowsPieces) return false;
+        return find_prepack(wp, d, run_par(ra->pw, wp->cin)) != nullptr;
     }
     return find_prepack(wp, d) != nullptr;
 }
@@ -502,7 +506,7 @@ int split_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 // 5.6, 6.7, 8.6, 12.7 (5.6); fp32 batch 64 146, 121, 112, 155 (element-wise: 190), batch 1 10.2, 13.2, 20.6, 35 (9.7).
 int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
 {
-    const int wo = (ra.w + 2 * ra.pw - ra.dw * (wp->kw - 1) - 1) / ra.sw + 1;
+    const int wo = (int)((ra.w + 2L * ra.pw - (long)ra.dw * (wp->kw - 1) - 1) / ra.sw) + 1;
     int pick = -1;
     for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
@@ -1146,7 +1150,7 @@ static int conv2d_impl(const void* x, nm_dtype_t xdt, int b, int h, int w, int c
     }
     const VariantDesc& d = variant_desc(v);
     ConvParams p;
-    fill_params(p, d, *find_prepack(wp, d, (pw * wp->cin) % 2), wp, x, y, bias, b, h, w, g, sh, sw, ph, pw,
+    fill_params(p, d, *find_prepack(wp, d, run_par(pw, wp->cin)), wp, x, y, bias, b, h, w, g, sh, sw, ph, pw,
                 dh, dw, relu, elem_size(xdt));
     p.res = res;
     if (d.ksplit > 1) {
@@ -1337,7 +1341,7 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
     // one timed group of `reps` launches of variant v on fresh tensor sets: ms per launch, < 0 on error
     auto time_group = [&](int v, int reps) -> float {
         const VariantDesc& d = variant_desc(v);
-        const Prepack* pp = find_prepack(wp, d, (pw * wp->cin) % 2);
+        const Prepack* pp = find_prepack(wp, d, run_par(pw, wp->cin));
         ConvParams p;
         float* partial = nullptr;
         if (d.ksplit > 1) {   // sized here, once: nm_conv2d then finds the workspace large enough

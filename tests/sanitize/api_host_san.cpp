@@ -122,6 +122,15 @@ static const VariantDesc kFake[] = {
     {"F_NB4_WP1_NJ1_CK32_SPC4_S4", 64, 4, 1, 1, 32, 4, 1, 0, 1, 4, 0},
     {"F_NB4_WP1_NJ1_CK32_SPC2_S16", 64, 4, 1, 1, 32, 2, 1, 0, 1, 16, 0},
     {"F_SCALAR_CK32_SPC8_S2", 256, 4, 4, 4, 32, 8, 0, 0, 1, 2, 0},
+    // fp32 as three bf16 planes, and few input channels out of staged rows (NBLK output rows a workgroup)
+    {"F_X3S_NB4_WP1_NJ2", 64, 4, 1, 2, 64, 1, 1, 8, 1, 1, 0, 1},
+    {"F_X3D_NB2_WP1_NJ1", 32, 2, 1, 1, 64, 1, 1, 9, 1, 1, 0, 1},
+    {"F_X3S_NB4_WP1_NJ2_S2", 64, 4, 1, 2, 64, 1, 1, 8, 1, 2, 0, 1},
+    {"F_RUN_ROWS1_NJ4_KS3", 16, 1, 4, 4, 192, 3, 1, 10, 1, 1, 0},
+    {"F_RUN_ROWS8_NJ4_KS3", 16, 8, 4, 4, 192, 3, 1, 10, 1, 1, 0},
+    {"F_RUN_ROWS4_NJ4_KS1", 16, 4, 4, 4, 64, 1, 1, 10, 1, 1, 0},
+    {"F_ROWF_R2_NJ2_KS3", 16, 2, 2, 2, 192, 3, 1, 11, 1, 1, 0},
+    {"F_ROWF_R4_NJ1_KS1", 16, 4, 1, 1, 64, 1, 1, 11, 1, 1, 0},
 };
 int variant_count() { return (int)(sizeof(kFake) / sizeof(kFake[0])); }
 const VariantDesc& variant_desc(int v) { return kFake[v]; }
@@ -145,7 +154,22 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
     const long eh = (long)p.H + 2L * p.ph - (long)p.dh * (p.Kh - 1) - 1, ew = (long)p.W + 2L * p.pw - (long)p.dw * (p.Kw - 1) - 1;
     CHECK(eh >= 0 && ew >= 0 && p.Ho == eh / p.sh + 1 && p.Wo == ew / p.sw + 1);
     CHECK(p.P == p.B * p.Ho * p.Wo && p.K == p.Kh * p.Kw * p.Cin);
-    CHECK(p.n_ptiles == (p.P + d.BP - 1) / d.BP && p.n_wg == p.n_ptiles * p.n_cblocks * p.ksplit);
+    const bool rows = d.kind == 10 || d.kind == 11;
+    CHECK(p.n_ptiles == (rows ? p.B * ((p.Ho + d.NBLK - 1) / d.NBLK) : (p.P + d.BP - 1) / d.BP));
+    CHECK(p.n_wg == p.n_ptiles * p.n_cblocks * p.ksplit);
+    if (d.kind >= 8) CHECK(p.tile == 16 && p.rbpt == 1 && p.n_rowblocks == (p.Cout + 15) / 16);
+    if (rows) {
+        // every operand of every output pixel of a workgroup lies in the staged rows, and these in the CU's LDS
+        const long last = (long)p.rows_front + ((long)(d.NBLK - 1) * p.sh + (long)(p.Kh - 1) * p.dh) * p.rows_pitch +
+                          2L * (p.Wo - 1) * p.sw * p.Cin + 16L * p.run_gr;
+        const long plane = (long)p.rows_n * p.rows_pitch;
+        CHECK(p.rows_r == d.NBLK && p.rows_pitch % 16 == 0 && p.rows_data % 16 == 0 && p.rows_front >= 0 && last <= plane);
+        // column 0 of the image is where the run of output column 0 finds it, and a whole row fits
+        CHECK((long)p.rows_data - p.rows_front == 2 * ((long)p.pw * p.Cin + p.run_d));
+        CHECK((long)p.rows_data + 2L * p.W * p.Cin <= p.rows_pitch);
+        CHECK(plane * (d.kind == 10 ? 1 : 3) <= p.rows_lds && p.rows_lds % 1024 == 0 && p.rows_lds + 4 * 16 * 144 <= 160 * 1024);
+        CHECK(p.dw == 1 && (p.sw * (long)p.Cin) % 2 == 0 && (p.W * p.Cin) % 2 == 0);
+    }
     CHECK(p.ksplit == (d.ksplit > 1 ? d.ksplit : 1));
     if (p.ksplit > 1) {   // every split owns chunks, together they cover the K axis, and the partial sums have a home
         CHECK(p.cps >= 1 && (p.ksplit - 1) * p.cps < p.nchunks && p.ksplit * p.cps >= p.nchunks);
@@ -311,6 +335,31 @@ static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, in
     CHECK(nm_packed_free(wp) == NM_OK);
 }
 
+// one layer of few input channels, each row-staged form forced: runs of both alignments, a padding far wider than any row,
+// a stride that leaves one column of a huge padded image
+static void rows_case(int b, int h, int w, int cin, int kh, int kw, nm_dtype_t dt, int sh, int sw, int ph, int pw, bool any)
+{
+    const int cout = 24;
+    std::vector<float> wt((size_t)cout * kh * kw * cin, 0.5f);
+    nm_packed_t* wp = nullptr;
+    CHECK(nm_prune(wt.data(), cout, kh, kw, cin, 1, 1, 16, dt, &wp) == NM_OK);
+    const size_t es = dt == NM_F32 ? 4 : 2;
+    const int ho = (int)(((long)h + 2L * ph - kh) / sh) + 1, wo = (int)(((long)w + 2L * pw - kw) / sw) + 1;
+    void* x = dev_alloc((size_t)b * h * w * cin * es);
+    void* y = dev_alloc((size_t)b * ho * wo * cout * es);
+    int ran = 0;
+    for (int u = -1; u < nm_variant_count(); ++u) {
+        if (u >= 0 && (!strstr(nm_variant_name(u), "ROW") || nm_variant_legal(u, wp, dt, dt) != 1)) continue;
+        CHECK(nm_force_variant(u) == NM_OK);
+        const int rc = nm_conv2d(x, dt, b, h, w, cin, wp, nullptr, sh, sw, ph, pw, 1, 1, 0, y, dt, nullptr);
+        CHECK(rc == NM_OK || (u >= 0 && rc == NM_ERR_UNSUPPORTED));
+        ran += u >= 0 && rc == NM_OK;
+    }
+    CHECK((ran > 0) == any);
+    CHECK(nm_force_variant(-1) == NM_OK);
+    CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
+}
+
 // a K split whose partial sums outgrow the static scratch, and one that would have to allocate under capture
 static void split_limits()
 {
@@ -400,6 +449,14 @@ int main(int argc, char** argv)
         CHECK(hipFree(xb) == hipSuccess && hipFree(yb) == hipSuccess && nm_packed_free(h8) == NM_OK);
     }
     split_limits();
+    for (nm_dtype_t dt : {NM_F32, NM_BF16}) {
+        rows_case(2, 17, 20, 3, 7, 7, dt, 2, 2, 3, 3, true);
+        rows_case(1, 9, 10, 2, 3, 3, dt, 1, 1, 1, 1, true);
+        rows_case(1, 9, 10, 2, 3, 3, dt, 3, 1, 0, 0, true);
+        rows_case(1, 9, 10, 2, 3, 3, dt, 1, 1, 1, 20000, false);                          // the padding alone fills the LDS
+        rows_case(1, 9, 10, 2, 3, 3, dt, 1, 0x3fffffff, 1, 0x20000000, false);            // two columns, 2^30 apart
+        rows_case(1, 9, 10, 2, 3, 3, dt, 1, 0x40000000, 1, 0x3ffffffa, false);
+    }
     // nothing leaked on the "device": what is left is the K-split workspace and the static scratch
     CHECK(g_allocs.size() <= 2);
     const int n_entries = nm_cache_size();
