@@ -271,21 +271,15 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
                 if (live) *reinterpret_cast<u4v*>(y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout)) = v[k];
             }
             if constexpr (PL == 3) {
-                if (lo < kSplitTiny || hi >= kSplitInf || any) {
+                if (__builtin_expect(lo < kSplitTiny || hi >= kSplitInf || any, 0)) {
                     kernarg_t kp = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
                     __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
                     const unsigned below = any ? kp->redo_below : kSplitTiny;
 #pragma unroll 1
-                    for (int k = 0; k < NP * 4; ++k) {
-                        const int row = r0 + k / 4 * RPP, r = k & 3;
-                        const unsigned w = *reinterpret_cast<const unsigned*>(piece + row * PITCH + cg * 16 + r * 4) << 1;
-                        if (((any ? w : w - 1u) >= below && w < kSplitInf) || blk + row >= npx || co_out + r >= p.Cout) continue;
-                        const unsigned o = (unsigned)(pix0 + blk + row) * (unsigned)p.Cout + (unsigned)(co_out + r);
-                        float f = split_redo(kp, pix0 + blk + row, co_out + r, 0, p.K, p.bias ? p.bias[co_out + r] : 0.f);
-                        if (res) f += load1(res + o);
-                        if (p.relu) f = relu1(f);
-                        store1(y + o, f);
-                    }
+                    for (int row = r0; row < 16; row += RPP)
+                        if (blk + row < npx && co_out < p.Cout)
+                            split_again(kp, *reinterpret_cast<const u4v*>(piece + row * PITCH + cg * 16), pix0 + blk + row, co_out, below,
+                                        any != 0, 0, p.K, p.bias, res, p.relu != 0, y);
                 }
             }
             __builtin_amdgcn_wave_barrier();

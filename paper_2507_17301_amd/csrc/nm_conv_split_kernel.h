@@ -113,6 +113,85 @@ __device__ inline float split_redo(kernarg_t kp, int pp, int co, int k_lo, int k
     return acc;
 }
 
+// The same for the channels co .. co + 3 of one column tile: the kept columns in pairs, whose loads are
+// under way together, the tap worked out anew only where it changes.
+__device__ inline f4 split_redo4(kernarg_t kp, int pp, int co, int k_lo, int k_hi, f4 acc)
+{
+    const int HoWo = kp->Ho * kp->Wo, Cin = kp->Cin, kprime = kp->kprime, T = kp->ctile;
+    const int b = pp / HoWo, rem = pp - b * HoWo, ho = rem / kp->Wo, wo = rem - ho * kp->Wo;
+    const int j = co / T, t = co - j * T, b_H = b * kp->H;
+    const int h0 = ho * kp->sh - kp->ph, w0 = wo * kp->sw - kp->pw;
+    const float* x = reinterpret_cast<const float*>(kp->x);
+    const int* const idx = kp->idx + (size_t)j * kprime;
+    const float* const vals = kp->vals + (size_t)j * kprime * T + t;
+    int kk = 0;
+    for (int n = kprime; n > 0;) {               // the first kept column from k_lo on
+        const int half = n >> 1;
+        if (idx[kk + half] < k_lo) { kk += half + 1; n -= half + 1; } else n = half;
+    }
+    int tap_end = -1;
+    bool in = false;
+    unsigned base = 0;                           // element of x (of fewer than 2^31) that column k of the tap is: base + k
+    for (; kk < kprime; kk += 2) {
+        int k[2];
+        f4 w[2];
+        float v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int at = kk + u < kprime ? kk + u : kprime - 1;
+            k[u] = idx[at];
+            w[u] = *reinterpret_cast<const f4*>(vals + (size_t)at * T);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (k[u] >= tap_end) {
+                kernarg_t kq = kp;               // (read here, not held through the loop)
+                asm volatile("" : "+s"(kq));
+                const int tap = k[u] / Cin, kh = tap / kq->Kw, kw = tap - kh * kq->Kw;
+                const int hi = h0 + kh * kq->dh, wi = w0 + kw * kq->dw;
+                in = ((unsigned)hi < (unsigned)kq->H) & ((unsigned)wi < (unsigned)kq->W);
+                base = (unsigned)(((b_H + hi) * kq->W + wi - tap) * Cin);
+                tap_end = (tap + 1) * Cin;
+            }
+            const bool live = in & (kk + u < kprime) & (k[u] < k_hi);
+            v[u] = x[live ? base + (unsigned)k[u] : 0u];
+            v[u] = live ? v[u] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = fmaf(w[u][r], v[u], acc[r]);
+        if (k[1] >= k_hi || ((acc[0] != acc[0]) & (acc[1] != acc[1]) & (acc[2] != acc[2]) & (acc[3] != acc[3]))) break;
+    }
+    return acc;
+}
+
+// Computes those of the outputs (pixel pp, channels co .. co + 3) again whose sums `sum` say so, and stores them.
+__device__ inline void split_again(kernarg_t kp, const u4v sum, int pp, int co, unsigned below, bool inexact, int k_lo, int k_hi,
+                                   const float* bias, const float* res, bool relu, float* y)
+{
+    asm volatile("" : "+s"(kp));
+    unsigned again = 0u;                         // a bit per channel
+    const int Cout = kp->Cout;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const unsigned w = sum[r] << 1;
+        again |= ((inexact ? w : w - 1u) < below || w >= kSplitInf) && co + r < Cout ? 1u << r : 0u;
+    }
+    if (!again) return;
+    unsigned off = (unsigned)pp * (unsigned)Cout + (unsigned)co;
+    const bool quad = kp->ctile % 4 == 0 && Cout % 4 == 0;
+    f4 o = f4{0.f, 0.f, 0.f, 0.f};
+    if (quad) o = split_redo4(kp, pp, co, k_lo, k_hi, bias ? *reinterpret_cast<const f4*>(bias + co) : o);
+#pragma unroll 1
+    for (; again; again >>= 1, ++off, ++co, o = f4{o.y, o.z, o.w, 0.f}) {
+        if (!(again & 1u)) continue;
+        float v = quad ? o.x : split_redo(kp, pp, co, k_lo, k_hi, bias ? bias[co] : 0.f);
+        if (res) v += res[off];
+        y[off] = relu ? relu1(v) : v;
+    }
+}
+
 // LDS accesses of a stage are ordered by hand around a bare barrier: this wavefront's LDS writes have
 // landed and its LDS reads have returned; global loads in flight stay in flight.
 __device__ inline void split_barrier()
@@ -465,22 +544,16 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
                     }
                 }
             }
-            if (lo < kSplitTiny || hi >= kSplitInf || inexact) {
+            if (__builtin_expect(lo < kSplitTiny || hi >= kSplitInf || inexact, 0)) {
                 __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
                 const unsigned below = inexact ? kp->redo_below : kSplitTiny;
                 const int k_lo = (c_begin / kp->ncpt) * kp->Cin + (c_begin % kp->ncpt) * kSplitCK;
                 const int k_hi = c_end < kp->nchunks ? (c_end / kp->ncpt) * kp->Cin + (c_end % kp->ncpt) * kSplitCK : kp->K;
 #pragma unroll 1
-                for (int i = 0; i < rows / RPP * 4; ++i) {
-                    const int row = i / 4 * RPP, r = i & 3, pp = pp0 + row;
-                    const unsigned w = *reinterpret_cast<const unsigned*>(src + row * PITCH + r * 4) << 1;
-                    if (((inexact ? w : w - 1u) >= below && w < kSplitInf) || pp >= P || co + r >= Cout) continue;
-                    const unsigned off = (unsigned)pp * (unsigned)Cout + (unsigned)(co + r);
-                    float o = split_redo(kp, pp, co + r, k_lo, k_hi, kp->bias && kp->ksplit <= 1 ? kp->bias[co + r] : 0.f);
-                    if (res) o += res[off];
-                    if (relu) o = relu1(o);
-                    y[off] = o;
-                }
+                for (int row = 0; row < rows; row += RPP)
+                    if (pp0 + row < P && co < Cout)
+                        split_again(kp, *reinterpret_cast<const u4v*>(src + row * PITCH), pp0 + row, co, below, inexact != 0, k_lo, k_hi,
+                                    kp->ksplit <= 1 ? kp->bias : nullptr, res, relu, y);
             }
             __builtin_amdgcn_wave_barrier();
         }

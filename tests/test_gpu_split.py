@@ -242,3 +242,30 @@ def test_fewest_columns_keep_the_fp32_instruction():
         v, _ = nm.nm_autotune(nm.NM_F32, 1, 9, 9, layer.Cin, wp, True, 1, 0, 1, False)
         assert not nm.nm_variant_name(v).startswith("X3")
     nm.nm_cache_clear()
+
+
+@pytest.mark.parametrize("tile,cout", [(1, 20), (5, 40), (4, 36), (12, 64), (32, 72), (16, 37)])
+@pytest.mark.parametrize("n,m", [(2, 4), (1, 1)])
+def test_outputs_computed_again_for_every_column_tile(tile, cout, n, m):
+    """Outputs that are computed again, singly or four channels at a time, with residual, ReLU and a K split."""
+    import torch
+    layer = L("again", 11, 10, 68, cout, 3, 3, 1, 2, 2, n, m, tile)
+    x, w, bias = wl.make_tensors(layer, 2, 43)
+    x[0], bias = np.ldexp(x[0] - 0.5, -118), bias * 0
+    x[1, 4, 5, 7], x[1, 9, 0, 60] = np.inf, -np.inf
+    w = np.ldexp(w, 30).astype(np.float32)
+    wp = nm.nm_prune(w, n, m, tile)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    for relu in (False, True):
+        ref = run(fp32_instruction(wp), xd, wp, bd, layer, relu)
+        rd = torch.from_numpy(np.random.default_rng(3).standard_normal(ref.shape, dtype=np.float32)).cuda()
+        ref2 = run(fp32_instruction(wp), xd, wp, bd, layer, relu, rd)
+        ok = np.isfinite(ref)
+        assert ok[0].all() and not ok[1].all()
+        for v in split_variants(wp):
+            got = run(v, xd, wp, bd, layer, relu)
+            assert rel64(got[0], ref[0].astype(np.float64)) <= 1e-6, nm.nm_variant_name(v)
+            assert (np.isnan(got) == np.isnan(ref)).all() and (got[np.isinf(ref)] == ref[np.isinf(ref)]).all(), nm.nm_variant_name(v)
+            assert rel64(got[ok], ref[ok].astype(np.float64)) <= 1e-6, nm.nm_variant_name(v)
+            got = run(v, xd, wp, bd, layer, relu, rd)
+            assert rel64(got[0], ref2[0].astype(np.float64)) <= 1e-6, nm.nm_variant_name(v)
