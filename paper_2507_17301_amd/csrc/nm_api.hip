@@ -136,7 +136,7 @@ ShapeKey make_key(nm_dtype_t xdt, nm_dtype_t ydt, int b, int h, int w, const nm_
     return k;
 }
 
-constexpr size_t kRowsPieces = 4 * 16 * 144;   // kinds 10, 11: the output pieces of four wavefronts
+constexpr size_t kRowsPieces = 4 * kRowsPiece;   // kinds 10, 11: the output pieces of four wavefronts
 
 // LDS footprint of variant d on the layer wp (the ring of the gather-free bf16
 // kernel is only as deep as the layer's K loop is long).
@@ -144,8 +144,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
 {
     // the epilogue's output tile [BP][channels of the workgroup] plus 16 bytes per pixel
     const size_t otile = (size_t)d.BP * ((size_t)(4 / d.WP) * d.NJ * 16 * (d.kind == 0 || d.kind == 5 ? 4 : 2) + 16);
-    if (is_split_kind(d.kind))   // two stages of three bf16 planes [BP][64], and each contracting wavefront's output piece
-        return (size_t)2 * d.BP * 384 + (size_t)4 * (d.NBLK > 1 ? 32 : 16) * (d.NJ * 64 + 16);
+    if (is_split_kind(d.kind)) return (size_t)split_lds_bytes(d.NBLK, d.WP, d.NJ);
     if (is_rows_kind(d.kind)) return kRowsPieces;   // and the staged rows, which depend on the image (rows_layout)
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
         return (size_t)4 * 16 * d.NBLK * (d.NJ * 32 + 16);

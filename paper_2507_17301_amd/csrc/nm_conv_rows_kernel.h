@@ -31,8 +31,6 @@
 
 namespace nm {
 
-constexpr int kRowsPiece = 16 * 144;     // a wavefront's output piece: 16 pixels x 128 bytes and 16 bytes of padding a row
-
 template <int PL, int NJ, int KS>
 __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_kernel(const ConvParams p)
 {

@@ -42,19 +42,8 @@
 
 namespace nm {
 
-constexpr int kSplitCK = 64;   // channels per chunk
 constexpr unsigned kSplitInf = 0xff000000u;              // infinity, as a word shifted left by one
 constexpr unsigned kSplitTiny = (127u - 100u) << 24;     // 2^-100, likewise
-// one LDS stage: three planes [BP][64] bf16
-constexpr int split_stage_bytes(int BP) { return 3 * BP * kSplitCK * 2; }
-// each contracting wavefront's output piece: up to 32 pixels x its 16 NJ channels, 16 bytes of padding a row
-constexpr int split_out_rows(int NBLK) { return NBLK > 1 ? 32 : 16; }
-constexpr int split_out_pitch(int NJ) { return NJ * 64 + 16; }
-constexpr int split_lds_bytes(int NBLK, int WP, int NJ)
-{
-    return 2 * split_stage_bytes(16 * NBLK * WP) + 4 * split_out_rows(NBLK) * split_out_pitch(NJ);
-}
-
 // wavefronts per SIMD to leave registers for: two workgroups per CU where accumulators and the two
 // weight sets fit 128 registers, one otherwise
 constexpr int split_waves(int NBLK, int WP, int NJ, bool sparse)

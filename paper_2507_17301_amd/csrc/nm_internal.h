@@ -115,6 +115,21 @@ constexpr int strip_stride(int BP, int CK, bool vec)
 // Vector mode stores im2col row r of a chunk (r = 4 * quad + j) in LDS row j * (CK / 4) + quad.
 constexpr int strip_row(int r, int CK) { return (r & 3) * (CK / 4) + (r >> 2); }
 
+// LDS of the three-plane fp32 kernel (kinds 8, 9).
+constexpr int kSplitCK = 64;   // channels per chunk
+// one LDS stage: three planes [BP][64] bf16
+constexpr int split_stage_bytes(int BP) { return 3 * BP * kSplitCK * 2; }
+// each contracting wavefront's output piece: up to 32 pixels x its 16 NJ channels, 16 bytes of padding a row
+constexpr int split_out_rows(int NBLK) { return NBLK > 1 ? 32 : 16; }
+constexpr int split_out_pitch(int NJ) { return NJ * 64 + 16; }
+constexpr int split_lds_bytes(int NBLK, int WP, int NJ)
+{
+    return 2 * split_stage_bytes(16 * NBLK * WP) + 4 * split_out_rows(NBLK) * split_out_pitch(NJ);
+}
+
+// Row-staged kernels (kinds 10, 11): a wavefront's output piece, 16 pixels x 128 bytes and 16 bytes of padding a row
+constexpr int kRowsPiece = 16 * 144;
+
 }  // namespace nm
 
 struct nm_packed {
