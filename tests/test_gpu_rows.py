@@ -26,6 +26,42 @@ GRID = [
 ]
 
 
+def expected_forms(layer, bf16):
+    """Names of the forms that this layer's rows, alignment and k-steps ask for (all of GRID's rows fit the LDS)."""
+    if (layer.W * layer.Cin) % 2 or (layer.stride * layer.Cin) % 2 or layer.dil != 1:
+        return set()
+    if layer.Cin % (8 if bf16 else 4) == 0 or layer.Cout % (8 if bf16 else 4):
+        return set()
+    ks = (layer.Kh * (((layer.pad * layer.Cin) % 2 + layer.Kw * layer.Cin + 7) // 8) + 7) // 8
+    if bf16:
+        return {f"RUN_ROWS{r}_NJ4_KS{ks}" for r in (1, 2, 4, 8)}
+    return {f"ROWF_R{r}_NJ{nj}_KS{ks}" for r in (1, 2, 4, 8) for nj in (1, 2) if ks < 4 or nj == 1}
+
+
+def each_form(layer, wp, bf16, call):
+    """call(name) under each row-staged form in turn: all that are due run, and what else the handle has tables for (the
+    k-steps of the other alignment) is refused as a form that cannot run this layer."""
+    due, dt = expected_forms(layer, bf16), nm.NM_BF16 if bf16 else nm.NM_F32
+    ran = set()
+    try:
+        for v in range(nm.nm_variant_count()):
+            name = nm.nm_variant_name(v)
+            if not name.startswith(("RUN_ROWS", "ROWF")) or not nm.nm_variant_legal(v, wp, dt, dt):
+                continue
+            say(f"{layer.name} {name}")
+            nm.nm_force_variant(v)
+            if name not in due:
+                with pytest.raises(nm.NMError, match="cannot run this layer"):
+                    call(name)
+                continue
+            call(name)
+            ran.add(name)
+    finally:
+        nm.nm_force_variant(-1)
+    assert ran == due
+    return ran
+
+
 @pytest.mark.parametrize("layer,batch", GRID, ids=[g[0].name for g in GRID])
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 def test_every_form(layer, batch, bf16):
@@ -37,27 +73,15 @@ def test_every_form(layer, batch, bf16):
     ref = oracle_conv(layer, x, w, bias, relu=False, bf16=bf16)
     res = torch.from_numpy(np.random.default_rng(5).standard_normal(ref.shape, dtype=np.float32)).cuda().to(tdt)
     tol = BF16_TOL if bf16 else FP32_TOL
-    ran = 0
-    try:
-        for v in range(nm.nm_variant_count()):
-            name = nm.nm_variant_name(v)
-            if not name.startswith(("RUN_ROWS", "ROWF")) or not nm.nm_variant_legal(v, wp, dt, dt):
-                continue
-            say(f"{layer.name} {name}")
-            nm.nm_force_variant(v)
-            try:
-                y = nm.nm_conv2d_res(xd, wp, None, bd, layer.stride, layer.pad, layer.dil, True)
-            except nm.NMError:                  # the k-steps of the other alignment
-                continue
-            z = nm.nm_conv2d_res(xd, wp, res, None, layer.stride, layer.pad, layer.dil, False)
-            torch.cuda.synchronize()
-            assert norm_err(y.float().cpu().numpy(), np.maximum(ref, 0)) <= tol, name
-            assert norm_err(z.float().cpu().numpy(), ref - bias + res.float().cpu().numpy()) <= 2 * tol, name   # (ref is rounded too)
-            ran += 1
-    finally:
-        nm.nm_force_variant(-1)
-    # cin6 is a multiple of neither 4 nor 8, cin 1, 2, 3, 5 likewise: both tensor types have the form wherever rows are even
-    assert ran or (layer.W * layer.Cin) % 2 or (layer.stride * layer.Cin) % 2
+
+    def check(name):
+        y = nm.nm_conv2d_res(xd, wp, None, bd, layer.stride, layer.pad, layer.dil, True)
+        z = nm.nm_conv2d_res(xd, wp, res, None, layer.stride, layer.pad, layer.dil, False)
+        torch.cuda.synchronize()
+        assert norm_err(y.float().cpu().numpy(), np.maximum(ref, 0)) <= tol, name
+        assert norm_err(z.float().cpu().numpy(), ref - bias + res.float().cpu().numpy()) <= 2 * tol, name   # (ref is rounded too)
+
+    each_form(layer, wp, bf16, check)
 
 
 def test_infinity_and_default():
@@ -109,31 +133,20 @@ def test_infinities_bf16(layer, relu):
     down = conv(pos, (wt < 0).double()) + conv(neg, (wt > 0).double())
     nan = (conv(np.isnan(x).astype(np.float64), torch.ones_like(wt)) > 0) | ((up > 0) & (down > 0))
     assert (up > 0).any() and (down > 0).any() and nan.any() and (hit == 0).any()
-    ran = 0
-    try:
-        for v in range(nm.nm_variant_count()):
-            name = nm.nm_variant_name(v)
-            if not name.startswith("RUN_ROWS") or not nm.nm_variant_legal(v, wp, nm.NM_BF16, nm.NM_BF16):
-                continue
-            say(f"inf {layer.name} {name}")
-            nm.nm_force_variant(v)
-            try:
-                y = nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, relu)
-            except nm.NMError:                  # the k-steps of the other alignment
-                continue
-            torch.cuda.synchronize()
-            y = y.float().cpu().numpy()
-            ok = hit == 0
-            assert norm_err(y[ok], np.maximum(ref, 0)[ok] if relu else ref[ok]) <= BF16_TOL, name
-            assert np.isposinf(y[(up > 0) & ~nan]).all(), name
-            if relu:
-                assert (y[(down > 0) & ~nan] == 0).all(), name
-            else:
-                assert np.isneginf(y[(down > 0) & ~nan]).all() and np.isnan(y[nan]).all(), name
-            ran += 1
-    finally:
-        nm.nm_force_variant(-1)
-    assert ran
+
+    def check(name):
+        y = nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, relu)
+        torch.cuda.synchronize()
+        y = y.float().cpu().numpy()
+        ok = hit == 0
+        assert norm_err(y[ok], np.maximum(ref, 0)[ok] if relu else ref[ok]) <= BF16_TOL, name
+        assert np.isposinf(y[(up > 0) & ~nan]).all(), name
+        if relu:
+            assert (y[(down > 0) & ~nan] == 0).all(), name
+        else:
+            assert np.isneginf(y[(down > 0) & ~nan]).all() and np.isnan(y[nan]).all(), name
+
+    assert each_form(dense, wp, True, check)
 
 
 @pytest.mark.parametrize("layer", [GRID[0][0], GRID[3][0], GRID[5][0]], ids=lambda l: l.name)
@@ -158,26 +171,22 @@ def test_values_too_small_for_their_planes(layer, xe, we):
         return float(np.sqrt((d * d).sum() / (ref * ref).sum()))
 
     legal = [v for v in range(nm.nm_variant_count()) if nm.nm_variant_legal(v, wp)]
-    forms = [v for v in legal if nm.nm_variant_name(v).startswith("ROWF")]
     try:
         nm.nm_force_variant(next(v for v in legal if nm.nm_variant_name(v).startswith("NB4_WP1_NJ1")))
         old = err(nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False))
-        ran = 0
-        for v in forms:
-            nm.nm_force_variant(v)
-            try:
-                y = nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False)
-            except nm.NMError:                  # the k-steps of the other alignment
-                continue
-            e = err(y)
-            say(f"{layer.name} 2^{xe} * 2^{we} {nm.nm_variant_name(v)} {e:.3g} (fp32 instruction {old:.3g})")
-            # one rounding per kept column, where the fp32 instruction has one per four: at most twice its distance
-            assert e <= 2 * old + 1e-7, nm.nm_variant_name(v)
-            ran += 1
     finally:
         nm.nm_force_variant(-1)
-    assert ran if we > -100 else not forms
-    nm.nm_force_variant(-1)
+
+    def check(name):
+        e = err(nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False))
+        say(f"2^{xe} * 2^{we} {e:.3g} (fp32 instruction {old:.3g})")
+        # one rounding per kept column, where the fp32 instruction has one per four: at most twice its distance
+        assert e <= 2 * old + 1e-7, name
+
+    if we > -100:
+        assert each_form(dense, wp, False, check)
+    else:
+        assert not any(nm.nm_variant_name(v).startswith("ROWF") for v in legal)
     assert err(nm.nm_conv2d(xd, wp, bd, dense.stride, dense.pad, 1, False)) <= 2 * old + 1e-7
 
 
@@ -208,20 +217,14 @@ def test_no_further_from_float64_than_the_fp32_instruction(kh, kw, cin, pad, kin
     run = lambda: nm.nm_conv2d(xd, wp, bd, layer.stride, layer.pad, 1, False)
     try:
         nm.nm_force_variant(next(v for v in legal if nm.nm_variant_name(v).startswith("NB4_WP1_NJ1")))
-        old, ran = dist64(run(), x, w, bias, layer), 0
-        for v in legal:
-            if not nm.nm_variant_name(v).startswith("ROWF"):
-                continue
-            nm.nm_force_variant(v)
-            try:
-                y = run()
-            except nm.NMError:                  # the k-steps of the other alignment
-                continue
-            assert dist64(y, x, w, bias, layer) <= old, nm.nm_variant_name(v)
-            ran += 1
-        assert ran
+        old = dist64(run(), x, w, bias, layer)
     finally:
         nm.nm_force_variant(-1)
+
+    def check(name):
+        assert dist64(run(), x, w, bias, layer) <= old, name
+
+    assert each_form(layer, wp, False, check)
 
 
 def test_fewest_columns_keep_the_fp32_instruction():

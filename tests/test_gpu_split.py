@@ -269,3 +269,25 @@ def test_outputs_computed_again_for_every_column_tile(tile, cout, n, m):
             assert rel64(got[ok], ref[ok].astype(np.float64)) <= 1e-6, nm.nm_variant_name(v)
             got = run(v, xd, wp, bd, layer, relu, rd)
             assert rel64(got[0], ref2[0].astype(np.float64)) <= 1e-6, nm.nm_variant_name(v)
+
+
+@pytest.mark.parametrize("layer", [L("one_chunk", 20011, 1, 64, 200, 1, 1, 1, 0, 1, 2, 4, 16), L("three_chunks", 20011, 1, 192, 200, 1, 1, 1, 0, 1, 2, 4, 16),
+                                   L("nine_chunks", 141, 142, 64, 136, 3, 3, 1, 1, 1, 2, 4, 16), L("two_chunks", 20011, 1, 68, 200, 1, 1, 1, 0, 1, 2, 4, 16),
+                                   L("dense1", 20011, 1, 64, 200, 1, 1, 1, 0, 1, 1, 1, 16), L("dense3", 20011, 1, 136, 200, 1, 1, 1, 0, 1, 4, 8, 12)],
+                         ids=lambda l: l.name)
+def test_workgroups_walk_several_tiles(layer):
+    """More output tiles than the chip holds workgroups, in numbers that do not divide evenly, with odd and even numbers of
+    chunks a tile, ragged last tiles in both directions, with and without a residual: every form, every output."""
+    import torch
+    x, w, bias = wl.make_tensors(layer, 1, 47)
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = conv64(layer, x, zero_filled(wp, layer), bias)
+    res = np.random.default_rng(5).standard_normal(ref.shape, dtype=np.float32)
+    rd = torch.from_numpy(res).cuda()
+    vs = split_variants(wp)
+    assert vs
+    for v in vs:
+        say(f"{layer.name} {nm.nm_variant_name(v)}")
+        assert norm_err(run(v, xd, wp, bd, layer, relu=True), np.maximum(ref, 0)) <= FP32_TOL, nm.nm_variant_name(v)
+        assert norm_err(run(v, xd, wp, bd, layer, relu=False, res=rd), ref + res) <= FP32_TOL, nm.nm_variant_name(v)
