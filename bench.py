@@ -25,7 +25,23 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f8": 5000.0}   # dense MFMA peaks of MI355X
+PEAK_PLANES_TFLOPS = PEAK_TFLOPS["bf16"] / 6                 # fp32 as three bf16 planes: six bf16 products per multiply-add
 PEAK_HBM_GBS = 8000.0
+
+# the kernel behind a variant's name, by the name's first part (longest match)
+KERNELS = {"NB": "nm_conv_kernel", "VAR": "nm_conv_kernel", "B16": "nm_conv_bf16_kernel", "SP": "nm_conv_sp16_kernel",
+           "RUN": "nm_conv_run16_kernel", "RUN_ROWS": "nm_conv_rows_kernel", "ROWF": "nm_conv_rows_kernel",
+           "X3S": "nm_conv_split_kernel", "X3D": "nm_conv_split_kernel", "F8": "nm_conv_f8_kernel",
+           "F8S": "nm_conv_sp16_kernel", "F8W": "nm_conv_sp16_kernel", "F8R": "nm_conv_sp16_kernel"}
+
+
+def kernel_of(variant):
+    return KERNELS[max((k for k in KERNELS if variant.startswith(k)), key=len)]
+
+
+def matrix_peak(variant, dtype):
+    """Peak rate, in the layer's own multiply-adds, of the matrix cores as this variant uses them."""
+    return PEAK_PLANES_TFLOPS if variant.startswith(("X3", "ROWF")) else PEAK_TFLOPS[dtype]
 
 
 def log(*a):
@@ -175,7 +191,7 @@ class Stack:
             ms = sorted(marks[k][i].elapsed_time(marks[k][i + 1]) for k in range(inst_steps))[inst_steps // 2]
             eff = l.effective_flops(self.B)
             byts = l.algorithmic_bytes(self.B, self.esize, self.esize_out)
-            t_flop = eff / (PEAK_TFLOPS[self.dtype] * 1e12) * 1e3
+            t_flop = eff / (matrix_peak(nm.nm_variant_name(self.launched[i]), self.dtype) * 1e12) * 1e3
             t_mem = byts / (PEAK_HBM_GBS * 1e9) * 1e3
             rows.append({
                 "layer": l.name, "variant": nm.nm_variant_name(self.launched[i]),
@@ -217,27 +233,33 @@ def profiled_traffic(dtype):
 
 
 def stack_roofline(st, ms_step, rows, headline, floor_ms=None):
-    """The convolution kernel, all launches of a step taken together, against the roofline that
-    binds the workload: each layer's lower bound is max(effective flops / matrix-core peak,
-    algorithmic bytes / HBM peak); the workload is bound by whichever side has the larger sum.
+    """The convolution kernels, all launches of a step taken together, against the roofline that
+    binds the workload: each layer's lower bound is max(effective flops / matrix-core peak of the
+    variant that ran it, algorithmic bytes / HBM peak); the workload is bound by whichever side has
+    the larger sum.
     The average launch duration comes from the timed region itself: the launches of a step run
     back to back on one stream, so step time / launches is the kernel's duration plus whatever
     gap the launches leave (an upper bound on the duration; the kernel trace shows no gap)."""
     dense, eff, byts = st.totals()
     kern_ms = sum(r["ms"] for r in rows)
     tmin_ms = sum(r["t_min_ms"] for r in rows)
-    hbm_bound = sum(r["t_mem_ms"] for r in rows) >= sum(r["t_flop_ms"] for r in rows)
+    t_flop = sum(r["t_flop_ms"] for r in rows)
+    hbm_bound = sum(r["t_mem_ms"] for r in rows) >= t_flop
     if hbm_bound:
         roofline = {"bound": "hbm", "achieved": byts / ms_step / 1e6, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": byts / ms_step / 1e6 / PEAK_HBM_GBS}
     else:
-        roofline = {"bound": "mfma", "achieved": eff / ms_step / 1e9, "peak": PEAK_TFLOPS[st.dtype],
-                    "unit": "TFLOP/s", "frac": eff / ms_step / 1e9 / PEAK_TFLOPS[st.dtype]}
+        # (layers on different instructions: the rate at which each would run at its own peak)
+        roofline = {"bound": "mfma", "achieved": eff / ms_step / 1e9, "peak": eff / t_flop / 1e9,
+                    "unit": "TFLOP/s", "frac": t_flop / ms_step}
     traffic, source = profiled_traffic(st.dtype) if headline else (None, None)
     families = sorted({(r["variant"] or "?").split("_")[0] for r in rows})
+    share = {}
+    for r in rows:
+        share[kernel_of(r["variant"])] = share.get(kernel_of(r["variant"]), 0.0) + r["ms"]
     roofline.update({
         "traffic": traffic, "traffic_source": source,
-        "kernel": "nm_conv_sp16_kernel<F8> (+ nm_conv_f8_kernel)" if st.f8 else ("nm_conv_sp16_kernel" if st.bf16 else "nm_conv_kernel"),
+        "kernel": " + ".join(f"{k} ({v / kern_ms * 100:.0f} %)" for k, v in sorted(share.items(), key=lambda kv: -kv[1])),
         "variant_families": families,
         "launches_per_step": len(rows), "avg_launch_ms": ms_step / len(rows),
         # with an event after every layer of three extra steps (adds the events' own cost)
@@ -598,12 +620,13 @@ def whole_network(args, n_, m_, t_):
             byts += int(torch.tensor(net.shapes[op.residual]).prod()) * esize
         if op.kind != "conv":
             byts += (int(torch.tensor(net.shapes[op.src]).prod()) + int(torch.tensor(net.shapes[op.dst]).prod())) * esize
-    if bf16:
+    peak = PEAK_TFLOPS["bf16"] if bf16 else PEAK_PLANES_TFLOPS   # (the faster of the two ways an fp32 layer is run)
+    if byts / PEAK_HBM_GBS >= eff / peak / 1e3:
         roofline = {"bound": "hbm", "achieved": byts / ms_step / 1e6, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": byts / ms_step / 1e6 / PEAK_HBM_GBS, "traffic": None}
     else:
-        roofline = {"bound": "mfma", "achieved": eff / ms_step / 1e9, "peak": PEAK_TFLOPS["f32"],
-                    "unit": "TFLOP/s", "frac": eff / ms_step / 1e9 / PEAK_TFLOPS["f32"], "traffic": None}
+        roofline = {"bound": "mfma", "achieved": eff / ms_step / 1e9, "peak": peak,
+                    "unit": "TFLOP/s", "frac": eff / ms_step / 1e9 / peak, "traffic": None}
     roofline["note"] = "whole step (all operators) against the convolutions' flops / all tensors' bytes"
     cpu = None
     if not args.no_cpu_baseline:
