@@ -107,21 +107,6 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
             }
         }
         NM_WAIT_VMCNT(0);
-        // Is there an infinity or NaN among what this wavefront staged?  (224x224x3 -> 64, batch 64: 34.5 -> 35.7 us; the
-        // sums of each block looked at instead, 57.)
-        unsigned found = 0u;                     // the top bit of either half: an exponent of all ones
-        auto look = [&](unsigned v) { found |= (v & 0x7f807f80u) + 0x00800080u; };
-        if (vec) {
-            for (int w = wave * 64; w < total; w += 256) {
-                const u4v v = *reinterpret_cast<const u4v*>(lds8 + (w + lane) * 16);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) look(v[u]);
-            }
-        } else {
-            for (int w = wave * 64; w < total * 4; w += 256) look(*reinterpret_cast<const unsigned*>(lds8 + (w + lane) * 4));
-        }
-        const bool any = __builtin_amdgcn_ballot_w64((found & 0x80008000u) != 0u) != 0ull;
-        if (lane == 0) *reinterpret_cast<int*>(piece + ROWB) = any;   // (the padding of a piece's first row)
     } else {
         const int total = p.rows_n * G * 2;      // quads of four values: 8 bytes of a plane
         unsigned lost = 0u;                      // (see the three-plane kernel)
@@ -179,11 +164,14 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
     const int pix0 = (b * p.Ho + ho0) * p.Wo;
     const int r0 = lane / GPR, cg = lane % GPR;
     const int co_out = rb0 * 16 + cg * (16 / ES);
-    // what the wavefronts found among the staged values: an infinity or NaN (bf16), values whose planes leave bits out (fp32)
+    // fp32: the planes of a staged value leave bits out
     int any = 0;
+    if constexpr (PL == 3) {
 #pragma unroll
-    for (int w = 0; w < 4; ++w) any |= *reinterpret_cast<const int*>(lds8 + p.rows_lds + w * kRowsPiece + ROWB);
-    any = __builtin_amdgcn_readfirstlane(any);
+        for (int w = 0; w < 4; ++w) any |= *reinterpret_cast<const int*>(lds8 + p.rows_lds + w * kRowsPiece + ROWB);
+        any = __builtin_amdgcn_readfirstlane(any);
+    }
+    float bad = 0.f;                             // bf16: NaN once a sum was not finite
     T* __restrict__ y = reinterpret_cast<T*>(p.y);
     const T* __restrict__ res = reinterpret_cast<const T*>(p.res);
     // (real_only: elements that are no tap of a run are taken for zero)
@@ -230,6 +218,12 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
             if constexpr (PL == 3) {
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj) acc[jj] = acc[jj] + low[jj];
+            }
+            if constexpr (PL == 1 && !real_only) {
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) bad = fmaf(acc[jj][r], 0.f, bad);
             }
             if constexpr (PL == 1) {
                 // residual (accumulator layout: the first layer of a network has none), activation, the one rounding
@@ -283,15 +277,17 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
             __builtin_amdgcn_wave_barrier();
         }
     };
+    blocks(std::false_type());
     if constexpr (PL == 1) {
         // An infinity or NaN in a padding slot (the lead-in and the rest of a run, K positions beyond the last kernel
-        // row) times its weight 0 would be a NaN that the output is not due.
-        if (any) {
+        // row) times its weight 0 is a NaN that the output is not due: once more without those slots.
+        // (224x224x3 -> 64, batch 64: x1.02 of the time without the look; the staged granules looked at instead, x1.03 to
+        // 1.05, and a branch per block x1.6)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != bad) != 0ull, 0)) {
+            __builtin_amdgcn_s_waitcnt(0);       // the stores above come first
             blocks(std::true_type());
-            return;
         }
     }
-    blocks(std::false_type());
 }
 
 template <int PL, int NJ, int KS>
