@@ -20,7 +20,7 @@
 // x0.45; 7x7x3 x0.84 and x0.33).
 //
 // Bound: memory (bf16, batch 64, 224x224x3 -> 112x112x64: 122 MB) and, in fp32, the matrix cores (K = 147
-// padded to 192, six products: 54 us).  36 and 112 us; the kernel before this one staged every pixel's 24 granules separately, 48 KB
+// padded to 192, six products: 54 us).  36 and 114 us; the kernel before this one staged every pixel's 24 granules separately, 48 KB
 // into LDS and ~360 vector instructions a thread for 8 KB
 // of output (80 us), the element-wise fp32 one took 190.
 #pragma once
