@@ -291,3 +291,22 @@ def test_workgroups_walk_several_tiles(layer):
         say(f"{layer.name} {nm.nm_variant_name(v)}")
         assert norm_err(run(v, xd, wp, bd, layer, relu=True), np.maximum(ref, 0)) <= FP32_TOL, nm.nm_variant_name(v)
         assert norm_err(run(v, xd, wp, bd, layer, relu=False, res=rd), ref + res) <= FP32_TOL, nm.nm_variant_name(v)
+
+
+@pytest.mark.parametrize("cin,n,m", [(64, 2, 4), (192, 2, 4), (64, 1, 1)])
+def test_small_activations_in_some_of_the_tiles_a_workgroup_walks(cin, n, m):
+    """What the producers say about a tile is there when that tile is finished, one chunk a tile included."""
+    import torch
+    layer = L("late", 20011, 1, cin, 136, 1, 1, 1, 0, 1, n, m, 16)
+    x, w, bias = wl.make_tensors(layer, 1, 53)
+    small = np.zeros(20011, bool)
+    small[[5, 64, 9000, 15003, 20010]] = True
+    small[12345:12400] = True
+    x[0, small], w, bias = np.ldexp(x[0, small] - 0.5, -128), np.ldexp(w, 60).astype(np.float32), bias * 0
+    wp = nm.nm_prune(w, n, m, 16)
+    xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+    ref = run(fp32_instruction(wp), xd, wp, bd, layer, False).astype(np.float64)[0, :, 0]
+    for v in split_variants(wp):
+        got = run(v, xd, wp, bd, layer, False)[0, :, 0]
+        assert rel64(got[small], ref[small]) <= 1e-6, nm.nm_variant_name(v)
+        assert rel64(got[~small], ref[~small]) <= 1e-6, nm.nm_variant_name(v)
