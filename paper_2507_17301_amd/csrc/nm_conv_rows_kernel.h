@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
         for (int w = 0; w < 4; ++w) any |= *reinterpret_cast<const int*>(lds8 + p.rows_lds + w * kRowsPiece + ROWB);
         any = __builtin_amdgcn_readfirstlane(any);
     }
-    float bad = 0.f;                             // bf16: NaN once a sum was not finite
+    float most = 0.f;                            // bf16: the largest sum so far, a NaN once there was one
     T* __restrict__ y = reinterpret_cast<T*>(p.y);
     const T* __restrict__ res = reinterpret_cast<const T*>(p.res);
     // (real_only: elements that are no tap of a run are taken for zero)
@@ -223,7 +223,9 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) bad = fmaf(acc[jj][r], 0.f, bad);
+                    for (int r = 0; r < 4; r += 2)
+                        most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(acc[jj][r]), fabsf(acc[jj][r + 1])), most);
+                asm volatile("" : "+v"(most));   // (here: put off to the end of the block it would keep the sums alive beside their rounded form)
             }
             if constexpr (PL == 1) {
                 // residual (accumulator layout: the first layer of a network has none), activation, the one rounding
@@ -281,9 +283,9 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
     if constexpr (PL == 1) {
         // An infinity or NaN in a padding slot (the lead-in and the rest of a run, K positions beyond the last kernel
         // row) times its weight 0 is a NaN that the output is not due: once more without those slots.
-        // (224x224x3 -> 64, batch 64: x1.02 of the time without the look; the staged granules looked at instead, x1.03 to
-        // 1.05, and a branch per block x1.6)
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad != bad) != 0ull, 0)) {
+        // (224x224x3 -> 64, batch 64: x1.045 of the time without the look; one multiply-add or class test a sum x1.06, the
+        // staged granules looked at instead x1.05, a branch per block x1.6.)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(most < INFINITY)) != 0ull, 0)) {
             __builtin_amdgcn_s_waitcnt(0);       // the stores above come first
             blocks(std::true_type());
         }
