@@ -117,6 +117,14 @@ def _shapes_split(name):
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
 
 
+def _shapes_wave():
+    """(PB, NJ) of NMWAVE_SHAPES in nm_variants.h."""
+    text = open(os.path.join(CSRC, "nm_variants.h")).read()
+    body = text[text.index("#define NMWAVE_SHAPES(X)") + 24:]
+    body = body[:body.index("#define")]
+    return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+)\)", body)]
+
+
 def _jobs():
     jobs = []
     for src in ("nm_api.hip", "nm_prune_kernels.hip", "nm_pool_kernels.hip", "nm_conv_registry.hip", "nm_scratch.hip"):
@@ -160,6 +168,10 @@ def _jobs():
     instrows = os.path.join(CSRC, "nm_conv_rows_inst.hip")
     for pl in (1, 3):
         jobs.append((instrows, os.path.join(OBJDIR, f"nm_conv_rows_inst_{pl}.o"), [f"-DNM_INST_PL={pl}"]))
+    instwave = os.path.join(CSRC, "nm_conv_wave_inst.hip")
+    for pb, nj in _shapes_wave():
+        jobs.append((instwave, os.path.join(OBJDIR, f"nm_conv_wave_inst_{pb}_{nj}.o"),
+                     [f"-DNM_INST_PB={pb}", f"-DNM_INST_NJ={nj}"]))
     instf8 = os.path.join(CSRC, "nm_conv_f8_inst.hip")
     for nb, wp, nj in _shapes_f8():
         jobs.append((instf8, os.path.join(OBJDIR, f"nm_conv_f8_inst_{nb}_{wp}_{nj}.o"),

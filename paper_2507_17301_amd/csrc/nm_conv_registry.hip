@@ -78,6 +78,11 @@ struct Entry {
 // kinds 10 (bf16) and 11 (fp32): few input channels out of staged rows; NBLK is the number of output rows
 #define NM_ENTRYROWB(R, NJ, KS) {{"RUN_ROWS" #R "_NJ" #NJ "_KS" #KS, 16, R, 4 / (4 / NJ), NJ, 64 * KS, KS, 1, 10, 1, 1, 0}, nullptr, &launch_rows_t<1, NJ, KS>},
 #define NM_ENTRYROWF(R, NJ, KS) {{"ROWF_R" #R "_NJ" #NJ "_KS" #KS, 16, R, 4 / (4 / NJ), NJ, 64 * KS, KS, 1, 11, 1, 1, 0}, &launch_rows_t<3, NJ, KS>, nullptr},
+// kind 12: fp32 MFMA kernel for small layers; the K axis is split over wavefronts, hence the name's ending
+#define NM_ENTRYWAVE(PB, NJ, CK, SPC, NW)                                                       \
+    {{"KW_PB" #PB "_NJ" #NJ "_CK" #CK "_SPC" #SPC "_S" #NW, 16 * PB, PB, 4, NJ, CK, SPC, 1, 12, 1, 1, 0, 0, NW}, \
+     &launch_wave_t<PB, NJ, CK, SPC, NW>, nullptr},
+#define NM_SHAPE_ENTRIESWAVE(PB, NJ) NMWAVE_##PB##_##NJ(NM_ENTRYWAVE)
 #define NM_HEIGHTSB(NJ, KS) NMROW_HEIGHTS(NM_ENTRYROWB, NJ, KS)
 #define NM_HEIGHTSF(NJ, KS) NMROW_HEIGHTS(NM_ENTRYROWF, NJ, KS)
 
@@ -86,7 +91,7 @@ const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTR
                           NMRUN_SHAPES(NM_SHAPE_ENTRIESRUN) NMVAR_SHAPES(NM_SHAPE_ENTRIESVAR)
                           NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)
                           NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)
-                          NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF)};
+                          NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF) NMWAVE_SHAPES(NM_SHAPE_ENTRIESWAVE)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
 // The fp32 kernels also run with their K axis split over several workgroups per output

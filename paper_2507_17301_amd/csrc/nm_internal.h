@@ -67,6 +67,7 @@ struct Prepack {
                                       // and LDS-staged
                                       // 10, 11: few input channels out of staged rows (bf16, fp32)
                                       // 8, 9: fp32 as three bf16 planes (sparse instruction, dense instruction)
+                                      // (12, the small-layer fp32 kernel, reads kind 0's weights and d_cols)
     ChunkGeom geom{};
     int SPC = 0;                      // k-steps per chunk (1, 2, 4 or 8)
     // kind 0: a k-step is 4 kept columns
@@ -95,7 +96,8 @@ struct Prepack {
     int par = 0;                      // kinds 4, 10, 11: 0 or 1 elements of lead-in per run (alignment of the run start)
     uint32_t* d_rows = nullptr;
     float* d_wfrag = nullptr;
-    size_t rows_bytes = 0, wfrag_bytes = 0, ktab_bytes = 0;   // (all inside the handle's d_tables block)
+    size_t rows_bytes = 0, wfrag_bytes = 0, ktab_bytes = 0, cols_bytes = 0;   // (all inside the handle's d_tables block)
+    uint8_t* d_cols = nullptr;        // kind 0, vector mode, CK = 32, fp32 handles: as d_rows, k - k0 + 4, 0 in unused slots
     uint32_t* d_ktab = nullptr;       // scalar mode only: [nchunks*CK] (kh | kw << 8 | ci << 16) per im2col row
 };
 
@@ -125,6 +127,16 @@ constexpr int split_out_pitch(int NJ) { return NJ * 64 + 16; }
 constexpr int split_lds_bytes(int NBLK, int WP, int NJ)
 {
     return 2 * split_stage_bytes(16 * NBLK * WP) + 4 * split_out_rows(NBLK) * split_out_pitch(NJ);
+}
+
+// Small-layer fp32 kernel (kind 12): bytes of a pixel's row in a wavefront's strip, of one 16 x 16 block of sums, LDS of
+// nw wavefronts
+constexpr int wave_row_bytes(int CK) { return CK * 4 + 16; }
+constexpr int kWavePiece = 4 * 80 * 4;
+constexpr int wave_lds_bytes(int PB, int NJ, int CK, int nw)
+{
+    const int strip = 16 * PB * wave_row_bytes(CK), sums = PB * NJ * kWavePiece;
+    return nw * (strip > sums ? strip : sums);
 }
 
 // Row-staged kernels (kinds 10, 11): a wavefront's output piece, 16 pixels x 128 bytes and 16 bytes of padding a row
@@ -171,6 +183,9 @@ struct ConvParams {
     int nchunks, ncpt;
     int tile, rbpt, n_rowblocks;
     int n_ptiles, n_cblocks, n_wg;   // pixel tiles, row-block groups, product
+    // kind 12: consecutive workgroups are pixel tiles of one row-block group; wavefronts; divisors as below
+    int px_fast, waves;
+    unsigned fast_mul, fast_shift, ncpt_mul, ncpt_shift, kw_mul, kw_shift, rbpt_mul, rbpt_shift;
     int wg_per_xcd;
     // launch-time divisors as multiply-shift pairs (x / d = umulhi(x, mul) >> shift, mul == 0: d == 1)
     unsigned howo_mul, howo_shift, wo_mul, wo_shift;
@@ -212,10 +227,12 @@ struct VariantDesc {
                // 6 = fp8 E4M3 kernel (fp8 activations, bf16 output): dense instruction on zero-filled weights
                // 10, 11 = few input channels out of staged rows, bf16 and fp32 (NBLK = output rows a workgroup)
                // 8, 9 = fp32 tensors as three bf16 planes on the sparse / dense bf16 instruction
+               // 12 = fp32 MFMA kernel for small layers, the K axis dealt out over the wavefronts (NBLK pixel blocks, WP = 4)
     int share; // kind 1: row blocks fed from one gathered operand
     int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)
     int areg;  // kinds 2, 3, 7: 1 = weights and index words go straight to registers, the LDS stages hold the strip alone
     int spec;  // kinds 2, 3, 7: 1 = four producer wavefronts issue the loads (512 threads)
+    int waves; // kind 12: most wavefronts the K axis is dealt out over
 };
 
 // Allows kernel `fn` more than 64 KB of dynamic LDS on the current device; done once per

@@ -171,12 +171,13 @@ __device__ inline void chunk_span(int k, int cin, int CK, int vec, int ncpt, int
 //   rows [j][c][q][SPC] u32      LDS row (strip_row() in vector mode) of the kept column used by quarter q in step s;
 //                                with_counts: the chunk's number of k-steps in the upper half of the first word
 //   wfrag[rb][c][lane][SPC]      weight for MFMA A-operand lane (q*16 + t)
+//   cols (or null) u8            as rows: k - k0 + 4 (CK <= 64)
 // err[0] is set if a chunk holds more than 4*SPC kept columns.
 // (One workgroup per column tile, its columns counted per chunk by one thread, took 38 us for 512x3x3x512.)
 __global__ __launch_bounds__(256) void build_prepack_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ vals, int n_tiles, int kprime, int T, int rbpt,
     int cin, int CK, int vec, int ncpt, int nchunks, int SPC, int with_counts,
-    uint32_t* __restrict__ rows, float* __restrict__ wfrag, int* __restrict__ err)
+    uint32_t* __restrict__ rows, float* __restrict__ wfrag, uint8_t* __restrict__ cols, int* __restrict__ err)
 {
     const int R = rbpt * 16;                     // rows of a column tile, whole row blocks
     const size_t total = (size_t)n_tiles * kprime * R;
@@ -196,7 +197,9 @@ __global__ __launch_bounds__(256) void build_prepack_kernel(
         }
         if (tt == 0) {
             const uint32_t row = (uint32_t)(vec ? strip_row(k - k0, CK) : k - k0);
-            uint32_t* const w = rows + (((size_t)j * nchunks + c) * 4 + q) * SPC + step;
+            const size_t slot = (((size_t)j * nchunks + c) * 4 + q) * SPC + step;
+            uint32_t* const w = rows + slot;
+            if (cols) cols[slot] = (uint8_t)(k - k0 + 4);
             if (with_counts && i < 4) {
                 // (all four quarters carry the count, also those without a column)
                 const int cnt = lower_bound_idx(idxj, kprime, k1) - first;
@@ -580,7 +583,7 @@ int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t s)
     } else if (pp.kind == 0 || pp.kind == 5)
         hipLaunchKernelGGL(build_prepack_kernel, dim3(grid_for((size_t)wp->n_tiles * wp->kprime * wp->rbpt * 16, 256)),
                            dim3(256), 0, s, wp->d_idx, wp->d_vals, wp->n_tiles, wp->kprime, wp->tile, wp->rbpt, wp->cin, g.CK, g.vec, g.ncpt,
-                           g.nchunks, pp.SPC, pp.kind == 5 ? 1 : 0, pp.d_rows, pp.d_wfrag, d_err);
+                           g.nchunks, pp.SPC, pp.kind == 5 ? 1 : 0, pp.d_rows, pp.d_wfrag, pp.d_cols, d_err);
     else if (pp.kind == 4 || pp.kind >= 10) {
         const int KwC = wp->kw * wp->cin, GR = (pp.par + KwC + 7) / 8;
         const int nrb = pp.kind == 4 ? wp->n_rowblocks : (wp->cout + 15) / 16;

@@ -110,3 +110,13 @@
 #define NMROWB_CHUNKS(Y) Y(4, 1) Y(4, 2) Y(4, 3) Y(4, 4)
 #define NMROWF_CHUNKS(Y) Y(1, 1) Y(1, 2) Y(1, 3) Y(1, 4) Y(2, 1) Y(2, 2) Y(2, 3)
 #define NMROW_HEIGHTS(X, NJ, KS) X(1, NJ, KS) X(2, NJ, KS) X(4, NJ, KS) X(8, NJ, KS)
+
+// small fp32 layers: the K axis over up to NW wavefronts of a workgroup of 16 PB pixels x 16 NJ channels (as many as
+// leave each the registers of two chunks).  (64-channel chunks and 32 pixels x 16 channels were first on no layer by
+// more than 3 %.)
+// X(PB, NJ); Y(PB, NJ, CK, SPC, NW)
+#define NMWAVE_SHAPES(X) X(1, 1) X(1, 2) X(2, 2) X(1, 4)
+#define NMWAVE_1_1(Y) Y(1, 1, 32, 2, 16) Y(1, 1, 32, 4, 16) Y(1, 1, 32, 8, 16)
+#define NMWAVE_1_2(Y) Y(1, 2, 32, 2, 16) Y(1, 2, 32, 4, 16) Y(1, 2, 32, 8, 16)
+#define NMWAVE_2_2(Y) Y(2, 2, 32, 2, 16) Y(2, 2, 32, 4, 12) Y(2, 2, 32, 8, 12)
+#define NMWAVE_1_4(Y) Y(1, 4, 32, 2, 16) Y(1, 4, 32, 4, 16) Y(1, 4, 32, 8, 8)

@@ -1,0 +1,101 @@
+"""The kernel for small fp32 layers (K axis dealt out over the wavefronts of a workgroup), every form forced, against
+the CPU oracle: edges of its tiles, of its chunks and of the images, and values that unused operand slots must not see."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2507_17301_amd import binding as nm
+from paper_2507_17301_amd import workloads as wl
+from gpu_util import FP32_TOL, say, norm_err
+
+pytestmark = pytest.mark.gpu
+
+L = wl.ConvLayer
+
+CASES = [
+    # name, H, W, Cin, Cout, Kh, Kw, stride, pad, dil, n, m, tile | batch
+    (L("kw_one_output", 1, 1, 4, 1, 1, 1, 1, 0, 1, 1, 1, 1), 1),                  # one pixel, one channel, four columns
+    (L("kw_3x3", 7, 9, 64, 48, 3, 3, 1, 1, 1, 2, 4, 16), 1),                      # 63 pixels: the last block is ragged
+    (L("kw_17_pixels", 17, 1, 64, 16, 1, 1, 1, 0, 1, 1, 1, 16), 1),
+    (L("kw_cin48_T8", 9, 5, 48, 72, 3, 3, 1, 2, 2, 1, 4, 8), 2),                  # chunks end with the tap, half-empty row blocks
+    (L("kw_cin100_s2", 11, 8, 100, 37, 3, 3, 2, 1, 1, 2, 4, 5), 1),               # odd channels out, images end inside a block
+    (L("kw_T32_1x1", 5, 5, 96, 80, 1, 1, 1, 0, 1, 2, 8, 32), 3),
+    (L("kw_1x1_s2", 9, 9, 128, 40, 1, 1, 2, 0, 1, 4, 8, 16), 1),
+    (L("kw_deep", 7, 7, 512, 32, 3, 3, 1, 1, 1, 2, 4, 16), 1),                    # 72 chunks of 64, 144 of 32
+    (L("kw_cin_groups", 6, 6, 64, 32, 3, 3, 1, 1, 1, 16, 64, 16), 1),             # uneven chunks: slots left over
+    (L("kw_two_chunks", 4, 5, 1024, 16, 1, 1, 1, 0, 1, 1, 1, 16), 1),             # two, three and five chunks a wavefront,
+    (L("kw_three_chunks", 5, 4, 128, 32, 3, 3, 2, 1, 1, 1, 1, 16), 3),            # all of a chunk kept, half, one column
+    (L("kw_five_chunks", 5, 4, 256, 48, 3, 3, 1, 1, 1, 4, 8, 16), 1),
+    (L("kw_five_sparse", 5, 4, 256, 48, 3, 3, 1, 1, 1, 1, 8, 32), 1),
+    (L("kw_5x3_pad0", 8, 8, 20, 24, 5, 3, 1, 0, 1, 1, 4, 16), 1),
+]
+
+
+def _forms(wp):
+    return [v for v in range(nm.nm_variant_count())
+            if nm.nm_variant_name(v).startswith("KW_") and nm.nm_variant_legal(v, wp, nm.NM_F32, nm.NM_F32)]
+
+
+def _forced(v, *a):
+    import torch
+    nm.nm_force_variant(v)
+    try:
+        y = nm.nm_conv2d_res(*a)
+        torch.cuda.synchronize()
+        assert nm.nm_last_variant() == v
+    finally:
+        nm.nm_force_variant(-1)
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("with_res", [False, True])
+@pytest.mark.parametrize("layer,batch", CASES, ids=[c[0].name for c in CASES])
+def test_every_form(layer, batch, with_res):
+    import torch
+    x, w, bias = wl.make_tensors(layer, batch, 17, weight_sigma=0.1)
+    _, _, wz = oracle.prune(w, layer.n, layer.m, layer.tile)
+    shape = (batch, layer.Ho, layer.Wo, layer.Cout)
+    res = np.random.default_rng(3).standard_normal(shape).astype(np.float32) if with_res else None
+    b = bias if with_res else None
+    geo = (layer.stride, layer.pad, layer.dil, not with_res)
+    ref = oracle.conv2d_res(x, wz, res, b, *geo) if with_res else oracle.conv2d(x, wz, b, *geo)
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    xd = torch.from_numpy(x).cuda()
+    rd = torch.from_numpy(res).cuda() if with_res else None
+    bd = torch.from_numpy(bias).cuda() if with_res else None
+    forms = _forms(wp)
+    assert len(forms) >= 4, "four shapes per chunk size"
+    for v in forms:
+        say(f"forced {nm.nm_variant_name(v)} on {layer.name} residual={with_res}")
+        assert norm_err(_forced(v, xd, wp, rd, bd, *geo), ref) <= FP32_TOL, nm.nm_variant_name(v)
+
+
+def test_values_of_columns_that_are_not_kept_stay_out():
+    """Infinities and NaN in every column that some tile does not keep, in chunks with unused operand slots: an output
+    is not finite only where the oracle's is not."""
+    import torch
+    layer = L("kw_inf", 6, 7, 40, 32, 3, 3, 1, 1, 1, 1, 4, 16)
+    x, w, _ = wl.make_tensors(layer, 1, 5, weight_sigma=0.1)
+    _, idx, wz = oracle.prune(w, 1, 4, 16)
+    dropped = sorted(set(range(layer.K)) - set(np.asarray(idx).ravel().tolist()))
+    for c in {k % 40 for k in dropped} - {int(k) % 40 for k in np.asarray(idx).ravel()}:
+        x[..., c] = np.inf
+    x[0, 2, 3, int(np.asarray(idx)[0].ravel()[0]) % 40] = np.nan     # and one value that the first tile does keep
+    # (the oracle skips nothing that is kept: only the columns of a tile enter its sums)
+    ref = np.zeros((1, 6, 7, 32), np.float32)
+    xp = np.zeros((8, 9, 40), np.float64)
+    xp[1:7, 1:8] = x[0]
+    for j in range(2):
+        kept = np.asarray(idx)[j].ravel()
+        for co in range(16 * j, 16 * j + 16):
+            wk = w[co].ravel()[kept].astype(np.float64)
+            for h in range(6):
+                for q in range(7):
+                    ref[0, h, q, co] = xp[h:h + 3, q:q + 3].ravel()[kept] @ wk
+    wp = nm.nm_prune(w, 1, 4, 16)
+    for v in _forms(wp):
+        say(f"forced {nm.nm_variant_name(v)} with infinities")
+        y = _forced(v, torch.from_numpy(x).cuda(), wp, None, None, 1, 1, 1, False)
+        ok = np.isfinite(ref)
+        assert np.array_equal(np.isfinite(y), ok), nm.nm_variant_name(v)
+        assert norm_err(y[ok], ref[ok]) <= FP32_TOL, nm.nm_variant_name(v)
