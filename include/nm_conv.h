@@ -133,7 +133,8 @@ int nm_packed_scale(const nm_packed_t* wp, float* scale);
  * handle's 2^-e before bias and activation, bf16 output; no residual dtype other
  * than bf16).  The call only enqueues work
  * on the stream and never synchronises -- with one exception: a K-split variant
- * (name ending in "_S<n>", only ever chosen by the tuner or the test hook) keeps
+ * (name ending in "_S<n>", only ever chosen by the tuner or the test hook; the
+ * "KW_..._S<n>" forms split K inside a workgroup and need nothing) keeps
  * its partial sums in a library-owned workspace per device, and the first call
  * that needs a larger one than exists allocates it (nm_autotune sizes it for the
  * shapes it tunes; under stream capture such a call fails with NM_ERR_ALLOC
@@ -182,6 +183,23 @@ int nm_conv2d_static(const void* x_dev, nm_dtype_t x_dtype, int b, int h, int w,
                      const nm_packed_t* wp, const float* bias_dev, const void* residual_dev,
                      int stride_h, int stride_w, int pad_h, int pad_w, int dil_h, int dil_w,
                      int relu, void* y_dev, nm_dtype_t y_dtype, void* hip_stream);
+
+/*
+ * nm_conv2d_args -- the three calls above with their arguments in one block, for bindings that
+ * pay for every argument (ctypes: 1.9 us for nineteen, 0.5 for a block).  static_only != 0 is
+ * nm_conv2d_static, else residual_dev != NULL or not is nm_conv2d_res / nm_conv2d.  The integers
+ * are taken as int.
+ */
+typedef struct nm_conv_args {
+    const void* x_dev;
+    const nm_packed_t* wp;
+    const float* bias_dev;
+    const void* residual_dev;
+    void* y_dev;
+    void* hip_stream;
+    int64_t x_dtype, b, h, w, cin, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, relu, y_dtype, static_only;
+} nm_conv_args_t;
+int nm_conv2d_args(const nm_conv_args_t* args);
 
 /*
  * The two pooling layers a ResNet needs around its convolutions, so that a whole

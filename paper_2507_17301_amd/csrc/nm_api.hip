@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <new>
 
 #include "nm_internal.h"
 
@@ -128,10 +129,9 @@ ShapeKey make_key(nm_dtype_t xdt, nm_dtype_t ydt, int b, int h, int w, const nm_
                   int sh, int sw, int ph, int pw, int dh, int dw, int has_bias, int relu)
 {
     ShapeKey k;
-    const DeviceId* id = device_id(wp->device);
     const int vals[kKeyInts] = {(int)xdt, (int)ydt, b, h, w, wp->cin, wp->cout, wp->kh, wp->kw,
                                 sh, sw, ph, pw, dh, dw, wp->n, wp->m, wp->tile, (int)wp->value_dtype,
-                                has_bias ? 1 : 0, relu ? 1 : 0, id ? id->hash : 0, wp->sig, 0};
+                                has_bias ? 1 : 0, relu ? 1 : 0, wp->device_hash, wp->sig, 0};
     memcpy(k.v, vals, sizeof(vals));
     return k;
 }
@@ -672,6 +672,28 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
     return best;
 }
 
+// The default of a shape, worked out once: it depends on nothing that the tuning key does not hold, and looking
+// through the variants took 3 to 13 us of a call.  Bounded; a full table starts anew.
+constexpr size_t kMaxDefaults = 4096;
+std::map<ShapeKey, int> g_defaults;   // guarded by g_mu
+
+int default_variant(const ShapeKey& key, const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto it = g_defaults.find(key);
+        if (it != g_defaults.end()) return it->second;
+    }
+    const int v = heuristic_variant(wp, P, xdt, &ra);
+    try {
+        std::lock_guard<std::mutex> lk(g_mu);
+        if (g_defaults.size() >= kMaxDefaults) g_defaults.clear();
+        g_defaults[key] = v;
+    } catch (const std::bad_alloc&) {   // (it is then worked out again)
+    }
+    return v;
+}
+
 // ---- workspace for the partial sums of K-split variants -----------------------------------
 // One grow-only device buffer per device, shared by every call on that device (calls that
 // overlap on different streams and both run a K-split variant would race on it: such variants
@@ -1038,6 +1060,8 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
         return NM_ERR_UNSUPPORTED;
     }
     wp->sig = prepack_signature(wp, no_planes);
+    const DeviceId* const id = device_id(wp->device);
+    wp->device_hash = id ? id->hash : 0;
     *out = wp;
     return NM_OK;
 }
@@ -1166,8 +1190,8 @@ static int conv2d_impl(const void* x, nm_dtype_t xdt, int b, int h, int w, int c
 
     int v = -1;
     bool forced = false;
+    const ShapeKey key = make_key(xdt, ydt, b, h, w, wp, sh, sw, ph, pw, dh, dw, bias != nullptr, relu);
     {
-        const ShapeKey key = make_key(xdt, ydt, b, h, w, wp, sh, sw, ph, pw, dh, dw, bias != nullptr, relu);
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_forced >= 0) {
             v = g_forced;
@@ -1185,7 +1209,7 @@ static int conv2d_impl(const void* x, nm_dtype_t xdt, int b, int h, int w, int c
         }
         v = -1;   // stale cache entry: fall back to the default
     }
-    if (v < 0) v = heuristic_variant(wp, g.P, xdt, &ra);
+    if (v < 0) v = default_variant(key, wp, g.P, xdt, ra);
     if (v < 0) {
         set_error("no kernel variant can run this layer");
         return NM_ERR_UNSUPPORTED;
@@ -1237,6 +1261,17 @@ int nm_conv2d_static(const void* x, nm_dtype_t xdt, int b, int h, int w, int cin
                      int relu, void* y, nm_dtype_t ydt, void* stream)
 {
     return conv2d_impl(x, xdt, b, h, w, cin, wp, bias, res, sh, sw, ph, pw, dh, dw, relu, y, ydt, stream, true);
+}
+
+int nm_conv2d_args(const nm_conv_args_t* a)
+{
+    if (!a) {
+        set_error("null pointer argument");
+        return NM_ERR_ARG;
+    }
+    return conv2d_impl(a->x_dev, (nm_dtype_t)a->x_dtype, (int)a->b, (int)a->h, (int)a->w, (int)a->cin, a->wp, a->bias_dev,
+                       a->residual_dev, (int)a->stride_h, (int)a->stride_w, (int)a->pad_h, (int)a->pad_w, (int)a->dil_h,
+                       (int)a->dil_w, (int)a->relu, a->y_dev, (nm_dtype_t)a->y_dtype, a->hip_stream, a->static_only != 0);
 }
 
 int nm_maxpool2d(const void* x, nm_dtype_t dt, int b, int h, int w, int c, int k, int stride, int pad,

@@ -154,6 +154,7 @@ struct nm_packed {
     int device;
     float scale = 1.f;   // fp8 handles: the stored E4M3 value is weight * scale (a power of two)
     unsigned redo_below = 0;   // kinds 8, 9, 11: see ConvParams
+    int device_hash = 0;   // identity of the device (part of the tuning-cache key)
     int sig = 0;      // hash of the operand tables built for this handle (part of the tuning-cache key)
     int32_t* d_idx = nullptr;   // [n_tiles][kprime]
     float* d_vals = nullptr;    // [n_tiles][kprime][tile]
