@@ -312,7 +312,8 @@ int nm_force_variant(int variant_or_minus1);
  * test hook or the default. */
 int nm_last_variant(void);
 
-/* Whether `variant` can run this layer (1), cannot (0), or bad arguments (<0). */
+/* Whether `variant` can run this layer (1), cannot (0), or bad arguments (<0).  The "_TAPS_" forms, which take an output as
+ * large as the input, depend on more of the call than the handle holds and are answered with 0. */
 int nm_variant_legal(int variant, const nm_packed_t* wp, nm_dtype_t x_dtype, nm_dtype_t y_dtype);
 
 #ifdef __cplusplus

@@ -117,6 +117,14 @@ def _shapes_split(name):
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
 
 
+def _shapes_taps(sparse):
+    """(NBLK, WP, NJ) of NMTAPS1_SHAPES or NMTAPS0_SHAPES in nm_variants.h."""
+    text = open(os.path.join(CSRC, "nm_variants.h")).read()
+    body = text[text.index(f"#define NMTAPS{sparse}_SHAPES(X)") + 25:]
+    body = body[:body.index("\n")]
+    return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
+
+
 def _shapes_wave():
     """(PB, NJ) of NMWAVE_SHAPES in nm_variants.h."""
     text = open(os.path.join(CSRC, "nm_variants.h")).read()
@@ -168,6 +176,12 @@ def _jobs():
     instrows = os.path.join(CSRC, "nm_conv_rows_inst.hip")
     for pl in (1, 3):
         jobs.append((instrows, os.path.join(OBJDIR, f"nm_conv_rows_inst_{pl}.o"), [f"-DNM_INST_PL={pl}"]))
+    insttaps = os.path.join(CSRC, "nm_conv_taps_inst.hip")
+    for sparse in (1, 0):
+        for nb, wp, nj in _shapes_taps(sparse):
+            jobs.append((insttaps, os.path.join(OBJDIR, f"nm_conv_taps_inst_{sparse}_{nb}_{wp}_{nj}.o"),
+                         [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}",
+                          f"-DNM_INST_SPARSE={sparse}"]))
     instwave = os.path.join(CSRC, "nm_conv_wave_inst.hip")
     for pb, nj in _shapes_wave():
         jobs.append((instwave, os.path.join(OBJDIR, f"nm_conv_wave_inst_{pb}_{nj}.o"),

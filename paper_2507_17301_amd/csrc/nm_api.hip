@@ -108,6 +108,8 @@ const DeviceId* device_id(int dev)
 inline bool is_split_kind(int kind) { return kind == 8 || kind == 9; }
 // kinds 10 (bf16) and 11 (fp32): few input channels out of staged rows
 inline bool is_rows_kind(int kind) { return kind == 10 || kind == 11; }
+// kinds 13 (sparse instruction) and 14 (dense): bf16, a tile's input staged once for all taps
+inline bool is_taps_kind(int kind) { return kind == 13 || kind == 14; }
 // kinds whose row blocks are 16 consecutive output channels, whatever the column tile
 inline bool flat_rowblocks(int kind) { return is_split_kind(kind) || is_rows_kind(kind); }
 
@@ -145,6 +147,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
     // the epilogue's output tile [BP][channels of the workgroup] plus 16 bytes per pixel
     const size_t otile = (size_t)d.BP * ((size_t)(4 / d.WP) * d.NJ * 16 * (d.kind == 0 || d.kind == 5 ? 4 : 2) + 16);
     if (is_split_kind(d.kind)) return (size_t)split_lds_bytes(d.NBLK, d.WP, d.NJ);
+    if (is_taps_kind(d.kind)) return taps_lds_bytes(d.NBLK, d.WP, d.NJ, 9 * d.BP, 1);   // and what depends on the image
     if (d.kind == 12) return (size_t)wave_lds_bytes(d.NBLK, d.NJ, d.CK, d.waves);
     if (is_rows_kind(d.kind)) return kRowsPieces;   // and the staged rows, which depend on the image (rows_layout)
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
@@ -172,7 +175,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
 // The part of the convolution arguments that decides whether the kernels for few input
 // channels apply and which of their two operand tables they need.
 struct RunArgs {
-    int w, sw, pw, dw, sh, dh;
+    int w, sw, pw, dw, sh, dh, ph, h, b;
 };
 
 // Elements of lead-in, 0 or 1, that put a kernel-row run on 4 bytes.
@@ -208,8 +211,8 @@ int run_ksteps(const nm_packed* wp, int par)
     return (wp->kh * gr + 7) / 8;
 }
 
-// kind 12 reads the tables of kind 0
-inline int table_kind(int kind) { return kind == 12 ? 0 : kind; }
+// kind 12 reads the tables of kind 0, kinds 13 and 14 those of 2 and 3
+inline int table_kind(int kind) { return kind == 12 ? 0 : is_taps_kind(kind) ? kind - 11 : kind; }
 
 const Prepack* find_prepack(const nm_packed* wp, const VariantDesc& d, int par = -1)
 {
@@ -232,13 +235,25 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     if ((d.kind == 5 || d.kind == 11 || d.kind == 12 || is_split_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
     // fp8: E4M3 tensors with an E4M3 handle run the fp8 kernels and nothing else does
     if (is_f8_kind(d.kind) != (xdt == NM_F8E4M3) || is_f8_kind(d.kind) != (wp->value_dtype == NM_F8E4M3)) return false;
-    if ((d.kind >= 1 && d.kind <= 4) || d.kind == 10) {
+    if ((d.kind >= 1 && d.kind <= 4) || d.kind == 10 || is_taps_kind(d.kind)) {
         // bf16 matrix cores: bf16 tensors, weights already rounded to bf16, and a
         // shared operand only for column tiles made of exactly two row blocks
         if (xdt != NM_BF16 || wp->value_dtype != NM_BF16) return false;
         if (d.share != 1 && d.share != wp->rbpt) return false;
     }
     if (is_rows_kind(d.kind) && wp->cout % (d.kind == 10 ? 8 : 4) != 0) return false;   // whole 16-byte output granules
+    if (is_taps_kind(d.kind)) {
+        // an output as large as the input, so that a tap is one shift of the whole tile; whole 16-byte output granules
+        if (!ra || ra->sh != 1 || ra->sw != 1 || wp->kh * wp->kw < 2 || wp->kh * wp->kw > 32) return false;
+        if (2L * ra->ph != (long)ra->dh * (wp->kh - 1) || 2L * ra->pw != (long)ra->dw * (wp->kw - 1)) return false;
+        if (wp->tile % 16 != 0 || wp->cout % 8 != 0) return false;
+        // (small enough for what follows, and for the kernel's products of 24 bits and quotients of 31)
+        if (ra->ph > 1000 || ra->pw > 1000 || ra->w > 3000) return false;
+        const double lines = (ra->b + 2.0) * ((double)ra->h + ra->ph);
+        if (lines >= 16777216.0 || lines * taps_line(ra->w, ra->pw) >= 2147483648.0) return false;
+        const long granules = taps_granules(d.BP, ra->h, ra->w, ra->ph, ra->pw);
+        if (taps_lds_bytes(d.NBLK, d.WP, d.NJ, granules, wp->cin / 64) > (size_t)kMaxLdsBytes) return false;
+    }
     if (d.ksplit > 1) {
         // every split must own at least one chunk of the K axis
         const Prepack* pp = find_prepack(wp, d);
@@ -441,9 +456,15 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
         magic_div((unsigned)wp->kw, &p.kw_mul, &p.kw_shift);
         magic_div((unsigned)wp->rbpt, &p.rbpt_mul, &p.rbpt_shift);
     }
+    if (is_taps_kind(d.kind)) {
+        p.rows_n = (int)taps_granules(d.BP, h, w, ph, pw);
+        p.rows_lds = taps_loads(p.rows_n) * 1024;
+        magic_div((unsigned)taps_line(w, pw), &p.padw_mul, &p.padw_shift);
+        magic_div((unsigned)(h + ph), &p.padh_mul, &p.padh_shift);
+    }
     p.partial = nullptr;   // the caller points it at a workspace of split_bytes()
     if (is_rows_kind(d.kind)) {
-        const RowsLayout r = rows_layout(d, wp, RunArgs{w, sw, pw, dw, sh, dh});
+        const RowsLayout r = rows_layout(d, wp, RunArgs{w, sw, pw, dw, sh, dh, ph, h, b});
         p.rows_r = d.NBLK; p.rows_n = r.n; p.rows_pitch = r.pitch; p.rows_front = r.front; p.rows_data = r.data;
         p.rows_lds = (int)r.lds;
         magic_div((unsigned)(r.pitch / 16), &p.rowg_mul, &p.rowg_shift);
@@ -534,6 +555,33 @@ int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
     return pick;
 }
 
+// The tap-staged form of a bf16 layer that runs without tuning, -1 where the others do it: the cheapest by rounds of
+// workgroups (one a CU) x (12 000 clocks of start and output + 1.2 x the matrix instructions of its chunks), where that
+// gives at least 176 CUs a workgroup of 224 pixels or more (224 CUs one of 160) and at least half of its channels exist.
+// Over 110 random 3x3 layers, sparse instruction, against the best of six gather-free forms or the rule below: x0.66 to
+// x1.05 of the time on the 38 within that (x1.15 on one, 64 -> 112 channels), x0.87 to x1.35 on the others.  (The dense
+// instruction keeps the matrix cores busy without it: x0.93 at best, x1.2 on most.)
+int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
+{
+    int pick = -1;
+    double best = 0;
+    for (int v : base_variants()) {
+        const VariantDesc& d = variant_desc(v);
+        const int channels = (4 / d.WP) * d.NJ * 16;
+        if (d.kind != 13 || d.NBLK < 5 || !variant_legal(v, wp, xdt, ra)) continue;
+        const long n_cb = (wp->cout + channels - 1) / channels, n_wg = (long)((P + d.BP - 1) / d.BP) * n_cb;
+        if (2L * wp->cout < n_cb * channels || (channels > 64 && wp->cout <= 64)) continue;
+        if (n_wg < (d.NBLK < 7 ? 224 : 176)) continue;
+        const double rounds = (double)((n_wg + kNumCU - 1) / kNumCU);
+        const double cost = rounds * (12000.0 + 1.2 * 16 * d.NBLK * d.NJ * (wp->K / 64));
+        if (pick < 0 || cost < best) {
+            pick = v;
+            best = cost;
+        }
+    }
+    return pick;
+}
+
 // 16 x 16 blocks of outputs: what the small-layer fp32 kernel (kind 12) deals out.
 long wave_blocks(const nm_packed* wp, int P) { return (long)((P + 15) / 16) * wp->n_rowblocks; }
 
@@ -589,7 +637,7 @@ double model_clocks(const VariantDesc& d, const nm_packed* wp, int P)
     return (0.32 * ceil(rounds) + 0.68 * rounds) * (5020.0 + nchunks * std::max(431.0, occ * chunk) + occ * ends) + 1.13 * ends;
 }
 
-// Deterministic default when the shape has not been tuned: rows_default, wave_default, split_default, else the cheapest by
+// Deterministic default when the shape has not been tuned: rows_default, wave_default, split_default, taps_default, else the cheapest by
 // model_clocks.
 //
 // For the gather-free bf16 and the staged fp8 kernels there is a rule read off tuned ResNet stacks: a tile of 128
@@ -610,6 +658,10 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
     }
     if (xdt == NM_F32 && (kinds & (1u << 8 | 1u << 9))) {
         const int v = split_default(wp, P, xdt, ra);
+        if (v >= 0) return v;
+    }
+    if (ra && (kinds & (1u << 2))) {
+        const int v = taps_default(wp, P, xdt, ra);
         if (v >= 0) return v;
     }
     if (kinds & (1u << 2 | 1u << 3 | 1u << 7)) {
@@ -913,7 +965,7 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
     const size_t kWindow = 0x80000000ull;   // the kernels read a table through a 2 GiB buffer window
     for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
-        if (d.kind == 12) continue;   // (reads kind 0's)
+        if (table_kind(d.kind) != d.kind) continue;   // (reads another kind's)
         if (is_f8_kind(d.kind) != (value_dtype == NM_F8E4M3)) continue;   // E4M3 handles feed the fp8 kernels only
         Prepack pp;
         pp.kind = d.kind;
@@ -1201,7 +1253,7 @@ static int conv2d_impl(const void* x, nm_dtype_t xdt, int b, int h, int w, int c
             if (it != g_cache.end()) v = it->second.variant;
         }
     }
-    const RunArgs ra = {w, sw, pw, dw, sh, dh};
+    const RunArgs ra = {w, sw, pw, dw, sh, dh, ph, h, b};
     if (v >= 0 && (!variant_legal(v, wp, xdt, &ra) || (!forced && !keeps_precision(v, wp)))) {
         if (forced) {
             set_error("variant %d (%s) cannot run this layer", v, nm_variant_name(v));
@@ -1361,7 +1413,7 @@ int nm_autotune(nm_dtype_t xdt, int b, int h, int w, int cin, const nm_packed_t*
     int rc = conv_geometry(b, h, w, wp, sh, sw, ph, pw, dh, dw, elem_size(xdt), &g);
     if (rc != NM_OK) return rc;
     const ShapeKey key = make_key(xdt, ydt, b, h, w, wp, sh, sw, ph, pw, dh, dw, has_bias, relu);
-    const RunArgs ra = {w, sw, pw, dw, sh, dh};
+    const RunArgs ra = {w, sw, pw, dw, sh, dh, ph, h, b};
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);

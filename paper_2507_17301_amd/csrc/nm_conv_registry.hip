@@ -42,6 +42,12 @@ struct Entry {
      nullptr, &launch_sp16_t<NB, WP, NJ, CK, (SP) != 0, true, true>},
 #define NM_SHAPE_ENTRIESSPR(NB, WP, NJ) NMSPR_CHUNKS(NM_ENTRYSPR, NB, WP, NJ)
 
+// kinds 13 (sparse instruction) and 14 (dense): a tile's input staged once for all taps
+#define NM_ENTRYTAPS1(NB, WP, NJ) \
+    {{"SPR1_TAPS_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 13, 1, 1, 1, 1}, nullptr, &launch_taps_t<NB, WP, NJ, true>},
+#define NM_ENTRYTAPS0(NB, WP, NJ) \
+    {{"SPR0_TAPS_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 14, 1, 1, 1, 1}, nullptr, &launch_taps_t<NB, WP, NJ, false>},
+
 // kind 4: contiguous kernel-row runs
 #define NM_ENTRYRUN(NB, WP, NJ, KS)                                                             \
     {{"RUN_NB" #NB "_WP" #WP "_NJ" #NJ "_KS" #KS, 16 * NB * WP, NB, WP, NJ, 64 * KS, KS, 1, 4, 1, 1, 0}, \
@@ -91,7 +97,8 @@ const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTR
                           NMRUN_SHAPES(NM_SHAPE_ENTRIESRUN) NMVAR_SHAPES(NM_SHAPE_ENTRIESVAR)
                           NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)
                           NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)
-                          NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF) NMWAVE_SHAPES(NM_SHAPE_ENTRIESWAVE)};
+                          NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF) NMWAVE_SHAPES(NM_SHAPE_ENTRIESWAVE)
+                          NMTAPS1_SHAPES(NM_ENTRYTAPS1) NMTAPS0_SHAPES(NM_ENTRYTAPS0)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
 // The fp32 kernels also run with their K axis split over several workgroups per output

@@ -67,7 +67,8 @@ struct Prepack {
                                       // and LDS-staged
                                       // 10, 11: few input channels out of staged rows (bf16, fp32)
                                       // 8, 9: fp32 as three bf16 planes (sparse instruction, dense instruction)
-                                      // (12, the small-layer fp32 kernel, reads kind 0's weights and d_cols)
+                                      // (12, the small-layer fp32 kernel, reads kind 0's weights and d_cols; 13 and 14, the
+                                      // tap-staged bf16 kernels, read 2's and 3's)
     ChunkGeom geom{};
     int SPC = 0;                      // k-steps per chunk (1, 2, 4 or 8)
     // kind 0: a k-step is 4 kept columns
@@ -139,6 +140,41 @@ constexpr int wave_lds_bytes(int PB, int NJ, int CK, int nw)
     return nw * (strip > sums ? strip : sums);
 }
 
+// Tap-staged bf16 kernels (kinds 13, 14): 16-byte granules of an image row and the zeros after it; the most that a tile
+// of BP pixels and what its taps reach around it span; wave-wide loads of that, which fill a stage
+constexpr long taps_line(long w, long pw) { return 9 * w + (9 * pw + 7) / 8 * 8; }
+constexpr long taps_granules(int BP, long h, long w, long ph, long pw)
+{
+    const long line = taps_line(w, pw);
+    return 9 * BP + (BP + w - 2) / w * (line - 9 * w) + (BP + h * w - 2) / (h * w) * ph * line + 2 * (ph * line + 9 * pw);
+}
+// What granule t of the padded images holds, one padded image added so that t is not negative where the taps of the first
+// rows reach before the first image: the pixel and which eight of its 64 channels, or zeros (pixel -1).  Divisors as multiply-shift pairs of taps_line() and
+// h + ph; t below 2^31, padded rows and pixels below 2^24, w below 3000 (g / 9 is exact for g < 32768).
+struct TapsSource {
+    int pixel;
+    unsigned oct;
+};
+constexpr unsigned taps_div(unsigned x, unsigned mul, unsigned shift) { return (unsigned)(((unsigned long long)(x << 1) * mul) >> 32) >> shift; }
+constexpr unsigned taps_mul(unsigned a, unsigned b) { return (a & 0xffffffu) * (b & 0xffffffu); }
+constexpr TapsSource taps_source(unsigned t, unsigned line_g, unsigned line_mul, unsigned line_shift, unsigned img_mul, unsigned img_shift,
+                                 unsigned b, unsigned h, unsigned w, unsigned ph)
+{
+    const unsigned line = taps_div(t, line_mul, line_shift), g = t - taps_mul(line, line_g);
+    const unsigned x = (g * 7282u) >> 16, oct = g - 9 * x;
+    const unsigned img = taps_div(line, img_mul, img_shift), y = line - taps_mul(img, h + ph);
+    const unsigned pixel = taps_mul(line - taps_mul(img, ph), w) + x - h * w;
+    const bool live = (x < w) & (oct < 8) & (y < h) & (img - 1 < b);
+    return TapsSource{live ? (int)pixel : -1, oct};
+}
+constexpr int taps_loads(long granules) { return (int)((granules + 63) / 64); }
+// two stages and the loads' offsets (one stage where there is one), or the output tile
+constexpr size_t taps_lds_bytes(int NBLK, int WP, int NJ, long granules, int ncpt)
+{
+    const size_t strip = (size_t)taps_loads(granules) * (ncpt > 1 ? 2 * 1024 + 256 : 1024), out = (size_t)16 * NBLK * WP * ((4 / WP) * NJ * 32 + 16);
+    return strip > out ? strip : out;
+}
+
 // Row-staged kernels (kinds 10, 11): a wavefront's output piece, 16 pixels x 128 bytes and 16 bytes of padding a row
 constexpr int kRowsPiece = 16 * 144;
 
@@ -192,6 +228,8 @@ struct ConvParams {
     unsigned howo_mul, howo_shift, wo_mul, wo_shift;
     int run_gr, run_d; // kind 4: granules per kernel-row run, lead-in elements of a run
     unsigned gr_mul, gr_shift, cin_mul, cin_shift;   // kind 4: multiply-shift pairs for / run_gr and / Cin
+    // kinds 13, 14: rows_n = granules of a stage, rows_lds = its bytes; division by taps_line() and by H + ph
+    unsigned padw_mul, padw_shift, padh_mul, padh_shift;
     // kinds 10, 11: output rows a workgroup, staged input rows, bytes of one, of the room before the run of column 0
     // and before the data, of all planes together (whole 1 KB windows)
     int rows_r, rows_n, rows_pitch, rows_front, rows_data, rows_lds;
@@ -228,6 +266,7 @@ struct VariantDesc {
                // 6 = fp8 E4M3 kernel (fp8 activations, bf16 output): dense instruction on zero-filled weights
                // 10, 11 = few input channels out of staged rows, bf16 and fp32 (NBLK = output rows a workgroup)
                // 8, 9 = fp32 tensors as three bf16 planes on the sparse / dense bf16 instruction
+               // 13, 14 = bf16 k x k kernel that stages a tile's input once for all taps, sparse / dense instruction
                // 12 = fp32 MFMA kernel for small layers, the K axis dealt out over the wavefronts (NBLK pixel blocks, WP = 4)
     int share; // kind 1: row blocks fed from one gathered operand
     int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)

@@ -76,6 +76,12 @@
     Y(NB, WP, NJ, 64, 1) Y(NB, WP, NJ, 128, 1) \
     Y(NB, WP, NJ, 64, 0) Y(NB, WP, NJ, 128, 0)
 
+// k x k layers whose output is as large as the input: a tile's input staged once for all taps, 64 channels at a time;
+// sparse instruction and dense one.  (64 x 256 and 128 x 128 tiles, 96 x 256 and 192 x 128 were first on no layer.)
+// X(NBLK, WP, NJ)
+#define NMTAPS1_SHAPES(X) X(4, 1, 2) X(5, 2, 4) X(7, 2, 4) X(8, 2, 4) X(8, 1, 4) X(7, 4, 4) X(8, 4, 4)
+#define NMTAPS0_SHAPES(X) X(5, 2, 4) X(7, 2, 4) X(7, 4, 4)
+
 // bf16 kernel for layers with very few input channels (contiguous kernel-row
 // runs, one chunk of KS 64-element k-steps): where output pixels are not whole
 // 16-byte granules or the staged rows do not fit the CU, and for very few pixels.
