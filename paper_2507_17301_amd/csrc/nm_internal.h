@@ -192,7 +192,7 @@ struct nm_packed {
     unsigned redo_below = 0;   // kinds 8, 9, 11: see ConvParams
     int device_hash = 0;   // identity of the device (part of the tuning-cache key)
     int sig = 0;      // hash of the operand tables built for this handle (part of the tuning-cache key)
-    int32_t* d_idx = nullptr;   // [n_tiles][kprime]
+    int32_t* d_idx = nullptr;   // [n_tiles][kprime], then whether a weight is not finite
     float* d_vals = nullptr;    // [n_tiles][kprime][tile]
     char* d_tables = nullptr;   // one block: the table builders' flags (256 bytes), then every operand table
     std::vector<int32_t> h_idx; // host copy of d_idx
