@@ -346,9 +346,18 @@ struct GeomNeeds {
     }
 };
 
-// Index of the first NaN or infinity, n if there is none.
+// Index of the first NaN or infinity, n if there is none.  The pass that decides has no exit, so that it runs on
+// vector registers.
 size_t first_not_finite(const float* w, size_t n)
 {
+    const uint32_t top = 0x7f800000u;
+    uint32_t bad = 0;
+    for (size_t i = 0; i < n; ++i) {
+        uint32_t u;
+        memcpy(&u, w + i, sizeof(u));
+        bad |= (u & top) == top ? 1u : 0u;
+    }
+    if (!bad) return n;
     size_t i = 0;
     while (i < n && isfinite(w[i])) ++i;
     return i;
@@ -877,6 +886,14 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
         return NM_ERR_ARG;
     }
     const size_t nw = (size_t)cout * K;
+    auto refuse_not_finite = [&]() {
+        const size_t bad = first_not_finite(w, nw);
+        if (bad < nw) set_error("weight %zu is not finite", bad);
+        return bad < nw;
+    };
+    // up to 128K weights here, before any device work (at most 7 us, what clearing the flag costs); more by the selection kernel
+    const bool flagged = nw > 131072;
+    if (!flagged && refuse_not_finite()) return NM_ERR_ARG;
     nm_packed* wp = new (std::nothrow) nm_packed();
     if (!wp) {
         set_error("out of host memory");
@@ -911,18 +928,20 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
     NM_TRY_HIP(hipMalloc(&wp->d_idx, (n_idx + 1) * sizeof(int32_t)), NM_ERR_ALLOC);   // and whether a weight is not finite
     NM_TRY_HIP(hipMalloc(&wp->d_vals, (size_t)wp->n_tiles * wp->kprime * tile * sizeof(float)), NM_ERR_ALLOC);
     NM_TRY_HIP(hipMemcpyAsync(d_w, w, nw * sizeof(float), hipMemcpyHostToDevice, s), NM_ERR_HIP);
-    NM_TRY_HIP(hipMemsetAsync(wp->d_idx + n_idx, 0, sizeof(int32_t), s), NM_ERR_HIP);
+    if (flagged) NM_TRY_HIP(hipMemsetAsync(wp->d_idx + n_idx, 0, sizeof(int32_t), s), NM_ERR_HIP);
     rc = run_prune(d_w, wp, s);
     if (rc != NM_OK) return fail(rc);
-    wp->h_idx.resize(n_idx + 1);
+    wp->h_idx.resize(n_idx + (flagged ? 1 : 0));
     NM_TRY_HIP(hipMemcpyAsync(wp->h_idx.data(), wp->d_idx, wp->h_idx.size() * sizeof(int32_t),
                               hipMemcpyDeviceToHost, s), NM_ERR_HIP);
     NM_TRY_HIP(hipStreamSynchronize(s), NM_ERR_HIP);
-    if (wp->h_idx.back()) {
-        set_error("weight %zu is not finite", first_not_finite(w, nw));
-        return fail(NM_ERR_ARG);
+    if (flagged) {
+        if (wp->h_idx.back()) {
+            (void)refuse_not_finite();
+            return fail(NM_ERR_ARG);
+        }
+        wp->h_idx.pop_back();
     }
-    wp->h_idx.pop_back();
 
     if (value_dtype == NM_F8E4M3) {
         // one power-of-two scale per layer: the largest 2^e that keeps every kept weight within

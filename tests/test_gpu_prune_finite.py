@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,n,m,tile", [((5, 1, 1, 8), 2, 4, 16), ((40, 3, 3, 12), 1, 4, 16), ((33, 3, 3, 64), 2, 8, 32),
-                                            ((24, 1, 1, 600), 300, 600, 8), ((4, 3, 3, 3), 1, 1, 1)])
+                                            ((24, 1, 1, 600), 300, 600, 8), ((4, 3, 3, 3), 1, 1, 1),
+                                            ((410, 3, 3, 36), 1, 4, 16), ((110, 1, 1, 1200), 300, 600, 8), ((980, 3, 3, 15), 1, 1, 1)])
 @pytest.mark.parametrize("value", [np.nan, -np.nan, np.inf, -np.inf])
 def test_refused_wherever_it_is(shape, n, m, tile, value):
     w = np.random.default_rng(1).standard_normal(shape, dtype=np.float32)
