@@ -724,7 +724,8 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
 }
 
 // The default of a shape, worked out once: it depends on nothing that the tuning key does not hold, and looking
-// through the variants took 3 to 13 us of a call.  Bounded; a full table starts anew.
+// through the variants took 3 to 13 us of a call.  The key holds the handle's tables as a hash of 31 bits, so that the
+// handle at hand is asked all the same, as for a tuned entry.  Bounded; a full table starts anew.
 constexpr size_t kMaxDefaults = 4096;
 std::map<ShapeKey, int> g_defaults;   // guarded by g_mu
 
@@ -733,7 +734,7 @@ int default_variant(const ShapeKey& key, const nm_packed* wp, int P, nm_dtype_t 
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_defaults.find(key);
-        if (it != g_defaults.end()) return it->second;
+        if (it != g_defaults.end() && variant_legal(it->second, wp, xdt, &ra) && keeps_precision(it->second, wp)) return it->second;
     }
     const int v = heuristic_variant(wp, P, xdt, &ra);
     try {

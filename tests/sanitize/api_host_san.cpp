@@ -384,6 +384,34 @@ static void split_limits()
     CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
 }
 
+// The default remembered for a shape, met by a handle that agrees in everything that the key holds but has no table for it
+// (the key holds a hash of the tables); and more shapes than the table holds.
+static void remembered_defaults()
+{
+    const int cout = 16, cin = 8;
+    std::vector<float> wt((size_t)cout * cin, 0.5f);
+    nm_packed_t *a = nullptr, *b = nullptr;
+    CHECK(nm_prune(wt.data(), cout, 1, 1, cin, 2, 4, 16, NM_F32, &a) == NM_OK);
+    CHECK(nm_prune(wt.data(), cout, 1, 1, cin, 2, 4, 16, NM_F32, &b) == NM_OK && a->sig == b->sig);
+    void* x = dev_alloc((size_t)6000 * cin * 4);
+    void* y = dev_alloc((size_t)6000 * cout * 4);
+    auto call = [&](nm_packed_t* wp, int h) {
+        return nm_conv2d(x, NM_F32, 1, h, 1, cin, wp, nullptr, 1, 1, 0, 0, 1, 1, 0, y, NM_F32, nullptr);
+    };
+    CHECK(call(a, 5) == NM_OK);
+    const int first = nm_last_variant();
+    const nm::VariantDesc& d = nm::variant_desc(first);
+    for (size_t i = 0; i < b->prepacks.size(); ++i)
+        if (b->prepacks[i].kind == d.kind && b->prepacks[i].geom.CK == d.CK && b->prepacks[i].SPC == d.SPC)
+            b->prepacks.erase(b->prepacks.begin() + (long)i--);
+    CHECK(!b->prepacks.empty() && nm_variant_legal(first, b, NM_F32, NM_F32) == 0);
+    CHECK(call(b, 5) == NM_OK && nm_last_variant() != first);
+    CHECK(call(a, 5) == NM_OK && nm_variant_legal(nm_last_variant(), a, NM_F32, NM_F32) == 1);
+    for (int h = 1; h <= 6000; ++h) CHECK(call(a, h) == NM_OK);
+    CHECK(call(a, 5) == NM_OK && nm_last_variant() == first);
+    CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(a) == NM_OK && nm_packed_free(b) == NM_OK);
+}
+
 int main(int argc, char** argv)
 {
     const std::string tmp = argc > 1 ? argv[1] : "/tmp";
@@ -449,6 +477,7 @@ int main(int argc, char** argv)
         CHECK(hipFree(xb) == hipSuccess && hipFree(yb) == hipSuccess && nm_packed_free(h8) == NM_OK);
     }
     split_limits();
+    remembered_defaults();
     for (nm_dtype_t dt : {NM_F32, NM_BF16}) {
         rows_case(2, 17, 20, 3, 7, 7, dt, 2, 2, 3, 3, true);
         rows_case(1, 9, 10, 2, 3, 3, dt, 1, 1, 1, 1, true);
