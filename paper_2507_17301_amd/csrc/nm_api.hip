@@ -892,8 +892,10 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
         if (bad < nw) set_error("weight %zu is not finite", bad);
         return bad < nw;
     };
-    // up to 128K weights here, before any device work (at most 7 us, what clearing the flag costs); more by the selection kernel
+    // up to 128K weights here, before any device work (at most 7 us, what clearing the flag costs); more by the selection
+    // kernel, or here where the call fails before that has spoken: such weights are refused as what they are all the same
     const bool flagged = nw > 131072;
+    bool unseen = flagged;
     if (!flagged && refuse_not_finite()) return NM_ERR_ARG;
     nm_packed* wp = new (std::nothrow) nm_packed();
     if (!wp) {
@@ -910,6 +912,7 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
     int rc = NM_OK;
     hipStream_t s = nullptr;
     auto fail = [&](int code) {
+        if (unseen && refuse_not_finite()) code = NM_ERR_ARG;
         (void)hipFree(d_w);
         free_packed(wp);
         return code;
@@ -938,10 +941,11 @@ int nm_prune(const float* w, int cout, int kh, int kw, int cin, int n, int m, in
     NM_TRY_HIP(hipStreamSynchronize(s), NM_ERR_HIP);
     if (flagged) {
         if (wp->h_idx.back()) {
-            (void)refuse_not_finite();
+            set_error("a weight is not finite");   // (if the caller has changed it by now)
             return fail(NM_ERR_ARG);
         }
         wp->h_idx.pop_back();
+        unseen = false;
     }
 
     if (value_dtype == NM_F8E4M3) {

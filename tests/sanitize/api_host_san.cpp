@@ -30,7 +30,7 @@
 
 // ------------------------------------------------------------------ fake HIP
 static std::map<char*, size_t> g_allocs;
-static bool g_fail_malloc = false;
+static bool g_fail_malloc = false, g_no_device = false;
 static int g_launches = 0;
 
 static bool inside(const void* p, size_t need)
@@ -42,7 +42,7 @@ static bool inside(const void* p, size_t need)
 }
 
 extern "C" {
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return g_no_device ? hipErrorNoDevice : hipSuccess; }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int)
 {
     memset(p, 0, sizeof(*p));
@@ -197,10 +197,13 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
 }
 
 // "prune": keep the first n columns of every group (ascending, valid), except that column
-// tile 0 of handles with m >= 32 keeps the LAST n, so that kept sets crowd into some chunks
-int run_prune(const float*, nm_packed* wp, hipStream_t)
+// tile 0 of handles with m >= 32 keeps the LAST n, so that kept sets crowd into some chunks;
+// behind the indices, whether a weight is not finite
+int run_prune(const float* w, nm_packed* wp, hipStream_t)
 {
-    CHECK(inside(wp->d_idx, (size_t)wp->n_tiles * wp->kprime * 4));
+    CHECK(inside(wp->d_idx, ((size_t)wp->n_tiles * wp->kprime + 1) * 4) && inside(w, (size_t)wp->cout * wp->K * 4));
+    for (size_t i = 0; i < (size_t)wp->cout * wp->K; ++i)
+        if (!isfinite(w[i])) wp->d_idx[(size_t)wp->n_tiles * wp->kprime] = 1;
     CHECK(inside(wp->d_vals, (size_t)wp->n_tiles * wp->kprime * wp->tile * 4));
     for (int j = 0; j < wp->n_tiles; ++j)
         for (int g = 0; g < wp->G; ++g)
@@ -412,6 +415,34 @@ static void remembered_defaults()
     CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(a) == NM_OK && nm_packed_free(b) == NM_OK);
 }
 
+// Weights that are not finite are refused as such, few or many, and whatever else would have gone wrong
+static void not_finite()
+{
+    for (int cout : {16, 600}) {   // 4096 weights and 153600: looked at by the host, and by the selection kernel
+        std::vector<float> wt((size_t)cout * 256, 0.5f);
+        nm_packed_t* wp = nullptr;
+        auto prune = [&]() { return nm_prune(wt.data(), cout, 1, 1, 256, 2, 4, 16, NM_F32, &wp); };
+        const size_t before = g_allocs.size();
+        for (float bad : {NAN, -INFINITY}) {
+            wt[1001] = wt[3000] = bad;
+            for (int how = 0; how < 3; ++how) {
+                g_fail_malloc = how == 1;
+                g_no_device = how == 2;
+                CHECK(prune() == NM_ERR_ARG && !wp && strstr(nm_last_error(), "weight 1001 is not finite"));
+                g_fail_malloc = g_no_device = false;
+            }
+        }
+        wt[1001] = wt[3000] = 1;
+        g_fail_malloc = true;
+        CHECK(prune() == NM_ERR_ALLOC && !wp);
+        g_fail_malloc = false;
+        g_no_device = true;
+        CHECK(prune() == NM_ERR_HIP && !wp && g_allocs.size() == before);
+        g_no_device = false;
+        CHECK(prune() == NM_OK && nm_packed_free(wp) == NM_OK && g_allocs.size() == before);
+    }
+}
+
 int main(int argc, char** argv)
 {
     const std::string tmp = argc > 1 ? argv[1] : "/tmp";
@@ -478,6 +509,7 @@ int main(int argc, char** argv)
     }
     split_limits();
     remembered_defaults();
+    not_finite();
     for (nm_dtype_t dt : {NM_F32, NM_BF16}) {
         rows_case(2, 17, 20, 3, 7, 7, dt, 2, 2, 3, 3, true);
         rows_case(1, 9, 10, 2, 3, 3, dt, 1, 1, 1, 1, true);
