@@ -556,10 +556,11 @@ int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
 
 // The tap-staged form of a bf16 layer that runs without tuning, -1 where the others do it: the cheapest by rounds of
 // workgroups (one a CU) x (12 000 clocks of start and output + 1.2 x the matrix instructions of its chunks), where that
-// gives at least 176 CUs a workgroup of 224 pixels or more (224 CUs one of 160) and at least half of its channels exist.
-// Over 110 random 3x3 layers, sparse instruction, against the best of six gather-free forms or the rule below: x0.66 to
-// x1.05 of the time on the 38 within that (x1.15 on one, 64 -> 112 channels), x0.87 to x1.35 on the others.  (The dense
-// instruction keeps the matrix cores busy without it: x0.93 at best, x1.2 on most.)
+// gives at least 176 CUs a workgroup of 224 pixels or more (224 CUs one of 160), more than half of its channels exist and
+// the launch is not a round and less than 0.4 of a second one.  Of 600 random 3x3 layers, sparse instruction, tensors out of
+// cache, the 393 within that take x0.58 to x1.00 of the time that the rule below gives them, x0.82 on average; where just
+// half of the channels exist (128 of 256) it would be x1.26 to x1.35, at 1.16 rounds x1.11.  (The dense instruction keeps
+// the matrix cores busy without it: x0.93 at best, x1.2 on most.)
 int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 {
     int pick = -1;
@@ -569,8 +570,8 @@ int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
         const int channels = (4 / d.WP) * d.NJ * 16;
         if (d.kind != 13 || d.NBLK < 5 || !variant_legal(v, wp, xdt, ra)) continue;
         const long n_cb = (wp->cout + channels - 1) / channels, n_wg = (long)((P + d.BP - 1) / d.BP) * n_cb;
-        if (2L * wp->cout < n_cb * channels || (channels > 64 && wp->cout <= 64)) continue;
-        if (n_wg < (d.NBLK < 7 ? 224 : 176)) continue;
+        if (2L * wp->cout <= n_cb * channels || (channels > 64 && wp->cout <= 64)) continue;
+        if (n_wg < (d.NBLK < 7 ? 224 : 176) || (n_wg > kNumCU && 5L * n_wg < 7L * kNumCU)) continue;
         const double rounds = (double)((n_wg + kNumCU - 1) / kNumCU);
         const double cost = rounds * (12000.0 + 1.2 * 16 * d.NBLK * d.NJ * (wp->K / 64));
         if (pick < 0 || cost < best) {

@@ -85,11 +85,14 @@ def test_refused(layer):
         nm.nm_force_variant(-1)
 
 
-# one round of 224-pixel tiles, one of 160, several of 448 x 64, 2:8 of a wider tile; the last has too few workgroups
+# one round of 224-pixel tiles, one of 160, several of 448 x 64, 2:8 of a wider tile; too few workgroups; then layers on which the
+# form that would otherwise be taken is slower than the strip-per-tap one: half of its 256 channels exist (194 workgroups of
+# 160 x 128 are too few), a second round of workgroups that has only begun
 @pytest.mark.parametrize("layer,batch,tap", [
     (L("d_28", 28, 28, 128, 128, 3, 3, 1, 1, 1, 2, 4, 16), 64, True), (L("d_odd", 61, 59, 128, 128, 3, 3, 1, 1, 1, 2, 8, 16), 11, True),
     (L("d_56", 56, 56, 64, 64, 3, 3, 1, 1, 1, 2, 4, 16), 32, True), (L("d_T32", 21, 19, 192, 384, 3, 3, 1, 1, 1, 1, 4, 32), 37, True),
-    (L("d_small", 14, 14, 256, 256, 3, 3, 1, 1, 1, 2, 4, 16), 4, False)], ids=lambda a: getattr(a, "name", None))
+    (L("d_small", 14, 14, 256, 256, 3, 3, 1, 1, 1, 2, 4, 16), 4, False),
+    (L("d_half", 35, 10, 128, 128, 3, 3, 1, 1, 1, 2, 4, 16), 71, False), (L("d_begun", 32, 52, 64, 64, 3, 3, 1, 1, 1, 1, 4, 16), 80, False)], ids=lambda a: getattr(a, "name", None))
 def test_untuned_default(layer, batch, tap):
     import torch
     x, w, bias = wl.make_tensors(layer, batch, 9)
