@@ -585,17 +585,24 @@ int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 // 16 x 16 blocks of outputs: what the small-layer fp32 kernel (kind 12) deals out.
 long wave_blocks(const nm_packed* wp, int P) { return (long)((P + 15) / 16) * wp->n_rowblocks; }
 
-// The small-layer fp32 kernel for a layer that runs without tuning, -1 where the others do it: up to four blocks a
-// CU.  Over 87 random layers within that (1 to 288 chunks of 32 channels, 1:8 to dense) it takes x0.27 to x1.11 of
-// the time of what the rules below pick, x0.65 on average, the less the longer the K axis; from 1024 to 2048 blocks x0.6 to x1.6.
+// The small-layer fp32 kernel for a layer that runs without tuning, -1 where the others do it.  What it saves is the chain
+// of chunks and the second launch, so that it wants the more chunks of 32 channels the more blocks a CU gets.  Over 440
+// random layers up to four blocks a CU (1 to 288 chunks, 1:8 to dense), tensors out of cache, time over that of what the
+// rules below pick: up to one block a CU 1 to 3 chunks x0.62 to x1.40, from 4 on x0.20 to x0.93; up to two 4 to 7 chunks
+// x0.82 to x1.09, from 8 on x0.30 to x0.93; up to three 9 to 35 chunks x0.80 to x1.32, from 40 on x0.50 to x0.93; up to
+// four 36 to 63 chunks x0.72 to x1.08, from 64 on x0.60 to x0.87.  Layers that keep all of a chunk take a row block a
+// workgroup: from two blocks a CU on x0.89 to x1.30 at any length.
 // One row block a workgroup up to 256 blocks, and where all of a chunk is kept (the weights are then more than the
 // pixels); else two, which share the pixels.  (x1.06 of the fastest of its forms on average.)
 int wave_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 {
-    const long blocks = wave_blocks(wp, P);
-    if (blocks > 4L * kNumCU) return -1;
+    long blocks = wave_blocks(wp, P);
+    if (blocks > kNumCU) blocks = (long)((P + 15) / 16) * (wp->n_rowblocks + wp->n_rowblocks % 2);   // (dealt out in pairs)
+    const int chunks = wp->K / 32;
+    if (blocks > 4L * kNumCU || chunks < (blocks <= kNumCU ? 4 : blocks <= 2L * kNumCU ? 8 : blocks <= 3L * kNumCU ? 40 : 64)) return -1;
     for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
+        if (d.SPC == 8 && blocks > 2L * kNumCU) continue;
         if (d.kind != 12 || d.NBLK != 1 || d.NJ != (blocks <= kNumCU || d.SPC == 8 ? 1 : 2)) continue;
         if (variant_legal(v, wp, xdt, ra)) return v;
     }

@@ -99,3 +99,23 @@ def test_values_of_columns_that_are_not_kept_stay_out():
         ok = np.isfinite(ref)
         assert np.array_equal(np.isfinite(y), ok), nm.nm_variant_name(v)
         assert norm_err(y[ok], ref[ok]) <= FP32_TOL, nm.nm_variant_name(v)
+
+
+# what the kernel gains grows with the K axis and falls with the blocks a CU gets: a layer on either side of each of the rule's
+# lines (chunks of 32 channels at up to 256, 512, 768 and 1024 blocks, row blocks in pairs; dense layers beyond 512 blocks)
+@pytest.mark.parametrize("layer,batch,wave", [
+    (L("kd_1", 12, 26, 24, 16, 1, 1, 1, 0, 1, 2, 4, 16), 1, False), (L("kd_4", 14, 14, 128, 64, 1, 1, 1, 0, 1, 2, 4, 16), 2, True),
+    (L("kd_7", 15, 36, 224, 128, 1, 1, 1, 0, 1, 1, 8, 16), 1, False), (L("kd_72", 14, 14, 256, 512, 3, 3, 1, 1, 1, 2, 4, 16), 1, True),
+    (L("kd_pairs", 22, 32, 56, 48, 3, 3, 1, 1, 1, 4, 8, 16), 3, False), (L("kd_18", 23, 46, 64, 64, 3, 3, 2, 1, 1, 4, 8, 16), 10, False),
+    (L("kd_3a_cu", 11, 11, 256, 256, 3, 3, 1, 1, 1, 2, 4, 16), 5, True), (L("kd_4a_cu", 61, 37, 16, 203, 3, 3, 2, 1, 1, 1, 4, 16), 2, False),
+    (L("kd_dense", 5, 35, 504, 141, 1, 1, 1, 0, 1, 1, 1, 32), 7, False)], ids=lambda a: getattr(a, "name", None))
+def test_untuned_default(layer, batch, wave):
+    import torch
+    x, w, bias = wl.make_tensors(layer, batch, 9, weight_sigma=0.1)
+    _, _, wz = oracle.prune(w, layer.n, layer.m, layer.tile)
+    wp = nm.nm_prune(w, layer.n, layer.m, layer.tile)
+    say(layer.name)
+    y = nm.nm_conv2d(torch.from_numpy(x).cuda(), wp, torch.from_numpy(bias).cuda(), layer.stride, layer.pad, layer.dil, True)
+    torch.cuda.synchronize()
+    assert nm.nm_variant_name(nm.nm_last_variant()).startswith("KW_") == wave
+    assert norm_err(y.cpu().numpy(), oracle.conv2d(x, wz, bias, layer.stride, layer.pad, layer.dil, True)) <= FP32_TOL
