@@ -254,7 +254,7 @@ def stack_roofline(st, ms_step, rows, headline, floor_ms=None):
         roofline = {"bound": "mfma", "achieved": eff / ms_step / 1e9, "peak": eff / t_flop / 1e9,
                     "unit": "TFLOP/s", "frac": t_flop / ms_step}
     traffic, source = profiled_traffic(st.dtype) if headline else (None, None)
-    families = sorted({(r["variant"] or "?").split("_")[0] for r in rows})
+    families = sorted({"_".join((r["variant"] or "?").split("_")[:2 if "_TAPS_" in (r["variant"] or "") else 1]) for r in rows})
     share = {}
     for r in rows:
         share[kernel_of(r["variant"])] = share.get(kernel_of(r["variant"]), 0.0) + r["ms"]

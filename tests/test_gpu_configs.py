@@ -126,14 +126,15 @@ def test_config4_resnet50_batch64_untuned_default(bf16):
         y = nm.nm_conv2d(xd, wp, torch.from_numpy(bias).cuda(), layer.stride, layer.pad, layer.dil, True)
         torch.cuda.synchronize()
         vname = nm.nm_variant_name(nm.nm_last_variant())
-        assert not re.search(r"_S\d+$", vname)   # the default never needs the K-split workspace
-        picks.add(vname.split("_")[0])
+        # the default never needs the K-split workspace (the KW forms split K inside a workgroup)
+        assert vname.startswith("KW_") or not re.search(r"_S\d+$", vname)
+        picks.add(vname.split("_")[0] + ("_TAPS" if "_TAPS_" in vname else ""))
         ref = oracle_conv(layer, x[[0, 63]], w, bias, relu=True, bf16=bf16)
         got = y[torch.tensor([0, 63], device=y.device)].float().cpu().numpy()
         for n_, b in enumerate((0, 63)):
             assert norm_err(got[n_], ref[n_]) <= tol, f"{layer.name} {vname} image {b}"
-    if bf16:   # the gather-free kernels (and the kernel-row-run kernel for the first layer), not the fp32 path on bf16 data
-        assert picks <= {"SP1", "SPW1", "SPR1", "RUN"}, picks
+    if bf16:   # the gather-free kernels (strips per tap or for all taps; the first layer's), not the fp32 path on bf16 data
+        assert picks <= {"SP1", "SPW1", "SPR1", "SPR1_TAPS", "RUN"} and "SPR1_TAPS" in picks, picks
 
 
 def test_config4_resnet50_batch64_large_groups():

@@ -27,6 +27,12 @@ CASES = [
 ]
 
 
+def splits(name):
+    """Workgroups that share the K axis of an output tile, 0 where none do (the KW forms deal it out inside one)."""
+    m = None if name.startswith("KW_") else re.search(r"_S(\d+)$", name)
+    return int(m.group(1)) if m else 0
+
+
 @pytest.mark.parametrize("layer,batch,bf16", CASES, ids=[c[0].name for c in CASES])
 @pytest.mark.parametrize("with_res", [False, True])
 def test_k_split_variants(layer, batch, bf16, with_res):
@@ -52,10 +58,9 @@ def test_k_split_variants(layer, batch, bf16, with_res):
     try:
         for v in range(nm.nm_variant_count()):
             name = nm.nm_variant_name(v)
-            m = re.search(r"_S(\d+)$", name)
-            if not m or not nm.nm_variant_legal(v, wp, ndt, ndt):
+            split = splits(name)
+            if not split or not nm.nm_variant_legal(v, wp, ndt, ndt):
                 continue
-            split = int(m.group(1))
             if ran.get(split, 0) >= 12:       # a dozen tile shapes per split count is plenty here
                 continue
             say(f"forced {name} on {layer.name} residual={with_res}")
@@ -74,7 +79,8 @@ def test_k_split_variants(layer, batch, bf16, with_res):
 
 def test_tuner_takes_a_split_where_the_tiles_cannot_fill_the_chip():
     """7x7x512 -> 512, 3x3, batch 1: 49 pixels and 32 row blocks are at most 32 output tiles
-    for 256 CUs; the tuner times the K-split forms too, and whatever it picks matches the oracle."""
+    for 256 CUs; the tuner times the K-split forms too, over workgroups and (KW) over wavefronts, and whatever it
+    picks matches the oracle."""
     import torch
     layer = L("deep_b1", 7, 7, 512, 512, 3, 3, 1, 1, 1, 2, 4, 16)
     x, w, bias = wl.make_tensors(layer, 1, 72)
@@ -90,6 +96,31 @@ def test_tuner_takes_a_split_where_the_tiles_cannot_fill_the_chip():
     assert norm_err(y.cpu().numpy(), ref) <= FP32_TOL
     assert re.search(r"_S\d+$", name), name   # with 9 x 8 = 72 chunks to share, a split wins here
     nm.nm_workspace_free()
-    y2 = nm.nm_conv2d(torch.from_numpy(x).cuda(), wp, torch.from_numpy(bias).cuda(), 1, 1, 1, True)   # grows it again
+    y2 = nm.nm_conv2d(torch.from_numpy(x).cuda(), wp, torch.from_numpy(bias).cuda(), 1, 1, 1, True)   # (a split over workgroups grows it again)
     torch.cuda.synchronize()
     assert torch.equal(y, y2)
+
+
+def test_workspace_grows_again_after_it_was_freed():
+    """A genuine split, forced: its partial sums need the library's workspace, which a larger
+    layer makes grow and which comes back after nm_workspace_free."""
+    import torch
+    for shape in ((7, 512), (14, 256)):      # 8 x 49 x 512 partial sums, then 8 x 196 x 256
+        layer = L("ws", shape[0], shape[0], shape[1], shape[1], 3, 3, 1, 1, 1, 2, 4, 16)
+        x, w, bias = wl.make_tensors(layer, 1, 72)
+        ref = oracle.conv2d(x, oracle.prune(w, 2, 4, 16)[2], bias, 1, 1, 1, True)
+        wp = nm.nm_prune(w, 2, 4, 16)
+        xd, bd = torch.from_numpy(x).cuda(), torch.from_numpy(bias).cuda()
+        v = next(v for v in range(nm.nm_variant_count()) if splits(nm.nm_variant_name(v)) == 8 and nm.nm_variant_legal(v, wp))
+        say(f"{nm.nm_variant_name(v)} on {shape}")
+        try:
+            nm.nm_force_variant(v)
+            y = nm.nm_conv2d(xd, wp, bd, 1, 1, 1, True)
+            torch.cuda.synchronize()
+            nm.nm_workspace_free()
+            y2 = nm.nm_conv2d(xd, wp, bd, 1, 1, 1, True)
+            torch.cuda.synchronize()
+            assert nm.nm_last_variant() == v
+        finally:
+            nm.nm_force_variant(-1)
+        assert norm_err(y.cpu().numpy(), ref) <= FP32_TOL and torch.equal(y, y2)

@@ -16,7 +16,8 @@ L = wl.ConvLayer
 def _split_variant(wp, splits):
     for v in range(nm.nm_variant_count()):
         name = nm.nm_variant_name(v)
-        if name.endswith(f"_S{splits}") and nm.nm_variant_legal(v, wp):
+        # (the KW forms deal K out over the wavefronts of a workgroup: no partial sums in memory)
+        if name.endswith(f"_S{splits}") and not name.startswith("KW_") and nm.nm_variant_legal(v, wp):
             return v
     raise AssertionError("no K-split variant is legal for this layer")
 
