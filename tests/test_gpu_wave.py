@@ -74,13 +74,14 @@ def test_values_of_columns_that_are_not_kept_stay_out():
     """Infinities and NaN in every column that some tile does not keep, in chunks with unused operand slots: an output
     is not finite only where the oracle's is not."""
     import torch
-    layer = L("kw_inf", 6, 7, 40, 32, 3, 3, 1, 1, 1, 1, 4, 16)
+    layer = L("kw_inf", 6, 7, 40, 32, 3, 3, 1, 1, 1, 1, 4, 16)   # 10 of 40 channels kept; the second chunk of a tap fills 2 of 8 slots
     x, w, _ = wl.make_tensors(layer, 1, 5, weight_sigma=0.1)
-    _, idx, wz = oracle.prune(w, 1, 4, 16)
-    dropped = sorted(set(range(layer.K)) - set(np.asarray(idx).ravel().tolist()))
-    for c in {k % 40 for k in dropped} - {int(k) % 40 for k in np.asarray(idx).ravel()}:
-        x[..., c] = np.inf
-    x[0, 2, 3, int(np.asarray(idx)[0].ravel()[0]) % 40] = np.nan     # and one value that the first tile does keep
+    w[..., ::4] *= 10
+    _, idx, _ = oracle.prune(w, 1, 4, 16)
+    assert set((np.asarray(idx) % 40 % 4).ravel().tolist()) == {0}   # every fourth channel is kept, at every tap
+    poison = [c for c in range(40) if c % 4]
+    x[..., poison] = np.array([np.inf, -np.inf, np.nan], np.float32)[np.arange(len(poison)) % 3]
+    x[0, 2, 3, 8] = np.nan                                           # and one value that is kept
     # (the oracle skips nothing that is kept: only the columns of a tile enter its sums)
     ref = np.zeros((1, 6, 7, 32), np.float32)
     xp = np.zeros((8, 9, 40), np.float64)
@@ -92,6 +93,7 @@ def test_values_of_columns_that_are_not_kept_stay_out():
             for h in range(6):
                 for q in range(7):
                     ref[0, h, q, co] = xp[h:h + 3, q:q + 3].ravel()[kept] @ wk
+    assert 0 < np.isnan(ref).sum() <= 9 * 32
     wp = nm.nm_prune(w, 1, 4, 16)
     for v in _forms(wp):
         say(f"forced {nm.nm_variant_name(v)} with infinities")
