@@ -98,7 +98,7 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t)
 namespace nm {
 
 static const VariantDesc kFake[] = {
-    // name, BP, NBLK, WP, NJ, CK, SPC, vec, kind, share, ksplit, areg
+    // name, BP, NBLK, WP, NJ, CK, SPC, vec, kind, share, ksplit, areg, spec, waves
     {"F_NB4_WP1_NJ1_CK32_SPC2", 64, 4, 1, 1, 32, 2, 1, 0, 1, 1, 0},
     {"F_NB4_WP1_NJ1_CK32_SPC4", 64, 4, 1, 1, 32, 4, 1, 0, 1, 1, 0},
     {"F_NB4_WP1_NJ1_CK32_SPC8", 64, 4, 1, 1, 32, 8, 1, 0, 1, 1, 0},
@@ -111,6 +111,7 @@ static const VariantDesc kFake[] = {
     {"F_B16_NB4_CK64_SPC2", 64, 4, 1, 1, 64, 2, 1, 1, 1, 1, 0},
     {"F_SP1_NB4_NJ2_CK64", 64, 4, 1, 2, 64, 1, 1, 2, 1, 1, 0},
     {"F_SP0_NB4_NJ2_CK128", 64, 4, 1, 2, 128, 2, 1, 3, 1, 1, 0},
+    {"F_SP0_NB4_NJ2_CK64", 64, 4, 1, 2, 64, 1, 1, 3, 1, 1, 0},
     {"F_SPR1_NB4_NJ2_CK64", 64, 4, 1, 2, 64, 1, 1, 2, 1, 1, 1},
     {"F_RUN_NB4_KS3", 64, 4, 1, 1, 192, 3, 1, 4, 1, 1, 0},
     {"F_RUN_NB4_KS1", 64, 4, 1, 1, 64, 1, 1, 4, 1, 1, 0},
@@ -131,6 +132,13 @@ static const VariantDesc kFake[] = {
     {"F_RUN_ROWS4_NJ4_KS1", 16, 4, 4, 4, 64, 1, 1, 10, 1, 1, 0},
     {"F_ROWF_R2_NJ2_KS3", 16, 2, 2, 2, 192, 3, 1, 11, 1, 1, 0},
     {"F_ROWF_R4_NJ1_KS1", 16, 4, 1, 1, 64, 1, 1, 11, 1, 1, 0},
+    // small fp32 layers, the K axis over wavefronts, and bf16 k x k layers staged once for all taps
+    {"F_KW_PB1_NJ1_CK32_SPC2", 16, 1, 4, 1, 32, 2, 1, 12, 1, 1, 0, 0, 16},
+    {"F_KW_PB1_NJ2_CK32_SPC4", 16, 1, 4, 2, 32, 4, 1, 12, 1, 1, 0, 0, 16},
+    {"F_KW_PB2_NJ2_CK32_SPC8", 32, 2, 4, 2, 32, 8, 1, 12, 1, 1, 0, 0, 12},
+    {"F_SPR1_TAPS_NB4_WP1_NJ2", 64, 4, 1, 2, 64, 1, 1, 13, 1, 1, 1, 1},
+    {"F_SPR1_TAPS_NB7_WP2_NJ4", 224, 7, 2, 4, 64, 1, 1, 13, 1, 1, 1, 1},
+    {"F_SPR0_TAPS_NB5_WP2_NJ4", 160, 5, 2, 4, 64, 1, 1, 14, 1, 1, 1, 1},
 };
 int variant_count() { return (int)(sizeof(kFake) / sizeof(kFake[0])); }
 const VariantDesc& variant_desc(int v) { return kFake[v]; }
@@ -157,7 +165,7 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
     const bool rows = d.kind == 10 || d.kind == 11;
     CHECK(p.n_ptiles == (rows ? p.B * ((p.Ho + d.NBLK - 1) / d.NBLK) : (p.P + d.BP - 1) / d.BP));
     CHECK(p.n_wg == p.n_ptiles * p.n_cblocks * p.ksplit);
-    if (d.kind >= 8) CHECK(p.tile == 16 && p.rbpt == 1 && p.n_rowblocks == (p.Cout + 15) / 16);
+    if (d.kind >= 8 && d.kind <= 11) CHECK(p.tile == 16 && p.rbpt == 1 && p.n_rowblocks == (p.Cout + 15) / 16);
     if (rows) {
         // every operand of every output pixel of a workgroup lies in the staged rows, and these in the CU's LDS
         const long last = (long)p.rows_front + ((long)(d.NBLK - 1) * p.sh + (long)(p.Kh - 1) * p.dh) * p.rows_pitch +
@@ -169,6 +177,29 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
         CHECK((long)p.rows_data + 2L * p.W * p.Cin <= p.rows_pitch);
         CHECK(plane * (d.kind == 10 ? 1 : 3) <= p.rows_lds && p.rows_lds % 1024 == 0 && p.rows_lds + 4 * 16 * 144 <= 160 * 1024);
         CHECK(p.dw == 1 && (p.sw * (long)p.Cin) % 2 == 0 && (p.W * p.Cin) % 2 == 0);
+    }
+    auto exact = [](unsigned div, unsigned mul, unsigned shift, unsigned most) {
+        for (unsigned x : {0u, 1u, div - 1, div, div + 1, most / 2, most / div * div, most})
+            if ((unsigned)(((unsigned long long)(2ull * x) * mul) >> 32) >> shift != x / div) return false;
+        return true;
+    };
+    if (d.kind == 12) {
+        // every wavefront owns chunks, together they cover the K axis; a place in a byte; what is divided by is the divisor
+        CHECK(p.waves >= 1 && p.waves <= d.waves && p.cps >= 1 && (p.waves - 1) * p.cps < p.nchunks && p.waves * p.cps >= p.nchunks);
+        CHECK(d.CK + 4 <= 256 && p.rows_bytes == (size_t)((p.Cout + p.tile - 1) / p.tile) * p.nchunks * 4 * d.SPC);
+        CHECK(wave_lds_bytes(d.NBLK, d.NJ, d.CK, p.waves) <= 160 * 1024);
+        CHECK(exact((unsigned)(p.px_fast ? p.n_ptiles : p.n_cblocks), p.fast_mul, p.fast_shift, (unsigned)p.n_wg));
+        CHECK(exact((unsigned)p.ncpt, p.ncpt_mul, p.ncpt_shift, (unsigned)p.nchunks) && exact((unsigned)p.Kw, p.kw_mul, p.kw_shift, (unsigned)(p.Kh * p.Kw)));
+        CHECK(exact((unsigned)p.rbpt, p.rbpt_mul, p.rbpt_shift, (unsigned)p.n_rowblocks + 16));
+    }
+    if (d.kind == 13 || d.kind == 14) {
+        // an output as large as the input, whole granules and row blocks of 16 channels, two stages in the CU's LDS
+        CHECK(p.sh == 1 && p.sw == 1 && p.Ho == p.H && p.Wo == p.W && p.Cin % 64 == 0 && p.Cout % 8 == 0 && p.tile % 16 == 0);
+        CHECK(p.rows_n == taps_granules(d.BP, p.H, p.W, p.ph, p.pw) && p.rows_lds == taps_loads(p.rows_n) * 1024 && p.rows_lds >= p.rows_n * 16);
+        CHECK(taps_lds_bytes(d.NBLK, d.WP, d.NJ, p.rows_n, p.ncpt) <= 160 * 1024 && p.ncpt == p.Cin / 64);
+        const long line = taps_line(p.W, p.pw), lines = (long)(p.B + 2) * (p.H + p.ph);
+        CHECK(lines < 1 << 24 && lines * line < 1l << 31 && p.P < 1 << 24);
+        CHECK(exact((unsigned)line, p.padw_mul, p.padw_shift, (unsigned)(lines * line)) && exact((unsigned)(p.H + p.ph), p.padh_mul, p.padh_shift, (unsigned)lines));
     }
     CHECK(p.ksplit == (d.ksplit > 1 ? d.ksplit : 1));
     if (p.ksplit > 1) {   // every split owns chunks, together they cover the K axis, and the partial sums have a home
@@ -216,6 +247,7 @@ int run_build_prepack(nm_packed* wp, Prepack& pp, hipStream_t)
 {
     CHECK(inside(pp.d_wfrag, pp.wfrag_bytes));
     CHECK(pp.rows_bytes == 0 || inside(pp.d_rows, pp.rows_bytes));
+    CHECK(pp.cols_bytes == 0 || (inside(pp.d_cols, pp.cols_bytes) && pp.cols_bytes * 4 == pp.rows_bytes));
     memset(pp.d_wfrag, 0, pp.wfrag_bytes);   // touches every byte the kernel would fill
     (void)wp;
     return NM_OK;
@@ -272,6 +304,8 @@ static void* dev_alloc(size_t n)
     return p;
 }
 
+static int g_taps_ran = 0;
+
 static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, int n, int m, int tile, nm_dtype_t dt,
                       int sh, int sw, int ph, int pw, int dh, int dw)
 {
@@ -299,10 +333,31 @@ static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, in
     CHECK(g_launches == before + 1 && nm_last_variant() >= 0);
     CHECK(nm_conv2d_res(x, dt, b, h, w, cin, wp, nullptr, r, sh, sw, ph, pw, dh, dw, 0, y, ydt, nullptr) == NM_OK);
     CHECK(nm_conv2d_res(x, dt, b, h, w, cin, wp, nullptr, y, sh, sw, ph, pw, dh, dw, 0, y, ydt, nullptr) == NM_ERR_ARG);
+    // the block of arguments: the same call, and the same refusals
+    nm_conv_args_t args = {x, wp, bias, r, y, nullptr, dt, b, h, w, cin, sh, sw, ph, pw, dh, dw, 1, ydt, 0};
+    for (int only = 0; only < 2; ++only) {
+        args.static_only = only;
+        CHECK(nm_conv2d_args(&args) == NM_OK);
+        auto refused = [&](int code, auto change) {
+            nm_conv_args_t a = args;
+            change(a);
+            return nm_conv2d_args(&a) == code;
+        };
+        CHECK(refused(NM_ERR_ARG, [](nm_conv_args_t& a) { a.x_dev = nullptr; }));
+        CHECK(refused(NM_ERR_ARG, [](nm_conv_args_t& a) { a.wp = nullptr; }));
+        CHECK(refused(NM_ERR_ARG, [](nm_conv_args_t& a) { a.y_dev = nullptr; }));
+        CHECK(refused(NM_ERR_ARG, [](nm_conv_args_t& a) { a.residual_dev = a.y_dev; }));
+        CHECK(refused(NM_ERR_ARG, [](nm_conv_args_t& a) { a.cin += 1; }));
+        CHECK(refused(NM_ERR_ARG, [](nm_conv_args_t& a) { a.stride_w = 0; }));
+        CHECK(refused(NM_ERR_UNSUPPORTED, [](nm_conv_args_t& a) { a.y_dtype = a.y_dtype == NM_F32 ? NM_BF16 : NM_F32; }));
+        CHECK(refused(NM_ERR_SHAPE, [](nm_conv_args_t& a) { a.b = 1 << 20; a.h = a.w = 4096; }));
+    }
+    CHECK(nm_conv2d_args(nullptr) == NM_ERR_ARG);
     int v = -1;
     float ms = 0.f;
     CHECK(nm_autotune(dt, b, h, w, cin, wp, 1, sh, sw, ph, pw, dh, dw, 1, ydt, nullptr, &v, &ms) == NM_OK);
-    CHECK(v >= 0 && ms > 0.f && nm_variant_legal(v, wp, dt, ydt) == 1);
+    auto taps = [](int u) { return strstr(nm_variant_name(u), "_TAPS_") != nullptr; };   // (depend on more than the handle)
+    CHECK(v >= 0 && ms > 0.f && nm_variant_legal(v, wp, dt, ydt) == (taps(v) ? 0 : 1));
     CHECK(nm_conv2d(x, dt, b, h, w, cin, wp, bias, sh, sw, ph, pw, dh, dw, 1, y, ydt, nullptr) == NM_OK);
     CHECK(nm_last_variant() == v);
     // every legal variant forced in turn, an illegal one refused
@@ -310,7 +365,8 @@ static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, in
         CHECK(nm_force_variant(u) == NM_OK);
         const int legal = nm_variant_legal(u, wp, dt, ydt);
         const int rc = nm_conv2d(x, dt, b, h, w, cin, wp, bias, sh, sw, ph, pw, dh, dw, 1, y, ydt, nullptr);
-        CHECK(legal ? (rc == NM_OK || rc == NM_ERR_UNSUPPORTED) : rc == NM_ERR_UNSUPPORTED);
+        CHECK(legal || taps(u) ? (rc == NM_OK || rc == NM_ERR_UNSUPPORTED) : rc == NM_ERR_UNSUPPORTED);
+        g_taps_ran += taps(u) && rc == NM_OK;
     }
     CHECK(nm_force_variant(-1) == NM_OK);
     // K-split variants: through the growable workspace, through the static scratch, and under capture
@@ -384,6 +440,42 @@ static void split_limits()
     g_capturing = false;
     CHECK(nm_conv2d(x, NM_F32, b, h, w, cin, wp, nullptr, 1, 1, 1, 1, 1, 1, 0, y, NM_F32, nullptr) == NM_OK);
     CHECK(nm_force_variant(-1) == NM_OK);
+    CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
+}
+
+// The tap-staged forms on either side of what bounds them: rows of 3000 pixels, padded rows below 2^24, padded granules below
+// 2^31 (padding far wider than the image), 32 taps
+static void taps_limits()
+{
+    std::vector<float> wt((size_t)8 * 35 * 64, 0.5f);
+    int form = -1;
+    for (int u = 0; u < nm_variant_count(); ++u)
+        if (strstr(nm_variant_name(u), "SPR1_TAPS_NB4")) form = u;
+    auto run = [&](int b, int h, int w, int kh, int kw, int dh, int dw, int ph, int pw) {
+        nm_packed_t* wp = nullptr;
+        CHECK(nm_prune(wt.data(), 8, kh, kw, 64, 2, 4, 16, NM_BF16, &wp) == NM_OK);
+        void* x = dev_alloc((size_t)b * h * w * 64 * 2);
+        void* y = dev_alloc((size_t)b * h * w * 8 * 2);
+        CHECK(nm_force_variant(form) == NM_OK);
+        const int rc = nm_conv2d(x, NM_BF16, b, h, w, 64, wp, nullptr, 1, 1, ph, pw, dh, dw, 0, y, NM_BF16, nullptr);
+        CHECK(nm_force_variant(-1) == NM_OK && (rc == NM_OK || rc == NM_ERR_UNSUPPORTED));
+        CHECK(nm_conv2d(x, NM_BF16, b, h, w, 64, wp, nullptr, 1, 1, ph, pw, dh, dw, 0, y, NM_BF16, nullptr) == NM_OK);
+        CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
+        return rc == NM_OK;
+    };
+    CHECK(run(1, 2, 3000, 1, 3, 1, 1, 0, 1) && !run(1, 2, 3001, 1, 3, 1, 1, 0, 1));
+    CHECK(run(8388605, 1, 1, 3, 3, 1, 1, 1, 1) && !run(8388606, 1, 1, 3, 3, 1, 1, 1, 1));
+    CHECK(run(3976819, 1, 4, 1, 3, 1, 56, 0, 56) && !run(3976820, 1, 4, 1, 3, 1, 56, 0, 56));
+    CHECK(run(1, 1, 64, 1, 3, 1, 300, 0, 300) && !run(1, 1, 64, 1, 3, 1, 1001, 0, 1001) && !run(1, 1, 64, 3, 1, 0x20000000, 1, 0x20000000, 0));
+    CHECK(run(1, 9, 9, 31, 1, 1, 1, 15, 0) && !run(1, 9, 9, 5, 7, 1, 1, 2, 3) && !run(1, 9, 9, 1, 1, 1, 1, 0, 0));
+    // ... and as the untuned default of a layer with enough workgroups
+    wt.resize((size_t)128 * 9 * 128, 0.5f);
+    nm_packed_t* wp = nullptr;
+    CHECK(nm_prune(wt.data(), 128, 3, 3, 128, 2, 4, 16, NM_BF16, &wp) == NM_OK);
+    void* x = dev_alloc((size_t)64 * 28 * 28 * 128 * 2);
+    void* y = dev_alloc((size_t)64 * 28 * 28 * 128 * 2);
+    CHECK(nm_conv2d(x, NM_BF16, 64, 28, 28, 128, wp, nullptr, 1, 1, 1, 1, 1, 1, 0, y, NM_BF16, nullptr) == NM_OK);
+    CHECK(strstr(nm_variant_name(nm_last_variant()), "_TAPS_"));
     CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
 }
 
@@ -494,6 +586,11 @@ int main(int argc, char** argv)
     conv_case(1, 5, 5, 128, 16, 1, 1, 4, 8, 16, NM_BF16, 1, 1, 0, 0, 1, 1);    // dense instruction only
     conv_case(1, 1, 1, 8, 5, 1, 1, 1, 2, 5, NM_F32, 1, 1, 0, 0, 1, 1);
     conv_case(2, 7, 6, 128, 40, 3, 3, 2, 4, 16, NM_F8E4M3, 2, 1, 1, 1, 1, 1);    // fp8 in, bf16 out
+    CHECK(g_taps_ran == 0);
+    conv_case(3, 9, 7, 128, 40, 3, 3, 2, 4, 16, NM_BF16, 1, 1, 1, 1, 1, 1);    // a tile's input staged once for all taps
+    conv_case(1, 12, 5, 64, 24, 1, 3, 4, 8, 32, NM_BF16, 1, 1, 0, 2, 3, 2);    // ... dense instruction only
+    CHECK(g_taps_ran == 3 + 1);
+    taps_limits();
     {   // E4M3 weights that the fp8 kernel cannot take, and fp8 tensors on weights of another type
         std::vector<float> wt(16 * 48, 0.25f);
         nm_packed_t* h8 = nullptr;
@@ -521,7 +618,7 @@ int main(int argc, char** argv)
     // nothing leaked on the "device": what is left is the K-split workspace and the static scratch
     CHECK(g_allocs.size() <= 2);
     const int n_entries = nm_cache_size();
-    CHECK(n_entries == 8);
+    CHECK(n_entries == 10);
 
     // ---- cache file round trip and hostile files
     const std::string path = tmp + "/nm_cache_san.txt";

@@ -1,6 +1,7 @@
 // The staged layout of the tap-staged bf16 kernel, on the CPU: every strip read of every output pixel and tap finds in
 // the stage what the convolution needs there (the channels of one input pixel, or zeros outside the image), for odd
-// images, kernels, dilations and tiles, and stays inside the stage.
+// images, kernels, dilations and tiles, and stays inside the stage; and in the first, middle and last tiles of layers next to
+// what the library lets through (pixels and padded rows below 2^24, rows of 3000 pixels, padded granules below 2^31).
 #include <cstdio>
 #include <vector>
 
@@ -18,7 +19,7 @@ static void magic(unsigned d, unsigned* mul, unsigned* shift)
 
 static long checked = 0;
 
-static bool layer(int B, int H, int W, int kh, int kw, int dh, int dw, int BP)
+static bool layer(int B, int H, int W, int kh, int kw, int dh, int dw, int BP, bool sampled = false)
 {
     const int ph = dh * (kh - 1) / 2, pw = dw * (kw - 1) / 2;
     const long line = taps_line(W, pw), Hp = H + ph, P = (long)B * H * W;
@@ -26,8 +27,11 @@ static bool layer(int B, int H, int W, int kh, int kw, int dh, int dw, int BP)
     magic((unsigned)line, &lm, &ls);
     magic((unsigned)Hp, &im, &is);
     auto place = [&](long p) { return (p / (H * W) * Hp + p % (H * W) / W) * line + p % W * 9; };
-    const long n = (long)taps_loads(taps_granules(BP, H, W, ph, pw)) * 64;
+    const long n = (long)taps_loads(taps_granules(BP, H, W, ph, pw)) * 64, tiles = (P + BP - 1) / BP;
+    if (sampled && ((B + 2.0) * Hp >= 16777216.0 || (B + 2.0) * Hp * line >= 2147483648.0 || P >= 16777216 || n > 10240)) return false;
     for (long p0 = 0; p0 < P; p0 += BP) {
+        const long tile = p0 / BP;
+        if (sampled && tile > 2 && tile + 3 < tiles && tile != tiles / 2) continue;
         const long t0 = place(p0) - (ph * line + pw * 9) + Hp * line;
         if (t0 < 0) return false;
         std::vector<TapsSource> stage;
@@ -68,6 +72,14 @@ int main()
                             return 1;
                         }
                     }
+    struct Far { int B, H, W, kh, kw, dh, dw; };
+    for (const Far& f : {Far{8388605, 1, 1, 3, 3, 1, 1}, Far{1, 5592300, 3, 3, 1, 1, 1}, Far{1, 5592, 3000, 1, 3, 1, 1}, Far{3976818, 1, 4, 1, 3, 1, 56},
+                         Far{2, 1398000, 6, 3, 3, 1, 1}, Far{1, 5592400, 1, 1, 5, 1, 1}, Far{239, 26000, 2, 5, 1, 2, 1}})
+        for (int BP : {64, 128})
+            if (!(BP == 128 && f.dw > 2) && !layer(f.B, f.H, f.W, f.kh, f.kw, f.dh, f.dw, BP, true)) {
+                printf("wrong: B %d H %d W %d kernel %dx%d dilation %d %d tile %d\n", f.B, f.H, f.W, f.kh, f.kw, f.dh, f.dw, BP);
+                return 1;
+            }
     printf("taps layout: ok, %ld reads\n", checked);
     return 0;
 }
