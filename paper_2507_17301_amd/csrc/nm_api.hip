@@ -482,8 +482,8 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
 }
 
 // The variants without a K split, in table order: what an untuned call chooses from.  Of these only the kinds
-// that the handle has operand tables for are looked at: the choice is made on every untuned call, and a look at
-// all 1500 variants took 20 us of it.
+// that the handle has operand tables for are looked at: the choice is made at the first untuned call of a shape (and where a
+// full table has forgotten it), and a look at all 1500 variants took 20 us of it.
 const std::vector<int>& base_variants()
 {
     static const std::vector<int> t = [] {

@@ -13,7 +13,13 @@
 // the strip reads of eight consecutive output pixels then fall on eight different granules modulo 128 bytes, also where
 // a row ends between them.
 //
-// What bounds it: a contracting wavefront has a SIMD to itself, so the chunks run at the rate of its instruction issue.  On
+// The sums run over all taps of 64 channels, then the next 64, where that kernel's run over all channels of a tap: beyond 64
+// input channels the last bits differ, by as much as between that kernel and the gather kernel (1 output in 10^4 is not the
+// bf16 number nearest to the exact one either way; logits of ResNet-50 x1.0005 +- 0.0015 as far from float64, of ResNet-101
+// x0.9998 +- 0.0019).
+//
+// What bounds it: a contracting wavefront has a SIMD to itself (but for one, which shares its with the wavefront that fetches),
+// so the chunks run at the rate of its instruction issue.  On
 // 28x28 128 -> 128 at batch 64 (196 or 224 workgroups, one round) of 16.0 us 2.7 are the launch, 3.5 the first stage and
 // the output tile, 2.7 its stores and 4.4 the matrix instructions; without the loads of the weights it takes 15.0, without
 // the strip reads 15.3.  Steps on the way: requests dealt out behind single matrix instructions and not behind four 17.3 ->
@@ -23,8 +29,8 @@
 // 576 -> 256 at batch 112 60.6 -> 38.7.  Few pixels (14x14 256 at batch 64: 196 tiles of 128 x 128, whose weights are as many
 // bytes as the strip) stay with the other.
 //
-// Four wavefronts contract; a fifth fills the other stage meanwhile.  (One is enough for a stage every nine taps, and
-// unlike four it leaves the registers for a second workgroup on the CU.)
+// Four wavefronts contract; a fifth fills the other stage meanwhile.  (One is enough for a stage every nine taps.  Of the
+// smallest form, 64 x 128 on 104 registers, two workgroups fit a CU; the others take 172 to 230 and have it to themselves.)
 #pragma once
 
 #include "nm_conv_sp16_kernel.h"

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * NW) void nm_conv_wave_kernel(const ConvParams 
         const bool live = c < c_end;
 #pragma unroll
         for (int it = 0; it < NIT; ++it)   // (channels beyond the tap's last are not asked for)
-            r.x[it] = buf_load4(xr, live & (ci0 + g * 4 < p.Cin) ? voff[it] + (unsigned)(ci0 * 4) : kOOB, 0, (const float*)nullptr);
+            r.x[it] = buf_load4(xr, (live & (ci0 + g * 4 < p.Cin)) ? voff[it] + (unsigned)(ci0 * 4) : kOOB, 0, (const float*)nullptr);
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             load_words<SPC>(r.w[jj], wr, live ? woff[jj] : kOOB, 0);
