@@ -226,7 +226,8 @@ const Prepack* find_prepack(const nm_packed* wp, const VariantDesc& d, int par =
 // kinds 6 (register-streaming) and 7 (LDS-staged) are the fp8 kernels; they share one operand table layout
 inline bool is_f8_kind(int kind) { return kind == 6 || kind == 7; }
 
-// With `ra` the answer is for that convolution; without, "for some convolution".
+// With `ra` the answer is for that convolution; without, "for some convolution" (the tap-staged kinds: no, since nearly all
+// that decides about them is in the call).
 bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra = nullptr)
 {
     if (v < 0 || v >= variant_count()) return false;
