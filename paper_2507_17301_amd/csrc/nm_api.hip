@@ -419,6 +419,14 @@ void magic_div(unsigned d, unsigned* mul, unsigned* shift)
     *shift = s;
 }
 
+// Whether an output of so many bytes is stored past the caches: where the 256 MB last-level cache would not hold it (and
+// the rest of a layer's tensors) until the next layer reads it.  Layer and the layer that reads it, written through
+// and past the caches: fp32 56x56 64 -> 256 and 256 -> 64 (206 MB between them) 73 + 58 and 59 + 53 us; bf16 28x28 128 -> 512 and
+// 512 -> 128 at batch 256 (206 MB) 93 + 56 and 89 + 53; 14x14 256 -> 1024 and 1024 -> 256 (103 MB) 62 + 34 and 63 + 36.  The first
+// layer of a network, read once by the pool behind it and not as a residual as well: bf16 (103 MB) 36 + 30 and 33 + 27, fp32
+// (206 MB) 113 + 48 and 114 + 50.
+bool stream_output(int kind, double bytes) { return bytes > (kind == 10 ? 96e6 : kind == 11 ? 256e6 : 150e6); }
+
 void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const nm_packed* wp,
                  const void* x, void* y, const float* bias, int b, int h, int w, const Geometry& g,
                  int sh, int sw, int ph, int pw, int dh, int dw, int relu, size_t es)
@@ -430,6 +438,7 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     p.Ho = g.Ho; p.Wo = g.Wo;
     p.sh = sh; p.sw = sw; p.ph = ph; p.pw = pw; p.dh = dh; p.dw = dw;
     p.relu = relu ? 1 : 0;
+    p.stream = stream_output(d.kind, (double)g.P * wp->cout * (es == 4 ? 4 : 2)) ? 1 : 0;   // (fp8 layers write bf16)
     p.P = g.P; p.K = wp->K;
     p.nchunks = pp.geom.nchunks; p.ncpt = pp.geom.ncpt;
     p.tile = wp->tile; p.rbpt = wp->rbpt; p.n_rowblocks = wp->n_rowblocks;

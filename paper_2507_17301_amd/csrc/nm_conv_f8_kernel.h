@@ -190,15 +190,18 @@ __global__ __launch_bounds__(256) void nm_conv_f8_kernel(const ConvParams p)
     const int cg = rb0 * 16 + g * 8;             // first channel of this lane's granule
     if (cg < p.Cout) {
         bf16_t* __restrict__ y = reinterpret_cast<bf16_t*>(p.y);
+        u4v v[BPW / RSTEP];
 #pragma unroll
-        for (int it = 0; it < BPW / RSTEP; ++it) {
-            const int pl = it * RSTEP + r0;
-            const int pp = wpix + pl;
-            if (pp < p.P) {
-                const u4v v = *reinterpret_cast<const u4v*>(tile + pl * PITCH + g * 16);
-                *reinterpret_cast<u4v*>(y + ((unsigned)pp * (unsigned)p.Cout + (unsigned)cg)) = v;
+        for (int it = 0; it < BPW / RSTEP; ++it) v[it] = *reinterpret_cast<const u4v*>(tile + (it * RSTEP + r0) * PITCH + g * 16);
+        auto store = [&](auto stream) {
+#pragma unroll
+            for (int it = 0; it < BPW / RSTEP; ++it) {
+                const int pp = wpix + it * RSTEP + r0;
+                if (pp < p.P) store_out16<decltype(stream)::value>(y + ((unsigned)pp * (unsigned)p.Cout + (unsigned)cg), v[it]);
             }
-        }
+        };
+        if (p.stream) store(std::true_type());
+        else store(std::false_type());
     }
 }
 

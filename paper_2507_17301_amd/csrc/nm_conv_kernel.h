@@ -29,6 +29,8 @@
 // between two sets instead of being copied.
 #pragma once
 
+#include <type_traits>
+
 #include "nm_launch_decl.h"
 
 namespace nm {
@@ -54,6 +56,19 @@ __device__ inline void store4(bf16_t* p, f4 v)
     u.x = pack_bf16(v.x, v.y);
     u.y = pack_bf16(v.z, v.w);
     *reinterpret_cast<uint2*>(p) = u;
+}
+// 16 bytes of an output row (rows of 64 bytes and more: nothing collects the pieces of a line any more).
+//   STREAM = false: written through the L2 (agent scope).  Each XCD has an L2 of its own, and the end of a kernel writes
+//     back what its L2 still holds of the output before the next kernel may start; written through, the rows are on
+//     their way as they are stored.
+//   STREAM = true: past the L2 and the 256 MB last-level cache too (nontemporal), where that would not hold the output
+//     until it is read (stream_output() has the sizes).
+// Plain and write-through stores, batch 64: 28x28 3x3 128 -> 128 bf16 15.4 and 13.7 us, 14x14 1x1 1024 -> 256 fp8 8.5 and
+// 8.0, the layers of ResNet-50 in bf16 1201 and 1153, in fp32 2973 and 2930.
+template <bool STREAM> __device__ inline void store_out16(void* p, u4v v)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u4v*>(p));
+    else __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u4v*)p, v, "agent");
 }
 __device__ inline void store1(float* p, float v) { *p = v; }
 __device__ inline void store1(bf16_t* p, float v) { p->v = to_bf16_bits(v); }
@@ -135,13 +150,23 @@ __device__ inline void tile_flush(const ConvParams& p, const char* tile, int p0,
     TOUT* __restrict__ y = reinterpret_cast<TOUT*>(p.y) + ((unsigned)(p0 + r0) * (unsigned)p.Cout + (unsigned)co);
     const char* src = tile + r0 * PITCH + cg * 16;
     const int rows_left = p.P - p0 - r0;             // rows r0 + k RSTEP with k RSTEP < rows_left exist
+    constexpr int NB = NG < 8 ? NG : 8;              // rows read before the first of them is stored
+    auto rows = [&](auto stream) {
 #pragma unroll
-    for (int it = 0; it < NG; ++it) {
-        if ((BP % RSTEP == 0 || r0 + it * RSTEP < BP) && it * RSTEP < rows_left) {
-            const u4v v = *reinterpret_cast<const u4v*>(src + it * (RSTEP * PITCH));
-            *reinterpret_cast<u4v*>(y + (unsigned)(it * RSTEP) * (unsigned)p.Cout) = v;
+        for (int i0 = 0; i0 < NG; i0 += NB) {
+            u4v v[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (i0 + k < NG && (BP % RSTEP == 0 || r0 + (i0 + k) * RSTEP < BP))
+                    v[k] = *reinterpret_cast<const u4v*>(src + (i0 + k) * (RSTEP * PITCH));
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (i0 + k < NG && (BP % RSTEP == 0 || r0 + (i0 + k) * RSTEP < BP) && (i0 + k) * RSTEP < rows_left)
+                    store_out16<decltype(stream)::value>(y + (unsigned)((i0 + k) * RSTEP) * (unsigned)p.Cout, v[k]);
         }
-    }
+    };
+    if (p.stream) rows(std::true_type());
+    else rows(std::false_type());
 }
 
 // The residual of a tile, fetched as the tile is written: whole rows, 16 bytes per lane, by 256 threads

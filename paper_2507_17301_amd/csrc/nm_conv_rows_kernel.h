@@ -262,7 +262,9 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
                     if (p.relu) f = relu4(f);
                     v[k] = __builtin_bit_cast(u4v, f);
                 }
-                if (live) *reinterpret_cast<u4v*>(y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout)) = v[k];
+                T* const to = y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout);
+                if (live & (p.stream != 0)) store_out16<true>(to, v[k]);
+                if (live & (p.stream == 0)) store_out16<false>(to, v[k]);
             }
             if constexpr (PL == 3) {
                 if (__builtin_expect(lo < kSplitTiny || hi >= kSplitInf || any, 0)) {

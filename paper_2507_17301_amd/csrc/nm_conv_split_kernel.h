@@ -512,10 +512,15 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
 #pragma unroll
                     for (int k = 0; k < NP; ++k) v[k] = relu4(v[k]);
                 }
+                auto store = [&](auto stream) {
 #pragma unroll
-                for (int k = 0; k < NP; ++k)
-                    if (k * RPP + r0 < rows && pp0 + k * RPP < P && co < Cout)
-                        store4(y + ((unsigned)(pp0 + k * RPP) * (unsigned)Cout + (unsigned)co), v[k]);
+                    for (int k = 0; k < NP; ++k)
+                        if (k * RPP + r0 < rows && pp0 + k * RPP < P && co < Cout)
+                            store_out16<decltype(stream)::value>(y + ((unsigned)(pp0 + k * RPP) * (unsigned)Cout + (unsigned)co),
+                                                                 __builtin_bit_cast(u4v, v[k]));
+                };
+                if (kp->stream) store(std::true_type());
+                else store(std::false_type());
             } else {
 #pragma unroll 1
                 for (int row = 0; row < rows; row += RPP) {

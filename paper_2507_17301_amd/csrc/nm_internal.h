@@ -215,6 +215,7 @@ struct ConvParams {
     int B, H, W, Cin, Cout, Kh, Kw, Ho, Wo;
     int sh, sw, ph, pw, dh, dw;
     int relu;
+    int stream;        // output rows are stored past the caches
     int P;             // B*Ho*Wo
     int K;
     int nchunks, ncpt;

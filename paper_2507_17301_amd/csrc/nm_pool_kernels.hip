@@ -114,8 +114,10 @@ __global__ __launch_bounds__(256) void maxpool_vec_kernel(const T* __restrict__ 
             }
     }
     T* const py = y + ((size_t)row * Wo + wo) * C + cv * V;
+    u4v o;
 #pragma unroll
-    for (int g = 0; g < V; g += 4) store4(py + g, f4{m[g], m[g + 1], m[g + 2], m[g + 3]});
+    for (int g = 0; g < 4; ++g) o[g] = V == 4 ? __float_as_uint(m[g]) : pack_bf16(m[g * V / 4], m[g * V / 4 + V / 4 - 1]);
+    store_out16<false>(py, o);
 }
 
 // one workgroup per (image, 64-channel slab): 4 wavefronts split the positions,

@@ -1,0 +1,56 @@
+"""Outputs larger than the last-level cache leave through other stores than smaller ones: a batch on the far side of the line
+against its two halves on the near side, bit for bit (the sums of a pixel do not know of the batch)."""
+import numpy as np
+import pytest
+
+from paper_2507_17301_amd import binding as nm
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # dtype, batch, size, Cin, Cout, k, stride, pad, N:M, residual, variants by prefix ("" = the default)
+    ("bf16", 98, 56, 64, 256, 1, 1, 0, (2, 4), True, ("", "SPR1_NB8_WP1_NJ4_CK64", "B16_NB4_WP1_NJ2_SH1")),
+    ("bf16", 50, 80, 64, 256, 3, 1, 1, (2, 4), False, ("SPR1_TAPS_NB7_WP2_NJ4",)),
+    ("f32", 50, 56, 64, 256, 1, 1, 0, (2, 4), True, ("X3S_NB4_WP1_NJ2", "NB4_WP1_NJ2_CK32")),
+    ("bf16", 62, 224, 3, 64, 7, 2, 3, (1, 1), False, ("", "RUN_NB4_WP1_NJ1")),
+    ("f32", 81, 224, 3, 64, 7, 2, 3, (1, 1), False, ("ROWF_R4_NJ2",)),
+    ("f8", 98, 56, 64, 256, 1, 1, 0, (2, 4), False, ("", "F8_NB4_WP1_NJ4")),
+]
+
+
+@pytest.mark.parametrize("dtype,batch,size,cin,cout,k,stride,pad,nm_,residual,variants", CASES)
+def test_both_sides_of_the_line(dtype, batch, size, cin, cout, k, stride, pad, nm_, residual, variants):
+    import torch
+    code, tdt = {"f32": (nm.NM_F32, torch.float32), "bf16": (nm.NM_BF16, torch.bfloat16),
+                 "f8": (nm.NM_F8E4M3, torch.float8_e4m3fn)}[dtype]
+    rng = np.random.default_rng(17)
+    wp = nm.nm_prune(rng.standard_normal((cout, k, k, cin), dtype=np.float32) * np.float32(0.05), *nm_, 16, code)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    x = torch.rand((batch, size, size, cin), generator=g, device="cuda").to(tdt)
+    ho = (size + 2 * pad - k) // stride + 1
+    ydt = torch.float32 if dtype == "f32" else torch.bfloat16
+    res = torch.rand((batch, ho, ho, cout), generator=g, device="cuda").to(ydt) if residual else None
+    bias = torch.rand(cout, generator=g, device="cuda")
+    half = batch // 2
+    names = [nm.nm_variant_name(v) for v in range(nm.nm_variant_count())]
+    ran = 0
+    try:
+        for want in variants:
+            picks = [i for i, n in enumerate(names) if want and n.startswith(want) and nm.nm_variant_legal(i, wp, code, nm.NM_F32 if dtype == "f32" else nm.NM_BF16)]
+            picks += [i for i, n in enumerate(names) if n == want and "_TAPS_" in n]   # (whether these run is decided by the call)
+            if want and not picks:
+                continue
+            nm.nm_force_variant(picks[0] if want else -1)
+            say(f"stream out {dtype} {batch}x{size}x{size}x{cin} -> {cout} {want}")
+            y = nm.nm_conv2d_res(x, wp, res, bias, stride, pad, 1, True)
+            nm.nm_force_variant(nm.nm_last_variant())
+            for lo, hi in ((0, half), (half, batch)):
+                part = nm.nm_conv2d_res(x[lo:hi].contiguous(), wp, None if res is None else res[lo:hi].contiguous(), bias, stride, pad, 1, True)
+                assert torch.equal(part, y[lo:hi]), (want, lo)
+            torch.cuda.synchronize()
+            nm.nm_force_variant(-1)
+            ran += 1
+    finally:
+        nm.nm_force_variant(-1)
+    assert ran
