@@ -31,7 +31,7 @@ PEAK_HBM_GBS = 8000.0
 # the kernel behind a variant's name, by the name's first part (longest match)
 KERNELS = {"NB": "nm_conv_kernel", "VAR": "nm_conv_kernel", "B16": "nm_conv_bf16_kernel", "SP": "nm_conv_sp16_kernel",
            "RUN": "nm_conv_run16_kernel", "RUN_ROWS": "nm_conv_rows_kernel", "ROWF": "nm_conv_rows_kernel",
-           "SPR1_TAPS": "nm_conv_taps_kernel", "SPR0_TAPS": "nm_conv_taps_kernel",
+           "SPR1_TAP": "nm_conv_taps_kernel", "SPR0_TAP": "nm_conv_taps_kernel",
            "X3S": "nm_conv_split_kernel", "X3D": "nm_conv_split_kernel", "KW": "nm_conv_wave_kernel", "F8": "nm_conv_f8_kernel",
            "F8S": "nm_conv_sp16_kernel", "F8W": "nm_conv_sp16_kernel", "F8R": "nm_conv_sp16_kernel"}
 
@@ -254,7 +254,7 @@ def stack_roofline(st, ms_step, rows, headline, floor_ms=None):
         roofline = {"bound": "mfma", "achieved": eff / ms_step / 1e9, "peak": eff / t_flop / 1e9,
                     "unit": "TFLOP/s", "frac": t_flop / ms_step}
     traffic, source = profiled_traffic(st.dtype) if headline else (None, None)
-    families = sorted({"_".join((r["variant"] or "?").split("_")[:2 if "_TAPS_" in (r["variant"] or "") else 1]) for r in rows})
+    families = sorted({"_".join((r["variant"] or "?").split("_")[:2 if "_TAP" in (r["variant"] or "") else 1]) for r in rows})
     share = {}
     for r in rows:
         share[kernel_of(r["variant"])] = share.get(kernel_of(r["variant"]), 0.0) + r["ms"]

@@ -117,10 +117,10 @@ def _shapes_split(name):
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
 
 
-def _shapes_taps(sparse):
-    """(NBLK, WP, NJ) of NMTAPS1_SHAPES or NMTAPS0_SHAPES in nm_variants.h."""
+def _shapes_taps(name):
+    """(NBLK, WP, NJ) of NMTAPS1_SHAPES, NMTAPS0_SHAPES, NMTAPSW1_SHAPES or NMTAPSW0_SHAPES in nm_variants.h."""
     text = open(os.path.join(CSRC, "nm_variants.h")).read()
-    body = text[text.index(f"#define NMTAPS{sparse}_SHAPES(X)") + 25:]
+    body = text[text.index(f"#define {name}(X)") + len(name) + 11:]
     body = body[:body.index("\n")]
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
 
@@ -177,11 +177,11 @@ def _jobs():
     for pl in (1, 3):
         jobs.append((instrows, os.path.join(OBJDIR, f"nm_conv_rows_inst_{pl}.o"), [f"-DNM_INST_PL={pl}"]))
     insttaps = os.path.join(CSRC, "nm_conv_taps_inst.hip")
-    for sparse in (1, 0):
-        for nb, wp, nj in _shapes_taps(sparse):
-            jobs.append((insttaps, os.path.join(OBJDIR, f"nm_conv_taps_inst_{sparse}_{nb}_{wp}_{nj}.o"),
+    for name, sparse, nw in (("NMTAPS1_SHAPES", 1, 4), ("NMTAPS0_SHAPES", 0, 4), ("NMTAPSW1_SHAPES", 1, 8), ("NMTAPSW0_SHAPES", 0, 8)):
+        for nb, wp, nj in _shapes_taps(name):
+            jobs.append((insttaps, os.path.join(OBJDIR, f"nm_conv_taps_inst_{sparse}_{nb}_{wp}_{nj}_{nw}.o"),
                          [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}",
-                          f"-DNM_INST_SPARSE={sparse}"]))
+                          f"-DNM_INST_SPARSE={sparse}", f"-DNM_INST_NW={nw}"]))
     instwave = os.path.join(CSRC, "nm_conv_wave_inst.hip")
     for pb, nj in _shapes_wave():
         jobs.append((instwave, os.path.join(OBJDIR, f"nm_conv_wave_inst_{pb}_{nj}.o"),

@@ -110,6 +110,8 @@ inline bool is_split_kind(int kind) { return kind == 8 || kind == 9; }
 inline bool is_rows_kind(int kind) { return kind == 10 || kind == 11; }
 // kinds 13 (sparse instruction) and 14 (dense): bf16, a tile's input staged once for all taps
 inline bool is_taps_kind(int kind) { return kind == 13 || kind == 14; }
+// wavefronts of a workgroup along the output channels
+inline int channel_waves(const VariantDesc& d) { return (is_taps_kind(d.kind) && d.waves == 8 ? 8 : 4) / d.WP; }
 // kinds whose row blocks are 16 consecutive output channels, whatever the column tile
 inline bool flat_rowblocks(int kind) { return is_split_kind(kind) || is_rows_kind(kind); }
 
@@ -147,7 +149,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
     // the epilogue's output tile [BP][channels of the workgroup] plus 16 bytes per pixel
     const size_t otile = (size_t)d.BP * ((size_t)(4 / d.WP) * d.NJ * 16 * (d.kind == 0 || d.kind == 5 ? 4 : 2) + 16);
     if (is_split_kind(d.kind)) return (size_t)split_lds_bytes(d.NBLK, d.WP, d.NJ);
-    if (is_taps_kind(d.kind)) return taps_lds_bytes(d.NBLK, d.WP, d.NJ, 9 * d.BP, 1);   // and what depends on the image
+    if (is_taps_kind(d.kind)) return taps_lds_bytes(d.NBLK, d.WP, d.NJ, 9 * d.BP, 1, channel_waves(d) * d.WP);   // and what depends on the image
     if (d.kind == 12) return (size_t)wave_lds_bytes(d.NBLK, d.NJ, d.CK, d.waves);
     if (is_rows_kind(d.kind)) return kRowsPieces;   // and the staged rows, which depend on the image (rows_layout)
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
@@ -253,7 +255,8 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
         const double lines = (ra->b + 2.0) * ((double)ra->h + ra->ph);
         if (lines >= 16777216.0 || lines * taps_line(ra->w, ra->pw) >= 2147483648.0) return false;
         const long granules = taps_granules(d.BP, ra->h, ra->w, ra->ph, ra->pw);
-        if (taps_lds_bytes(d.NBLK, d.WP, d.NJ, granules, wp->cin / 64) > (size_t)kMaxLdsBytes) return false;
+        if (taps_lds_bytes(d.NBLK, d.WP, d.NJ, granules, wp->cin / 64, channel_waves(d) * d.WP) > (size_t)kMaxLdsBytes) return false;
+        if (d.waves == 8 && taps_loads(granules) > 8 * kTapsWideLoads) return false;
     }
     if (d.ksplit > 1) {
         // every split must own at least one chunk of the K axis
@@ -447,7 +450,7 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     }
     p.idx = wp->d_idx; p.vals = wp->d_vals; p.kprime = wp->kprime; p.ctile = wp->tile;
     p.redo_below = wp->redo_below;
-    const int rb_per_wg = (4 / d.WP) * d.NJ;
+    const int rb_per_wg = channel_waves(d) * d.NJ;
     p.n_ptiles = (g.P + d.BP - 1) / d.BP;
     p.n_cblocks = (p.n_rowblocks + rb_per_wg - 1) / rb_per_wg;
     p.oscale = 1.0f / wp->scale;
@@ -565,25 +568,34 @@ int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
 }
 
 // The tap-staged form of a bf16 layer that runs without tuning, -1 where the others do it: the cheapest by rounds of
-// workgroups (one a CU) x (12 000 clocks of start and output + 1.2 x the matrix instructions of its chunks), where that
+// workgroups (one a CU) x (12 000 clocks of start and output + 1.2 x the matrix instructions of its chunks; 11 000 and 1.14
+// with eight contracting wavefronts), where that
 // gives at least 176 CUs a workgroup of 224 pixels or more (224 CUs one of 160), more than half of its channels exist and
 // the launch is not a round and less than 0.4 of a second one.  Of 600 random 3x3 layers, sparse instruction, tensors out of
 // cache, the 393 within that take x0.58 to x1.00 of the time that the rule below gives them, x0.82 on average; where just
-// half of the channels exist (128 of 256) it would be x1.26 to x1.35, at 1.16 rounds x1.11.  (The dense instruction keeps
-// the matrix cores busy without it: x0.93 at best, x1.2 on most.)
+// half of the channels exist (128 of 256) it would be x1.26 to x1.35, at 1.16 rounds x1.11.  Eight wavefronts: of 220 such
+// layers the 82 that go from a form of four to one of eight take x0.73 to x1.07 of its time, x0.85 on average.
+// The dense instruction (layers that the sparse one does not do): the forms of eight wavefronts alone, from 150 workgroups on
+// and with two thirds of their channels in existence.  67 of 100 random layers are within that and take x0.73 to x1.05 of the
+// time that the rule below gives them, x0.83 on average; at 128 to 150 workgroups it would be up to x1.32.  (Four wavefronts:
+// x0.93 at best, x1.2 on most.)
 int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
 {
     int pick = -1;
     double best = 0;
+    const bool sparse = kinds_of(wp) >> 2 & 1u;
     for (int v : base_variants()) {
         const VariantDesc& d = variant_desc(v);
-        const int channels = (4 / d.WP) * d.NJ * 16;
-        if (d.kind != 13 || d.NBLK < 5 || !variant_legal(v, wp, xdt, ra)) continue;
+        const int channels = channel_waves(d) * d.NJ * 16;
+        const bool wide = d.waves == 8;
+        if (d.kind != (sparse ? 13 : 14) || d.NBLK < 5 || (!sparse && !wide) || !variant_legal(v, wp, xdt, ra)) continue;
         const long n_cb = (wp->cout + channels - 1) / channels, n_wg = (long)((P + d.BP - 1) / d.BP) * n_cb;
         if (2L * wp->cout <= n_cb * channels || (channels > 64 && wp->cout <= 64)) continue;
-        if (n_wg < (d.NBLK < 7 ? 224 : 176) || (n_wg > kNumCU && 5L * n_wg < 7L * kNumCU)) continue;
+        if (!sparse && 3L * wp->cout < 2L * n_cb * channels) continue;
+        if (n_wg < (!sparse ? 150 : d.NBLK < 7 ? 224 : 176) || (n_wg > kNumCU && 5L * n_wg < 7L * kNumCU)) continue;
         const double rounds = (double)((n_wg + kNumCU - 1) / kNumCU);
-        const double cost = rounds * (12000.0 + 1.2 * 16 * d.NBLK * d.NJ * (wp->K / 64));
+        const double clocks = (sparse ? 16.0 : 32.0) * d.NBLK * d.NJ * (wp->K / 64);   // of a wavefront's matrix instructions
+        const double cost = rounds * (wide ? 11000.0 + 1.14 * 2 * clocks : 12000.0 + 1.2 * clocks);
         if (pick < 0 || cost < best) {
             pick = v;
             best = cost;
@@ -677,7 +689,7 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
         const int v = split_default(wp, P, xdt, ra);
         if (v >= 0) return v;
     }
-    if (ra && (kinds & (1u << 2))) {
+    if (ra && (kinds & (1u << 2 | 1u << 3))) {
         const int v = taps_default(wp, P, xdt, ra);
         if (v >= 0) return v;
     }

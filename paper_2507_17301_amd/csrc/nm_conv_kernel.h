@@ -135,14 +135,14 @@ __device__ inline void tile_put4(const ConvParams& p, char* dst, unsigned goff, 
 }
 // the tile [BP][WGC] (first pixel p0, first channel co0) from LDS to the NHWC output: a thread
 // keeps its 16-byte column and walks down the rows, so one compare and one add per store
-template <typename TOUT, int BP, int WGC>
+template <typename TOUT, int BP, int WGC, int THREADS = 256>
 __device__ inline void tile_flush(const ConvParams& p, const char* tile, int p0, int co0)
 {
     constexpr int CPG = 16 / (int)sizeof(TOUT);      // channels per 16-byte granule
     constexpr int GPR = WGC / CPG;                   // granules per pixel
     constexpr int PITCH = tile_pitch<TOUT>(WGC);
-    static_assert(GPR <= 256 && 256 % GPR == 0, "a row's granules divide the workgroup");
-    constexpr int RSTEP = 256 / GPR;                 // rows covered by one pass of the workgroup
+    static_assert(GPR <= THREADS && THREADS % GPR == 0, "a row's granules divide the workgroup");
+    constexpr int RSTEP = THREADS / GPR;             // rows covered by one pass of the workgroup
     constexpr int NG = (BP + RSTEP - 1) / RSTEP;
     const int r0 = (int)threadIdx.x / GPR, cg = (int)threadIdx.x % GPR;
     const int co = co0 + cg * CPG;
@@ -169,13 +169,13 @@ __device__ inline void tile_flush(const ConvParams& p, const char* tile, int p0,
     else rows(std::false_type());
 }
 
-// The residual of a tile, fetched as the tile is written: whole rows, 16 bytes per lane, by 256 threads
+// The residual of a tile, fetched as the tile is written: whole rows, 16 bytes per lane, by THREADS threads
 // (`t`), into the places where tile_put4_lds() picks it up.  Read straight into the accumulator layout it
 // comes in 32-byte pieces (bf16).  ResNet-50 in bf16, batch 64, before and after: 56x56 64 -> 256 53 and 43 us
 // (231 MB), 28x28 128 -> 512 34.9 and 27.5, 14x14 256 -> 1024 24.8 and 22.2, 7x7 512 -> 2048 20.6 and 18.8.
-template <typename TOUT, int BP, int WGC> struct ResTile {
+template <typename TOUT, int BP, int WGC, int THREADS = 256> struct ResTile {
     static constexpr int CPG = 16 / (int)sizeof(TOUT), GPR = WGC / CPG, PITCH = tile_pitch<TOUT>(WGC);
-    static constexpr int RSTEP = 256 / GPR, NG = (BP + RSTEP - 1) / RSTEP;
+    static constexpr int RSTEP = THREADS / GPR, NG = (BP + RSTEP - 1) / RSTEP;
     u4v v[NG];
     __device__ inline void load(const ConvParams& p, int t, int p0, int co0)
     {

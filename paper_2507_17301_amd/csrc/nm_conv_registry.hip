@@ -44,9 +44,13 @@ struct Entry {
 
 // kinds 13 (sparse instruction) and 14 (dense): a tile's input staged once for all taps
 #define NM_ENTRYTAPS1(NB, WP, NJ) \
-    {{"SPR1_TAPS_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 13, 1, 1, 1, 1}, nullptr, &launch_taps_t<NB, WP, NJ, true>},
+    {{"SPR1_TAPS_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 13, 1, 1, 1, 1}, nullptr, &launch_taps_t<NB, WP, NJ, true, 4>},
 #define NM_ENTRYTAPS0(NB, WP, NJ) \
-    {{"SPR0_TAPS_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 14, 1, 1, 1, 1}, nullptr, &launch_taps_t<NB, WP, NJ, false>},
+    {{"SPR0_TAPS_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 14, 1, 1, 1, 1}, nullptr, &launch_taps_t<NB, WP, NJ, false, 4>},
+#define NM_ENTRYTAPSW1(NB, WP, NJ) \
+    {{"SPR1_TAP8_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 13, 1, 1, 1, 1, 8}, nullptr, &launch_taps_t<NB, WP, NJ, true, 8>},
+#define NM_ENTRYTAPSW0(NB, WP, NJ) \
+    {{"SPR0_TAP8_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 14, 1, 1, 1, 1, 8}, nullptr, &launch_taps_t<NB, WP, NJ, false, 8>},
 
 // kind 4: contiguous kernel-row runs
 #define NM_ENTRYRUN(NB, WP, NJ, KS)                                                             \
@@ -98,7 +102,7 @@ const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTR
                           NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)
                           NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)
                           NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF) NMWAVE_SHAPES(NM_SHAPE_ENTRIESWAVE)
-                          NMTAPS1_SHAPES(NM_ENTRYTAPS1) NMTAPS0_SHAPES(NM_ENTRYTAPS0)};
+                          NMTAPS1_SHAPES(NM_ENTRYTAPS1) NMTAPS0_SHAPES(NM_ENTRYTAPS0) NMTAPSW1_SHAPES(NM_ENTRYTAPSW1) NMTAPSW0_SHAPES(NM_ENTRYTAPSW0)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
 // The fp32 kernels also run with their K axis split over several workgroups per output

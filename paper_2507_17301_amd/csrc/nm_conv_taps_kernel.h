@@ -31,13 +31,21 @@
 //
 // Four wavefronts contract; a fifth fills the other stage meanwhile.  (One is enough for a stage every nine taps.  Of the
 // smallest form, 64 x 128 on 104 registers, two workgroups fit a CU; the others take 172 to 230 and have it to themselves.)
+// Or eight contract, two a SIMD, so that one issues while the other's matrix instruction runs, on twice the channels (or half
+// of each wavefront's), and each requests an eighth of the next stage as it leaves the last one, which costs it a register
+// per request and no wavefront that registers would have to be left for.  One tile of 224 x 256 replaces two of 224 x 128 and
+// stages its input once.  Batch 256, T = 32, out of cache: 14x14 256 -> 256 2:8 38.2 -> 31.8 us (224 workgroups in one round for
+// 448 in two), 7x7 512 -> 512 4:8 (dense, 224 x 128) 50.9 -> 48.2.  Of 34.5 us (another card) 31.4 are left without the loads of
+// the weights, 32.5 without the strip reads, 29.1 without either: 13.4 of matrix instructions and what one round cannot hide,
+// the launch, the first stage and the output.  A longer ring of strip reads (4 to 6 blocks) gains nothing.
 #pragma once
 
 #include "nm_conv_sp16_kernel.h"
 
 namespace nm {
 
-constexpr int kTapsThreads = 320;
+// four contracting wavefronts and the one that fetches, or eight that do both
+constexpr int taps_threads(int NW) { return NW == 4 ? 320 : 512; }
 
 // keeps what is computed from (into) these scalars behind (before) this place
 template <typename... T> __device__ inline __attribute__((always_inline)) void taps_pin(T&... v)
@@ -63,12 +71,14 @@ template <int U, typename F> __device__ inline __attribute__((always_inline)) vo
     while (!taps_round<U>(n, step)) {}
 }
 
-template <int NBLK, int WP, int NJ, bool SPARSE>
-__global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv_taps_kernel(const ConvParams p)
+template <int NBLK, int WP, int NJ, bool SPARSE, int NW>
+__global__ __launch_bounds__(taps_threads(NW), NW == 4 && NBLK * NJ <= 16 ? 3 : 2) void nm_conv_taps_kernel(const ConvParams p)
 {
+    static_assert((NW == 4 || NW == 8) && NW % WP == 0, "contracting wavefronts");
+    constexpr bool WIDE = NW == 8;
     constexpr int BPW = 16 * NBLK;
     constexpr int BP = BPW * WP;
-    constexpr int WC = 4 / WP;
+    constexpr int WC = NW / WP;
     constexpr int AH = SPARSE ? 1 : 2;           // 16-byte A operands per k-step and row block
     constexpr int WGC = WC * NJ * 16;            // output channels of the workgroup
 
@@ -76,7 +86,7 @@ __global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // 4: the producer
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (of five: 4 is the producer)
     const int q = lane >> 4;
     const int n = lane & 15;
 
@@ -114,39 +124,58 @@ __global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv
         char* dst = lds8 + (cc & 1) * p.rows_lds + i * 1024;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_ptr_t)dst, 16, off, cc * 128, 0, 0);
     };
-    // The first stage is fetched by all five wavefronts, four loads at a time so that their address arithmetic overlaps
-    // (past the last load it is repeated); the offsets are left in LDS for the stages that follow, which the producer fetches
-    unsigned* const offs = reinterpret_cast<unsigned*>(lds8 + (p.ncpt > 1 ? 2 : 1) * p.rows_lds) + lane;
-    for (int i0 = wave; i0 < nload; i0 += 20) {
-        unsigned off[4];
+    // Eight wavefronts: each issues every eighth load of every stage, whose offsets it keeps.
+    unsigned woff[WIDE ? kTapsWideLoads : 1];
+    auto fetch_own = [&](int cc) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) off[k] = offset(min(i0 + 5 * k, nload - 1));
+        for (int k = 0; k < (WIDE ? kTapsWideLoads : 1); ++k)
+            if (wave + 8 * k < nload) fetch(wave + 8 * k, woff[k], cc);
+    };
+    if constexpr (WIDE) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int i = min(i0 + 5 * k, nload - 1);
-            fetch(i, off[k], 0);
-            if (p.ncpt > 1) offs[i * 64] = off[k];
+        for (int k0 = 0; k0 < kTapsWideLoads; k0 += 4) {
+            if (wave + 8 * k0 >= nload) break;
+#pragma unroll
+            for (int k = k0; k < k0 + 4; ++k) woff[k] = offset(min(wave + 8 * k, nload - 1));
+#pragma unroll
+            for (int k = k0; k < k0 + 4; ++k)
+                if (wave + 8 * k < nload) fetch(wave + 8 * k, woff[k], 0);
         }
-    }
-
-    if (wave == 4) {
-        for (int cc = 0; cc < p.ncpt; ++cc) {
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // stage cc is there
-            if (cc > 0) asm volatile("s_barrier" ::: "memory");                        // stage cc - 1 has been read
-            if (cc + 1 == p.ncpt) break;
-            for (int i0 = 0; i0 < nload; i0 += 8) {
-                unsigned off[8];
+    } else {
+        // The first stage is fetched by all five wavefronts, four loads at a time so that their address arithmetic overlaps
+        // (past the last load it is repeated); the offsets are left in LDS for the stages that follow, which the producer fetches
+        unsigned* const offs = reinterpret_cast<unsigned*>(lds8 + (p.ncpt > 1 ? 2 : 1) * p.rows_lds) + lane;
+        for (int i0 = wave; i0 < nload; i0 += 20) {
+            unsigned off[4];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) off[k] = offs[min(i0 + k, nload - 1) * 64];
+            for (int k = 0; k < 4; ++k) off[k] = offset(min(i0 + 5 * k, nload - 1));
 #pragma unroll
-                for (int k = 0; k < 8; ++k) fetch(min(i0 + k, nload - 1), off[k], cc + 1);
+            for (int k = 0; k < 4; ++k) {
+                const int i = min(i0 + 5 * k, nload - 1);
+                fetch(i, off[k], 0);
+                if (p.ncpt > 1) offs[i * 64] = off[k];
             }
         }
-        // the barriers of the epilogue
-        __syncthreads();
-        if (p.res) __syncthreads();
-        __syncthreads();
-        return;
+
+        if (wave == 4) {
+            for (int cc = 0; cc < p.ncpt; ++cc) {
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // stage cc is there
+                if (cc > 0) asm volatile("s_barrier" ::: "memory");                        // stage cc - 1 has been read
+                if (cc + 1 == p.ncpt) break;
+                for (int i0 = 0; i0 < nload; i0 += 8) {
+                    unsigned off[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) off[k] = offs[min(i0 + k, nload - 1) * 64];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) fetch(min(i0 + k, nload - 1), off[k], cc + 1);
+                }
+            }
+            // the barriers of the epilogue
+            __syncthreads();
+            if (p.res) __syncthreads();
+            __syncthreads();
+            return;
+        }
     }
 
     const int wpx = wave % WP, wcx = wave / WP;
@@ -274,15 +303,18 @@ __global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv
         const int stage = cross;
         const unsigned next = there;
         const int fc = f_chunk;
-        if (__builtin_expect(stage, 0)) asm volatile("s_barrier" ::: "memory");   // the next stage is there
+        // the next stage is there (of these eight: all but the last chunk's loads of weights are older than that)
+        if (__builtin_expect(stage, 0)) {
+            if constexpr (WIDE) NM_WAIT_VMCNT(NJ * AH + (SPARSE ? 1 : 0));
+            asm volatile("s_barrier" ::: "memory");
+        }
 #pragma unroll
         for (int b = 0; b < NBLK; ++b) {
             constexpr int first = (u * NBLK) % RD;
             const int nb = b + RD - 1;
             const unsigned addr = base[nb % NBLK] + (nb < NBLK ? here : next);
             u4v(&bo)[2] = ring[(first + b) % RD];
-            if constexpr (RD == 4) asm volatile("s_waitcnt lgkmcnt(4)" : "+v"(bo[0]), "+v"(bo[1]));
-            else asm volatile("s_waitcnt lgkmcnt(2)" : "+v"(bo[0]), "+v"(bo[1]));
+            asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(bo[0]), "+v"(bo[1]) : "n"(2 * (RD - 2)));
 #pragma unroll
             for (int jj = 0; jj < NJ; ++jj) {
                 if constexpr (SPARSE) {
@@ -319,11 +351,21 @@ __global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (__builtin_expect(stage, 0)) asm volatile("s_barrier" ::: "memory");   // the last stage has been read
+        if (__builtin_expect(stage, 0)) {
+            asm volatile("s_barrier" ::: "memory");   // the last stage has been read
+            if constexpr (WIDE) {
+                if (g_cc + 1 < p.ncpt) fetch_own(g_cc + 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
         here = next;
         spread(ops[(u + 1) % NSET].idx);
     };
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the first stage and the offsets are there
+    if constexpr (WIDE) {
+        if (p.ncpt > 1) fetch_own(1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int b = 0; b < RD - 1; ++b) {
         read_lo(base[b], ring[b]);
@@ -336,7 +378,7 @@ __global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv
 
     // ---- epilogue: whole 128-byte lines through an LDS tile, once every wavefront is past its last strip read ------
     constexpr int PITCH = tile_pitch<bf16_t>(WGC);
-    ResTile<bf16_t, BP, WGC> rt;
+    ResTile<bf16_t, BP, WGC, 64 * NW> rt;
     if (p.res) rt.load(p, tid, p0, cblock * WGC);
     __syncthreads();
     if (p.res) {
@@ -349,24 +391,24 @@ __global__ __launch_bounds__(kTapsThreads, NBLK * NJ <= 16 ? 3 : 2) void nm_conv
         for (int b = 0; b < NBLK; ++b)
             tile_put4_lds<bf16_t>(p, lds8 + (wpix + b * 16 + n) * PITCH + ((wcx * NJ + jj) * 16 + q * 4) * 2, acc[jj][b]);
     __syncthreads();
-    tile_flush<bf16_t, BP, WGC>(p, lds8, p0, cblock * WGC);
+    tile_flush<bf16_t, BP, WGC, 64 * NW>(p, lds8, p0, cblock * WGC);
 }
 
-template <int NBLK, int WP, int NJ, bool SPARSE>
+template <int NBLK, int WP, int NJ, bool SPARSE, int NW>
 int launch_taps_t(const ConvParams& p, hipStream_t s)
 {
-    auto kern = nm_conv_taps_kernel<NBLK, WP, NJ, SPARSE>;
+    auto kern = nm_conv_taps_kernel<NBLK, WP, NJ, SPARSE, NW>;
     constexpr size_t most = 160 * 1024;
     static unsigned long long done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(kern), most, &done);
     if (rc != NM_OK) return rc;
-    const size_t lds = taps_lds_bytes(NBLK, WP, NJ, p.rows_n, p.ncpt);
+    const size_t lds = taps_lds_bytes(NBLK, WP, NJ, p.rows_n, p.ncpt, NW);
     if (lds > most || p.tile % 16 != 0 || p.Cout % 8 != 0 || p.Cin % 64 != 0 || p.sh != 1 || p.sw != 1 || p.Ho != p.H ||
-        p.Wo != p.W) {
+        p.Wo != p.W || (NW == 8 && taps_loads(p.rows_n) > 8 * kTapsWideLoads)) {
         set_error("internal: a layer that the tap-staged kernel does not do");
         return NM_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL(kern, dim3(p.wg_per_xcd * 8), dim3(kTapsThreads), lds, s, p);
+    hipLaunchKernelGGL(kern, dim3(p.wg_per_xcd * 8), dim3(taps_threads(NW)), lds, s, p);
     NM_HIP_CHECK(hipGetLastError());
     return NM_OK;
 }

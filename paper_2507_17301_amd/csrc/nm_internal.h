@@ -168,10 +168,12 @@ constexpr TapsSource taps_source(unsigned t, unsigned line_g, unsigned line_mul,
     return TapsSource{live ? (int)pixel : -1, oct};
 }
 constexpr int taps_loads(long granules) { return (int)((granules + 63) / 64); }
+// eight contracting wavefronts: loads of a stage that one of them fetches, whose offsets it holds in registers
+constexpr int kTapsWideLoads = 8;
 // two stages and the loads' offsets (one stage where there is one), or the output tile
-constexpr size_t taps_lds_bytes(int NBLK, int WP, int NJ, long granules, int ncpt)
+constexpr size_t taps_lds_bytes(int NBLK, int WP, int NJ, long granules, int ncpt, int waves = 4)
 {
-    const size_t strip = (size_t)taps_loads(granules) * (ncpt > 1 ? 2 * 1024 + 256 : 1024), out = (size_t)16 * NBLK * WP * ((4 / WP) * NJ * 32 + 16);
+    const size_t strip = (size_t)taps_loads(granules) * (ncpt > 1 ? 2 * 1024 + 256 : 1024), out = (size_t)16 * NBLK * WP * ((waves / WP) * NJ * 32 + 16);
     return strip > out ? strip : out;
 }
 
@@ -273,7 +275,7 @@ struct VariantDesc {
     int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)
     int areg;  // kinds 2, 3, 7: 1 = weights and index words go straight to registers, the LDS stages hold the strip alone
     int spec;  // kinds 2, 3, 7: 1 = four producer wavefronts issue the loads (512 threads)
-    int waves; // kind 12: most wavefronts the K axis is dealt out over
+    int waves; // kind 12: most wavefronts the K axis is dealt out over; kinds 13, 14: 8 = eight contracting wavefronts, else four
 };
 
 // Allows kernel `fn` more than 64 KB of dynamic LDS on the current device; done once per

@@ -81,6 +81,9 @@
 // X(NBLK, WP, NJ)
 #define NMTAPS1_SHAPES(X) X(4, 1, 2) X(5, 2, 4) X(7, 2, 4) X(8, 2, 4) X(8, 1, 4) X(7, 4, 4) X(8, 4, 4)
 #define NMTAPS0_SHAPES(X) X(5, 2, 4) X(7, 2, 4) X(7, 4, 4)
+// the same with eight contracting wavefronts (512 x 64, 320 x 128, 128 x 256 and, dense, 256 x 128 were first on no layer)
+#define NMTAPSW1_SHAPES(X) X(7, 2, 4) X(8, 2, 4)
+#define NMTAPSW0_SHAPES(X) X(7, 2, 4) X(7, 2, 2)
 
 // bf16 kernel for layers with very few input channels (contiguous kernel-row
 // runs, one chunk of KS 64-element k-steps): where output pixels are not whole
