@@ -125,6 +125,14 @@ def _shapes_taps(name):
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+)\)", body)]
 
 
+def _shapes_split_taps(name):
+    """(NBLK, WP, NJ, KG) of NMST1_SHAPES or NMST0_SHAPES in nm_variants.h."""
+    text = open(os.path.join(CSRC, "nm_variants.h")).read()
+    body = text[text.index(f"#define {name}(X)") + len(name) + 11:]
+    body = body[:body.index("\n")]
+    return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+),\s*(\d+)\)", body)]
+
+
 def _shapes_wave():
     """(PB, NJ) of NMWAVE_SHAPES in nm_variants.h."""
     text = open(os.path.join(CSRC, "nm_variants.h")).read()
@@ -182,6 +190,12 @@ def _jobs():
             jobs.append((insttaps, os.path.join(OBJDIR, f"nm_conv_taps_inst_{sparse}_{nb}_{wp}_{nj}_{nw}.o"),
                          [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}",
                           f"-DNM_INST_SPARSE={sparse}", f"-DNM_INST_NW={nw}"]))
+    instst = os.path.join(CSRC, "nm_conv_split_taps_inst.hip")
+    for name, sparse in (("NMST1_SHAPES", 1), ("NMST0_SHAPES", 0)):
+        for nb, wp, nj, kg in _shapes_split_taps(name):
+            jobs.append((instst, os.path.join(OBJDIR, f"nm_conv_split_taps_inst_{sparse}_{nb}_{wp}_{nj}_{kg}.o"),
+                         [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}", f"-DNM_INST_KG={kg}",
+                          f"-DNM_INST_SPARSE={sparse}"]))
     instwave = os.path.join(CSRC, "nm_conv_wave_inst.hip")
     for pb, nj in _shapes_wave():
         jobs.append((instwave, os.path.join(OBJDIR, f"nm_conv_wave_inst_{pb}_{nj}.o"),

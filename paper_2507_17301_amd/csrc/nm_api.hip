@@ -110,10 +110,16 @@ inline bool is_split_kind(int kind) { return kind == 8 || kind == 9; }
 inline bool is_rows_kind(int kind) { return kind == 10 || kind == 11; }
 // kinds 13 (sparse instruction) and 14 (dense): bf16, a tile's input staged once for all taps
 inline bool is_taps_kind(int kind) { return kind == 13 || kind == 14; }
+// kinds 15 and 16: the three planes of 8 and 9, a tile's input staged once for all taps
+inline bool is_split_taps_kind(int kind) { return kind == 15 || kind == 16; }
 // wavefronts of a workgroup along the output channels
-inline int channel_waves(const VariantDesc& d) { return (is_taps_kind(d.kind) && d.waves == 8 ? 8 : 4) / d.WP; }
+inline int channel_waves(const VariantDesc& d)
+{
+    if (is_split_taps_kind(d.kind)) return 8 / d.waves / d.WP;
+    return (is_taps_kind(d.kind) && d.waves == 8 ? 8 : 4) / d.WP;
+}
 // kinds whose row blocks are 16 consecutive output channels, whatever the column tile
-inline bool flat_rowblocks(int kind) { return is_split_kind(kind) || is_rows_kind(kind); }
+inline bool flat_rowblocks(int kind) { return is_split_kind(kind) || is_rows_kind(kind) || is_split_taps_kind(kind); }
 
 // Which variants may run a layer depends on its weights, not only on its shape: the
 // k-steps per chunk its kept sets need (groups wider than a chunk spread unevenly) and
@@ -150,6 +156,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
     const size_t otile = (size_t)d.BP * ((size_t)(4 / d.WP) * d.NJ * 16 * (d.kind == 0 || d.kind == 5 ? 4 : 2) + 16);
     if (is_split_kind(d.kind)) return (size_t)split_lds_bytes(d.NBLK, d.WP, d.NJ);
     if (is_taps_kind(d.kind)) return taps_lds_bytes(d.NBLK, d.WP, d.NJ, 9 * d.BP, 1, channel_waves(d) * d.WP);   // and what depends on the image
+    if (is_split_taps_kind(d.kind)) return split_taps_lds_bytes(d.NBLK, d.NJ, d.waves, 9 * d.BP, 1);
     if (d.kind == 12) return (size_t)wave_lds_bytes(d.NBLK, d.NJ, d.CK, d.waves);
     if (is_rows_kind(d.kind)) return kRowsPieces;   // and the staged rows, which depend on the image (rows_layout)
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
@@ -213,8 +220,8 @@ int run_ksteps(const nm_packed* wp, int par)
     return (wp->kh * gr + 7) / 8;
 }
 
-// kind 12 reads the tables of kind 0, kinds 13 and 14 those of 2 and 3
-inline int table_kind(int kind) { return kind == 12 ? 0 : is_taps_kind(kind) ? kind - 11 : kind; }
+// kind 12 reads the tables of kind 0, kinds 13 and 14 those of 2 and 3, kinds 15 and 16 those of 8 and 9
+inline int table_kind(int kind) { return kind == 12 ? 0 : is_taps_kind(kind) ? kind - 11 : is_split_taps_kind(kind) ? kind - 7 : kind; }
 
 const Prepack* find_prepack(const nm_packed* wp, const VariantDesc& d, int par = -1)
 {
@@ -235,7 +242,7 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     if (v < 0 || v >= variant_count()) return false;
     const VariantDesc& d = variant_desc(v);
     if (lds_bytes(d, wp) > (size_t)kMaxLdsBytes) return false;
-    if ((d.kind == 5 || d.kind == 11 || d.kind == 12 || is_split_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
+    if ((d.kind == 5 || d.kind == 11 || d.kind == 12 || is_split_kind(d.kind) || is_split_taps_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
     // fp8: E4M3 tensors with an E4M3 handle run the fp8 kernels and nothing else does
     if (is_f8_kind(d.kind) != (xdt == NM_F8E4M3) || is_f8_kind(d.kind) != (wp->value_dtype == NM_F8E4M3)) return false;
     if ((d.kind >= 1 && d.kind <= 4) || d.kind == 10 || is_taps_kind(d.kind)) {
@@ -245,18 +252,22 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
         if (d.share != 1 && d.share != wp->rbpt) return false;
     }
     if (is_rows_kind(d.kind) && wp->cout % (d.kind == 10 ? 8 : 4) != 0) return false;   // whole 16-byte output granules
-    if (is_taps_kind(d.kind)) {
+    if (is_taps_kind(d.kind) || is_split_taps_kind(d.kind)) {
         // an output as large as the input, so that a tap is one shift of the whole tile; whole 16-byte output granules
         if (!ra || ra->sh != 1 || ra->sw != 1 || wp->kh * wp->kw < 2 || wp->kh * wp->kw > 32) return false;
         if (2L * ra->ph != (long)ra->dh * (wp->kh - 1) || 2L * ra->pw != (long)ra->dw * (wp->kw - 1)) return false;
-        if (wp->tile % 16 != 0 || wp->cout % 8 != 0) return false;
+        if (is_taps_kind(d.kind) && (wp->tile % 16 != 0 || wp->cout % 8 != 0)) return false;
+        if (is_split_taps_kind(d.kind) && (wp->cin % 64 != 0 || wp->kh * wp->kw < d.waves)) return false;
         // (small enough for what follows, and for the kernel's products of 24 bits and quotients of 31)
         if (ra->ph > 1000 || ra->pw > 1000 || ra->w > 3000) return false;
         const double lines = (ra->b + 2.0) * ((double)ra->h + ra->ph);
         if (lines >= 16777216.0 || lines * taps_line(ra->w, ra->pw) >= 2147483648.0) return false;
         const long granules = taps_granules(d.BP, ra->h, ra->w, ra->ph, ra->pw);
-        if (taps_lds_bytes(d.NBLK, d.WP, d.NJ, granules, wp->cin / 64, channel_waves(d) * d.WP) > (size_t)kMaxLdsBytes) return false;
-        if (d.waves == 8 && taps_loads(granules) > 8 * kTapsWideLoads) return false;
+        if (is_split_taps_kind(d.kind)) {
+            if (split_taps_lds_bytes(d.NBLK, d.NJ, d.waves, granules, wp->cin / 64) > (size_t)kMaxLdsBytes) return false;
+            if (wp->cin > 64 && taps_loads(granules) > 8 * kSplitTapsItems) return false;
+        } else if (taps_lds_bytes(d.NBLK, d.WP, d.NJ, granules, wp->cin / 64, channel_waves(d) * d.WP) > (size_t)kMaxLdsBytes) return false;
+        if (is_taps_kind(d.kind) && d.waves == 8 && taps_loads(granules) > 8 * kTapsWideLoads) return false;
     }
     if (d.ksplit > 1) {
         // every split must own at least one chunk of the K axis
@@ -283,8 +294,9 @@ constexpr int kPlanesMinKept = 7;
 bool keeps_precision(int v, const nm_packed* wp)
 {
     const VariantDesc& d = variant_desc(v);
-    if (!is_split_kind(d.kind) && d.kind != 11) return true;
+    if (!is_split_kind(d.kind) && !is_split_taps_kind(d.kind) && d.kind != 11) return true;
     long kept = wp->kprime;
+    if (is_split_taps_kind(d.kind)) return kept / d.waves >= kPlanesMinKept;
     if (d.ksplit > 1) {
         const int nchunks = wp->kh * wp->kw * ((wp->cin + d.CK - 1) / d.CK);
         kept = kept * ((nchunks + d.ksplit - 1) / d.ksplit) / nchunks;
@@ -468,7 +480,8 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
         magic_div((unsigned)wp->kw, &p.kw_mul, &p.kw_shift);
         magic_div((unsigned)wp->rbpt, &p.rbpt_mul, &p.rbpt_shift);
     }
-    if (is_taps_kind(d.kind)) {
+    if (is_taps_kind(d.kind) || is_split_taps_kind(d.kind)) {
+        magic_div((unsigned)wp->kw, &p.kw_mul, &p.kw_shift);
         p.rows_n = (int)taps_granules(d.BP, h, w, ph, pw);
         p.rows_lds = taps_loads(p.rows_n) * 1024;
         magic_div((unsigned)taps_line(w, pw), &p.padw_mul, &p.padw_shift);
@@ -514,6 +527,34 @@ unsigned kinds_of(const nm_packed* wp)
     return m;
 }
 
+// The tap-staged form of a layer on three planes that runs without tuning, -1 where the strip-per-tap one does it: the cheaper of two and four groups by rounds of
+// workgroups (one a CU) x (14 000 clocks of start and output + 1.2 x the matrix instructions), in one round where that fills
+// half of the CUs and two thirds of the channels exist; in more with three quarters of them, a last round that is not mostly
+// empty, and a sum long enough to pay for a staging that nothing else runs beside.  Of 136 random 3x3 layers that the
+// rule below does on three planes 32 on the sparse instruction take x0.78 to x1.01 of their time, x0.88 on average, and 59 on
+// the dense one x0.66 to x0.99, x0.87; with several rounds of 9 to 27 chunks it would be x1.02 to x1.27.
+int split_taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra, bool sparse)
+{
+    int pick = -1;
+    double best = 0;
+    const int chunks = wp->K / 64;
+    for (int v : base_variants()) {
+        const VariantDesc& d = variant_desc(v);
+        if (d.kind != (sparse ? 15 : 16) || !keeps_precision(v, wp) || !variant_legal(v, wp, xdt, ra)) continue;
+        const int channels = channel_waves(d) * d.NJ * 16;
+        const long n_cb = (wp->cout + channels - 1) / channels, n_wg = (long)((P + d.BP - 1) / d.BP) * n_cb;
+        const long rounds = (n_wg + kNumCU - 1) / kNumCU;
+        if (rounds == 1 && (2 * n_wg < kNumCU || 3L * wp->cout < 2L * n_cb * channels)) continue;
+        if (rounds > 1 && (chunks < (sparse ? 36 : 27) || 4L * wp->cout < 3L * n_cb * channels || 5L * rounds * kNumCU > 7L * n_wg)) continue;
+        const double cost = rounds * (14000.0 + 1.2 * 12 * 16 * d.NBLK * d.NJ * (sparse ? 1 : 2) * chunks / d.waves);
+        if (pick < 0 || cost < best) {
+            pick = v;
+            best = cost;
+        }
+    }
+    return pick;
+}
+
 // The three-plane form of an fp32 layer that runs without tuning, -1 where the fp32 instruction does it.
 //
 // Clocks of the matrix cores per 64 channels and 16 x 16 outputs: 16 x 32 times the kept fraction on the fp32
@@ -536,6 +577,8 @@ int split_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
     if (fp32_clocks < 256.0) return -1;
     if (sparse && cout <= 64 && wp->kh * wp->kw * ((wp->cin + 63) / 64) <= 9 && P > 16 * kNumCU) return -1;
     if (!sparse && fp32_clocks < 512.0 && (cout < 128 || (long)P * cout < 300000)) return -1;
+    const int taps = split_taps_default(wp, P, xdt, ra, sparse);
+    if (taps >= 0) return taps;
     const int c64 = (cout + 63) / 64, c128 = (cout + 127) / 128;
     const bool wide = cout > 64 && (sparse || 16 * c128 <= 9 * c64);
     const long t64 = (long)((P + 63) / 64) * (wide ? c128 : c64), t32 = (long)((P + 31) / 32) * c128;

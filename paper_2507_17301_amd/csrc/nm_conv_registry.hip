@@ -85,6 +85,12 @@ struct Entry {
 #define NM_ENTRYSD(NB, WP, NJ)                                                                  \
     {{"X3D_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 9, 1, 1, 0, 1}, &launch_split_t<NB, WP, NJ, false>, nullptr},
 
+// kinds 15, 16: the same with a tile's input staged once for all taps
+#define NM_ENTRYST1(NB, WP, NJ, KG)                                                             \
+    {{"X3S_TAP_NB" #NB "_WP" #WP "_NJ" #NJ "_KG" #KG, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 15, 1, 1, 1, 0, KG}, &launch_split_taps_t<NB, WP, NJ, KG, true>, nullptr},
+#define NM_ENTRYST0(NB, WP, NJ, KG)                                                             \
+    {{"X3D_TAP_NB" #NB "_WP" #WP "_NJ" #NJ "_KG" #KG, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 16, 1, 1, 1, 0, KG}, &launch_split_taps_t<NB, WP, NJ, KG, false>, nullptr},
+
 // kinds 10 (bf16) and 11 (fp32): few input channels out of staged rows; NBLK is the number of output rows
 #define NM_ENTRYROWB(R, NJ, KS) {{"RUN_ROWS" #R "_NJ" #NJ "_KS" #KS, 16, R, 4 / (4 / NJ), NJ, 64 * KS, KS, 1, 10, 1, 1, 0}, nullptr, &launch_rows_t<1, NJ, KS>},
 #define NM_ENTRYROWF(R, NJ, KS) {{"ROWF_R" #R "_NJ" #NJ "_KS" #KS, 16, R, 4 / (4 / NJ), NJ, 64 * KS, KS, 1, 11, 1, 1, 0}, &launch_rows_t<3, NJ, KS>, nullptr},
@@ -102,7 +108,8 @@ const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTR
                           NMF8_SHAPES(NM_ENTRYF8) NMF8S_SHAPES(NM_SHAPE_ENTRIESF8S)
                           NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)
                           NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF) NMWAVE_SHAPES(NM_SHAPE_ENTRIESWAVE)
-                          NMTAPS1_SHAPES(NM_ENTRYTAPS1) NMTAPS0_SHAPES(NM_ENTRYTAPS0) NMTAPSW1_SHAPES(NM_ENTRYTAPSW1) NMTAPSW0_SHAPES(NM_ENTRYTAPSW0)};
+                          NMTAPS1_SHAPES(NM_ENTRYTAPS1) NMTAPS0_SHAPES(NM_ENTRYTAPS0) NMTAPSW1_SHAPES(NM_ENTRYTAPSW1) NMTAPSW0_SHAPES(NM_ENTRYTAPSW0)
+                          NMST1_SHAPES(NM_ENTRYST1) NMST0_SHAPES(NM_ENTRYST0)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
 // The fp32 kernels also run with their K axis split over several workgroups per output

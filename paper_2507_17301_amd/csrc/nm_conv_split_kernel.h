@@ -190,6 +190,107 @@ __device__ inline void split_barrier()
     asm volatile("" ::: "memory");
 }
 
+// The finished blocks of a wavefront (pixels from pix0, row blocks from rb0): bias (where rows do not come in whole quads,
+// `fast`, and it is not in the accumulators), residual, activation, store, and what has to be computed again; span(lo, hi)
+// says which kept columns the sums run over.  `piece` is the wavefront's own LDS, split_out_rows(NBLK) rows.
+template <int NBLK, int NJ, typename Span>
+__device__ inline __attribute__((always_inline)) void split_finish(kernarg_t kp, const f4 (&acc)[NJ][NBLK], char* piece, int lane, int pix0, int rb0,
+                                                                   int inexact, bool fast, float* __restrict__ y,
+                                                                   const float* __restrict__ res, bool relu, Span&& span)
+{
+    const int q = lane >> 4, n = lane & 15;
+    // Through LDS, so that every store covers whole rows of this wavefront's channels (64 NJ bytes a pixel)
+    // instead of 64-byte pieces.  The piece is the wavefront's own: no barrier, and the producers are
+    // already staging the next tile.
+    constexpr int PITCH = split_out_pitch(NJ);
+    constexpr int PB = split_out_rows(NBLK) / 16;   // blocks per piece
+    constexpr int GPR = NJ * 4;                     // 16-byte granules per row
+    constexpr int RPP = 64 / GPR;                   // rows per pass of the wavefront
+    const int r0 = lane / GPR, cg = lane % GPR;
+    const int co = rb0 * 16 + cg * 4;
+    const char* const src = piece + r0 * PITCH + cg * 16;
+    const int P = kp->P, Cout = kp->Cout;
+    constexpr int NP = PB * 16 / RPP;               // passes per piece
+#pragma unroll
+    for (int b0 = 0; b0 < NBLK; b0 += PB) {
+#pragma unroll
+        for (int b = b0; b < b0 + PB && b < NBLK; ++b)
+#pragma unroll
+            for (int jj = 0; jj < NJ; ++jj)
+                *reinterpret_cast<f4*>(piece + ((b - b0) * 16 + n) * PITCH + jj * 64 + q * 16) = acc[jj][b];
+        __builtin_amdgcn_wave_barrier();
+        const int rows = (NBLK - b0 < PB ? NBLK - b0 : PB) * 16;
+        const int pp0 = pix0 + b0 * 16 + r0;
+        unsigned lo = ~0u, hi = 0u;          // of the words without their sign; a zero counts as large in lo
+        auto look = [&](const f4 v) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const unsigned w = __float_as_uint(v[r]) << 1;
+                lo = w - 1u < lo ? w - 1u : lo;
+                hi = w > hi ? w : hi;
+            }
+        };
+        if (fast) {
+            f4 v[NP];
+#pragma unroll
+            for (int k = 0; k < NP; ++k) v[k] = *reinterpret_cast<const f4*>(src + k * (RPP * PITCH));
+#pragma unroll
+            for (int k = 0; k < NP; ++k) look(v[k]);   // (values of rows that do not exist are sorted out below)
+            if (res) {   // all of the piece's at once: the memory counter makes a load wait for the stores before it
+                f4 rv[NP];
+#pragma unroll
+                for (int k = 0; k < NP; ++k) {
+                    const bool live = k * RPP + r0 < rows && pp0 + k * RPP < P && co < Cout;
+                    rv[k] = load4(res + (live ? (unsigned)(pp0 + k * RPP) * (unsigned)Cout + (unsigned)co : 0u));
+                }
+#pragma unroll
+                for (int k = 0; k < NP; ++k) v[k] = v[k] + rv[k];
+            }
+            if (relu) {
+#pragma unroll
+                for (int k = 0; k < NP; ++k) v[k] = relu4(v[k]);
+            }
+            auto store = [&](auto stream) {
+#pragma unroll
+                for (int k = 0; k < NP; ++k)
+                    if (k * RPP + r0 < rows && pp0 + k * RPP < P && co < Cout)
+                        store_out16<decltype(stream)::value>(y + ((unsigned)(pp0 + k * RPP) * (unsigned)Cout + (unsigned)co),
+                                                             __builtin_bit_cast(u4v, v[k]));
+            };
+            if (kp->stream) store(std::true_type());
+            else store(std::false_type());
+        } else {
+#pragma unroll 1
+            for (int row = 0; row < rows; row += RPP) {
+                const f4 v = *reinterpret_cast<const f4*>(src + row * PITCH);
+                if (pp0 + row >= P) continue;
+                look(v);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (co + r >= Cout) continue;
+                    const unsigned off = (unsigned)(pp0 + row) * (unsigned)Cout + (unsigned)(co + r);
+                    float o = v[r] + (kp->bias && kp->ksplit <= 1 ? kp->bias[co + r] : 0.f);
+                    if (res) o += res[off];
+                    if (relu) o = relu1(o);
+                    y[off] = o;
+                }
+            }
+        }
+        if (__builtin_expect(lo < kSplitTiny || hi >= kSplitInf || inexact, 0)) {
+            __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
+            const unsigned below = inexact ? kp->redo_below : kSplitTiny;
+            int k_lo, k_hi;
+            span(k_lo, k_hi);
+#pragma unroll 1
+            for (int row = 0; row < rows; row += RPP)
+                if (pp0 + row < P && co < Cout)
+                    split_again(kp, *reinterpret_cast<const u4v*>(src + row * PITCH), pp0 + row, co, below, inexact != 0, k_lo, k_hi,
+                                kp->ksplit <= 1 ? kp->bias : nullptr, res, relu, y);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 template <int NBLK, int WP, int NJ, bool SPARSE>
 __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_conv_split_kernel(const ConvParams p)
 {
@@ -452,105 +553,18 @@ __global__ __launch_bounds__(512, split_waves(NBLK, WP, NJ, SPARSE)) void nm_con
         asm volatile("" : "+s"(kp));
         int lane = tid & 63;                     // (opaque: the addresses below are worked out here, not kept through the chunks)
         asm volatile("" : "+v"(lane));
-        const int q = lane >> 4, n = lane & 15;
         // K split: partial sums [split][pixel][channel]; bias, residual and activation come where they are added up
         float* __restrict__ y = kp->ksplit > 1 ? kp->partial + (size_t)ks * (size_t)kp->P * (size_t)kp->Cout : reinterpret_cast<float*>(kp->y);
         const float* __restrict__ res = kp->ksplit > 1 ? nullptr : reinterpret_cast<const float*>(kp->res);
         const bool relu = kp->ksplit <= 1 && kp->relu;
-        // Through LDS, so that every store covers whole rows of this wavefront's channels (64 NJ bytes a pixel)
-        // instead of 64-byte pieces.  The piece is the wavefront's own: no barrier, and the producers are
-        // already staging the next tile.
-        constexpr int PITCH = split_out_pitch(NJ);
-        constexpr int PB = split_out_rows(NBLK) / 16;   // blocks per piece
-        constexpr int GPR = NJ * 4;                     // 16-byte granules per row
-        constexpr int RPP = 64 / GPR;                   // rows per pass of the wavefront
-        const int r0 = lane / GPR, cg = lane % GPR;
-        const int co = rb0 * 16 + cg * 4;
-        const char* const src = piece + r0 * PITCH + cg * 16;
-        const int P = kp->P, Cout = kp->Cout;
-        constexpr int NP = PB * 16 / RPP;               // passes per piece
-        int inexact = 0;                                // the planes of some activation so far left bits out
+        int inexact = 0;                         // the planes of some activation so far left bits out
 #pragma unroll
         for (int w = 0; w < 4; ++w)
-            inexact |= *reinterpret_cast<const int*>(lds8 + 2 * STAGE + w * (split_out_rows(NBLK) * PITCH) + NJ * 64);
-#pragma unroll
-        for (int b0 = 0; b0 < NBLK; b0 += PB) {
-#pragma unroll
-            for (int b = b0; b < b0 + PB && b < NBLK; ++b)
-#pragma unroll
-                for (int jj = 0; jj < NJ; ++jj)
-                    *reinterpret_cast<f4*>(piece + ((b - b0) * 16 + n) * PITCH + jj * 64 + q * 16) = acc[jj][b];
-            __builtin_amdgcn_wave_barrier();
-            const int rows = (NBLK - b0 < PB ? NBLK - b0 : PB) * 16;
-            const int pp0 = p0 + wpix + b0 * 16 + r0;
-            unsigned lo = ~0u, hi = 0u;          // of the words without their sign; a zero counts as large in lo
-            auto look = [&](const f4 v) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const unsigned w = __float_as_uint(v[r]) << 1;
-                    lo = w - 1u < lo ? w - 1u : lo;
-                    hi = w > hi ? w : hi;
-                }
-            };
-            if (fast) {
-                f4 v[NP];
-#pragma unroll
-                for (int k = 0; k < NP; ++k) v[k] = *reinterpret_cast<const f4*>(src + k * (RPP * PITCH));
-#pragma unroll
-                for (int k = 0; k < NP; ++k) look(v[k]);   // (values of rows that do not exist are sorted out below)
-                if (res) {   // all of the piece's at once: the memory counter makes a load wait for the stores before it
-                    f4 rv[NP];
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) {
-                        const bool live = k * RPP + r0 < rows && pp0 + k * RPP < P && co < Cout;
-                        rv[k] = load4(res + (live ? (unsigned)(pp0 + k * RPP) * (unsigned)Cout + (unsigned)co : 0u));
-                    }
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) v[k] = v[k] + rv[k];
-                }
-                if (relu) {
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) v[k] = relu4(v[k]);
-                }
-                auto store = [&](auto stream) {
-#pragma unroll
-                    for (int k = 0; k < NP; ++k)
-                        if (k * RPP + r0 < rows && pp0 + k * RPP < P && co < Cout)
-                            store_out16<decltype(stream)::value>(y + ((unsigned)(pp0 + k * RPP) * (unsigned)Cout + (unsigned)co),
-                                                                 __builtin_bit_cast(u4v, v[k]));
-                };
-                if (kp->stream) store(std::true_type());
-                else store(std::false_type());
-            } else {
-#pragma unroll 1
-                for (int row = 0; row < rows; row += RPP) {
-                    const f4 v = *reinterpret_cast<const f4*>(src + row * PITCH);
-                    if (pp0 + row >= P) continue;
-                    look(v);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (co + r >= Cout) continue;
-                        const unsigned off = (unsigned)(pp0 + row) * (unsigned)Cout + (unsigned)(co + r);
-                        float o = v[r] + (kp->bias && kp->ksplit <= 1 ? kp->bias[co + r] : 0.f);
-                        if (res) o += res[off];
-                        if (relu) o = relu1(o);
-                        y[off] = o;
-                    }
-                }
-            }
-            if (__builtin_expect(lo < kSplitTiny || hi >= kSplitInf || inexact, 0)) {
-                __builtin_amdgcn_s_waitcnt(0);   // the stores above come first
-                const unsigned below = inexact ? kp->redo_below : kSplitTiny;
-                const int k_lo = (c_begin / kp->ncpt) * kp->Cin + (c_begin % kp->ncpt) * kSplitCK;
-                const int k_hi = c_end < kp->nchunks ? (c_end / kp->ncpt) * kp->Cin + (c_end % kp->ncpt) * kSplitCK : kp->K;
-#pragma unroll 1
-                for (int row = 0; row < rows; row += RPP)
-                    if (pp0 + row < P && co < Cout)
-                        split_again(kp, *reinterpret_cast<const u4v*>(src + row * PITCH), pp0 + row, co, below, inexact != 0, k_lo, k_hi,
-                                    kp->ksplit <= 1 ? kp->bias : nullptr, res, relu, y);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
+            inexact |= *reinterpret_cast<const int*>(lds8 + 2 * STAGE + w * (split_out_rows(NBLK) * split_out_pitch(NJ)) + NJ * 64);
+        split_finish<NBLK, NJ>(kp, acc, piece, lane, p0 + wpix, rb0, inexact, fast, y, res, relu, [&](int& k_lo, int& k_hi) {
+            k_lo = (c_begin / kp->ncpt) * kp->Cin + (c_begin % kp->ncpt) * kSplitCK;
+            k_hi = c_end < kp->nchunks ? (c_end / kp->ncpt) * kp->Cin + (c_end % kp->ncpt) * kSplitCK : kp->K;
+        });
     };
 
     if constexpr (RING == 2) {

@@ -68,7 +68,8 @@ struct Prepack {
                                       // 10, 11: few input channels out of staged rows (bf16, fp32)
                                       // 8, 9: fp32 as three bf16 planes (sparse instruction, dense instruction)
                                       // (12, the small-layer fp32 kernel, reads kind 0's weights and d_cols; 13 and 14, the
-                                      // tap-staged bf16 kernels, read 2's and 3's)
+                                      // tap-staged bf16 kernels, read 2's and 3's; 15 and 16, the tap-staged three-plane
+                                      // kernels, 8's and 9's)
     ChunkGeom geom{};
     int SPC = 0;                      // k-steps per chunk (1, 2, 4 or 8)
     // kind 0: a k-step is 4 kept columns
@@ -177,6 +178,17 @@ constexpr size_t taps_lds_bytes(int NBLK, int WP, int NJ, long granules, int ncp
     return strip > out ? strip : out;
 }
 
+// Tap-staged three-plane kernels (kinds 15, 16): room for the wavefronts' words before the stages, granules of a stage that a
+// thread holds in registers where there is more than one stage, bytes of the sums that the groups exchange
+constexpr int kSplitTapsFlags = 128, kSplitTapsItems = 3;
+constexpr int split_taps_sums(int NBLK, int NJ, int KG) { return 8 * (KG - 1) * (NBLK / KG) * NJ * 1024; }
+constexpr size_t split_taps_lds_bytes(int NBLK, int NJ, int KG, long granules, int ncpt)
+{
+    const size_t stages = (size_t)taps_loads(granules) * 1024 * 3 * (ncpt > 1 ? 2 : 1);
+    const size_t out = (size_t)split_taps_sums(NBLK, NJ, KG) + 8 * split_out_rows(NBLK / KG) * split_out_pitch(NJ);
+    return kSplitTapsFlags + (stages > out ? stages : out);
+}
+
 // Row-staged kernels (kinds 10, 11): a wavefront's output piece, 16 pixels x 128 bytes and 16 bytes of padding a row
 constexpr int kRowsPiece = 16 * 144;
 
@@ -270,12 +282,13 @@ struct VariantDesc {
                // 10, 11 = few input channels out of staged rows, bf16 and fp32 (NBLK = output rows a workgroup)
                // 8, 9 = fp32 tensors as three bf16 planes on the sparse / dense bf16 instruction
                // 13, 14 = bf16 k x k kernel that stages a tile's input once for all taps, sparse / dense instruction
+               // 15, 16 = fp32 as three bf16 planes, a tile's input staged and cut once for all taps, sparse / dense instruction
                // 12 = fp32 MFMA kernel for small layers, the K axis dealt out over the wavefronts (NBLK pixel blocks, WP = 4)
     int share; // kind 1: row blocks fed from one gathered operand
     int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)
     int areg;  // kinds 2, 3, 7: 1 = weights and index words go straight to registers, the LDS stages hold the strip alone
     int spec;  // kinds 2, 3, 7: 1 = four producer wavefronts issue the loads (512 threads)
-    int waves; // kind 12: most wavefronts the K axis is dealt out over; kinds 13, 14: 8 = eight contracting wavefronts, else four
+    int waves; // kinds 15, 16: groups of wavefronts that take the chunks in turn; kind 12: most wavefronts the K axis is dealt out over; kinds 13, 14: 8 = eight contracting wavefronts, else four
 };
 
 // Allows kernel `fn` more than 64 KB of dynamic LDS on the current device; done once per

@@ -114,6 +114,12 @@
 #define NMSS_SHAPES(X) X(4, 1, 2) X(4, 1, 4) X(3, 1, 2) X(2, 1, 2) X(2, 2, 2) X(4, 1, 1) X(2, 1, 1)
 #define NMSD_SHAPES(X) X(4, 1, 2) X(2, 1, 2) X(2, 2, 2) X(4, 1, 1) X(2, 1, 1)
 
+// k x k layers of the same whose output is as large as the input: a tile's input staged and cut once for all taps, eight
+// contracting wavefronts in KG groups that take the chunks in turn (128-pixel tiles were first on no layer)
+// X(NBLK, WP, NJ, KG)
+#define NMST1_SHAPES(X) X(4, 1, 4, 2) X(4, 1, 4, 4)
+#define NMST0_SHAPES(X) X(4, 1, 2, 2) X(4, 1, 2, 4)
+
 // few input channels out of staged input rows: R output rows a workgroup, 64 channels, KS 64-element k-steps
 // Y(NJ, KS); X(R, NJ, KS)
 #define NMROWB_CHUNKS(Y) Y(4, 1) Y(4, 2) Y(4, 3) Y(4, 4)
