@@ -308,6 +308,10 @@ bool keeps_precision(int v, const nm_packed* wp)
 // tile, so a chunk's columns are one run: the chunk is worked out once per run, not per column.
 int max_kept_per_chunk(const nm_packed* wp, const ChunkGeom& g)
 {
+    // Whole groups to a chunk (and to a tap, where chunks do not cross taps): what a group keeps, times the groups of the longest.
+    // (Counted, the two chunk lengths of a 512x3x3x512 layer took 0.10 ms of 0.63.)
+    const int most = std::min(g.CK, g.vec ? wp->cin : wp->K);
+    if (g.CK % wp->m == 0 && (!g.vec || wp->cin % wp->m == 0)) return most / wp->m * wp->n;
     int best = 0;
     for (int j = 0; j < wp->n_tiles; ++j) {
         const int32_t* idx = wp->h_idx.data() + (size_t)j * wp->kprime;
