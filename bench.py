@@ -31,7 +31,7 @@ PEAK_HBM_GBS = 8000.0
 # the kernel behind a variant's name, by the name's first part (longest match)
 KERNELS = {"NB": "nm_conv_kernel", "VAR": "nm_conv_kernel", "B16": "nm_conv_bf16_kernel", "SP": "nm_conv_sp16_kernel",
            "RUN": "nm_conv_run16_kernel", "RUN_ROWS": "nm_conv_rows_kernel", "ROWF": "nm_conv_rows_kernel",
-           "SPR1_TAP": "nm_conv_taps_kernel", "SPR0_TAP": "nm_conv_taps_kernel",
+           "SPR1_COLS": "nm_conv_cols_kernel", "SPR1_TAP": "nm_conv_taps_kernel", "SPR0_TAP": "nm_conv_taps_kernel",
            "X3S": "nm_conv_split_kernel", "X3D": "nm_conv_split_kernel",
            "X3S_TAP": "nm_conv_split_taps_kernel", "X3D_TAP": "nm_conv_split_taps_kernel", "KW": "nm_conv_wave_kernel", "F8": "nm_conv_f8_kernel",
            "F8S": "nm_conv_sp16_kernel", "F8W": "nm_conv_sp16_kernel", "F8R": "nm_conv_sp16_kernel"}

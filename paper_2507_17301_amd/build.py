@@ -133,6 +133,13 @@ def _shapes_split_taps(name):
     return [tuple(int(v) for v in m) for m in re.findall(r"X\((\d+),\s*(\d+),\s*(\d+),\s*(\d+)\)", body)]
 
 
+def _shapes_cols():
+    """NBLK of NMCOLS_SHAPES in nm_variants.h."""
+    text = open(os.path.join(CSRC, "nm_variants.h")).read()
+    body = text[text.index("#define NMCOLS_SHAPES(X)") + 24:]
+    return [int(v) for v in re.findall(r"X\((\d+)\)", body[:body.index("\n")])]
+
+
 def _shapes_wave():
     """(PB, NJ) of NMWAVE_SHAPES in nm_variants.h."""
     text = open(os.path.join(CSRC, "nm_variants.h")).read()
@@ -190,6 +197,9 @@ def _jobs():
             jobs.append((insttaps, os.path.join(OBJDIR, f"nm_conv_taps_inst_{sparse}_{nb}_{wp}_{nj}_{nw}.o"),
                          [f"-DNM_INST_NBLK={nb}", f"-DNM_INST_WP={wp}", f"-DNM_INST_NJ={nj}",
                           f"-DNM_INST_SPARSE={sparse}", f"-DNM_INST_NW={nw}"]))
+    instcols = os.path.join(CSRC, "nm_conv_cols_inst.hip")
+    for nb in _shapes_cols():
+        jobs.append((instcols, os.path.join(OBJDIR, f"nm_conv_cols_inst_{nb}.o"), [f"-DNM_INST_NBLK={nb}"]))
     instst = os.path.join(CSRC, "nm_conv_split_taps_inst.hip")
     for name, sparse in (("NMST1_SHAPES", 1), ("NMST0_SHAPES", 0)):
         for nb, wp, nj, kg in _shapes_split_taps(name):

@@ -157,6 +157,7 @@ size_t lds_bytes(const VariantDesc& d, const nm_packed* wp)
     if (is_split_kind(d.kind)) return (size_t)split_lds_bytes(d.NBLK, d.WP, d.NJ);
     if (is_taps_kind(d.kind)) return taps_lds_bytes(d.NBLK, d.WP, d.NJ, 9 * d.BP, 1, channel_waves(d) * d.WP);   // and what depends on the image
     if (is_split_taps_kind(d.kind)) return split_taps_lds_bytes(d.NBLK, d.NJ, d.waves, 9 * d.BP, 1);
+    if (d.kind == 17) return (size_t)cols_lds_bytes(d.NBLK, d.waves);
     if (d.kind == 12) return (size_t)wave_lds_bytes(d.NBLK, d.NJ, d.CK, d.waves);
     if (is_rows_kind(d.kind)) return kRowsPieces;   // and the staged rows, which depend on the image (rows_layout)
     if (d.kind == 6)   // only the wavefront-private output tiles [16 NBLK][16 NJ] bf16 with 16 bytes of padding per row
@@ -220,8 +221,8 @@ int run_ksteps(const nm_packed* wp, int par)
     return (wp->kh * gr + 7) / 8;
 }
 
-// kind 12 reads the tables of kind 0, kinds 13 and 14 those of 2 and 3, kinds 15 and 16 those of 8 and 9
-inline int table_kind(int kind) { return kind == 12 ? 0 : is_taps_kind(kind) ? kind - 11 : is_split_taps_kind(kind) ? kind - 7 : kind; }
+// kind 12 reads the tables of kind 0, kind 17 those of 2, kinds 13 and 14 those of 2 and 3, kinds 15 and 16 those of 8 and 9
+inline int table_kind(int kind) { return kind == 12 ? 0 : kind == 17 ? 2 : is_taps_kind(kind) ? kind - 11 : is_split_taps_kind(kind) ? kind - 7 : kind; }
 
 const Prepack* find_prepack(const nm_packed* wp, const VariantDesc& d, int par = -1)
 {
@@ -245,13 +246,17 @@ bool variant_legal(int v, const nm_packed* wp, nm_dtype_t xdt, const RunArgs* ra
     if ((d.kind == 5 || d.kind == 11 || d.kind == 12 || is_split_kind(d.kind) || is_split_taps_kind(d.kind)) && xdt != NM_F32) return false;   // instantiated for fp32 tensors only
     // fp8: E4M3 tensors with an E4M3 handle run the fp8 kernels and nothing else does
     if (is_f8_kind(d.kind) != (xdt == NM_F8E4M3) || is_f8_kind(d.kind) != (wp->value_dtype == NM_F8E4M3)) return false;
-    if ((d.kind >= 1 && d.kind <= 4) || d.kind == 10 || is_taps_kind(d.kind)) {
+    if ((d.kind >= 1 && d.kind <= 4) || d.kind == 10 || d.kind == 17 || is_taps_kind(d.kind)) {
         // bf16 matrix cores: bf16 tensors, weights already rounded to bf16, and a
         // shared operand only for column tiles made of exactly two row blocks
         if (xdt != NM_BF16 || wp->value_dtype != NM_BF16) return false;
         if (d.share != 1 && d.share != wp->rbpt) return false;
     }
     if (is_rows_kind(d.kind) && wp->cout % (d.kind == 10 ? 8 : 4) != 0) return false;   // whole 16-byte output granules
+    if (d.kind == 17) {   // 1x1 without padding, this many input channels; whole row blocks and 16-byte output granules
+        if (!ra || ra->ph != 0 || ra->pw != 0 || wp->kh != 1 || wp->kw != 1 || wp->cin != 64 * d.waves) return false;
+        if (wp->tile % 16 != 0 || wp->cout % 8 != 0) return false;
+    }
     if (is_taps_kind(d.kind) || is_split_taps_kind(d.kind)) {
         // an output as large as the input, so that a tap is one shift of the whole tile; whole 16-byte output granules
         if (!ra || ra->sh != 1 || ra->sw != 1 || wp->kh * wp->kw < 2 || wp->kh * wp->kw > 32) return false;
@@ -446,6 +451,15 @@ void magic_div(unsigned d, unsigned* mul, unsigned* shift)
 // (206 MB) 113 + 48 and 114 + 50.
 bool stream_output(int kind, double bytes) { return bytes > (kind == 10 ? 96e6 : kind == 11 ? 256e6 : 150e6); }
 
+// Groups of 256 output channels that a workgroup of kind 17 walks: all of them, or as many as leave three quarters of the CUs'
+// places (two a CU) a workgroup.  14x14 256 -> 1024 with a residual, 1, 2 and 4 groups: batch 256 (784 pixel tiles) 67.7, 60.4 and 61.0
+// us, batch 64 19.2, 16.2 and 19.0.
+int cols_walk(int n_ptiles, int n_cblocks)
+{
+    const int parts = (3 * kNumCU / 2 + n_ptiles - 1) / n_ptiles;
+    return parts >= n_cblocks ? 1 : (n_cblocks + parts - 1) / parts;
+}
+
 void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const nm_packed* wp,
                  const void* x, void* y, const float* bias, int b, int h, int w, const Geometry& g,
                  int sh, int sw, int ph, int pw, int dh, int dw, int relu, size_t es)
@@ -500,6 +514,11 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
         p.n_ptiles = b * ((g.Ho + d.NBLK - 1) / d.NBLK);
     }
     p.n_wg = p.n_ptiles * p.n_cblocks * p.ksplit;
+    if (d.kind == 17) {
+        magic_div((unsigned)wp->rbpt, &p.rbpt_mul, &p.rbpt_shift);
+        p.cps = cols_walk(p.n_ptiles, p.n_cblocks);
+        p.n_wg = p.n_ptiles * ((p.n_cblocks + p.cps - 1) / p.cps);
+    }
     p.wg_per_xcd = (p.n_wg + 7) / 8;
     magic_div((unsigned)(g.Ho * g.Wo), &p.howo_mul, &p.howo_shift);
     magic_div((unsigned)g.Wo, &p.wo_mul, &p.wo_shift);
@@ -651,6 +670,23 @@ int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
     return pick;
 }
 
+// The channel-walking form of a bf16 1x1 layer that runs without tuning, -1 where the others do it: from 4096 pixels on and with
+// more than one group of 256 output channels, half of the last of which may be empty in launches that the CUs hold at once (448
+// tiles of 64 pixels), a quarter beyond, where fewer than 192 input channels stay with the others too; 64 pixels a tile from 400
+// such tiles on.  Of 330 random 1x1 layers of up to 256 input channels the 68 within take x0.57 to x1.03 of the time that the
+// rule below gives them, x0.84 on average; beyond, one group x1.2 to x1.5, 128 input channels and 2000 tiles x1.1 to x1.2.
+int cols_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
+{
+    const long n_cb = (wp->cout + 255) / 256, tiles = (P + 63) / 64;
+    if (P < 4096 || n_cb < 2 || 2L * wp->cout < n_cb * 256) return -1;
+    if (tiles > 448 && (wp->cin < 192 || 4L * wp->cout < 3 * n_cb * 256)) return -1;
+    for (int v : base_variants()) {
+        const VariantDesc& d = variant_desc(v);
+        if (d.kind == 17 && d.NBLK == (tiles >= 400 ? 4 : 2) && variant_legal(v, wp, xdt, ra)) return v;
+    }
+    return -1;
+}
+
 // 16 x 16 blocks of outputs: what the small-layer fp32 kernel (kind 12) deals out.
 long wave_blocks(const nm_packed* wp, int P) { return (long)((P + 15) / 16) * wp->n_rowblocks; }
 
@@ -713,8 +749,8 @@ double model_clocks(const VariantDesc& d, const nm_packed* wp, int P)
     return (0.32 * ceil(rounds) + 0.68 * rounds) * (5020.0 + nchunks * std::max(431.0, occ * chunk) + occ * ends) + 1.13 * ends;
 }
 
-// Deterministic default when the shape has not been tuned: rows_default, wave_default, split_default, taps_default, else the cheapest by
-// model_clocks.
+// Deterministic default when the shape has not been tuned: rows_default, wave_default, split_default, taps_default, cols_default, else the cheapest
+// by model_clocks.
 //
 // For the gather-free bf16 and the staged fp8 kernels there is a rule read off tuned ResNet stacks: a tile of 128
 // pixels x 128 channels (64 pixels where that leaves under half the CUs a workgroup, 64 channels
@@ -738,6 +774,10 @@ int heuristic_variant(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs*
     }
     if (ra && (kinds & (1u << 2 | 1u << 3))) {
         const int v = taps_default(wp, P, xdt, ra);
+        if (v >= 0) return v;
+    }
+    if (ra && (kinds & (1u << 2))) {
+        const int v = cols_default(wp, P, xdt, ra);
         if (v >= 0) return v;
     }
     if (kinds & (1u << 2 | 1u << 3 | 1u << 7)) {

@@ -52,6 +52,11 @@ struct Entry {
 #define NM_ENTRYTAPSW0(NB, WP, NJ) \
     {{"SPR0_TAP8_NB" #NB "_WP" #WP "_NJ" #NJ, 16 * NB * WP, NB, WP, NJ, 64, 1, 1, 14, 1, 1, 1, 1, 8}, nullptr, &launch_taps_t<NB, WP, NJ, false, 8>},
 
+// kind 17: 1x1, output channels pass over resident pixels
+#define NM_ENTRYCOLS(NB, NCH) \
+    {{"SPR1_COLS_NB" #NB "_C" #NCH, 16 * NB, NB, 1, 4, 64, 1, 1, 17, 1, 1, 1, 0, NCH}, nullptr, &launch_cols_t<NB, NCH>},
+#define NM_SHAPE_ENTRIESCOLS(NB) NMCOLS_CHUNKS(NM_ENTRYCOLS, NB)
+
 // kind 4: contiguous kernel-row runs
 #define NM_ENTRYRUN(NB, WP, NJ, KS)                                                             \
     {{"RUN_NB" #NB "_WP" #WP "_NJ" #NJ "_KS" #KS, 16 * NB * WP, NB, WP, NJ, 64 * KS, KS, 1, 4, 1, 1, 0}, \
@@ -109,7 +114,7 @@ const Entry kEntries[] = {NM_SHAPES(NM_SHAPE_ENTRIES) NM_SCALAR_VARIANTS(NM_ENTR
                           NMSS_SHAPES(NM_ENTRYSS) NMSD_SHAPES(NM_ENTRYSD)
                           NMROWB_CHUNKS(NM_HEIGHTSB) NMROWF_CHUNKS(NM_HEIGHTSF) NMWAVE_SHAPES(NM_SHAPE_ENTRIESWAVE)
                           NMTAPS1_SHAPES(NM_ENTRYTAPS1) NMTAPS0_SHAPES(NM_ENTRYTAPS0) NMTAPSW1_SHAPES(NM_ENTRYTAPSW1) NMTAPSW0_SHAPES(NM_ENTRYTAPSW0)
-                          NMST1_SHAPES(NM_ENTRYST1) NMST0_SHAPES(NM_ENTRYST0)};
+                          NMCOLS_SHAPES(NM_SHAPE_ENTRIESCOLS) NMST1_SHAPES(NM_ENTRYST1) NMST0_SHAPES(NM_ENTRYST0)};
 constexpr int kCount = (int)(sizeof(kEntries) / sizeof(kEntries[0]));
 
 // The fp32 kernels also run with their K axis split over several workgroups per output

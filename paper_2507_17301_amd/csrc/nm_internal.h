@@ -68,7 +68,7 @@ struct Prepack {
                                       // 10, 11: few input channels out of staged rows (bf16, fp32)
                                       // 8, 9: fp32 as three bf16 planes (sparse instruction, dense instruction)
                                       // (12, the small-layer fp32 kernel, reads kind 0's weights and d_cols; 13 and 14, the
-                                      // tap-staged bf16 kernels, read 2's and 3's; 15 and 16, the tap-staged three-plane
+                                      // tap-staged bf16 kernels, read 2's and 3's; 17, the channel-walking one, 2's; 15 and 16, the tap-staged three-plane
                                       // kernels, 8's and 9's)
     ChunkGeom geom{};
     int SPC = 0;                      // k-steps per chunk (1, 2, 4 or 8)
@@ -189,6 +189,9 @@ constexpr size_t split_taps_lds_bytes(int NBLK, int NJ, int KG, long granules, i
     return kSplitTapsFlags + (stages > out ? stages : out);
 }
 
+// Channel-walking 1x1 kernel (kind 17): the pixels' whole input and an output piece per wavefront
+constexpr int cols_lds_bytes(int NBLK, int NCH) { return 16 * NBLK * (NCH * 128 + 4 * 144); }
+
 // Row-staged kernels (kinds 10, 11): a wavefront's output piece, 16 pixels x 128 bytes and 16 bytes of padding a row
 constexpr int kRowsPiece = 16 * 144;
 
@@ -256,7 +259,7 @@ struct ConvParams {
     // chunks and writes its partial sums to partial[split][P][Cout] (fp32); a second kernel adds
     // them up and applies bias, residual and activation.  ksplit <= 1: no split, partial unused.
     float* partial;
-    int ksplit, cps;
+    int ksplit, cps;   // (kind 17: cps = groups of 256 output channels that a workgroup walks)
     // the compressed format itself (kinds 8, 9 compute outputs that came out infinite or NaN from it again)
     const int32_t* idx;
     const float* vals;
@@ -283,6 +286,7 @@ struct VariantDesc {
                // 8, 9 = fp32 tensors as three bf16 planes on the sparse / dense bf16 instruction
                // 13, 14 = bf16 k x k kernel that stages a tile's input once for all taps, sparse / dense instruction
                // 15, 16 = fp32 as three bf16 planes, a tile's input staged and cut once for all taps, sparse / dense instruction
+               // 17 = bf16 1x1 kernel that walks the output channels over resident pixels (CK = all input channels)
                // 12 = fp32 MFMA kernel for small layers, the K axis dealt out over the wavefronts (NBLK pixel blocks, WP = 4)
     int share; // kind 1: row blocks fed from one gathered operand
     int ksplit; // kinds 0, 5, 8, 9: workgroups that share the K axis of one output tile (1 = no split)

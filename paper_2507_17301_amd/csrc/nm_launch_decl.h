@@ -20,6 +20,8 @@ template <int NBLK, int WP, int NJ, bool SPARSE>
 int launch_split_t(const ConvParams& p, hipStream_t s);
 template <int NBLK, int WP, int NJ, int KG, bool SPARSE>
 int launch_split_taps_t(const ConvParams& p, hipStream_t s);
+template <int NBLK, int NCH>
+int launch_cols_t(const ConvParams& p, hipStream_t s);
 template <int PB, int NJ, int CK, int SPC, int NW>
 int launch_wave_t(const ConvParams& p, hipStream_t s);
 template <int PL, int NJ, int KS>

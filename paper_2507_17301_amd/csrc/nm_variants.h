@@ -85,6 +85,11 @@
 #define NMTAPSW1_SHAPES(X) X(7, 2, 4) X(8, 2, 4)
 #define NMTAPSW0_SHAPES(X) X(7, 2, 4) X(7, 2, 2)
 
+// 1x1 layers of up to 256 input channels: the input of 16 NBLK pixels stays, the output channels pass
+// X(NBLK); Y(NBLK, chunks of 64 input channels)
+#define NMCOLS_SHAPES(X) X(4) X(2)
+#define NMCOLS_CHUNKS(Y, NB) Y(NB, 1) Y(NB, 2) Y(NB, 3) Y(NB, 4)
+
 // bf16 kernel for layers with very few input channels (contiguous kernel-row
 // runs, one chunk of KS 64-element k-steps): where output pixels are not whole
 // 16-byte granules or the staged rows do not fit the CU, and for very few pixels.
