@@ -543,6 +543,16 @@ const std::vector<int>& base_variants()
     }();
     return t;
 }
+// Those of one kind (a look at all of them is 1.5 us).
+const std::vector<int>& variants_of(int kind)
+{
+    static const std::vector<std::vector<int>> t = [] {
+        std::vector<std::vector<int>> r(32);
+        for (int v : base_variants()) r[(size_t)variant_desc(v).kind].push_back(v);
+        return r;
+    }();
+    return t[(size_t)kind];
+}
 unsigned kinds_of(const nm_packed* wp)
 {
     unsigned m = 0;
@@ -561,9 +571,9 @@ int split_taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs
     int pick = -1;
     double best = 0;
     const int chunks = wp->K / 64;
-    for (int v : base_variants()) {
+    for (int v : variants_of(sparse ? 15 : 16)) {
         const VariantDesc& d = variant_desc(v);
-        if (d.kind != (sparse ? 15 : 16) || !keeps_precision(v, wp) || !variant_legal(v, wp, xdt, ra)) continue;
+        if (!keeps_precision(v, wp) || !variant_legal(v, wp, xdt, ra)) continue;
         const int channels = channel_waves(d) * d.NJ * 16;
         const long n_cb = (wp->cout + channels - 1) / channels, n_wg = (long)((P + d.BP - 1) / d.BP) * n_cb;
         const long rounds = (n_wg + kNumCU - 1) / kNumCU;
@@ -650,11 +660,11 @@ int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
     int pick = -1;
     double best = 0;
     const bool sparse = kinds_of(wp) >> 2 & 1u;
-    for (int v : base_variants()) {
+    for (int v : variants_of(sparse ? 13 : 14)) {
         const VariantDesc& d = variant_desc(v);
         const int channels = channel_waves(d) * d.NJ * 16;
         const bool wide = d.waves == 8;
-        if (d.kind != (sparse ? 13 : 14) || d.NBLK < 5 || (!sparse && !wide) || !variant_legal(v, wp, xdt, ra)) continue;
+        if (d.NBLK < 5 || (!sparse && !wide) || !variant_legal(v, wp, xdt, ra)) continue;
         const long n_cb = (wp->cout + channels - 1) / channels, n_wg = (long)((P + d.BP - 1) / d.BP) * n_cb;
         if (2L * wp->cout <= n_cb * channels || (channels > 64 && wp->cout <= 64)) continue;
         if (!sparse && 3L * wp->cout < 2L * n_cb * channels) continue;
@@ -680,9 +690,9 @@ int cols_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)
     const long n_cb = (wp->cout + 255) / 256, tiles = (P + 63) / 64;
     if (P < 4096 || n_cb < 2 || 2L * wp->cout < n_cb * 256) return -1;
     if (tiles > 448 && (wp->cin < 192 || 4L * wp->cout < 3 * n_cb * 256)) return -1;
-    for (int v : base_variants()) {
+    for (int v : variants_of(17)) {
         const VariantDesc& d = variant_desc(v);
-        if (d.kind == 17 && d.NBLK == (tiles >= 400 ? 4 : 2) && variant_legal(v, wp, xdt, ra)) return v;
+        if (d.NBLK == (tiles >= 400 ? 4 : 2) && variant_legal(v, wp, xdt, ra)) return v;
     }
     return -1;
 }
