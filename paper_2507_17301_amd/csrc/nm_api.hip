@@ -443,13 +443,19 @@ void magic_div(unsigned d, unsigned* mul, unsigned* shift)
     *shift = s;
 }
 
-// Whether an output of so many bytes is stored past the caches: where the 256 MB last-level cache would not hold it (and
-// the rest of a layer's tensors) until the next layer reads it.  Layer and the layer that reads it, written through
-// and past the caches: fp32 56x56 64 -> 256 and 256 -> 64 (206 MB between them) 73 + 58 and 59 + 53 us; bf16 28x28 128 -> 512 and
-// 512 -> 128 at batch 256 (206 MB) 93 + 56 and 89 + 53; 14x14 256 -> 1024 and 1024 -> 256 (103 MB) 62 + 34 and 63 + 36.  The first
-// layer of a network, read once by the pool behind it and not as a residual as well: bf16 (103 MB) 36 + 30 and 33 + 27, fp32
-// (206 MB) 113 + 48 and 114 + 50.
-bool stream_output(int kind, double bytes) { return bytes > (kind == 10 ? 96e6 : kind == 11 ? 256e6 : 150e6); }
+// Whether an output of so many bytes is stored past the caches: where the 256 MB last-level cache would not hold it (and the
+// rest of a layer's tensors) until the next layer reads it.  Whole networks, called again and again, no output past the caches,
+// those over 256 MB, those over 150: ResNet-101 in bf16 at batch 256 5742, 5672 and 5632 us, ResNet-50 in bf16 at batch 96 1561,
+// 1563 and 1532, in fp32 at batch 64 2785, 2782 and 2770; called once after other memory has been filled, the same order
+// (5767, 5710, 5670) or no difference.  A layer and the one that reads it by themselves gain nothing, and lose where the cache is full of what others wrote:
+// bf16 56x56 64 -> 256 and 256 -> 64, written through and past, repeated 111 and 112 us (167 MB), 136 and 136 (206); once after a
+// fill 147 and 165, 175 and 195.
+// Below the line past the caches is slower: a first layer in bf16 with its pool, 77, 103 and 128 MB, repeated 43 -> 47, 58 -> 62,
+// 80 -> 76, once after a fill 49 -> 66, 67 -> 86, 76 -> 104; ResNet-50 at batch 64 (103 MB) repeated 1125 either way, once after a
+// fill 1136 -> 1155.  (The layer alone, whose output nobody reads: 40 -> 33 on three tensors in turn, 33.5 -> 34 on two.)
+// fp32 first layers (kind 11) are bound by their arithmetic and gain from 256 MB on: with the pool, 206 MB repeated 154 and 156,
+// once after a fill 151 and 190; 308 MB 240 -> 233, 263 -> 260.
+bool stream_output(int kind, double bytes) { return bytes > (kind == 11 ? 256e6 : 150e6); }
 
 // Groups of 256 output channels that a workgroup of kind 17 walks: all of them, or as many as leave three quarters of the CUs'
 // places (two a CU) a workgroup.  14x14 256 -> 1024 with a residual, 1, 2 and 4 groups: batch 256 (784 pixel tiles) 67.7, 60.4 and 61.0

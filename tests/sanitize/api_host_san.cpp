@@ -32,6 +32,7 @@
 static std::map<char*, size_t> g_allocs;
 static bool g_fail_malloc = false, g_no_device = false;
 static int g_launches = 0;
+static int g_stream = -1;   // whether the last launch was to store past the caches
 
 static bool inside(const void* p, size_t need)
 {
@@ -149,6 +150,7 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
     const VariantDesc& d = kFake[v];
     g_timer_variant = v;
     ++g_launches;
+    g_stream = p.stream;
     const size_t es = xdt == NM_F32 ? 4 : (xdt == NM_BF16 ? 2 : 1), yes = ydt == NM_F32 ? 4 : 2;
     CHECK(xdt == ydt || (xdt == NM_F8E4M3 && ydt == NM_BF16));
     const bool f8 = d.kind == 6 || d.kind == 7;
@@ -443,6 +445,46 @@ static void split_limits()
     CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
 }
 
+// Which outputs are stored past the caches, on either side of the line: by their size, the same for every bf16 form that may run
+// a layer (a first layer among them), and where fp32 kernels of few input channels run it
+static void store_limits()
+{
+    auto all = [](nm_dtype_t dt, int b, int hw, int cin, int cout, int k, int stride, int pad, const char* form, int want) {
+        std::vector<float> wt((size_t)cout * k * k * cin, 0.5f);
+        nm_packed_t* wp = nullptr;
+        CHECK(nm_prune(wt.data(), cout, k, k, cin, 1, cin % 4 ? 1 : 4, 16, dt, &wp) == NM_OK);
+        const size_t es = dt == NM_F32 ? 4 : 2;
+        const int ho = (hw + 2 * pad - k) / stride + 1;
+        void* x = dev_alloc((size_t)b * hw * hw * cin * es);
+        void* y = dev_alloc((size_t)b * ho * ho * cout * es);
+        int ran = 0;
+        for (int u = 0; u < nm_variant_count(); ++u) {
+            if (!strstr(nm_variant_name(u), form)) continue;
+            CHECK(nm_force_variant(u) == NM_OK);
+            const int rc = nm_conv2d(x, dt, b, hw, hw, cin, wp, nullptr, stride, stride, pad, pad, 1, 1, 0, y, dt, nullptr);
+            CHECK(rc == NM_OK || rc == NM_ERR_UNSUPPORTED);
+            if (rc != NM_OK) continue;
+            CHECK(g_stream == want);
+            ++ran;
+        }
+        CHECK(ran > 0 && nm_force_variant(-1) == NM_OK);
+        CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
+    };
+    for (const char* form : {"F_RUN_NB4", "F_RUN_ROWS"}) {   // 1.6 MB an image
+        all(NM_BF16, 64, 224, 3, 64, 7, 2, 3, form, 0);
+        all(NM_BF16, 93, 224, 3, 64, 7, 2, 3, form, 0);
+        all(NM_BF16, 94, 224, 3, 64, 7, 2, 3, form, 1);
+    }
+    for (const char* form : {"F_SP", "F_B16"}) {
+        all(NM_BF16, 93, 56, 64, 256, 1, 1, 0, form, 0);
+        all(NM_BF16, 94, 56, 64, 256, 1, 1, 0, form, 1);
+    }
+    all(NM_F32, 46, 56, 64, 256, 1, 1, 0, "F_", 0);          // 3.2 MB an image
+    all(NM_F32, 47, 56, 64, 256, 1, 1, 0, "F_X3S_NB4_WP1_NJ2", 1);
+    all(NM_F32, 79, 224, 3, 64, 7, 2, 3, "F_ROWF", 0);
+    all(NM_F32, 80, 224, 3, 64, 7, 2, 3, "F_ROWF", 1);
+}
+
 // The tap-staged forms on either side of what bounds them: rows of 3000 pixels, padded rows below 2^24, padded granules below
 // 2^31 (padding far wider than the image), 32 taps
 static void taps_limits()
@@ -605,6 +647,7 @@ int main(int argc, char** argv)
         CHECK(hipFree(xb) == hipSuccess && hipFree(yb) == hipSuccess && nm_packed_free(h8) == NM_OK);
     }
     split_limits();
+    store_limits();
     remembered_defaults();
     not_finite();
     for (nm_dtype_t dt : {NM_F32, NM_BF16}) {
