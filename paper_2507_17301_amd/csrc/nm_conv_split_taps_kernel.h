@@ -9,7 +9,8 @@
 // wavefront's own tile is 64 pixels x 16 NJ channels whatever the workgroup's: smaller ones read more from LDS and from the
 // cache of the weights than these deliver beside six matrix instructions a block (64 x 64: half of 1536 clocks either).
 // The groups' sums are added in the order of the groups, each of them by the group that finishes the block, and chunks that do
-// not make a whole round are done by all groups, each on its blocks (nine taps of 64 channels in four groups: 2.25 rounds for 3).
+// not make a whole round are done by all groups, each on its blocks (nine taps of 64 channels in four groups: 2.25 rounds for 3),
+// and added last.
 //
 // Barriers: all wavefronts have done m chunks each at the same time, whatever group, so both kinds stand at a place m of
 // their own.  "Stage w - 2 has been read" at ceil(ntaps (w - 1) / KG), behind which its place may be written for stage w;
@@ -167,7 +168,8 @@ __global__ __launch_bounds__(512, 2) void nm_conv_split_taps_kernel(const ConvPa
     if (p.ncpt > 1) fetch(1);
 
     // products of pixel block b, smallest first; the row blocks take turns, so that no instruction waits for the one before it
-    auto products = [&](const Ops& o, unsigned off, int b, f4 (&sum)[NJ][NBLK], auto&& behind) __attribute__((always_inline)) {
+    // (added to sum[row block][sb])
+    auto products = [&](const Ops& o, unsigned off, int b, auto& sum, int sb, auto&& behind) __attribute__((always_inline)) {
         u4v x[3][2];
 #pragma unroll
         for (int pl = 2; pl >= 0; --pl)
@@ -184,23 +186,25 @@ __global__ __launch_bounds__(512, 2) void nm_conv_split_taps_kernel(const ConvPa
                                                          6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj)
-                    sum[jj][b] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
-                        __builtin_bit_cast(bf8x, o.a[jj][WPL[k]][0]), bv, sum[jj][b], (int)o.idx[jj], 0, 0);
+                    sum[jj][sb] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(
+                        __builtin_bit_cast(bf8x, o.a[jj][WPL[k]][0]), bv, sum[jj][sb], (int)o.idx[jj], 0, 0);
             } else {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int jj = 0; jj < NJ; ++jj)
-                        sum[jj][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        sum[jj][sb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                             __builtin_bit_cast(bf8x, o.a[jj][WPL[k]][AH == 2 ? h : 0]),
-                            __builtin_bit_cast(bf8x, x[XP[k]][h]), sum[jj][b], 0, 0, 0);
+                            __builtin_bit_cast(bf8x, x[XP[k]][h]), sum[jj][sb], 0, 0, 0);
             }
             behind(k);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
     // The chunks are dealt out in `full` rounds; those that are left over, fewer than groups, all groups do, each on the
-    // blocks that it finishes.  Chunk i of the sum is tap i % ntaps of stage i / ntaps.
+    // blocks that it finishes, in a sum of its own: added to the group's, whose turn a chunk is would depend on the block, and
+    // the same image would come out in other bits at another place of the batch.  Chunk i of the sum is tap i % ntaps of stage
+    // i / ntaps.
     const int full = total / KG;
     auto advance = [&](int m) {                  // from this wavefront's chunk m to the next one
         const int step = m + 1 < full ? KG : m + 1 == full ? KG - grp : 1;
@@ -222,19 +226,20 @@ __global__ __launch_bounds__(512, 2) void nm_conv_split_taps_kernel(const ConvPa
         const int cn = cc < p.ncpt ? tap * p.ncpt + cc : c;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
-            products(o, off, b, acc, [&](int k) __attribute__((always_inline)) {
+            products(o, off, b, acc, b, [&](int k) __attribute__((always_inline)) {
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj)
                     if (jj * NBLK / NJ == b && jj - (b * NJ + NBLK - 1) / NBLK == (k + 3) % 6) load_op(next, jj, cn);
             });
     };
+    f4 rest[NJ][NO];                             // of the chunks left over
     auto left_over = [&](int m) __attribute__((always_inline)) {
         const unsigned off = place_of();
 #pragma unroll
         for (int to = 0; to < KG; ++to)
             if (to == grp) {
 #pragma unroll
-                for (int b = 0; b < NO; ++b) products(oa, off, to * NO + b, acc, [](int) {});
+                for (int b = 0; b < NO; ++b) products(oa, off, to * NO + b, rest, b, [](int) {});
             }
         advance(m);
         if (cc == p.ncpt) return;
@@ -285,6 +290,11 @@ __global__ __launch_bounds__(512, 2) void nm_conv_split_taps_kernel(const ConvPa
         chunk(ob, oa, m);
         if (++m == full) break;
     }
+#pragma unroll
+    for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+        for (int b = 0; b < NO; ++b) rest[jj][b] = f4{0.f, 0.f, 0.f, 0.f};
+    const bool more = total % KG != 0;
     for (int m = full; m < full + total % KG; ++m) left_over(m);
 
     // ---- the groups' sums, and the output ------------------------------------------------------------------------------
@@ -320,7 +330,7 @@ __global__ __launch_bounds__(512, 2) void nm_conv_split_taps_kernel(const ConvPa
                 if (from != grp) v = *reinterpret_cast<const f4*>(slot(grp, from) + (b * NJ + jj) * 1024);
                 s = from == 0 ? v : s + v;
             }
-            fin[jj][b] = s;
+            fin[jj][b] = more ? s + rest[jj][b] : s;
         }
     kernarg_t kp = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(kp));

@@ -80,6 +80,23 @@ def test_every_form(h, w, cin, cout, k, dil, n, m, tile, batch):
     assert ran
 
 
+@pytest.mark.parametrize("h,w,cin,k,n,m", [(7, 7, 64, (3, 3), 2, 4), (5, 6, 128, (3, 3), 1, 1), (7, 9, 192, (3, 5), 2, 4), (6, 7, 64, (5, 1), 4, 8),
+                                           (14, 14, 320, (3, 3), 1, 4)])
+def test_an_image_gives_the_same_bits_wherever_it_is_in_the_batch(h, w, cin, k, n, m):
+    """Images that begin at every place of a tile, with chunks left over beyond whole rounds of the groups (9, 18, 45, 5 and 45 chunks)."""
+    import torch
+    rng = np.random.default_rng(3)
+    wp = nm.nm_prune(rng.standard_normal((72, *k, cin), dtype=np.float32) * np.float32(0.1), n, m, 16)
+    one = torch.from_numpy(rng.standard_normal((1, h, w, cin), dtype=np.float32)).cuda()
+    x = one.expand(19, h, w, cin).contiguous()
+    pad = ((k[0] - 1) // 2, (k[1] - 1) // 2)
+    bias = torch.from_numpy(rng.standard_normal(72, dtype=np.float32)).cuda()
+    for name, v in forms(n <= 2 and m % 4 == 0).items():
+        say(f"place in the batch {h}x{w} {cin} {k} {name}")
+        y = run(v, x, wp, bias, pad, (1, 1), False)
+        assert (y == y[:1]).all() and (y[:1] == run(v, one, wp, bias, pad, (1, 1), False)).all(), name
+
+
 @pytest.mark.parametrize("n,m,cin", [(2, 4, 64), (2, 4, 512), (1, 1, 64), (4, 8, 256)])
 @pytest.mark.parametrize("kind", ["uniform", "signed", "tiny"])
 def test_no_further_from_float64_than_the_fp32_instruction(n, m, cin, kind):
