@@ -450,12 +450,23 @@ void magic_div(unsigned d, unsigned* mul, unsigned* shift)
 // (5767, 5710, 5670) or no difference.  A layer and the one that reads it by themselves gain nothing, and lose where the cache is full of what others wrote:
 // bf16 56x56 64 -> 256 and 256 -> 64, written through and past, repeated 111 and 112 us (167 MB), 136 and 136 (206); once after a
 // fill 147 and 165, 175 and 195.
-// Below the line past the caches is slower: a first layer in bf16 with its pool, 77, 103 and 128 MB, repeated 43 -> 47, 58 -> 62,
-// 80 -> 76, once after a fill 49 -> 66, 67 -> 86, 76 -> 104; ResNet-50 at batch 64 (103 MB) repeated 1125 either way, once after a
-// fill 1136 -> 1155.  (The layer alone, whose output nobody reads: 40 -> 33 on three tensors in turn, 33.5 -> 34 on two.)
+// Below the line past the caches is slower for a layer that is read at once: a first layer in bf16 and its pool, 64, 90, 103 and 128 MB,
+// the faster of the other two ways and past, on three tensors in turn 36 and 40, 57 and 61, 57 and 66, 79 and 76, on one 35 and 39,
+// 50 and 56, 52 and 60, 60 and 69, on new ones 49 and 54, 64 and 69, 66 and 72, 74 and 83; ResNet-18 at batch 64, images of 224 and 256
+// (103 and 134 MB), 416 and 420, 454 and 469, ResNet-50 1123 and 1122, 1312 and 1309, once after a fill 428 and 442, 473 and 504, 1137
+// and 1150, 1332 and 1353.  (The first layer alone, whose output nobody reads, is faster past them where it does not find its
+// output in the cache: 39 and 32 on three tensors in turn, 33 and 34 on two.)
 // fp32 first layers (kind 11) are bound by their arithmetic and gain from 256 MB on: with the pool, 206 MB repeated 154 and 156,
 // once after a fill 151 and 190; 308 MB 240 -> 233, 263 -> 260.
 bool stream_output(int kind, double bytes) { return bytes > (kind == 11 ? 256e6 : 150e6); }
+
+// Whether kind 10 leaves its output to the L2's own write-back: stores that pass the L2 one by one slow a first layer in bf16 down from
+// about 72 MB on (likely where it writes faster than the memory behind takes them).  The layer on three tensors in turn,
+// through and kept, 13, 38, 51, 64, 77, 82, 90, 103, 128 and 149 MB: 8.4 and 9.4, 13.3 and 15.3, 18.7 and 19.8, 22.5 and 22.6, 27.2
+// and 24.8, 33.2 and 29.8, 39.3 and 37.1, 41.0 and 38.5, 46.1 and 43.4, 55.5 and 53.2 us; on new tensors and with the pool the same
+// way from 82 MB on by 1 to 4 us; ResNet-18 at batch 64 and images of 256 (134 MB) 460 and 454.  (fp32, whose arithmetic takes longer, is
+// faster through the L2 at every size, by 1 to 3 us.)
+bool keep_output(int kind, double bytes) { return kind == 10 && bytes > 72e6 && !stream_output(kind, bytes); }
 
 // Groups of 256 output channels that a workgroup of kind 17 walks: all of them, or as many as leave three quarters of the CUs'
 // places (two a CU) a workgroup.  14x14 256 -> 1024 with a residual, 1, 2 and 4 groups: batch 256 (784 pixel tiles) 67.7, 60.4 and 61.0
@@ -477,7 +488,9 @@ void fill_params(ConvParams& p, const VariantDesc& d, const Prepack& pp, const n
     p.Ho = g.Ho; p.Wo = g.Wo;
     p.sh = sh; p.sw = sw; p.ph = ph; p.pw = pw; p.dh = dh; p.dw = dw;
     p.relu = relu ? 1 : 0;
-    p.stream = stream_output(d.kind, (double)g.P * wp->cout * (es == 4 ? 4 : 2)) ? 1 : 0;   // (fp8 layers write bf16)
+    const double ybytes = (double)g.P * wp->cout * (es == 4 ? 4 : 2);   // (fp8 layers write bf16)
+    p.stream = stream_output(d.kind, ybytes) ? 1 : 0;
+    p.keep = keep_output(d.kind, ybytes) ? 1 : 0;
     p.P = g.P; p.K = wp->K;
     p.nchunks = pp.geom.nchunks; p.ncpt = pp.geom.ncpt;
     p.tile = wp->tile; p.rbpt = wp->rbpt; p.n_rowblocks = wp->n_rowblocks;

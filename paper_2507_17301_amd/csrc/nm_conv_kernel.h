@@ -70,6 +70,12 @@ template <bool STREAM> __device__ inline void store_out16(void* p, u4v v)
     if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u4v*>(p));
     else __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u4v*)p, v, "agent");
 }
+// 16 bytes left to the L2, which writes them back when it needs the room or the kernel ends (keep_output() has the sizes).  The
+// builtin as above: of a plain and a nontemporal store on two sides of a branch the compiler makes one plain store.
+__device__ inline void store_out16_kept(void* p, u4v v)
+{
+    __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u4v*)p, v, "wavefront");
+}
 __device__ inline void store1(float* p, float v) { *p = v; }
 __device__ inline void store1(bf16_t* p, float v) { p->v = to_bf16_bits(v); }
 __device__ inline f4 load4(const float* p) { return *reinterpret_cast<const f4*>(p); }

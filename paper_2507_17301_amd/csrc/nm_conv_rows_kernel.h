@@ -264,7 +264,8 @@ __global__ __launch_bounds__(256, PL == 1 && KS < 4 ? 3 : 2) void nm_conv_rows_k
                 }
                 T* const to = y + (out0 + (unsigned)(k * RPP) * (unsigned)p.Cout);
                 if (live & (p.stream != 0)) store_out16<true>(to, v[k]);
-                if (live & (p.stream == 0)) store_out16<false>(to, v[k]);
+                if (live & (p.stream == 0) & (PL == 3 || !p.keep)) store_out16<false>(to, v[k]);
+                if (PL == 1 && (live & (p.keep != 0))) store_out16_kept(to, v[k]);
             }
             if constexpr (PL == 3) {
                 if (__builtin_expect(lo < kSplitTiny || hi >= kSplitInf || any, 0)) {

@@ -233,6 +233,7 @@ struct ConvParams {
     int sh, sw, ph, pw, dh, dw;
     int relu;
     int stream;        // output rows are stored past the caches
+    int keep;          // kind 10: output rows are left to the L2 (never with stream)
     int P;             // B*Ho*Wo
     int K;
     int nchunks, ncpt;

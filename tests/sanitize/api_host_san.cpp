@@ -32,7 +32,7 @@
 static std::map<char*, size_t> g_allocs;
 static bool g_fail_malloc = false, g_no_device = false;
 static int g_launches = 0;
-static int g_stream = -1;   // whether the last launch was to store past the caches
+static int g_stream = -1, g_keep = -1;   // whether the last launch was to store past the caches, to leave the output to the L2
 
 static bool inside(const void* p, size_t need)
 {
@@ -151,6 +151,8 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
     g_timer_variant = v;
     ++g_launches;
     g_stream = p.stream;
+    g_keep = p.keep;
+    CHECK(p.keep == 0 || (d.kind == 10 && p.stream == 0));
     const size_t es = xdt == NM_F32 ? 4 : (xdt == NM_BF16 ? 2 : 1), yes = ydt == NM_F32 ? 4 : 2;
     CHECK(xdt == ydt || (xdt == NM_F8E4M3 && ydt == NM_BF16));
     const bool f8 = d.kind == 6 || d.kind == 7;
@@ -446,10 +448,10 @@ static void split_limits()
 }
 
 // Which outputs are stored past the caches, on either side of the line: by their size, the same for every bf16 form that may run
-// a layer (a first layer among them), and where fp32 kernels of few input channels run it
+// a layer (a first layer among them), and where fp32 kernels of few input channels run it; which are left to the L2
 static void store_limits()
 {
-    auto all = [](nm_dtype_t dt, int b, int hw, int cin, int cout, int k, int stride, int pad, const char* form, int want) {
+    auto all = [](nm_dtype_t dt, int b, int hw, int cin, int cout, int k, int stride, int pad, const char* form, int want, int keep = 0) {
         std::vector<float> wt((size_t)cout * k * k * cin, 0.5f);
         nm_packed_t* wp = nullptr;
         CHECK(nm_prune(wt.data(), cout, k, k, cin, 1, cin % 4 ? 1 : 4, 16, dt, &wp) == NM_OK);
@@ -464,16 +466,19 @@ static void store_limits()
             const int rc = nm_conv2d(x, dt, b, hw, hw, cin, wp, nullptr, stride, stride, pad, pad, 1, 1, 0, y, dt, nullptr);
             CHECK(rc == NM_OK || rc == NM_ERR_UNSUPPORTED);
             if (rc != NM_OK) continue;
-            CHECK(g_stream == want);
+            CHECK(g_stream == want && g_keep == keep);
             ++ran;
         }
         CHECK(ran > 0 && nm_force_variant(-1) == NM_OK);
         CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
     };
     for (const char* form : {"F_RUN_NB4", "F_RUN_ROWS"}) {   // 1.6 MB an image
-        all(NM_BF16, 64, 224, 3, 64, 7, 2, 3, form, 0);
-        all(NM_BF16, 93, 224, 3, 64, 7, 2, 3, form, 0);
-        all(NM_BF16, 94, 224, 3, 64, 7, 2, 3, form, 1);
+        const int rows = strstr(form, "ROWS") != nullptr;
+        all(NM_BF16, 44, 224, 3, 64, 7, 2, 3, form, 0, 0);
+        all(NM_BF16, 45, 224, 3, 64, 7, 2, 3, form, 0, rows);
+        all(NM_BF16, 64, 224, 3, 64, 7, 2, 3, form, 0, rows);
+        all(NM_BF16, 93, 224, 3, 64, 7, 2, 3, form, 0, rows);
+        all(NM_BF16, 94, 224, 3, 64, 7, 2, 3, form, 1, 0);
     }
     for (const char* form : {"F_SP", "F_B16"}) {
         all(NM_BF16, 93, 56, 64, 256, 1, 1, 0, form, 0);
