@@ -12,7 +12,28 @@ pytestmark = pytest.mark.gpu
 # channels and of a tile; walks of one to nine groups, whole and shared by several workgroups
 CASES = [(1, 1, 1, 64, 16, 1, 2, 4, 16, False, True), (1, 7, 9, 128, 264, 1, 1, 4, 16, True, True), (3, 13, 11, 192, 520, 2, 2, 8, 32, True, False),
          (2, 8, 8, 256, 1024, 1, 2, 4, 16, True, True), (70, 14, 13, 64, 2056, 1, 2, 4, 16, False, True), (130, 14, 14, 256, 776, 1, 2, 8, 48, True, True),
-         (9, 28, 27, 128, 512, 2, 1, 8, 16, True, True)]
+         (9, 28, 27, 128, 512, 2, 1, 8, 16, True, True),
+         # two and three chunks whose workgroups walk: all four groups and, in tiles of 64 pixels, all three; two of four at a time
+         (130, 14, 14, 128, 776, 1, 2, 4, 16, True, True), (130, 14, 14, 192, 520, 1, 2, 8, 16, True, True),
+         (64, 14, 13, 192, 1016, 1, 1, 4, 16, True, False), (66, 14, 13, 128, 1000, 1, 2, 4, 16, False, True)]
+
+
+def walk(pixels, cout, blocks):
+    """Groups of 256 output channels that a workgroup of 16 `blocks` pixels walks."""
+    tiles, groups = -(-pixels // (16 * blocks)), -(-cout // 256)
+    parts = -(-384 // tiles)
+    return 1 if parts >= groups else -(-groups // parts)
+
+
+def test_the_cases_walk():
+    """For every number of chunks and either tile a walk of several groups, the last one ragged, beyond one chunk with a residual;
+    walks of all groups and of a part of them."""
+    walks = [(cin, blocks, residual, steps < -(-cout // 256)) for b, h, w, cin, cout, stride, _, _, _, residual, _ in CASES if cout % 256
+             for blocks in (2, 4) for steps in [walk(b * -(-h // stride) * -(-w // stride), cout, blocks)] if steps > 1]
+    for blocks in (2, 4):
+        assert {c for c, k, _, _ in walks if k == blocks} == {64, 128, 192, 256}
+        assert {c for c, k, r, _ in walks if k == blocks and r} == {128, 192, 256}
+    assert {part for *_, part in walks} == {False, True}
 
 
 @pytest.mark.parametrize("b,h,w,cin,cout,stride,n,m,tile,residual,bias", CASES)
