@@ -1,5 +1,5 @@
-"""Outputs larger than the last-level cache leave through other stores than smaller ones: a batch on the far side of the line
-against its two halves on the near side, bit for bit (the sums of a pixel do not know of the batch)."""
+"""Outputs larger than the last-level cache leave through other stores than smaller ones (first layers in bf16 in three ways): a batch on
+the far side of a line against its two halves on the near side, bit for bit (the sums of a pixel do not know of the batch)."""
 import numpy as np
 import pytest
 
@@ -8,11 +8,20 @@ from gpu_util import say
 
 pytestmark = pytest.mark.gpu
 
+# Every end of a tile that stores in either way: the tile in LDS with 256 and 512 threads (gather, strip and tap-staged forms), the
+# row-staged, three-plane, fp8 and channel-walking ones.
 CASES = [  # dtype, batch, size, Cin, Cout, k, stride, pad, N:M, residual, variants by prefix ("" = the default)
     ("bf16", 98, 56, 64, 256, 1, 1, 0, (2, 4), True, ("", "SPR1_NB8_WP1_NJ4_CK64", "B16_NB4_WP1_NJ2_SH1")),
     ("bf16", 50, 80, 64, 256, 3, 1, 1, (2, 4), False, ("SPR1_TAPS_NB7_WP2_NJ4",)),
     ("f32", 50, 56, 64, 256, 1, 1, 0, (2, 4), True, ("X3S_NB4_WP1_NJ2", "NB4_WP1_NJ2_CK32")),
-    ("bf16", 62, 224, 3, 64, 7, 2, 3, (1, 1), False, ("", "RUN_NB4_WP1_NJ1")),
+    ("bf16", 200, 28, 64, 512, 3, 1, 1, (2, 4), True, ("SPR1_TAP8_NB7_WP2_NJ4", "SPR1_TAP8_NB8_WP2_NJ4")),
+    ("bf16", 200, 28, 64, 512, 3, 1, 1, (4, 8), False, ("SPR0_TAP8_NB7_WP2_NJ4", "SPR0_TAP8_NB7_WP2_NJ2")),
+    ("bf16", 200, 28, 128, 512, 1, 1, 0, (2, 4), True, ("SPR1_COLS_NB4_C2", "SPR1_COLS_NB2_C2")),
+    ("bf16", 200, 28, 256, 512, 1, 1, 0, (2, 4), False, ("", "SPR1_COLS_NB4_C4")),
+    ("f32", 100, 28, 64, 512, 3, 1, 1, (2, 4), True, ("X3S_TAP_NB4_WP1_NJ4_KG2", "X3S_TAP_NB4_WP1_NJ4_KG4")),
+    ("f32", 100, 28, 64, 512, 3, 1, 1, (4, 8), False, ("X3D_TAP_NB4_WP1_NJ2_KG2", "X3D_TAP_NB4_WP1_NJ2_KG4")),
+    ("bf16", 96, 224, 3, 64, 7, 2, 3, (1, 1), False, ("", "RUN_NB4_WP1_NJ1", "RUN_ROWS4_NJ4")),
+    ("bf16", 48, 224, 3, 64, 7, 2, 3, (1, 1), True, ("", "RUN_ROWS1_NJ4", "RUN_ROWS8_NJ4")),
     ("f32", 81, 224, 3, 64, 7, 2, 3, (1, 1), False, ("ROWF_R4_NJ2",)),
     ("f8", 98, 56, 64, 256, 1, 1, 0, (2, 4), False, ("", "F8_NB4_WP1_NJ4")),
 ]
@@ -33,14 +42,15 @@ def test_both_sides_of_the_line(dtype, batch, size, cin, cout, k, stride, pad, n
     res = torch.rand((batch, ho, ho, cout), generator=g, device="cuda").to(ydt) if residual else None
     bias = torch.rand(cout, generator=g, device="cuda")
     half = batch // 2
+    yb = batch * ho * ho * cout * (4 if dtype == "f32" else 2)
+    lines = (150e6,) if cin > 3 else (256e6,) if dtype == "f32" else (72e6, 150e6)
+    assert any(yb * (batch - half) / batch < line < yb for line in lines)
     names = [nm.nm_variant_name(v) for v in range(nm.nm_variant_count())]
-    ran = 0
     try:
         for want in variants:
             picks = [i for i, n in enumerate(names) if want and n.startswith(want) and nm.nm_variant_legal(i, wp, code, nm.NM_F32 if dtype == "f32" else nm.NM_BF16)]
-            picks += [i for i, n in enumerate(names) if n == want and "_TAPS_" in n]   # (whether these run is decided by the call)
-            if want and not picks:
-                continue
+            picks += [i for i, n in enumerate(names) if n == want and ("_TAP" in n or "_COLS_" in n)]   # (whether these run is decided by the call)
+            assert picks or not want, want
             nm.nm_force_variant(picks[0] if want else -1)
             say(f"stream out {dtype} {batch}x{size}x{size}x{cin} -> {cout} {want}")
             y = nm.nm_conv2d_res(x, wp, res, bias, stride, pad, 1, True)
@@ -50,7 +60,5 @@ def test_both_sides_of_the_line(dtype, batch, size, cin, cout, k, stride, pad, n
                 assert torch.equal(part, y[lo:hi]), (want, lo)
             torch.cuda.synchronize()
             nm.nm_force_variant(-1)
-            ran += 1
     finally:
         nm.nm_force_variant(-1)
-    assert ran
