@@ -50,9 +50,23 @@ GRID = [(1, 1, 64, 16, (3, 3), (1, 1), 2, 4, 16, 1), (9, 13, 64, 37, (3, 3), (1,
         (7, 7, 320, 128, (3, 3), (1, 1), 2, 8, 8, 5), (11, 10, 192, 72, (1, 3), (1, 2), 2, 4, 16, 3), (12, 9, 128, 136, (2, 2), (2, 2), 2, 4, 32, 2),
         (6, 7, 64, 64, (5, 5), (1, 1), 2, 4, 16, 3), (5, 12, 192, 40, (5, 1), (1, 1), 2, 4, 16, 2),
         (14, 13, 128, 130, (3, 3), (1, 1), 64, 128, 16, 2), (8, 8, 64, 72, (3, 3), (2, 2), 1, 1, 16, 3), (7, 7, 192, 100, (3, 3), (1, 1), 4, 8, 4, 4)]
+# one stage of more granules than the threads hold at a time (three each): two to three passes over it, the last one ragged
+WIDE = [(56, 56, 64, 130, (3, 3), (1, 1), 2, 4, 16, 2), (28, 100, 64, 72, (3, 3), (1, 1), 1, 4, 8, 2), (30, 40, 64, 40, (5, 5), (1, 1), 2, 4, 16, 2),
+        (40, 44, 64, 36, (3, 3), (1, 1), 1, 1, 16, 2), (30, 90, 64, 72, (3, 3), (1, 1), 4, 8, 16, 1)]
 
 
-@pytest.mark.parametrize("h,w,cin,cout,k,dil,n,m,tile,batch", GRID)
+def granules(h, w, ph, pw, pixels=64):
+    """16-byte granules that a tile of 64 pixels and what its taps reach span at most: nine a pixel, and the zeros between rows and images."""
+    line = 9 * w + (9 * pw + 7) // 8 * 8
+    return 9 * pixels + (pixels + w - 2) // w * (line - 9 * w) + (pixels + h * w - 2) // (h * w) * ph * line + 2 * (ph * line + 9 * pw)
+
+
+def test_the_wide_layers_are_wide():
+    for h, w, cin, _, k, dil, *_ in WIDE:
+        assert cin == 64 and granules(h, w, dil[0] * (k[0] - 1) // 2, dil[1] * (k[1] - 1) // 2) > 3 * 512
+
+
+@pytest.mark.parametrize("h,w,cin,cout,k,dil,n,m,tile,batch", GRID + WIDE)
 def test_every_form(h, w, cin, cout, k, dil, n, m, tile, batch):
     import torch
     rng = np.random.default_rng(11)
@@ -181,4 +195,19 @@ def test_untuned(batch, cin, cout, n, m, form):
     assert nm.nm_variant_name(nm.nm_last_variant()).startswith(form), nm.nm_variant_name(nm.nm_last_variant())
     pts = wl.sample_points(layer, batch, 2000, 1)
     ref = oracle.conv2d_points(x, oracle.prune(w, n, m, 16)[2], pts, bias, 1, 1, 1, True)
+    assert norm_err(y.cpu().numpy()[pts[:, 0], pts[:, 1], pts[:, 2], pts[:, 3]], ref) <= FP32_TOL
+
+
+def test_untuned_wide():
+    """56x56: one stage in two passes, as a call without tuning runs it; sampled outputs against the oracle."""
+    import torch
+    layer = L("wide", 56, 56, 64, 128, 3, 3, 1, 1, 1, 2, 4, 16)
+    assert granules(56, 56, 1, 1) > 3 * 512
+    x, w, bias = wl.make_tensors(layer, 4, 13)
+    wp = nm.nm_prune(w, 2, 4, 16)
+    say("untuned 56x56 64 -> 128")
+    y = nm.nm_conv2d(torch.from_numpy(x).cuda(), wp, torch.from_numpy(bias).cuda(), 1, 1, 1, True)
+    assert nm.nm_variant_name(nm.nm_last_variant()).startswith("X3S_TAP_"), nm.nm_variant_name(nm.nm_last_variant())
+    pts = wl.sample_points(layer, 4, 4000, 1)
+    ref = oracle.conv2d_points(x, oracle.prune(w, 2, 4, 16)[2], pts, bias, 1, 1, 1, True)
     assert norm_err(y.cpu().numpy()[pts[:, 0], pts[:, 1], pts[:, 2], pts[:, 3]], ref) <= FP32_TOL
