@@ -32,6 +32,7 @@
 static std::map<char*, size_t> g_allocs;
 static bool g_fail_malloc = false, g_no_device = false;
 static int g_launches = 0;
+static int g_walk = 0;   // groups of output channels that a workgroup of the last such launch walks
 static int g_stream = -1, g_keep = -1;   // whether the last launch was to store past the caches, to leave the output to the L2
 
 static bool inside(const void* p, size_t need)
@@ -140,6 +141,16 @@ static const VariantDesc kFake[] = {
     {"F_SPR1_TAPS_NB4_WP1_NJ2", 64, 4, 1, 2, 64, 1, 1, 13, 1, 1, 1, 1},
     {"F_SPR1_TAPS_NB7_WP2_NJ4", 224, 7, 2, 4, 64, 1, 1, 13, 1, 1, 1, 1},
     {"F_SPR0_TAPS_NB5_WP2_NJ4", 160, 5, 2, 4, 64, 1, 1, 14, 1, 1, 1, 1},
+    // the same with eight contracting wavefronts; fp32 as three planes staged once for all taps; 1x1, output channels over resident pixels
+    {"F_SPR1_TAP8_NB7_WP2_NJ4", 224, 7, 2, 4, 64, 1, 1, 13, 1, 1, 1, 1, 8},
+    {"F_SPR0_TAP8_NB7_WP2_NJ2", 224, 7, 2, 2, 64, 1, 1, 14, 1, 1, 1, 1, 8},
+    {"F_X3S_TAP_NB4_WP1_NJ4_KG2", 64, 4, 1, 4, 64, 1, 1, 15, 1, 1, 1, 0, 2},
+    {"F_X3S_TAP_NB4_WP1_NJ4_KG4", 64, 4, 1, 4, 64, 1, 1, 15, 1, 1, 1, 0, 4},
+    {"F_X3D_TAP_NB4_WP1_NJ2_KG4", 64, 4, 1, 2, 64, 1, 1, 16, 1, 1, 1, 0, 4},
+    {"F_SPR1_COLS_NB4_C1", 64, 4, 1, 4, 64, 1, 1, 17, 1, 1, 1, 0, 1},
+    {"F_SPR1_COLS_NB2_C1", 32, 2, 1, 4, 64, 1, 1, 17, 1, 1, 1, 0, 1},
+    {"F_SPR1_COLS_NB4_C4", 64, 4, 1, 4, 64, 1, 1, 17, 1, 1, 1, 0, 4},
+    {"F_SPR1_COLS_NB2_C4", 32, 2, 1, 4, 64, 1, 1, 17, 1, 1, 1, 0, 4},
 };
 int variant_count() { return (int)(sizeof(kFake) / sizeof(kFake[0])); }
 const VariantDesc& variant_desc(int v) { return kFake[v]; }
@@ -168,8 +179,9 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
     CHECK(p.P == p.B * p.Ho * p.Wo && p.K == p.Kh * p.Kw * p.Cin);
     const bool rows = d.kind == 10 || d.kind == 11;
     CHECK(p.n_ptiles == (rows ? p.B * ((p.Ho + d.NBLK - 1) / d.NBLK) : (p.P + d.BP - 1) / d.BP));
-    CHECK(p.n_wg == p.n_ptiles * p.n_cblocks * p.ksplit);
-    if (d.kind >= 8 && d.kind <= 11) CHECK(p.tile == 16 && p.rbpt == 1 && p.n_rowblocks == (p.Cout + 15) / 16);
+    const bool walks = d.kind == 17, staged = d.kind >= 13 && d.kind <= 16, planes = d.kind == 15 || d.kind == 16;
+    CHECK(p.n_wg == (walks ? p.n_ptiles * ((p.n_cblocks + p.cps - 1) / p.cps) : p.n_ptiles * p.n_cblocks * p.ksplit));
+    if ((d.kind >= 8 && d.kind <= 11) || planes) CHECK(p.tile == 16 && p.rbpt == 1 && p.n_rowblocks == (p.Cout + 15) / 16);
     if (rows) {
         // every operand of every output pixel of a workgroup lies in the staged rows, and these in the CU's LDS
         const long last = (long)p.rows_front + ((long)(d.NBLK - 1) * p.sh + (long)(p.Kh - 1) * p.dh) * p.rows_pitch +
@@ -196,21 +208,34 @@ int launch_conv(int v, nm_dtype_t xdt, nm_dtype_t ydt, const ConvParams& p, hipS
         CHECK(exact((unsigned)p.ncpt, p.ncpt_mul, p.ncpt_shift, (unsigned)p.nchunks) && exact((unsigned)p.Kw, p.kw_mul, p.kw_shift, (unsigned)(p.Kh * p.Kw)));
         CHECK(exact((unsigned)p.rbpt, p.rbpt_mul, p.rbpt_shift, (unsigned)p.n_rowblocks + 16));
     }
-    if (d.kind == 13 || d.kind == 14) {
-        // an output as large as the input, whole granules and row blocks of 16 channels, two stages in the CU's LDS
-        CHECK(p.sh == 1 && p.sw == 1 && p.Ho == p.H && p.Wo == p.W && p.Cin % 64 == 0 && p.Cout % 8 == 0 && p.tile % 16 == 0);
+    if (staged) {
+        // an output as large as the input, whole granules and row blocks of 16 channels, the stages and what follows in the CU's LDS
+        CHECK(p.sh == 1 && p.sw == 1 && p.Ho == p.H && p.Wo == p.W && p.Cin % 64 == 0 && p.tile % 16 == 0 && (planes || p.Cout % 8 == 0));
         CHECK(p.rows_n == taps_granules(d.BP, p.H, p.W, p.ph, p.pw) && p.rows_lds == taps_loads(p.rows_n) * 1024 && p.rows_lds >= p.rows_n * 16);
-        CHECK(taps_lds_bytes(d.NBLK, d.WP, d.NJ, p.rows_n, p.ncpt) <= 160 * 1024 && p.ncpt == p.Cin / 64);
+        const int waves = d.waves == 8 ? 8 : 4;
+        CHECK((planes ? split_taps_lds_bytes(d.NBLK, d.NJ, d.waves, p.rows_n, p.ncpt)
+                      : taps_lds_bytes(d.NBLK, d.WP, d.NJ, p.rows_n, p.ncpt, waves)) <= 160 * 1024 && p.ncpt == p.Cin / 64);
         const long line = taps_line(p.W, p.pw), lines = (long)(p.B + 2) * (p.H + p.ph);
         CHECK(lines < 1 << 24 && lines * line < 1l << 31 && p.P < 1 << 24);
         CHECK(exact((unsigned)line, p.padw_mul, p.padw_shift, (unsigned)(lines * line)) && exact((unsigned)(p.H + p.ph), p.padh_mul, p.padh_shift, (unsigned)lines));
+        // what the registers of a wavefront or thread hold of a stage; a group of wavefronts for every tap at least
+        CHECK(planes ? p.ncpt == 1 || taps_loads(p.rows_n) <= 8 * kSplitTapsItems : d.waves != 8 || taps_loads(p.rows_n) <= 8 * kTapsWideLoads);
+        CHECK(!planes || (p.Kh * p.Kw >= d.waves && exact((unsigned)p.Kw, p.kw_mul, p.kw_shift, (unsigned)(p.Kh * p.Kw))));
+    }
+    if (walks) {
+        // 1x1 without padding, the channels of the form, whole granules; every group of 256 output channels is walked by one workgroup
+        CHECK(p.Kh == 1 && p.Kw == 1 && p.ph == 0 && p.pw == 0 && p.Cin == 64 * d.waves && p.nchunks == d.waves && p.Cout % 8 == 0 && p.tile % 16 == 0);
+        g_walk = p.cps;
+        CHECK(p.cps >= 1 && p.cps <= p.n_cblocks && cols_lds_bytes(d.NBLK, d.waves) <= 80 * 1024);
+        CHECK(exact((unsigned)p.rbpt, p.rbpt_mul, p.rbpt_shift, (unsigned)p.n_rowblocks));
     }
     CHECK(p.ksplit == (d.ksplit > 1 ? d.ksplit : 1));
     if (p.ksplit > 1) {   // every split owns chunks, together they cover the K axis, and the partial sums have a home
         CHECK(p.cps >= 1 && (p.ksplit - 1) * p.cps < p.nchunks && p.ksplit * p.cps >= p.nchunks);
         CHECK(inside(p.partial, (size_t)p.ksplit * p.P * p.Cout * 4));
     }
-    CHECK(p.n_cblocks * (4 / d.WP) * d.NJ >= p.n_rowblocks && (p.n_cblocks - 1) * (4 / d.WP) * d.NJ < p.n_rowblocks);
+    const int wc = (planes ? 8 / d.waves : staged && d.waves == 8 ? 8 : 4) / d.WP;   // wavefronts along the output channels
+    CHECK(p.n_cblocks * wc * d.NJ >= p.n_rowblocks && (p.n_cblocks - 1) * wc * d.NJ < p.n_rowblocks);
     CHECK(p.wg_per_xcd * 8 >= p.n_wg);
     CHECK((size_t)p.x_elems * es == p.x_bytes && p.x_bytes < 0x80000000u);
     // multiply-shift division is exact on every value the kernels feed it
@@ -308,7 +333,7 @@ static void* dev_alloc(size_t n)
     return p;
 }
 
-static int g_taps_ran = 0;
+static int g_taps_ran = 0, g_wide_ran = 0, g_planes_ran = 0, g_cols_ran = 0;
 
 static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, int n, int m, int tile, nm_dtype_t dt,
                       int sh, int sw, int ph, int pw, int dh, int dw)
@@ -360,7 +385,8 @@ static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, in
     int v = -1;
     float ms = 0.f;
     CHECK(nm_autotune(dt, b, h, w, cin, wp, 1, sh, sw, ph, pw, dh, dw, 1, ydt, nullptr, &v, &ms) == NM_OK);
-    auto taps = [](int u) { return strstr(nm_variant_name(u), "_TAPS_") != nullptr; };   // (depend on more than the handle)
+    auto named = [](int u, const char* part) { return strstr(nm_variant_name(u), part) != nullptr; };
+    auto taps = [&](int u) { return named(u, "_TAP") || named(u, "_COLS_"); };   // (depend on more than the handle)
     CHECK(v >= 0 && ms > 0.f && nm_variant_legal(v, wp, dt, ydt) == (taps(v) ? 0 : 1));
     CHECK(nm_conv2d(x, dt, b, h, w, cin, wp, bias, sh, sw, ph, pw, dh, dw, 1, y, ydt, nullptr) == NM_OK);
     CHECK(nm_last_variant() == v);
@@ -370,7 +396,11 @@ static void conv_case(int b, int h, int w, int cin, int cout, int kh, int kw, in
         const int legal = nm_variant_legal(u, wp, dt, ydt);
         const int rc = nm_conv2d(x, dt, b, h, w, cin, wp, bias, sh, sw, ph, pw, dh, dw, 1, y, ydt, nullptr);
         CHECK(legal || taps(u) ? (rc == NM_OK || rc == NM_ERR_UNSUPPORTED) : rc == NM_ERR_UNSUPPORTED);
-        g_taps_ran += taps(u) && rc == NM_OK;
+        if (rc != NM_OK) continue;
+        g_taps_ran += named(u, "_TAPS_");
+        g_wide_ran += named(u, "_TAP8_");
+        g_planes_ran += named(u, "_TAP_");
+        g_cols_ran += named(u, "_COLS_");
     }
     CHECK(nm_force_variant(-1) == NM_OK);
     // K-split variants: through the growable workspace, through the static scratch, and under capture
@@ -526,6 +556,29 @@ static void taps_limits()
     CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
 }
 
+// Layers whose output channels a workgroup walks whole or in part, forced and as the untuned default
+static void cols_walks()
+{
+    struct Case { int b, cin, cout, walk2, walk4; };   // groups of 256 channels walked with tiles of 32 and 64 pixels
+    for (const Case& c : {Case{70, 64, 2056, 9, 5}, Case{40, 64, 1000, 2, 1}, Case{64, 256, 1024, 4, 2}, Case{256, 256, 1024, 4, 4}}) {
+        std::vector<float> wt((size_t)c.cout * c.cin, 0.5f);
+        nm_packed_t* wp = nullptr;
+        CHECK(nm_prune(wt.data(), c.cout, 1, 1, c.cin, 2, 4, 16, NM_BF16, &wp) == NM_OK);
+        void* x = dev_alloc((size_t)c.b * 14 * 14 * c.cin * 2);
+        void* y = dev_alloc((size_t)c.b * 14 * 14 * c.cout * 2);
+        auto run = [&]() { return nm_conv2d(x, NM_BF16, c.b, 14, 14, c.cin, wp, nullptr, 1, 1, 0, 0, 1, 1, 0, y, NM_BF16, nullptr); };
+        for (int u = 0; u < nm_variant_count(); ++u) {
+            if (!strstr(nm_variant_name(u), "_COLS_")) continue;
+            const int walk = strstr(nm_variant_name(u), "NB2") ? c.walk2 : c.walk4;
+            const bool fits = strstr(nm_variant_name(u), c.cin == 64 ? "_C1" : "_C4") != nullptr;
+            CHECK(nm_force_variant(u) == NM_OK && run() == (fits ? NM_OK : NM_ERR_UNSUPPORTED) && (!fits || g_walk == walk));
+        }
+        CHECK(nm_force_variant(-1) == NM_OK && run() == NM_OK);
+        if (c.cin == 256) CHECK(strstr(nm_variant_name(nm_last_variant()), "_COLS_"));
+        CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
+    }
+}
+
 // The default remembered for a shape, met by a handle that agrees in everything that the key holds but has no table for it
 // (the key holds a hash of the tables); and more shapes than the table holds.
 static void remembered_defaults()
@@ -636,7 +689,16 @@ int main(int argc, char** argv)
     CHECK(g_taps_ran == 0);
     conv_case(3, 9, 7, 128, 40, 3, 3, 2, 4, 16, NM_BF16, 1, 1, 1, 1, 1, 1);    // a tile's input staged once for all taps
     conv_case(1, 12, 5, 64, 24, 1, 3, 4, 8, 32, NM_BF16, 1, 1, 0, 2, 3, 2);    // ... dense instruction only
-    CHECK(g_taps_ran == 3 + 1);
+    CHECK(g_taps_ran == 3 + 1 && g_wide_ran == 2 + 1 && g_planes_ran == 0);
+    conv_case(3, 9, 7, 128, 37, 3, 3, 2, 4, 5, NM_F32, 1, 1, 1, 1, 1, 1);      // ... as three planes
+    conv_case(1, 56, 40, 64, 24, 1, 3, 1, 1, 16, NM_F32, 1, 1, 0, 1, 1, 1);    // ... dense, fewer taps than groups
+    conv_case(1, 56, 60, 64, 24, 2, 2, 1, 1, 16, NM_F32, 1, 1, 1, 1, 2, 2);    // ... as many, one stage that threads take in two passes
+    CHECK(g_planes_ran == 2 + 0 + 1);
+    g_cols_ran = 0;
+    conv_case(3, 28, 27, 64, 776, 1, 1, 2, 8, 48, NM_BF16, 2, 1, 0, 0, 1, 1);  // output channels walked over resident pixels
+    conv_case(2, 7, 7, 256, 1024, 1, 1, 1, 4, 16, NM_BF16, 1, 1, 0, 0, 1, 1);
+    CHECK(g_cols_ran == 2 + 2);
+    cols_walks();
     taps_limits();
     {   // E4M3 weights that the fp8 kernel cannot take, and fp8 tensors on weights of another type
         std::vector<float> wt(16 * 48, 0.25f);
@@ -666,7 +728,7 @@ int main(int argc, char** argv)
     // nothing leaked on the "device": what is left is the K-split workspace and the static scratch
     CHECK(g_allocs.size() <= 2);
     const int n_entries = nm_cache_size();
-    CHECK(n_entries == 10);
+    CHECK(n_entries == 15);
 
     // ---- cache file round trip and hostile files
     const std::string path = tmp + "/nm_cache_san.txt";
