@@ -447,24 +447,25 @@ void magic_div(unsigned d, unsigned* mul, unsigned* shift)
 // rest of a layer's tensors) until the next layer reads it.  Whole networks, called again and again, no output past the caches,
 // those over 256 MB, those over 150: ResNet-101 in bf16 at batch 256 5742, 5672 and 5632 us, ResNet-50 in bf16 at batch 96 1561,
 // 1563 and 1532, in fp32 at batch 64 2785, 2782 and 2770; called once after other memory has been filled, the same order
-// (5767, 5710, 5670) or no difference.  A layer and the one that reads it by themselves gain nothing, and lose where the cache is full of what others wrote:
-// bf16 56x56 64 -> 256 and 256 -> 64, written through and past, repeated 111 and 112 us (167 MB), 136 and 136 (206); once after a
-// fill 147 and 165, 175 and 195.
-// Below the line past the caches is slower for a layer that is read at once: a first layer in bf16 and its pool, 64, 90, 103 and 128 MB,
-// the faster of the other two ways and past, on three tensors in turn 36 and 40, 57 and 61, 57 and 66, 79 and 76, on one 35 and 39,
-// 50 and 56, 52 and 60, 60 and 69, on new ones 49 and 54, 64 and 69, 66 and 72, 74 and 83; ResNet-18 at batch 64, images of 224 and 256
-// (103 and 134 MB), 416 and 420, 454 and 469, ResNet-50 1123 and 1122, 1312 and 1309, once after a fill 428 and 442, 473 and 504, 1137
-// and 1150, 1332 and 1353.  (The first layer alone, whose output nobody reads, is faster past them where it does not find its
-// output in the cache: 39 and 32 on three tensors in turn, 33 and 34 on two.)
-// fp32 first layers (kind 11) are bound by their arithmetic and gain from 256 MB on: with the pool, 206 MB repeated 154 and 156,
-// once after a fill 151 and 190; 308 MB 240 -> 233, 263 -> 260.
-bool stream_output(int kind, double bytes) { return bytes > (kind == 11 ? 256e6 : 150e6); }
+// (5767, 5710, 5670) or no difference.  By themselves such layers gain nothing, and lose where the cache is full of what others
+// wrote: bf16 56x56 64 -> 256 with a residual, through and past, repeated 74 and 71 us (167 MB), 88 and 85 (206), once after a fill
+// 105 and 114, 122 and 140.
+// First layers (kinds 10 and 11) are read by the pool at once, and not as a residual later: past only where the cache does not hold
+// the output.  The layer and its pool, 64, 90, 103 and 128 MB in bf16, the faster of the other two ways and past, on three tensors
+// in turn 36 and 40, 57 and 61, 57 and 66, 79 and 76, on one 35 and 39, 50 and 56, 52 and 60, 60 and 69, on new ones 49 and 54, 64 and
+// 69, 66 and 72, 74 and 83; ResNet-18, 103, 134, 154, 180, 206 and 257 MB, 416 and 420, 454 and 469, 548 and 549, 594 and 592, 675
+// and 674, 766 and 755, once after a fill 428 and 442, 473 and 504, 551 and 588, 594 and 634, 689 and 713, 788 and 785; ResNet-50,
+// 103, 154 and 206 MB, 1123 and 1122, 1536 and 1533, 1916 and 1903, once after a fill 1137 and 1150, 1559 and 1574, 1941 and 1943.
+// (The first layer alone, whose output nobody reads, is faster past them where it does not find its output in the cache: 39 and 32
+// on three tensors of 103 MB in turn, 33 and 34 on two.)  fp32 with the pool, through and past, 206 MB 154 and 156, once after a fill 151
+// and 190; 308 MB 240 and 233, 263 and 260.
+bool stream_output(int kind, double bytes) { return bytes > (is_rows_kind(kind) ? 256e6 : 150e6); }
 
 // Whether kind 10 leaves its output to the L2's own write-back: stores that pass the L2 one by one slow a first layer in bf16 down from
 // about 72 MB on (likely where it writes faster than the memory behind takes them).  The layer on three tensors in turn,
 // through and kept, 13, 38, 51, 64, 77, 82, 90, 103, 128 and 149 MB: 8.4 and 9.4, 13.3 and 15.3, 18.7 and 19.8, 22.5 and 22.6, 27.2
 // and 24.8, 33.2 and 29.8, 39.3 and 37.1, 41.0 and 38.5, 46.1 and 43.4, 55.5 and 53.2 us; on new tensors and with the pool the same
-// way from 82 MB on by 1 to 4 us; ResNet-18 at batch 64 and images of 256 (134 MB) 460 and 454.  (fp32, whose arithmetic takes longer, is
+// way from 82 MB on by 1 to 4 us; ResNet-18, 134, 154 and 206 MB 460 and 454, 551 and 548, 676 and 675.  (fp32, whose arithmetic takes longer, is
 // faster through the L2 at every size, by 1 to 3 us.)
 bool keep_output(int kind, double bytes) { return kind == 10 && bytes > 72e6 && !stream_output(kind, bytes); }
 

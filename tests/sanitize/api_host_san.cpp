@@ -477,8 +477,8 @@ static void split_limits()
     CHECK(hipFree(x) == hipSuccess && hipFree(y) == hipSuccess && nm_packed_free(wp) == NM_OK);
 }
 
-// Which outputs are stored past the caches, on either side of the line: by their size, the same for every bf16 form that may run
-// a layer (a first layer among them), and where fp32 kernels of few input channels run it; which are left to the L2
+// Which outputs are stored past the caches, on either side of the line: by their size, the same for every form that may run a layer
+// but those of staged rows, which run first layers; and which of these are left to the L2
 static void store_limits()
 {
     auto all = [](nm_dtype_t dt, int b, int hw, int cin, int cout, int k, int stride, int pad, const char* form, int want, int keep = 0) {
@@ -508,7 +508,9 @@ static void store_limits()
         all(NM_BF16, 45, 224, 3, 64, 7, 2, 3, form, 0, rows);
         all(NM_BF16, 64, 224, 3, 64, 7, 2, 3, form, 0, rows);
         all(NM_BF16, 93, 224, 3, 64, 7, 2, 3, form, 0, rows);
-        all(NM_BF16, 94, 224, 3, 64, 7, 2, 3, form, 1, 0);
+        all(NM_BF16, 94, 224, 3, 64, 7, 2, 3, form, !rows, rows);
+        all(NM_BF16, 159, 224, 3, 64, 7, 2, 3, form, !rows, rows);
+        all(NM_BF16, 160, 224, 3, 64, 7, 2, 3, form, 1, 0);
     }
     for (const char* form : {"F_SP", "F_B16"}) {
         all(NM_BF16, 93, 56, 64, 256, 1, 1, 0, form, 0);
