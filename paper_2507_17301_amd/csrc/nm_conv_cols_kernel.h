@@ -12,7 +12,9 @@
 // What bounds it: memory, and the start and end of a launch.  14x14 256 -> 1024 with a residual, out of cache, against the fastest
 // of the others and the one that untuned calls took: batch 64 16.2 us, 17.8 and 23.7; batch 256 (231 MB) 60.4, 63.0 and 74 to
 // 78.  28x28 128 -> 512 at batch 256 (463 MB) 89.6, 90.2 and 95.3; up to 256 output channels there is nothing to walk, x1.2 to
-// x1.5.  Beginning the walk of neighbouring tiles at different groups: 61.4 for 60.4, 94 for 90.
+// x1.5.  Beginning the walk of neighbouring tiles at different groups: 61.4 for 60.4, 94 for 90.  Without requests past the last group
+// of a walk (another card, before and after): 14x14 at batch 64, 128 and 256 15.7 and 15.5, 34.5 and 33.7, 60.5 and 59.1, 28x28 at 256
+// 88.4 and 86.7.
 #pragma once
 
 #include "nm_conv_sp16_kernel.h"
@@ -82,11 +84,11 @@ __global__ __launch_bounds__(256, 2) void nm_conv_cols_kernel(const ConvParams p
         if (at >= p.n_rowblocks) at = p.n_rowblocks - 1;
         return fdiv((unsigned)at, p.rbpt_mul, p.rbpt_shift) * (NCH * 16u) + (unsigned)q * 4u;
     };
-    auto load_ops = [&](Ops& o, int rb, unsigned words, int c) {
+    auto load_ops = [&](Ops& o, int rb, unsigned mine, unsigned words, int c) {
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             const int at = rb + jj < p.n_rowblocks ? rb + jj : p.n_rowblocks - 1;
-            o.a[jj] = __builtin_amdgcn_raw_buffer_load_b128(wr, (unsigned)lane * 16u, (unsigned)(at * NCH + c) * 1024u, 0);
+            o.a[jj] = __builtin_amdgcn_raw_buffer_load_b128(wr, mine, (unsigned)(at * NCH + c) * 1024u, 0);
         }
         o.idx = __builtin_amdgcn_raw_buffer_load_b32(rr, words, (unsigned)c * 16u, 0);
     };
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(256, 2) void nm_conv_cols_kernel(const ConvParams p
     auto row_block = [&](int it) { return (it * 4 + wave) * NJ; };
     int rb0 = row_block(first);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) load_ops(ops[c], rb0, index_words(rb0), c);
+    for (int c = 0; c < NCH; ++c) load_ops(ops[c], rb0, (unsigned)lane * 16u, index_words(rb0), c);
     load_bias(rb0);
     if (res) load_res(rb0);
 
@@ -127,8 +129,12 @@ __global__ __launch_bounds__(256, 2) void nm_conv_cols_kernel(const ConvParams p
     NM_WAIT_VMCNT(0);
     __syncthreads();                             // the input is there
     for (int it = first; it < end; ++it) {
-        const int rbn = row_block(it + 1 < end ? it + 1 : it);   // (past the last group its own again, not used)
-        const unsigned words = index_words(rbn);
+        // Past the last group nothing is requested: weights and index words out of range (which costs no memory traffic and keeps the
+        // loop in one piece), the residual not at all.  (Its addresses set to one place of the tensor instead: 60.5 -> 67, every
+        // workgroup asking for the same line.)
+        const bool more = it + 1 < end;
+        const int rbn = row_block(more ? it + 1 : it);
+        const unsigned mine = more ? (unsigned)lane * 16u : kOOB, words = more ? index_words(rbn) : kOOB;
         f4 acc[NJ][NBLK];
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj)
@@ -153,7 +159,7 @@ __global__ __launch_bounds__(256, 2) void nm_conv_cols_kernel(const ConvParams p
                     acc[jj][b] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf8x, ops[c].a[jj]), bv, acc[jj][b], idx[jj], 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            load_ops(ops[c], rbn, words, c);
+            load_ops(ops[c], rbn, mine, words, c);
         }
         load_bias(rbn);
         // the output: residual, activation and the one rounding in the wavefront's own piece of LDS, then whole lines
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(256, 2) void nm_conv_cols_kernel(const ConvParams p
 #pragma unroll
             for (int k = 0; k < NP; ++k) *reinterpret_cast<u4v*>(piece + (k * 8 + r0) * PITCH + cg * 16) = rv[k];
             __builtin_amdgcn_wave_barrier();
-            load_res(rbn);
+            if (more) load_res(rbn);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
