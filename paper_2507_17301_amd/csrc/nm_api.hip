@@ -469,8 +469,9 @@ bool stream_output(int kind, double bytes) { return bytes > (is_rows_kind(kind) 
 // faster through the L2 at every size, by 1 to 3 us.)
 bool keep_output(int kind, double bytes) { return kind == 10 && bytes > 72e6 && !stream_output(kind, bytes); }
 
-// Groups of 256 output channels that a workgroup of kind 17 walks: all of them, or as many as leave three quarters of the CUs'
-// places (two a CU) a workgroup.  14x14 256 -> 1024 with a residual, 1, 2 and 4 groups: batch 256 (784 pixel tiles) 67.7, 60.4 and 61.0
+// Groups of 256 output channels that a workgroup of kind 17 walks: all of them where the pixel tiles alone are three quarters of the
+// CUs' places (two a CU) or more, else an equal part of them, of as many parts as that takes, rounded up to whole groups (so that there
+// may be fewer workgroups: 130 tiles and four groups are three parts, walks of two groups, 260 of 384).  14x14 256 -> 1024 with a residual, 1, 2 and 4 groups: batch 256 (784 pixel tiles) 67.7, 60.4 and 61.0
 // us, batch 64 19.2, 16.2 and 19.0.
 int cols_walk(int n_ptiles, int n_cblocks)
 {
@@ -672,7 +673,7 @@ int rows_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs& ra)
 // half of the channels exist (128 of 256) it would be x1.26 to x1.35, at 1.16 rounds x1.11.  Eight wavefronts: of 220 such
 // layers the 82 that go from a form of four to one of eight take x0.73 to x1.07 of its time, x0.85 on average.
 // The dense instruction (layers that the sparse one does not do): the forms of eight wavefronts alone, from 150 workgroups on
-// and with two thirds of their channels in existence.  67 of 100 random layers are within that and take x0.73 to x1.05 of the
+// and with two thirds of their channels in existence.  67 of 100 random layers are within that and take x0.72 to x1.05 of the
 // time that the rule below gives them, x0.83 on average; at 128 to 150 workgroups it would be up to x1.32.  (Four wavefronts:
 // x0.93 at best, x1.2 on most.)
 int taps_default(const nm_packed* wp, int P, nm_dtype_t xdt, const RunArgs* ra)

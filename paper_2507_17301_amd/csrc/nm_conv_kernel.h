@@ -63,8 +63,8 @@ __device__ inline void store4(bf16_t* p, f4 v)
 //     their way as they are stored.
 //   STREAM = true: past the L2 and the 256 MB last-level cache too (nontemporal), where that would not hold the output
 //     until it is read (stream_output() has the sizes).
-// Plain and write-through stores, batch 64: 28x28 3x3 128 -> 128 bf16 15.4 and 13.7 us, 14x14 1x1 1024 -> 256 fp8 8.5 and
-// 8.0, the layers of ResNet-50 in bf16 1201 and 1153, in fp32 2973 and 2930.
+// Plain and write-through stores, batch 64, two builds in turn with the same picks: 28x28 3x3 128 -> 128 bf16 15.0 and 13.9 us, 14x14 1x1
+// 1024 -> 256 fp8 8.2 and 7.8, ResNet-50 in bf16 1149 and 1129, in fp32 2752 and 2731.
 template <bool STREAM> __device__ inline void store_out16(void* p, u4v v)
 {
     if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u4v*>(p));
