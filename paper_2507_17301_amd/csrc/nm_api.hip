@@ -451,22 +451,22 @@ void magic_div(unsigned d, unsigned* mul, unsigned* shift)
 // wrote: bf16 56x56 64 -> 256 with a residual, through and past, repeated 74 and 71 us (167 MB), 88 and 85 (206), once after a fill
 // 105 and 114, 122 and 140.
 // First layers (kinds 10 and 11) are read by the pool at once, and not as a residual later: past only where the cache does not hold
-// the output.  The layer and its pool, 64, 90, 103 and 128 MB in bf16, the faster of the other two ways and past, on three tensors
-// in turn 36 and 40, 57 and 61, 57 and 66, 79 and 76, on one 35 and 39, 50 and 56, 52 and 60, 60 and 69, on new ones 49 and 54, 64 and
-// 69, 66 and 72, 74 and 83; ResNet-18, 103, 134, 154, 180, 206 and 257 MB, 416 and 420, 454 and 469, 548 and 549, 594 and 592, 675
-// and 674, 766 and 755, once after a fill 428 and 442, 473 and 504, 551 and 588, 594 and 634, 689 and 713, 788 and 785; ResNet-50,
-// 103, 154 and 206 MB, 1123 and 1122, 1536 and 1533, 1916 and 1903, once after a fill 1137 and 1150, 1559 and 1574, 1941 and 1943.
-// (The first layer alone, whose output nobody reads, is faster past them where it does not find its output in the cache: 39 and 32
-// on three tensors of 103 MB in turn, 33 and 34 on two.)  fp32 with the pool, through and past, 206 MB 154 and 156, once after a fill 151
-// and 190; 308 MB 240 and 233, 263 and 260.
+// the output.  In bf16, left to the L2 (keep_output) and past: the layer and its pool, 77, 103, 128, 180, 206 and 257 MB, on three
+// tensors in turn 40 and 50, 56 and 64, 78 and 76, 103 and 108, 116 and 113, 143 and 137, on one 38 and 44, 51 and 59, 58 and 69, 92 and
+// 95, 97 and 103, 138 and 129; ResNet-18, 77, 103, 134, 154, 206 and 257 MB, 354 and 358, 417 and 426, 462 and 478, 550 and 557, 678
+// and 681, 775 and 769, once after a fill 371 and 382, 435 and 449, 486 and 512, 563 and 596, 703 and 719, 803 and 799; ResNet-50, 103,
+// 134, 154, 206 and 257 MB, 1123 and 1132, 1334 and 1328, 1536 and 1541, 1911 and 1916, 2264 and 2253.  (The first layer alone, whose
+// output nobody reads, is faster past them where it does not find its output in the cache: 128 MB on three tensors in turn 43 and 39,
+// on one 35 and 37.)  fp32, through and past, with the pool on three tensors 206, 254 and 308 MB 154 and 156, 197 and 194, 242 and 236.
 bool stream_output(int kind, double bytes) { return bytes > (is_rows_kind(kind) ? 256e6 : 150e6); }
 
 // Whether kind 10 leaves its output to the L2's own write-back: stores that pass the L2 one by one slow a first layer in bf16 down from
 // about 72 MB on (likely where it writes faster than the memory behind takes them).  The layer on three tensors in turn,
-// through and kept, 13, 38, 51, 64, 77, 82, 90, 103, 128 and 149 MB: 8.4 and 9.4, 13.3 and 15.3, 18.7 and 19.8, 22.5 and 22.6, 27.2
-// and 24.8, 33.2 and 29.8, 39.3 and 37.1, 41.0 and 38.5, 46.1 and 43.4, 55.5 and 53.2 us; on new tensors and with the pool the same
-// way from 82 MB on by 1 to 4 us; ResNet-18, 134, 154 and 206 MB 460 and 454, 551 and 548, 676 and 675.  (fp32, whose arithmetic takes longer, is
-// faster through the L2 at every size, by 1 to 3 us.)
+// through and kept, 13, 38, 51, 64, 77, 82, 103, 128, 149 and 180 MB: 8.1 and 9.0, 13.3 and 15.0, 17.2 and 18.3, 21.2 and 22.2, 27.2
+// and 24.4, 32.4 and 29.8, 39.4 and 37.1, 44.8 and 43.0, 55.1 and 52.7, 65.2 and 62.4 us; with the pool, 38 to 180 MB, 22.5 and 24.3,
+// 28.7 and 29.2, 37.7 and 35.9, 41.8 and 40.3, 50.9 and 48.2, 57.1 and 55.8, 79.6 and 77.7, 94.2 and 93.3, 105.5 and 103.2; ResNet-18, 51,
+// 77, 103, 154 and 206 MB 281 and 282, 356 and 354, 421 and 417, 555 and 550, 683 and 678.  (fp32, whose arithmetic takes longer, is
+// faster through the L2 up to 51 MB and the same beyond.)
 bool keep_output(int kind, double bytes) { return kind == 10 && bytes > 72e6 && !stream_output(kind, bytes); }
 
 // Groups of 256 output channels that a workgroup of kind 17 walks: all of them where the pixel tiles alone are three quarters of the
